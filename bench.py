@@ -261,9 +261,9 @@ def bench_train(w, steps, warmup, with_dense=True, with_bwd=True, dense_steps=3,
 
     # roofline of the dominant kernel.  Flops attributed per kernel (sums to 14*D*pairs):
     # forward 4*D*pairs (QK^T, PV); dK/dV kernel 8*D*pairs (S, dP, dV, dK); dQ kernel 2*D*pairs.
-    # (head_dim 128 with mask blocks of 64 tokens or more runs the hand-scheduled forward and dQ kernels)
+    # (head_dim 128 with mask blocks of 64 tokens or more runs the hand-scheduled dQ kernel)
     fast = D == 128 and S >= 64 and N % 128 == 0
-    kernels = {"fwd_pipe_kernel" if fast else "fwd_kernel": (res["ms_fwd"], 4.0)}
+    kernels = {"fwd_pipe_kernel": (res["ms_fwd"], 4.0)}
     if with_bwd:
         kernels["dkdv_kernel"] = (res["ms_bwd_dkdv"], 8.0)
         dq_name = "dq_gemm_kernel" if res["backward_path"] == "keeping dS" else "dq_pipe_kernel" if fast else "dq_kernel"
@@ -542,15 +542,12 @@ def main():
 
     if varlen:
         d = bench_prefill_varlen(w, args.steps, args.warmup)
-        # two launches per call: the pipelined kernel on each sequence's whole 128-row tiles, the plain one on
-        # the partial last tiles
-        parts = [measured_traffic(d["workload"], k) for k in ("fwd_pipe_kernel", "fwd_kernel")]
-        traffic = None if any(t is None for t in parts) else sum(parts)
+        traffic = measured_traffic(d["workload"], "fwd_pipe_kernel")
         out = {"metric": "effective sparse-attn TFLOP/s, forward on a packed variable-length prefill batch",
                "value": d["tflops"], "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
                "ms_per_step": d["ms"], "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
                "dtype": "bf16", "data": "synthetic", "config": d,
-               "roofline": {"kernel": "fwd_pipe_kernel + fwd_kernel (variable-length)", "bound": "mfma",
+               "roofline": {"kernel": "fwd_pipe_kernel (variable-length)", "bound": "mfma",
                             "achieved": d["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                             "frac": d["tflops"] / PEAK_BF16_TFLOPS, "traffic": traffic},
                "cpu_baseline": None}

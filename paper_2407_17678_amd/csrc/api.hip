@@ -46,9 +46,9 @@ void free_tiles(s2::TileList& t) {
 }
 
 void free_device_copies(s2_layout* L) {
-  free_tiles(L->fwd_tiles);
   free_tiles(L->q_tiles);
   free_tiles(L->kv_tiles);
+  free_tiles(L->q_block_tiles);
   if (L->d_row_ptr) (void)hipFree(L->d_row_ptr);
   if (L->d_col_idx) (void)hipFree(L->d_col_idx);
   if (L->d_dq_units) (void)hipFree(L->d_dq_units);
@@ -174,9 +174,10 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
   if (st == S2_OK) {
     try {
       const int S = L->p.block_size;
-      s2::build_tiles(*L, s2::kFwdBM / S, false, L->fwd_tiles);
+      static_assert(s2::kFwdBM == s2::kBwdBM, "forward and dQ walk the same lists");
       s2::build_tiles(*L, s2::kBwdBM / S, false, L->q_tiles);
       s2::build_tiles(*L, s2::kBwdBN / S, true, L->kv_tiles);
+      if (S == 16) s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_block_tiles);
       s2::build_ds_units(*L);
     } catch (const std::bad_alloc&) {
       st = S2_ERR_OVERFLOW;
@@ -189,8 +190,8 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0) {
     int dev = 0;
-    bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->fwd_tiles) && upload_tiles(L->q_tiles) &&
-              upload_tiles(L->kv_tiles) && upload(L->row_ptr, &L->d_row_ptr) &&
+    bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->q_tiles) && upload_tiles(L->kv_tiles) &&
+              (L->p.block_size != 16 || upload_tiles(L->q_block_tiles)) && upload(L->row_ptr, &L->d_row_ptr) &&
               upload(L->col_idx, &L->d_col_idx) && upload(L->dq_units, &L->d_dq_units);
     if (!ok) {
       free_device_copies(L);
@@ -262,7 +263,7 @@ int s2_layout_get(const s2_layout* L, s2_layout_view* out) {
 int s2_layout_get_tiles(const s2_layout* L, int which, s2_tile_view* out) {
   if (!L || !out) return S2_ERR_NULL;
   if (which != S2_TILES_FWD && which != S2_TILES_DQ && which != S2_TILES_DKDV) return S2_ERR_BAD_PARAM;
-  const s2::TileList& t = which == S2_TILES_FWD ? L->fwd_tiles : which == S2_TILES_DQ ? L->q_tiles : L->kv_tiles;
+  const s2::TileList& t = which == S2_TILES_DKDV ? L->kv_tiles : L->q_tiles;
   out->ptr = t.ptr.data();
   out->ent = t.ent.data();
   out->order = t.order.data();
@@ -290,7 +291,7 @@ int s2_attn_fwd(const s2_layout* layout, const s2_tensors* t, float scale, void*
   if (!layout_on_current_device(layout)) return S2_ERR_NO_DEVICE;
   s2::AttnParams p = make_params(t, scale);
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->fwd_tiles);
+  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
   p.q_tiles = dev_tiles(layout->q_tiles);
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
@@ -340,7 +341,7 @@ int s2_attn_fwd_rows(const s2_layout* layout, const s2_tensors* t, int32_t q_row
   p.q_row0 = q_row_start;
   p.q_rows = q_rows;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->fwd_tiles);
+  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
   p.q_tiles = dev_tiles(layout->q_tiles);
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
@@ -362,7 +363,7 @@ int s2_attn_fwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.q_rows = max_seqlen;
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->fwd_tiles);
+  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
   p.q_tiles = dev_tiles(layout->q_tiles);
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   // one grid slot per (sequence, head, 128-row tile of the longest length allowed)
@@ -399,7 +400,7 @@ int s2_attn_bwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.q_rows = max_seqlen;
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->fwd_tiles);
+  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
   p.q_tiles = dev_tiles(layout->q_tiles);
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   p.delta = static_cast<float*>(workspace);
@@ -427,7 +428,7 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
   p.delta = static_cast<float*>(workspace);
   p.lse2 = p.delta + s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim) / 8;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->fwd_tiles);
+  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
   p.q_tiles = dev_tiles(layout->q_tiles);
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   // a workspace large enough to keep dS selects the backward that computes nothing twice

@@ -144,6 +144,16 @@ __device__ __forceinline__ void dma16_group(const void* gbase, uint32_t lds_base
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0" ::"s"(gbase), "s"(lds_base), "v"(o0)
                  : "m0");
 }
+// One load by the first kLanes lanes only.  EXEC is all ones where this is used (uniform control
+// flow, full wavefronts) and is put back; the scalar instruction between the write of M0 and the load
+// is the wait state M0 needs.
+template <int kLanes>
+__device__ __forceinline__ void dma16_lanes(const void* gbase, uint32_t lds_base, uint32_t off) {
+  static_assert(kLanes > 0 && kLanes < 64, "a part of the wavefront");
+  asm volatile("s_mov_b32 m0, %1\n\ts_bfm_b64 exec, %3, 0\n\tglobal_load_lds_dwordx4 %2, %0\n\ts_mov_b64 exec, -1"
+               ::"s"(gbase), "s"(lds_base), "v"(off), "n"(kLanes)
+               : "m0");
+}
 #pragma clang diagnostic pop
 
 template <int D, int ROWS = 64, int NW = 4>
@@ -269,6 +279,69 @@ struct DmaTile {
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_bit_cast(bf16x8, both);
+  }
+};
+
+// ---------------------------------------------------------------------------------------------
+// PieceTile: how the four wavefronts of a workgroup fill a 64-row DmaTile by pieces of 16 rows, one
+// piece each.  Sixteen padded rows are 4864 bytes (D = 128) or 3328 (D = 64), so a piece is a few
+// whole kilobytes and a remainder: the last load of a piece runs with only the lanes that still
+// belong to it (48 or 16 of them).  The four pieces are then back to back - the tile looks exactly
+// as if it had been filled front to back - and where each piece comes from is up to the wavefront
+// that fetches it: one scalar row number.  For mask blocks of 64 or 128 tokens the pieces are
+// consecutive; for 16- and 32-token blocks a chunk is gathered from whatever blocks come next in the
+// tile's list, at no cost per lane.
+// ---------------------------------------------------------------------------------------------
+template <int D>
+struct PieceTile {
+  static constexpr int kStride = DmaTile<D>::kStride;              // elements
+  static constexpr int kRows = 16;
+  static constexpr int kBytes = kRows * kStride * 2;               // 4864 / 3328
+  static constexpr int kFull = kBytes / 1024;                      // whole wavefront-wide loads: 4 / 3
+  static constexpr int kTailLanes = (kBytes - kFull * 1024) / 16;  // lanes of the last one: 48 / 16
+  static constexpr int kLoads = kFull + 1;
+  static constexpr int kGroups = 2;  // the whole loads (one write of M0), then the last
+  static constexpr uint32_t kBias = 3072;
+  static_assert(kFull >= 1 && kFull <= 4 && kTailLanes > 0 && kTailLanes < 64, "piece = a few whole loads and a remainder");
+
+  // Byte offset of each of this lane's loads from the piece's first row, plus kBias, minus the
+  // immediate the load is issued with (it is added to the LDS address and to the global one).
+  struct Plan {
+    uint32_t goff[kLoads];
+  };
+  __device__ static constexpr uint32_t imm(int n) { return n < kFull ? 1024u * n : 0u; }
+  __device__ static __forceinline__ Plan plan(int64_t row_stride, int lane) {
+    Plan pl;
+#pragma unroll
+    for (int n = 0; n < kLoads; ++n) {
+      const int pos = n * 1024 + lane * 16;
+      int row = pos / (kStride * 2);
+      int col = (pos - row * kStride * 2) / 16;
+      if (col >= D / 8) col -= D / 8;       // row padding: fetches a part of the row again, nothing reads it
+      if (row >= kRows) row = kRows - 1;    // (lanes the last load is issued without)
+      pl.goff[n] = (uint32_t)(row * row_stride * 2) + 16 * col + kBias - imm(n);
+    }
+    return pl;
+  }
+  // Group G of the loads of this wavefront's piece into `tile`.  gbase_biased: address of the piece's
+  // first row minus kBias bytes.  All 64 lanes must be active (the last load switches lanes off and
+  // on again by itself).
+  template <int G>
+  __device__ static __forceinline__ void issue(const Plan& pl, const void* gbase_biased, const uint16_t* tile, int wave) {
+    const uint32_t lds = lds_addr(tile) + wave * kBytes;
+    if constexpr (G == 0)
+      dma16_group<kFull>(gbase_biased, lds, pl.goff[0], pl.goff[kFull > 1 ? 1 : 0], pl.goff[kFull > 2 ? 2 : 0],
+                         pl.goff[kFull > 3 ? 3 : 0]);
+    else
+      dma16_lanes<kTailLanes>(gbase_biased, lds + kFull * 1024, pl.goff[kFull]);
+  }
+  // Limits a plan to pieces of which only the first `rows_valid` (>= 1) rows exist: no lane then reads
+  // past the last of them (later rows come out as copies of parts of it; nothing may use them).  A plan
+  // limited once can be limited again to fewer rows.
+  __device__ static __forceinline__ void limit(Plan& pl, int rows_valid, int64_t row_stride) {
+    const uint32_t last = (uint32_t)((rows_valid - 1) * row_stride * 2) + 2 * D - 16 + kBias;
+#pragma unroll
+    for (int n = 0; n < kLoads; ++n) pl.goff[n] = min(pl.goff[n], last - imm(n));
   }
 };
 

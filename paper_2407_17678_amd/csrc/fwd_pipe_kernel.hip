@@ -1,8 +1,18 @@
-// Forward kernel for head_dim 128 and mask blocks of 64 or 128 tokens: the fast path of
-// block-sparse causal attention (section 3.2: K/V tiles of the kept blocks only go through on-chip
-// memory; section 4.2: which blocks a head keeps).  Same tiles, lists, staging and orientation as
-// fwd_kernel.hip (a 128-row query tile that spans several mask rows, four wavefronts of 32 query
-// rows, scores computed transposed so that a lane owns one query); what differs is the inner loop:
+// Forward kernel: block-sparse causal attention with per-head lists of kept KV blocks (section 3.2:
+// iterate K/V tiles of the kept blocks through on-chip memory, softmax over the kept keys only;
+// section 4.2: which blocks a head keeps).  One workgroup owns a query tile of 128 rows that spans
+// several mask rows (the Merge-Q idea of section 3.2: a big tile, a fine mask); it walks the merged
+// list of KV blocks any of its rows keeps, 64 keys a step, and each of its four wavefronts (32 query
+// rows) leaves out what its own mask rows do not keep.
+//
+// Orientation: the score tile is computed transposed, S^T = K Q^T, so that a lane owns one query (one
+// column of the C layout).  Row max / row sum are then in-lane reductions plus one exchange with the
+// other half of the wavefront, and the probabilities feed the second contraction O^T += V^T P^T
+// straight from the accumulator registers.
+//
+// K and V chunks (64 keys) are brought in by direct global -> LDS loads, double buffered, each
+// wavefront fetching 16 of the 64 rows (PieceTile in device_util.h); K is read as row fragments, V
+// through the LDS transpose read.  The inner loop:
 //
 //   * it is software pipelined by one step: while the matrix pipe computes the scores of step i+1
 //     and then P(i) V(i), the vector pipe turns the scores of step i into probabilities and finds
@@ -15,7 +25,17 @@
 //     accumulators are rescaled in a rarely taken branch instead of in every step;
 //   * the direct loads of a tile are issued four to a write of M0 (their LDS targets are told apart
 //     by the instruction's immediate offset).
+//
+// One loop serves both head sizes, every block size and ragged ends.  Against the phase-by-phase kernel
+// that head_dim 64, blocks below 64 tokens and partial 128-row tiles used to run (per launch): 2 x 16
+// heads x 4096 x 64, blocks of 64: 38.3 -> 36.0 us; 2 x 16 x 3904 x 128 (61 blocks): 53.7 -> 48.8 us;
+// 1 x 16 x 8192 x 128, blocks of 16: 64.0 -> 54.5 us; a packed batch of 8 sequences of 200 to 8192 rows x 32
+// heads: 367 us in two launches -> 348 us in one.  What bounds it: with many steps per tile the matrix and
+// vector pipes (head_dim 128 about 1.05 PFLOP/s; at 64 the vector work per MFMA doubles), with few the
+// latency of a tile's start and end (about 12 us of a workgroup slot against 1.6 us per step).
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "config.h"
 #include "device_util.h"
@@ -29,53 +49,67 @@ namespace {
 constexpr float kNegInf = -__builtin_inff();
 constexpr float kTau = 8.0f;  // log2 units a score may exceed the reference maximum by
 
+// FINE: mask blocks of 16 or 32 tokens.  A step's 64 keys are then four pieces of 16 gathered from the
+// next blocks of the tile's list (entries of single blocks, with one bit per mask row of the tile), so
+// such masks run the same loop with full chunks, at the same rate, as blocks of 64 tokens; a wavefront's 32
+// rows are one or two mask rows, and a piece that not all of them keep whole is masked lane by lane.
+//
 // VARLEN: a packed batch of sequences of different lengths.  A workgroup finds its sequence's rows in
-// cu_seqlens and treats them as a sequence of its own; this kernel computes the whole 128-row tiles of
-// each sequence (all their keys exist), a partial last tile is left to fwd_kernel.
-template <int D, bool DENSE, bool VARLEN = false>
-__global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams p) {
+// cu_seqlens and treats them as a sequence of its own.  In its last, partial tile no lane fetches past
+// the sequence's last token (keys after it lie after every query, which the causal mask drops) and
+// stores are guarded per row.
+template <int D, bool DENSE, bool FINE, bool VARLEN>
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(const AttnParams p) {
   typedef DmaTile<D, 64, 4> Tile;
+  typedef PieceTile<D> Piece;
   __shared__ __attribute__((aligned(16))) uint16_t sk[2][Tile::kElems];
   __shared__ __attribute__((aligned(16))) uint16_t sv[2][Tile::kElems];
   constexpr int BM = kFwdBM, MW = 32, CH = 64;
   constexpr int KK = D / 16, DT = D / 32;
   constexpr int NQK = 2 * KK;  // MFMAs of the score contraction per step
   constexpr int NPV = 4 * DT;  // MFMAs of the second contraction per step
-  constexpr int NG = Tile::kGroups;
-  constexpr int kLead = 5, kRing = kLead + 1;  // LDS fragments are requested kLead MFMAs ahead (3 to 7 measure the same)
-  static_assert(D == 128, "the slot schedule below is laid out for head_dim 128");
-  static_assert(NQK == 16 && NPV == 16, "32 slots");
+  constexpr int NS = NQK + NPV;
+  constexpr int NG = Piece::kGroups;
+  // LDS fragments are requested kLead MFMAs ahead (3 to 7 measure the same at D = 128; at D = 64 three keep a
+  // wavefront at 168 registers, so that three fit a SIMD)
+  constexpr int kLead = D == 128 ? 5 : 3, kRing = kLead + 1;
+  static_assert(!(DENSE && (FINE || VARLEN)), "the dense form walks 64-key blocks of whole sequences");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-  const int T = p.fwd_tiles.tiles_per_head;    // tiles of the whole sequence (indexes the lists)
-  const int T_run = p.q_rows / BM;             // tiles this launch computes
+  const int T = p.fwd_tiles.tiles_per_head;      // tiles of the whole sequence (indexes the lists)
+  const int T_run = (p.q_rows + BM - 1) / BM;    // tiles this launch computes
   int bh, rank;
   if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
+  // longest tiles first: by the layout's order for a whole sequence, else simply last row first
   const bool whole = !VARLEN && p.q_row0 == 0 && T_run == T;
   int tile = (DENSE || !whole) ? p.q_row0 / BM + (T_run - 1 - rank) : p.fwd_tiles.order[h * T + rank];
-  int N = p.seqlen, row_base = 0;  // my sequence's length, and the rows of the tensors before it
+  // my sequence's length, its query rows in this call, and the rows of the tensors before it
+  int N = p.seqlen, n_q = p.q_rows, row_base = 0;
   if (VARLEN) {
     const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
     row_base = min(max(lo, 0), p.seqlen);  // whatever the array holds, stay inside the tensors
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
-    const int T_full = N / BM;
-    if (rank >= T_full) return;
-    tile = T_full - 1 - rank;
+    n_q = N;
+    const int T_seq = (N + BM - 1) / BM;
+    if (rank >= T_seq) return;
+    tile = T_seq - 1 - rank;
   }
-  const int S = DENSE ? CH : p.block_size;  // 64 or 128
-  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;
+  const int S = DENSE ? CH : p.block_size;  // FINE: 16 or 32, else 64 or 128
+  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
+  const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-key pieces per list entry
   const int qw0 = tile * BM + wave * MW;    // first query row of this wavefront (sequence position)
   const int ql0 = qw0 - p.q_row0;           // the same as a row of q / o / lse
+  const bool wave_on = ql0 < n_q;           // whether I have query rows at all
   const int my_member = (qw0 / S) - tile * (BM / S);
 
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
   // minus the bias the grouped direct loads put into their lane offsets
-  const uint16_t* kb = p.k + kv_off - Tile::kBias / 2;
-  const uint16_t* vb = p.v + kv_off - Tile::kBias / 2;
+  const uint16_t* kb = p.k + kv_off - Piece::kBias / 2;
+  const uint16_t* vb = p.v + kv_off - Piece::kBias / 2;
 
   int ent_lo = 0, n_ent;
   if (DENSE) {
@@ -84,41 +118,88 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
     ent_lo = p.fwd_tiles.ptr[h * T + tile];
     n_ent = p.fwd_tiles.ptr[h * T + tile + 1] - ent_lo;
   }
-  const int total = n_ent << cpb_sh;
+  // steps: chunks of an entry, or (FINE) as many as the entries' pieces fill
+  const int total = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent << cpb_sh;
   if (total <= 0) return;
   EntryList list;
   if (!DENSE) list.init(p.fwd_tiles.ent + ent_lo, n_ent, lane);
 
-  // Q^T fragments stay in registers for the whole tile (B operands of the score MFMAs)
+  // Q^T fragments stay in registers for the whole tile (B operands of the score MFMAs); a lane without
+  // a row of its own reads the last row, its result is never stored
   bf16x8 qf[KK];
+  const int q_lane = min(ql0 + l32, n_q - 1);
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk)
-    qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + q_off + (int64_t)(ql0 + l32) * p.q_st + 16 * kk + 8 * half);
+    qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + q_off + (int64_t)q_lane * p.q_st + 16 * kk + 8 * half);
 
-  // step j of the tile's list (clamped to the last one): its first key row, and whether this
-  // wavefront has anything to compute there (its mask row keeps the block, and not every key lies
-  // after every one of its queries)
-  auto chunk_at = [&](int j, int& kv0, bool& act) S2_INLINE {
+  // FINE: piece pc (0..3) of step j: its first key row, and which of my two groups of 16 query rows keep
+  // it (bits 0 and 1; both or neither for 32-token blocks)
+  auto piece_at = [&](int j, int pc, int& row, int& bits) S2_INLINE {
+    const int x = 4 * j + pc;
+    const int i = x >> ppe_sh;
+    const uint32_t e = (uint32_t)list.peek(min(i, n_ent - 1));
+    row = (int)(e >> 16) * S + ((x & ppe_sh) << 4);
+    bits = ppe_sh ? ((e >> wave) & 1) * 3 : (e >> (2 * wave)) & 3;
+    if (i >= n_ent) bits = 0;
+  };
+  // Step j of the tile's list (clamped to the last one): the first key row of the 16 that I fetch;
+  // whether I have anything to compute there (my mask rows keep some of it, and not every key lies
+  // after every one of my queries); and whether some of it has to be masked for me.
+  auto chunk_at = [&](int j, int& row, bool& act, bool& masked) S2_INLINE {
     const bool inside = j < total;
     j = min(j, total - 1);
-    if (DENSE) {
-      kv0 = j * CH;
-      act = inside && kv0 <= qw0 + MW - 1;
+    if constexpr (FINE) {
+      int all = 0xFF, any = 0, last = 0;
+      row = 0;
+#pragma unroll
+      for (int pc = 0; pc < 4; ++pc) {
+        int r, bits;
+        piece_at(j, pc, r, bits);
+        all &= bits | ~3;
+        any |= bits;
+        if (pc == wave) row = r;
+        last = r;
+      }
+      act = inside && wave_on && any != 0;
+      masked = all != 0xFF || last + 15 > qw0;
     } else {
-      const int e = list.peek(j >> cpb_sh);
-      kv0 = (e >> 16) * S + (j & cpb_m) * CH;
-      act = inside && ((e >> my_member) & 1) && kv0 <= qw0 + MW - 1;
+      int kv0;
+      bool keep = true;
+      if (DENSE) {
+        kv0 = j * CH;
+      } else {
+        const int e = list.peek(j >> cpb_sh);
+        kv0 = (e >> 16) * S + (j & cpb_m) * CH;
+        keep = (e >> my_member) & 1;
+      }
+      row = kv0 + 16 * wave;
+      act = inside && wave_on && keep && kv0 <= qw0 + MW - 1;
+      masked = kv0 + CH - 1 > qw0;
     }
+    if (VARLEN) row = min(row, N - 1);
   };
 
   f32x16 acc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x16{};
   float m_ref = kNegInf;  // reference maximum (raw scores) of my query
-  float mc = kNegInf;     // the same times scale * log2(e); 0 while nothing was seen
+  float mc = 0.f;         // the same times scale * log2(e); 0 while nothing was seen
   float l_run = 0.f;      // sum of the probabilities over my half's key rows
   const float c = p.scale_log2e;
-  const typename Tile::BlockPlan plan = Tile::block_plan(p.kv_st, wave, lane);
+  // The lane offsets of my direct loads, for K and for V.  Where a packed sequence ends inside the rows
+  // I fetch (VARLEN) they are limited to the rows that exist; the lists ascend, so from then on every
+  // piece is such a piece, with fewer and fewer rows.
+  typename Piece::Plan plan_k = Piece::plan(p.kv_st, lane), plan_v = plan_k;
+  auto limit_plan = [&](typename Piece::Plan& pl, int row) S2_INLINE {
+    if (VARLEN && row + 16 > N) Piece::limit(pl, N - row, p.kv_st);
+  };
+  // group g of the loads of my 16 rows from key row `row` on
+  auto dma_k = [&](auto gc, int row, const uint16_t* stage) S2_INLINE {
+    Piece::template issue<decltype(gc)::value>(plan_k, kb + (int64_t)row * p.kv_st, stage, wave);
+  };
+  auto dma_v = [&](auto gc, int row, const uint16_t* stage) S2_INLINE {
+    Piece::template issue<decltype(gc)::value>(VARLEN ? plan_v : plan_k, vb + (int64_t)row * p.kv_st, stage, wave);
+  };
   const int trb = Tile::tr_base(lane);
 
   // scores [parity of the step][32-key half].  Zero to begin with: the registers of a step this
@@ -181,17 +262,29 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
       }
     }
   };
-  // element index reached after slot sl: five elements every four slots
-  auto p_upto = [](int sl) S2_INLINE { return (5 * (sl + 1)) / 4; };
-  auto mask_diag = [&](f32x16 (&sn)[2], int kv0) S2_INLINE {
+  // element index reached after slot sl: five elements every four slots, or (D = 64) three a slot
+  constexpr int kPace = D == 128 ? 40 : 48;
+  auto p_upto = [](int sl) S2_INLINE { return (kPace * (sl + 1)) / NS; };
+  // drops what my query does not see of step j: keys after it and (FINE) pieces its mask row does not keep
+  auto mask_step = [&](f32x16 (&sn)[2], int j) S2_INLINE {
     const int qpos = qw0 + l32;
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kv0 + 32 * kt + 8 * (r >> 2) + 4 * half + (r & 3);
-        if (key > qpos) sn[kt][r] = kNegInf;
+    for (int pc = 0; pc < 4; ++pc) {
+      int row, bits = 3;
+      if constexpr (FINE) {
+        piece_at(j, pc, row, bits);
+      } else if (DENSE) {
+        row = j * CH + 16 * pc;
+      } else {
+        row = (list.peek(j >> cpb_sh) >> 16) * S + (j & cpb_m) * CH + 16 * pc;
       }
+      // how many of the piece's keys I see, counted from the first one my half of the wavefront holds
+      int lim = qpos - row + 1 - 4 * half;
+      if (FINE && !((bits >> (l32 >> 4)) & 1)) lim = -4;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (8 * (i >> 2) + (i & 3) >= lim) sn[pc >> 1][8 * (pc & 1) + i] = kNegInf;
+    }
   };
   // running maximum over score registers r0 .. r1-1 (of 32)
   auto max_part = [&](int r0, int r1, const f32x16 (&sn)[2], float& mx) S2_INLINE {
@@ -202,7 +295,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
   // first step, when it is -inf) and rescales what has been accumulated so far
   auto update_ref = [&](float mx) S2_INLINE {
     mx = max_halves(mx);
-    if (__any(__builtin_fmaf(mx, c, -mc) > kTau)) {
+    // (a lane that has seen no key yet has m_ref = -inf: its first score always exceeds that, and while it
+    // sees none the difference is not a number, which does not)
+    if (__any((mx - m_ref) * c > kTau)) {
       const float m_new = fmaxf(m_ref, mx);
       const float m_use = (m_new == kNegInf) ? 0.f : m_new;
       const float alpha = fast_exp2((m_ref - m_use) * c);
@@ -216,9 +311,9 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
     }
   };
   // maximum of the scores in sn (masked on the diagonal), then the reference maximum
-  auto finish_scores = [&](f32x16 (&sn)[2], int kv0, bool act, bool masked, float mx) S2_INLINE {
+  auto finish_scores = [&](f32x16 (&sn)[2], int j, bool act, bool masked, float mx) S2_INLINE {
     if (masked) {
-      mask_diag(sn, kv0);
+      mask_step(sn, min(j, total - 1));
       mx = kNegInf;
       max_part(0, 32, sn, mx);
     }
@@ -231,16 +326,21 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
   // lies after its queries) runs through the same instruction stream when the step before or
   // after it is its own, with its scores kept out of the maximum and its probabilities forced to
   // zero; two such steps in a row are skipped.
-  int kv0_c, kv0_n, kv0_nn;
-  bool act_c, act_n, act_nn;
-  chunk_at(0, kv0_c, act_c);
-  chunk_at(1, kv0_n, act_n);
-  static_for<NG>([&](auto gc) S2_INLINE {
-    constexpr int g = decltype(gc)::value;
-    Tile::template issue_group<g>(plan, kb + (int64_t)kv0_c * p.kv_st, sk[0], wave);
-    Tile::template issue_group<g>(plan, vb + (int64_t)kv0_c * p.kv_st, sv[0], wave);
-    Tile::template issue_group<g>(plan, kb + (int64_t)kv0_n * p.kv_st, sk[1], wave);
-  });
+  int row_n, row_nn;  // the key rows I fetch of the next step and the one after it
+  bool act_c, act_n, act_nn, masked_c, masked_n, masked_nn;
+  {
+    int row_c;
+    chunk_at(0, row_c, act_c, masked_c);
+    chunk_at(1, row_n, act_n, masked_n);
+    limit_plan(plan_k, row_c);
+    limit_plan(plan_v, row_c);
+    static_for<NG>([&](auto gc) S2_INLINE {
+      dma_k(gc, row_c, sk[0]);
+      dma_v(gc, row_c, sv[0]);
+    });
+    limit_plan(plan_k, row_n);
+    static_for<NG>([&](auto gc) S2_INLINE { dma_k(gc, row_n, sk[1]); });
+  }
   wait_all_loads();
   __syncthreads();
   if (act_c) {
@@ -254,7 +354,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
       S2_FENCE();
     });
   }
-  finish_scores(s[0], kv0_c, act_c, true, kNegInf);  // `true`: the first step may be the diagonal
+  {
+    float mx = kNegInf;
+    if (!masked_c) max_part(0, 32, s[0], mx);
+    finish_scores(s[0], 0, act_c, masked_c, mx);
+  }
   __syncthreads();  // all wavefronts are done with K(0) before step 0 loads K(2) over it
 
   // ------------------------------------------------------------------ one step
@@ -262,23 +366,21 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
   // maximum already covers them.
   auto step = [&](int it, f32x16 (&sc)[2], f32x16 (&sn)[2]) S2_INLINE {
     const int par = it & 1;
-    chunk_at(it + 2, kv0_nn, act_nn);
-    const uint16_t* kg = kb + (int64_t)kv0_nn * p.kv_st;  // K(it+2) -> the stage K(it) was in
-    const uint16_t* vg = vb + (int64_t)kv0_n * p.kv_st;   // V(it+1) -> the stage V(it-1) was in
+    chunk_at(it + 2, row_nn, act_nn, masked_nn);
     const uint16_t* ks = sk[par ^ 1];
     const uint16_t* vs = sv[par];
-    uint16_t* kn = sk[par];
-    uint16_t* vn = sv[par ^ 1];
-    // group d of this step's direct loads: 0..NG-1 for K, NG..2*NG-1 for V
-    auto dma = [&](auto dc) S2_INLINE {
+    // group d of this step's direct loads: 0..NG-1 for K(it+2), into the stage K(it) was in, then
+    // V(it+1), into the stage V(it-1) was in
+    auto step_dma = [&](auto dc) S2_INLINE {
       constexpr int d = decltype(dc)::value;
       if constexpr (d < NG)
-        Tile::template issue_group<d>(plan, kg, kn, wave);
-      else if constexpr (d < 2 * NG)
-        Tile::template issue_group<d - NG>(plan, vg, vn, wave);
+        dma_k(dc, row_nn, sk[par]);
+      else
+        dma_v(std::integral_constant<int, d - NG>{}, row_n, sv[par ^ 1]);
     };
+    limit_plan(plan_k, row_nn);
+    limit_plan(plan_v, row_n);
     if (act_c || act_n) {
-      const bool mask_next = kv0_n + CH - 1 > qw0;
       // a step that is not mine: every probability exp2(s*c - inf) = 0
       const float mc_keep = mc;
       if (!act_c) mc = __builtin_inff();
@@ -289,37 +391,41 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
       for (int f = 0; f < kLead; ++f) frag_load(f, ks, vs, fr);
       S2_FENCE();
       // NQK + NPV slots, one MFMA each
-      static_for<NQK + NPV>([&](auto slc) S2_INLINE {
+      static_for<NS>([&](auto slc) S2_INLINE {
         constexpr int sl = decltype(slc)::value;
-        if constexpr (sl + kLead < NQK + NPV) frag_load(sl + kLead, ks, vs, fr);
+        if constexpr (sl + kLead < NS) frag_load(sl + kLead, ks, vs, fr);
         if constexpr (sl < NQK)
           qk_mfma(sl, sn, fr);
         else
           pv_mfma(sl - NQK, fr, pb);
-        // probabilities of this step, five elements every four slots, each stage one slot behind
-        // the one before it (elements 8 g .. 8 g + 7 are packed by slot 7 g + 8 at the latest,
-        // their MFMAs start at slot 16 + 4 g)
+        // probabilities of this step, each stage one slot behind the one before it (elements
+        // 8 g .. 8 g + 7 are packed before slot NQK + DT * g, where their MFMAs start)
+        static_assert(kPace * (NQK - 2) / NS >= 8 && kPace * (NQK + 3 * DT - 2) / NS >= 32, "packed in time");
         p_stage1(p_upto(sl - 1), p_upto(sl), sc);
         p_stage2(p_upto(sl - 2), p_upto(sl - 1), sc);
         p_stage3(p_upto(sl - 3), p_upto(sl - 2), sc, pb);
         // maximum of the next step's scores, once its MFMAs are done
-        if constexpr (sl >= 18 && sl < 26) max_part(4 * (sl - 18), 4 * (sl - 18) + 4, sn, mx);
+        constexpr int kMaxSlots = D == 128 ? 8 : 6, kMaxStep = D == 128 ? 4 : 6;
+        static_assert(NQK + 2 + kMaxSlots <= NS && kMaxSlots * kMaxStep >= 32, "all 32 registers");
+        if constexpr (sl >= NQK + 2 && sl < NQK + 2 + kMaxSlots)
+          max_part(kMaxStep * (sl - NQK - 2), std::min(32, kMaxStep * (sl - NQK - 1)), sn, mx);
         // Nothing to execute: ties the running sum and maximum to this slot, or the optimiser
         // collects their additions and comparisons after the last MFMA.
         asm volatile("" : "+v"(l_run), "+v"(mx));
-        if constexpr (sl < 2 * NG) dma(std::integral_constant<int, sl>{});
+        if constexpr (sl < 2 * NG) step_dma(std::integral_constant<int, sl>{});
         S2_FENCE();
       });
       mc = mc_keep;
-      finish_scores(sn, kv0_n, act_n, mask_next, mx);
+      finish_scores(sn, it + 1, act_n, masked_n, mx);
     } else {
-      static_for<2 * NG>([&](auto dc) S2_INLINE { dma(dc); });
+      static_for<2 * NG>([&](auto dc) S2_INLINE { step_dma(dc); });
     }
-    if (!DENSE) (void)list.get(min(it + 1, total - 1) >> cpb_sh, lane);  // keeps the entry window moving
-    kv0_c = kv0_n;
+    // keeps the entry window moving (entries of step it+1 on)
+    if (!DENSE) (void)list.get(FINE ? min((4 * (it + 1)) >> ppe_sh, n_ent - 1) : min(it + 1, total - 1) >> cpb_sh, lane);
     act_c = act_n;
-    kv0_n = kv0_nn;
+    row_n = row_nn;
     act_n = act_nn;
+    masked_n = masked_nn;
     wait_all_loads();
     __syncthreads();
   };
@@ -336,6 +442,7 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
   // region of its own, so no barrier): a lane holds its row's features four at a time, and storing
   // them from there would touch 32 rows per instruction with 16 bytes each; read back 16 bytes per
   // lane, row after row, an instruction stores four whole rows.
+  if (!wave_on) return;
   const float l_tot = sum_halves(l_run);
   const float inv = 1.0f / l_tot;
   constexpr int RS = D + 8;  // staging row stride (elements): 8-byte writes of a row group spread over the banks
@@ -351,34 +458,39 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_pipe_kernel(const AttnParams 
       *reinterpret_cast<bf16x4*>(stage + l32 * RS + 32 * dt + 8 * g + 4 * half) = w;
     }
   uint16_t* obase = p.o + q_off + (int64_t)ql0 * p.q_st;
+  constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
 #pragma unroll
-  for (int i = 0; i < MW / 4; ++i) {
-    const int r = 4 * i + (lane >> 4), piece = lane & 15;
+  for (int i = 0; i < MW / RPI; ++i) {
+    const int r = RPI * i + lane / PPR, piece = lane % PPR;
     const u32x4 x = *reinterpret_cast<const u32x4*>(stage + r * RS + 8 * piece);
-    *reinterpret_cast<u32x4*>(obase + (int64_t)r * p.q_st + 8 * piece) = x;
+    if (!VARLEN || ql0 + r < n_q) *reinterpret_cast<u32x4*>(obase + (int64_t)r * p.q_st + 8 * piece) = x;
   }
   const int64_t lse_row = VARLEN ? (int64_t)h * p.seqlen + row_base + ql0 + l32  // [heads, rows of the tensors]
                                  : ((int64_t)b * p.heads + h) * p.q_rows + ql0 + l32;
-  if (half == 0) p.lse[lse_row] = m_ref * p.scale + __logf(l_tot);
+  if (half == 0 && (!VARLEN || ql0 + l32 < n_q)) p.lse[lse_row] = m_ref * p.scale + __logf(l_tot);
+}
+
+template <int D>
+hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
+  const dim3 grid(grid_for(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM)), block(kThreads);
+  const bool fine = !dense && p.block_size < 64;
+  if (dense)
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, true, false, false>), grid, block, 0, stream, p);
+  else if (p.cu_seqlens && fine)
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true, true>), grid, block, 0, stream, p);
+  else if (p.cu_seqlens)
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false, true>), grid, block, 0, stream, p);
+  else if (fine)
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true, false>), grid, block, 0, stream, p);
+  else
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false, false>), grid, block, 0, stream, p);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-bool fwd_pipe_applies(const AttnParams& p, bool dense) {
-  if (p.cu_seqlens)  // packed batch: the whole tiles of each sequence
-    return !dense && p.head_dim == 128 && p.block_size >= 64 && p.q_row0 == 0 && p.q_rows >= kFwdBM;
-  return p.head_dim == 128 && (dense || p.block_size >= 64) && p.q_rows % 128 == 0 && p.q_row0 % 128 == 0;
-}
-
-hipError_t launch_fwd_pipe(const AttnParams& p, bool dense, hipStream_t stream) {
-  const int grid = grid_for(p.batch * p.heads, p.q_rows / kFwdBM);
-  if (p.cu_seqlens)
-    hipLaunchKernelGGL((fwd_pipe_kernel<128, false, true>), dim3(grid), dim3(kThreads), 0, stream, p);
-  else if (dense)
-    hipLaunchKernelGGL((fwd_pipe_kernel<128, true>), dim3(grid), dim3(kThreads), 0, stream, p);
-  else
-    hipLaunchKernelGGL((fwd_pipe_kernel<128, false>), dim3(grid), dim3(kThreads), 0, stream, p);
-  return hipGetLastError();
+hipError_t launch_fwd(const AttnParams& p, bool dense, hipStream_t stream) {
+  return p.head_dim == 128 ? launch_one<128>(p, dense, stream) : launch_one<64>(p, dense, stream);
 }
 
 }  // namespace s2

@@ -83,11 +83,6 @@ struct DecodeParams {
 
 // Each returns the hipError_t of the launch (hipGetLastError after the launch).
 hipError_t launch_fwd(const AttnParams& p, bool dense, hipStream_t stream);
-// The forward's fast path (head_dim 128, mask blocks of 64 or 128 tokens, whole 128-row tiles; of a
-// packed batch the whole tiles of each sequence): whether it covers a call, and its launch.  launch_fwd
-// uses it where it applies.
-bool fwd_pipe_applies(const AttnParams& p, bool dense);
-hipError_t launch_fwd_pipe(const AttnParams& p, bool dense, hipStream_t stream);
 // `stages` selects which of the three backward launches run: 1 = delta, 2 = dK/dV, 4 = dQ.
 constexpr int kBwdDelta = 1, kBwdDkDv = 2, kBwdDq = 4, kBwdAll = 7;
 hipError_t launch_bwd(const AttnParams& p, bool dense, int stages, hipStream_t stream);

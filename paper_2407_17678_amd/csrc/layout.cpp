@@ -194,10 +194,9 @@ int build_from_csr(int num_heads, int num_blocks, int block_size, const int32_t*
 // column tiles of one length that a head must have before they walk their rows in step (see below)
 constexpr int kRotateMinTiles = 8;
 
-void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
-  // partner blocks per entry: the kernels walk partners in units of at least 32 tokens, so with
-  // 16-token blocks an entry covers two of them
-  const int sub = L.p.block_size < 32 ? 32 / L.p.block_size : 1;
+namespace {
+// sub: partner blocks per entry
+void build_lists(const s2_layout& L, int group, bool transpose, int sub, TileList& out) {
   const int H = L.p.num_heads, B = L.p.num_blocks;
   const std::vector<int32_t>& ptr = transpose ? L.col_ptr : L.row_ptr;
   const std::vector<int32_t>& idx = transpose ? L.row_idx : L.col_idx;
@@ -241,7 +240,7 @@ void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
             bits |= 1 << (r * sub + idx[cur[r]] % sub);
             ++cur[r];
           }
-        out.ent.push_back((int32_t)((best << 16) | bits));
+        out.ent.push_back((int32_t)(((uint32_t)best << 16) | (uint32_t)bits));
       }
       // Column tiles are walked from the last query block down.  Every stripe tile of a head ends
       // at the last row, so tiles started together then read the same Q / dO blocks at the same
@@ -267,7 +266,7 @@ void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
         const int n = hp[t + 1] - hp[t];
         if (n < 2 || same[n] < kRotateMinTiles) continue;
         int32_t* e = out.ent.data() + hp[t];
-        const int top = e[0] >> 16, bottom = e[n - 1] >> 16;
+        const int top = (int)((uint32_t)e[0] >> 16), bottom = (int)((uint32_t)e[n - 1] >> 16);
         if (top - bottom != n - 1) continue;  // not one unbroken run
         std::rotate(e, e + (top - (top / n) * n), e + n);
       }
@@ -278,6 +277,17 @@ void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
     const int32_t* hp = out.ptr.data() + (size_t)h * T;
     std::stable_sort(ord, ord + T, [&](int a, int b) { return hp[a + 1] - hp[a] > hp[b + 1] - hp[b]; });
   }
+}
+
+}  // namespace
+
+void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
+  // an entry covers partners in units of at least 32 tokens: two blocks of 16
+  build_lists(L, group, transpose, L.p.block_size < 32 ? 32 / L.p.block_size : 1, out);
+}
+
+void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
+  build_lists(L, group, transpose, 1, out);
 }
 
 void build_ds_units(s2_layout& L) {
