@@ -261,12 +261,10 @@ def bench_train(w, steps, warmup, with_dense=True, with_bwd=True, dense_steps=3,
 
     # roofline of the dominant kernel.  Flops attributed per kernel (sums to 14*D*pairs):
     # forward 4*D*pairs (QK^T, PV); dK/dV kernel 8*D*pairs (S, dP, dV, dK); dQ kernel 2*D*pairs.
-    # (head_dim 128 with mask blocks of 64 tokens or more runs the hand-scheduled dQ kernel)
-    fast = D == 128 and S >= 64 and N % 128 == 0
     kernels = {"fwd_pipe_kernel": (res["ms_fwd"], 4.0)}
     if with_bwd:
         kernels["dkdv_kernel"] = (res["ms_bwd_dkdv"], 8.0)
-        dq_name = "dq_gemm_kernel" if res["backward_path"] == "keeping dS" else "dq_pipe_kernel" if fast else "dq_kernel"
+        dq_name = "dq_gemm_kernel" if res["backward_path"] == "keeping dS" else "dq_pipe_kernel"
         kernels[dq_name] = (res["ms_bwd_dq"], 2.0)
     dom = max(kernels, key=lambda n: kernels[n][0])
     ach = kernels[dom][1] * D * pairs / (kernels[dom][0] * 1e-3) / 1e12

@@ -292,7 +292,7 @@ int s2_attn_fwd(const s2_layout* layout, const s2_tensors* t, float scale, void*
   s2::AttnParams p = make_params(t, scale);
   p.block_size = layout->p.block_size;
   p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = dev_tiles(layout->q_tiles);
+  p.q_tiles = p.fwd_tiles;
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
@@ -342,7 +342,7 @@ int s2_attn_fwd_rows(const s2_layout* layout, const s2_tensors* t, int32_t q_row
   p.q_rows = q_rows;
   p.block_size = layout->p.block_size;
   p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = dev_tiles(layout->q_tiles);
+  p.q_tiles = p.fwd_tiles;
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
@@ -364,7 +364,7 @@ int s2_attn_fwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
   p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = dev_tiles(layout->q_tiles);
+  p.q_tiles = p.fwd_tiles;
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   // one grid slot per (sequence, head, 128-row tile of the longest length allowed)
   const int64_t slots = 8 * (((int64_t)num_seqs * t->heads + 7) / 8) * ((max_seqlen + s2::kFwdBM - 1) / s2::kFwdBM);
@@ -401,7 +401,7 @@ int s2_attn_bwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
   p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = dev_tiles(layout->q_tiles);
+  p.q_tiles = p.fwd_tiles;
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   p.delta = static_cast<float*>(workspace);
   p.lse2 = p.delta + need / 8;
@@ -429,7 +429,7 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
   p.lse2 = p.delta + s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim) / 8;
   p.block_size = layout->p.block_size;
   p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = dev_tiles(layout->q_tiles);
+  p.q_tiles = p.fwd_tiles;
   p.kv_tiles = dev_tiles(layout->kv_tiles);
   // a workspace large enough to keep dS selects the backward that computes nothing twice
   const size_t small = s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim);

@@ -4,9 +4,9 @@
 // Two launches (three kernels exist), no atomics, bitwise reproducible:
 //   delta  : delta[t] = sum_d dO[t][d] * O[t][d].  Folded into the dq launch, which holds the dO
 //            fragments anyway; the stand-alone kernel runs only when dK/dV is asked for alone.
-//   dq     : row-stationary.  A workgroup owns 128 query rows and walks the merged list of KV
-//            blocks its mask rows keep (as the forward does), recomputing P and forming
-//            dS = P * (dP - delta), dQ += scale * dS K.
+//   dq     : row-stationary, in dq_pipe_kernel.hip (dq_gemm_kernel.hip where dS is kept).  A workgroup
+//            owns 128 query rows and walks the merged list of KV blocks its mask rows keep (as the
+//            forward does), recomputing P and forming dS = P * (dP - delta), dQ += scale * dS K.
 //   dkdv   : column-stationary.  A workgroup owns 128 keys - one or two mask columns, paired by
 //            the layout builder so that both are attended by nearly the same query blocks - and
 //            walks the query blocks that keep them: dV += P^T dO, dK += scale * dS^T Q.
@@ -58,235 +58,6 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p) {
     p.delta[row] = acc;
     p.lse2[row] = p.lse[row] * kLog2e;  // the main kernels want LSE in base-2 units
   }
-}
-
-// ------------------------------------------------------------------------------------ dq
-
-// CH = keys per step: 64, or 32 for 32-token mask blocks.
-template <int D, int CH>
-struct DqSmem {
-  uint16_t k[2][DmaTile<D, CH>::kElems];
-  uint16_t v[2][DmaTile<D, CH>::kElems];
-};
-
-// VARLEN: a packed batch of sequences of different lengths (see the forward kernel): the workgroup
-// finds its sequence in cu_seqlens; loads that would pass the sequence's last token are clamped to
-// it (keys there lie after every query, which the causal mask drops) and stores are guarded per lane.
-template <int D, bool DENSE, int CH, bool VARLEN = false>
-__global__ __launch_bounds__(kThreads, 2) void dq_kernel(const AttnParams p) {
-  typedef DmaTile<D, CH> Tile;
-  constexpr int KT = CH / 32;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  DqSmem<D, CH>& sm = *reinterpret_cast<DqSmem<D, CH>*>(smem_raw);
-
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-  const int T = p.q_tiles.tiles_per_head;
-  // (of a packed batch's sequences possibly the last tile only)
-  const int T_run = VARLEN ? (p.varlen_tail ? 1 : (p.q_rows + kBwdBM - 1) / kBwdBM) : T;
-  int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, bh, rank)) return;
-  const int b = bh / p.heads, h = bh - b * p.heads;
-  int tile = DENSE ? (T - 1 - rank) : VARLEN ? 0 : p.q_tiles.order[h * T + rank];
-  int row_base = 0, N = p.seqlen;
-  if (VARLEN) {
-    const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
-    row_base = min(max(lo, 0), p.seqlen);  // whatever the array holds, stay inside the tensors
-    N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
-    const int T_seq = (N + kBwdBM - 1) / kBwdBM;
-    if (rank >= T_seq) return;
-    tile = T_seq - 1 - rank;
-    if (p.varlen_tail && N % kBwdBM == 0) return;  // no partial tile: the fast-path launch has computed them all
-  }
-  const int S = DENSE ? kChunk : p.block_size;
-  // 16-token blocks: a list entry is a unit of two blocks (32 keys, one step) and my 32 query rows
-  // are two mask rows, so which keys a lane may see is a 2 x 2 pattern of bits per wavefront
-  const bool fine = !DENSE && CH == 32 && S == 16;
-  const int Sg = fine ? 32 : S;  // tokens per list entry
-  const int cpb = Sg / CH;  // a power of two: / and % below are a shift and a mask
-  const int cpb_sh = __builtin_ctz(cpb), cpb_m = cpb - 1;
-  const int qw0 = tile * kBwdBM + wave * 32;
-  const bool wave_active = qw0 < N;
-  const int my_member = (qw0 / Sg) - tile * (kBwdBM / Sg);
-
-  const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
-  const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
-  const uint16_t* kb = p.k + kv_off;
-  const uint16_t* vb = p.v + kv_off;
-
-  int ent_lo = 0, n_ent;
-  if (DENSE) {
-    n_ent = min(N, (tile + 1) * kBwdBM) / kChunk;  // dense blocks are kChunk keys
-  } else {
-    ent_lo = p.q_tiles.ptr[h * T + tile];
-    n_ent = p.q_tiles.ptr[h * T + tile + 1] - ent_lo;
-  }
-  const int total = n_ent * cpb;
-  EntryList list;
-  if (!DENSE) list.init(p.q_tiles.ent + ent_lo, n_ent, lane);
-  // chunk `it` of the tile's list: its first row, and whether my mask row / column keeps it
-  // `pat` (16-token blocks only): bit 2m + c set when mask row m of my two keeps block c of the unit
-  auto chunk_of = [&](int it, int& kv0, bool& keep, int& pat) {
-    pat = 0xF;
-    if (DENSE) {
-      kv0 = it * CH;
-      keep = true;
-    } else {
-      const int e = list.get((it >> cpb_sh), lane);
-      kv0 = (e >> 16) * Sg + ((it & cpb_m)) * CH;
-      if (fine) {
-        pat = (e >> (4 * wave)) & 0xF;
-        keep = pat != 0;
-      } else {
-        keep = (e >> my_member) & 1;
-      }
-    }
-  };
-  // first row of chunk it+1, right after chunk_of(it)
-  auto next_chunk_of = [&](int it, int& kv0_n) {
-    if (DENSE) {
-      kv0_n = (it + 1) * CH;
-    } else {
-      const int e = ((it + 1) >> cpb_sh) == (it >> cpb_sh) ? list.get((it >> cpb_sh), lane) : list.peek_next((it >> cpb_sh));
-      kv0_n = (e >> 16) * Sg + (((it + 1) & cpb_m)) * CH;
-    }
-  };
-
-  const typename Tile::Plan plan = Tile::plan(p.kv_st, wave, lane);
-  const int trb = Tile::tr_base(lane);
-  if (total > 0) {
-    int kv0, pat;
-    bool keep;
-    chunk_of(0, kv0, keep, pat);
-    if (VARLEN && kv0 + CH > N) {
-      const typename Tile::Plan pr = Tile::plan_rows(p.kv_st, wave, lane, N - kv0);
-      Tile::issue(pr, kb + (int64_t)min(kv0, N - 1) * p.kv_st, sm.k[0], wave);
-      Tile::issue(pr, vb + (int64_t)min(kv0, N - 1) * p.kv_st, sm.v[0], wave);
-    } else {
-      Tile::issue(plan, kb + (int64_t)kv0 * p.kv_st, sm.k[0], wave);
-      Tile::issue(plan, vb + (int64_t)kv0 * p.kv_st, sm.v[0], wave);
-    }
-  }
-
-  bf16x8 qf[D / 16], gf[D / 16];  // Q^T and dO^T fragments (B operands), lane = query
-  float lse_l = 0.f, delta_l = 0.f;
-  // delta = rowsum(dO * O) of my query, computed here from the dO fragments the kernel holds
-  // anyway (my half of the row's features, then the two halves added), so that a whole backward
-  // needs no separate pass over O and dO; it is also written out, with LSE in base-2 units, for
-  // the dK/dV kernel, which runs after this one.
-  float part = 0.f;
-  // my query's row; a lane past the ragged end of a packed sequence reads the last row (never stored)
-  const int my_row = VARLEN ? min(qw0 + l32, N - 1) : qw0 + l32;
-  const bool my_row_exists = !VARLEN || qw0 + l32 < N;
-#pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
-    if (wave_active) {
-      const int64_t o = q_off + (int64_t)my_row * p.q_st + 16 * kk + 8 * half;
-      qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + o);
-      gf[kk] = *reinterpret_cast<const bf16x8*>(p.d_o + o);
-      const bf16x8 of = *reinterpret_cast<const bf16x8*>(p.o + o);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)gf[kk][e], (float)of[e], part);
-    } else {
-      qf[kk] = bf16x8{};
-      gf[kk] = bf16x8{};
-    }
-  }
-  delta_l = sum_halves(part);
-  if (wave_active) {
-    const int64_t r = VARLEN ? (int64_t)h * p.seqlen + row_base + my_row  // [heads, rows of the tensors]
-                             : ((int64_t)b * p.heads + h) * N + my_row;
-    lse_l = p.lse[r] * kLog2e;
-    if (half == 0 && my_row_exists) {
-      p.delta[r] = delta_l;
-      p.lse2[r] = lse_l;
-    }
-  }
-
-  f32x16 acc[D / 32];
-#pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt) acc[dt] = f32x16{};
-  const float c = p.scale_log2e;
-
-  wait_all_loads();
-  __syncthreads();
-
-  for (int it = 0; it < total; ++it) {
-    const int buf = it & 1;
-    int kv0, pat;
-    bool keep;
-    chunk_of(it, kv0, keep, pat);
-    if (it + 1 < total) {
-      int kv1;
-      next_chunk_of(it, kv1);
-      if (VARLEN && kv1 + CH > N) {
-        const typename Tile::Plan pr = Tile::plan_rows(p.kv_st, wave, lane, N - kv1);
-        Tile::issue(pr, kb + (int64_t)min(kv1, N - 1) * p.kv_st, sm.k[buf ^ 1], wave);
-        Tile::issue(pr, vb + (int64_t)min(kv1, N - 1) * p.kv_st, sm.v[buf ^ 1], wave);
-      } else {
-        Tile::issue(plan, kb + (int64_t)kv1 * p.kv_st, sm.k[buf ^ 1], wave);
-        Tile::issue(plan, vb + (int64_t)kv1 * p.kv_st, sm.v[buf ^ 1], wave);
-      }
-    }
-
-    if (wave_active && keep && kv0 <= qw0 + 31) {
-      const uint16_t* ks = sm.k[buf];
-      const uint16_t* vs = sm.v[buf];
-      const int qpos = qw0 + l32;
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt) {
-        const int kbase = kv0 + 32 * kt;
-        if (kbase > qw0 + 31) continue;  // every key of this half-chunk lies after my queries
-        f32x16 s = f32x16{}, dp = f32x16{};
-#pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) s = mfma32(Tile::row_frag(ks, kt, kk, l32, half), qf[kk], s);
-#pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) dp = mfma32(Tile::row_frag(vs, kt, kk, l32, half), gf[kk], dp);
-        const bool diag = kbase + 31 > qw0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] = fast_exp2(__builtin_fmaf(s[r], c, -lse_l));
-        if (diag) {  // only the half-chunks on the diagonal pay for the causal mask
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = kbase + 8 * (r >> 2) + 4 * half + (r & 3);
-            if (key > qpos) s[r] = 0.f;
-          }
-        }
-        if (CH == 32 && pat != 0xF) {  // 16-token blocks: drop the blocks my mask row does not keep
-          const int mine = pat >> (2 * (l32 >> 4));
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            if (!((mine >> (r >> 3)) & 1)) s[r] = 0.f;  // registers 0..7: block 0, 8..15: block 1
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[r] *= dp[r] - delta_l;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const bf16x8 dsb = pack8(s[8 * u + 0], s[8 * u + 1], s[8 * u + 2], s[8 * u + 3], s[8 * u + 4],
-                                   s[8 * u + 5], s[8 * u + 6], s[8 * u + 7]);
-#pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt)
-            acc[dt] = mfma32(Tile::tr_frag(ks, dt, 2 * kt + u, trb), dsb, acc[dt]);
-        }
-      }
-    }
-
-    wait_all_loads();
-    __syncthreads();
-  }
-
-  if (!wave_active || !my_row_exists) return;
-  uint16_t* row = p.dq + q_off + (int64_t)(qw0 + l32) * p.q_st;
-#pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[dt][4 * g + e] * p.scale);
-      *reinterpret_cast<bf16x4*>(row + 32 * dt + 8 * g + 4 * half) = w;
-    }
 }
 
 // ------------------------------------------------------------------------------------ dk, dv
@@ -637,10 +408,8 @@ hipError_t set_smem(K kernel, size_t bytes, SmemSet& flags) {
 
 template <int D, bool DENSE, int CH, bool VARLEN = false>
 hipError_t launch_one(const AttnParams& p, int stages, hipStream_t stream) {
-  static SmemSet dq_set, dkdv_set;  // zero-initialised
-  hipError_t e = set_smem(&dq_kernel<D, DENSE, CH, VARLEN>, sizeof(DqSmem<D, CH>), dq_set);
-  if (e != hipSuccess) return e;
-  e = set_smem(&dkdv_kernel<D, DENSE, CH, VARLEN>, sizeof(DkvSmem<D, CH>), dkdv_set);
+  static SmemSet dkdv_set;  // zero-initialised
+  hipError_t e = set_smem(&dkdv_kernel<D, DENSE, CH, VARLEN>, sizeof(DkvSmem<D, CH>), dkdv_set);
   if (e != hipSuccess) return e;
 
   const int64_t rows = (int64_t)p.batch * p.heads * p.seqlen;
@@ -676,25 +445,8 @@ hipError_t launch_one(const AttnParams& p, int stages, hipStream_t stream) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if ((stages & kBwdDq) && VARLEN && CH == 64 && dq_pipe_applies(p, DENSE)) {
-    // packed batch: whole 128-row tiles by the fast path, each sequence's partial last tile by dq_kernel
-    e = launch_dq_pipe(p, DENSE, stream);
-    if (e != hipSuccess) return e;
-    AttnParams tail = p;
-    tail.varlen_tail = 1;
-    hipLaunchKernelGGL((dq_kernel<D, DENSE, CH, VARLEN>), dim3(grid_for(bh, 1)), dim3(kThreads), sizeof(DqSmem<D, CH>),
-                       stream, tail);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  } else if ((stages & kBwdDq) && !VARLEN && CH == 64 && dq_pipe_applies(p, DENSE)) {
-    e = launch_dq_pipe(p, DENSE, stream);
-    if (e != hipSuccess) return e;
-  } else if (stages & kBwdDq) {
-    // one slot per 128-row tile: of the sequence, or of the longest length a packed batch allows
-    const int q_tiles = VARLEN ? (p.q_rows + kBwdBM - 1) / kBwdBM : p.q_tiles.tiles_per_head;
-    hipLaunchKernelGGL((dq_kernel<D, DENSE, CH, VARLEN>), dim3(grid_for(bh, q_tiles)), dim3(kThreads),
-                       sizeof(DqSmem<D, CH>), stream, p);
-    e = hipGetLastError();
+  if (stages & kBwdDq) {
+    e = launch_dq(p, DENSE, stream);
     if (e != hipSuccess) return e;
   }
   if (stages & kBwdDkDv) {
