@@ -459,7 +459,9 @@ hipError_t launch_one(const AttnParams& p, int stages, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_bwd(const AttnParams& p, bool dense, int stages, hipStream_t stream) {
+hipError_t launch_bwd(const AttnParams& params, bool dense, int stages, hipStream_t stream) {
+  AttnParams p = params;
+  p.map_group = map_group(p.batch * p.heads, (p.q_rows + kBwdBM - 1) / kBwdBM, p.cu_seqlens != nullptr);
   if (!dense && p.cu_seqlens) {  // packed variable-length batch: a whole backward, sparse layouts only
     if (p.block_size <= 32)
       return p.head_dim == 128 ? launch_one<128, false, 32, true>(p, kBwdAll, stream)

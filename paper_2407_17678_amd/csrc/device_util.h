@@ -408,11 +408,16 @@ struct EntryList {
 // run on one XCD.  Workgroups are handed to the 8 XCDs round-robin by linear index, and each XCD
 // has its own L2: keeping a head's key/value stripes and moving window on one XCD lets every
 // later query tile of that head hit in that L2.
-__device__ __forceinline__ bool map_workgroup(int wg, int bh_total, int tiles, int& bh, int& rank) {
+// The pairs of an XCD are taken `group` at a time, a group's tiles by rank: all its longest tiles first,
+// then all its second longest (map_group chooses).
+__device__ __forceinline__ bool map_workgroup(int wg, int bh_total, int tiles, int group, int& bh, int& rank) {
   const int x = wg & 7, slot = wg >> 3;
-  const int k = slot / tiles;
-  rank = slot - k * tiles;
-  bh = x + 8 * k;
+  const int per_xcd = (bh_total + 7) >> 3;  // slots are laid out for the fullest XCD
+  const int g = slot / (group * tiles);
+  const int in = slot - g * (group * tiles);
+  const int size = min(group, per_xcd - g * group);
+  rank = in / size;
+  bh = x + 8 * (g * group + in - rank * size);
   return bh < bh_total;
 }
 // Same XCD assignment, but the (batch, head) pairs of an XCD are interleaved: all their longest
@@ -426,6 +431,16 @@ __device__ __forceinline__ bool map_workgroup_interleaved(int wg, int bh_total, 
   rank = slot / per_xcd;
   bh = x + 8 * (slot - rank * per_xcd);
   return bh < bh_total;
+}
+// How many pairs of an XCD to take at a time.  One after the other leaves the longest tiles of the last
+// pair for the end of the launch, which counts when an XCD's 64 workgroup slots go round only a few
+// times: forward / dQ of 2 x 16 heads x 4096 x 64 36.1 / 46.6 us one by one, 32.9 / 42.6 in fours; dense 32
+// heads x 8192 542 / 781 and 518 / 731; packed 8 x 32 heads of 200 to 8192 rows 351 / 481 and 348 / 476.
+// From about eight rounds on the tail is nothing, while four heads' stripes then share an L2: 32 heads x
+// 32768 the same both ways, 32 heads x 131072 (2 MB of stripes a head) 5.90 ms one by one, 6.06 in fours.
+// (Eight at a time, or all: the same as four, packed batches up to 3 % slower.)
+__host__ inline int map_group(int bh_total, int tiles, bool packed) {
+  return packed || (int64_t)((bh_total + 7) / 8) * tiles <= 8 * 64 ? 4 : 1;
 }
 __host__ __device__ inline int grid_for(int bh_total, int tiles) { return 8 * ((bh_total + 7) / 8) * tiles; }
 

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
   const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int T = p.q_tiles.tiles_per_head;
   int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T, bh, rank)) return;
+  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T, p.map_group, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
   const int tile = p.q_tiles.order[h * T + rank];
   const int S = p.block_size;  // 64 or 128

@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   const int T = p.q_tiles.tiles_per_head;
   const int T_run = VARLEN ? (p.q_rows + BM - 1) / BM : T;  // packed batch: tiles of the longest length allowed
   int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, bh, rank)) return;
+  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, p.map_group, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
   int tile = DENSE ? (T - 1 - rank) : VARLEN ? 0 : p.q_tiles.order[h * T + rank];
   int N = p.seqlen, row_base = 0;  // my sequence's length, and the rows of the tensors before it

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   const int T = p.fwd_tiles.tiles_per_head;      // tiles of the whole sequence (indexes the lists)
   const int T_run = (p.q_rows + BM - 1) / BM;    // tiles this launch computes
   int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, bh, rank)) return;
+  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, p.map_group, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
   // longest tiles first: by the layout's order for a whole sequence, else simply last row first
   const bool whole = !VARLEN && p.q_row0 == 0 && T_run == T;
@@ -489,7 +489,9 @@ hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_fwd(const AttnParams& p, bool dense, hipStream_t stream) {
+hipError_t launch_fwd(const AttnParams& params, bool dense, hipStream_t stream) {
+  AttnParams p = params;
+  p.map_group = map_group(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM, p.cu_seqlens != nullptr);
   return p.head_dim == 128 ? launch_one<128>(p, dense, stream) : launch_one<64>(p, dense, stream);
 }
 

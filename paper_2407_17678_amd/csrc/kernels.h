@@ -36,6 +36,7 @@ struct AttnParams {
   // sequence b owns rows cu_seqlens[b] .. cu_seqlens[b+1]-1 of q, k, v, o and lse; then batch is
   // the number of sequences, seqlen the rows in the tensors and q_rows the longest length allowed
   const int32_t* cu_seqlens;
+  int map_group;  // (batch, head) pairs of an XCD taken at a time by the row-tile kernels (map_group in device_util.h)
   int64_t q_sb, q_sh, q_st;
   int64_t kv_sb, kv_sh, kv_st;
   float scale;        // softmax scale
