@@ -193,12 +193,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   auto limit_plan = [&](typename Piece::Plan& pl, int row) S2_INLINE {
     if (VARLEN && row + 16 > N) Piece::limit(pl, N - row, p.kv_st);
   };
-  // group g of the loads of my 16 rows from key row `row` on
-  auto dma_k = [&](auto gc, int row, const uint16_t* stage) S2_INLINE {
-    Piece::template issue<decltype(gc)::value>(plan_k, kb + (int64_t)row * p.kv_st, stage, wave);
+  // group g of the loads of my 16 rows, which start at `base`
+  auto dma_k = [&](auto gc, const uint16_t* base, const uint16_t* stage) S2_INLINE {
+    Piece::template issue<decltype(gc)::value>(plan_k, base, stage, wave);
   };
-  auto dma_v = [&](auto gc, int row, const uint16_t* stage) S2_INLINE {
-    Piece::template issue<decltype(gc)::value>(VARLEN ? plan_v : plan_k, vb + (int64_t)row * p.kv_st, stage, wave);
+  auto dma_v = [&](auto gc, const uint16_t* base, const uint16_t* stage) S2_INLINE {
+    Piece::template issue<decltype(gc)::value>(VARLEN ? plan_v : plan_k, base, stage, wave);
   };
   const int trb = Tile::tr_base(lane);
 
@@ -335,11 +335,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     limit_plan(plan_k, row_c);
     limit_plan(plan_v, row_c);
     static_for<NG>([&](auto gc) S2_INLINE {
-      dma_k(gc, row_c, sk[0]);
-      dma_v(gc, row_c, sv[0]);
+      dma_k(gc, kb + (int64_t)row_c * p.kv_st, sk[0]);
+      dma_v(gc, vb + (int64_t)row_c * p.kv_st, sv[0]);
     });
     limit_plan(plan_k, row_n);
-    static_for<NG>([&](auto gc) S2_INLINE { dma_k(gc, row_n, sk[1]); });
+    static_for<NG>([&](auto gc) S2_INLINE { dma_k(gc, kb + (int64_t)row_n * p.kv_st, sk[1]); });
   }
   wait_all_loads();
   __syncthreads();
@@ -371,12 +371,14 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     const uint16_t* vs = sv[par];
     // group d of this step's direct loads: 0..NG-1 for K(it+2), into the stage K(it) was in, then
     // V(it+1), into the stage V(it-1) was in
+    const uint16_t* kg = kb + (int64_t)row_nn * p.kv_st;
+    const uint16_t* vg = vb + (int64_t)row_n * p.kv_st;
     auto step_dma = [&](auto dc) S2_INLINE {
       constexpr int d = decltype(dc)::value;
       if constexpr (d < NG)
-        dma_k(dc, row_nn, sk[par]);
+        dma_k(dc, kg, sk[par]);
       else
-        dma_v(std::integral_constant<int, d - NG>{}, row_n, sv[par ^ 1]);
+        dma_v(std::integral_constant<int, d - NG>{}, vg, sv[par ^ 1]);
     };
     limit_plan(plan_k, row_nn);
     limit_plan(plan_v, row_n);
