@@ -177,7 +177,9 @@ int s2_layout_get(const s2_layout* layout, s2_layout_view* out);
  * length n, each attending one unbroken run of rows (the local-window tiles), such a tile starts at
  * its row that is a multiple of n and goes down from there, wrapping round to the run's last row, so
  * that tiles running side by side read the same query block at the same time.  order[h*T + k] is the
- * k-th tile of head h by descending length.  Errors: NULL, BAD_PARAM (which). */
+ * k-th tile of head h by descending length.  With 16-token blocks the kernels walk the same pattern
+ * block by block (an entry per block; key tiles of any columns that nearly the same rows attend); what is
+ * shown here are its lists by unit.  Errors: NULL, BAD_PARAM (which). */
 enum { S2_TILES_FWD = 0, S2_TILES_DQ = 1, S2_TILES_DKDV = 2 };
 typedef struct {
   const int32_t* ptr;      /* [H*T + 1]                              */

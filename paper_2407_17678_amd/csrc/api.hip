@@ -49,6 +49,7 @@ void free_device_copies(s2_layout* L) {
   free_tiles(L->q_tiles);
   free_tiles(L->kv_tiles);
   free_tiles(L->q_block_tiles);
+  free_tiles(L->kv_block_tiles);
   if (L->d_row_ptr) (void)hipFree(L->d_row_ptr);
   if (L->d_col_idx) (void)hipFree(L->d_col_idx);
   if (L->d_dq_units) (void)hipFree(L->d_dq_units);
@@ -64,6 +65,13 @@ s2::DevTiles dev_tiles(const s2::TileList& t) {
   d.tiles_per_head = t.tiles_per_head;
   d.group = t.group;
   return d;
+}
+
+// The lists the row-tile and key-tile kernels walk.
+void set_tiles(s2::AttnParams& p, const s2_layout* L) {
+  const bool by_block = L->p.block_size == 16;
+  p.fwd_tiles = p.q_tiles = dev_tiles(by_block ? L->q_block_tiles : L->q_tiles);
+  p.kv_tiles = dev_tiles(by_block ? L->kv_block_tiles : L->kv_tiles);
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -177,7 +185,10 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
       static_assert(s2::kFwdBM == s2::kBwdBM, "forward and dQ walk the same lists");
       s2::build_tiles(*L, s2::kBwdBM / S, false, L->q_tiles);
       s2::build_tiles(*L, s2::kBwdBN / S, true, L->kv_tiles);
-      if (S == 16) s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_block_tiles);
+      if (S == 16) {
+        s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_block_tiles);
+        s2::build_block_tiles(*L, s2::kBwdBN / S, true, L->kv_block_tiles);
+      }
       s2::build_ds_units(*L);
     } catch (const std::bad_alloc&) {
       st = S2_ERR_OVERFLOW;
@@ -190,8 +201,8 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0) {
     int dev = 0;
-    bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->q_tiles) && upload_tiles(L->kv_tiles) &&
-              (L->p.block_size != 16 || upload_tiles(L->q_block_tiles)) && upload(L->row_ptr, &L->d_row_ptr) &&
+    bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->p.block_size == 16 ? L->q_block_tiles : L->q_tiles) &&
+              upload_tiles(L->p.block_size == 16 ? L->kv_block_tiles : L->kv_tiles) && upload(L->row_ptr, &L->d_row_ptr) &&
               upload(L->col_idx, &L->d_col_idx) && upload(L->dq_units, &L->d_dq_units);
     if (!ok) {
       free_device_copies(L);
@@ -291,9 +302,7 @@ int s2_attn_fwd(const s2_layout* layout, const s2_tensors* t, float scale, void*
   if (!layout_on_current_device(layout)) return S2_ERR_NO_DEVICE;
   s2::AttnParams p = make_params(t, scale);
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = p.fwd_tiles;
-  p.kv_tiles = dev_tiles(layout->kv_tiles);
+  set_tiles(p, layout);
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 
@@ -341,9 +350,7 @@ int s2_attn_fwd_rows(const s2_layout* layout, const s2_tensors* t, int32_t q_row
   p.q_row0 = q_row_start;
   p.q_rows = q_rows;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = p.fwd_tiles;
-  p.kv_tiles = dev_tiles(layout->kv_tiles);
+  set_tiles(p, layout);
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 
@@ -363,9 +370,7 @@ int s2_attn_fwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.q_rows = max_seqlen;
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = p.fwd_tiles;
-  p.kv_tiles = dev_tiles(layout->kv_tiles);
+  set_tiles(p, layout);
   // one grid slot per (sequence, head, 128-row tile of the longest length allowed)
   const int64_t slots = 8 * (((int64_t)num_seqs * t->heads + 7) / 8) * ((max_seqlen + s2::kFwdBM - 1) / s2::kFwdBM);
   if (slots > std::numeric_limits<int32_t>::max()) return S2_ERR_SHAPE;
@@ -400,9 +405,7 @@ int s2_attn_bwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.q_rows = max_seqlen;
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = p.fwd_tiles;
-  p.kv_tiles = dev_tiles(layout->kv_tiles);
+  set_tiles(p, layout);
   p.delta = static_cast<float*>(workspace);
   p.lse2 = p.delta + need / 8;
   // one grid slot per (sequence, head, tile): query tiles of the longest length allowed, key tiles of the layout
@@ -428,9 +431,7 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
   p.delta = static_cast<float*>(workspace);
   p.lse2 = p.delta + s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim) / 8;
   p.block_size = layout->p.block_size;
-  p.fwd_tiles = dev_tiles(layout->p.block_size == 16 ? layout->q_block_tiles : layout->q_tiles);
-  p.q_tiles = p.fwd_tiles;
-  p.kv_tiles = dev_tiles(layout->kv_tiles);
+  set_tiles(p, layout);
   // a workspace large enough to keep dS selects the backward that computes nothing twice
   const size_t small = s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim);
   if (keeps_ds(layout, t->seqlen, t->head_dim) &&

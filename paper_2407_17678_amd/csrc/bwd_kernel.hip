@@ -24,6 +24,7 @@
 #include "config.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "sched_util.h"
 
 namespace s2 {
 
@@ -62,16 +63,22 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p) {
 
 // ------------------------------------------------------------------------------------ dk, dv
 
-template <int D, int CH>
+template <int D>
 struct DkvSmem {
-  uint16_t q[2][DmaTile<D, CH>::kElems];
-  uint16_t g[2][DmaTile<D, CH>::kElems];
+  uint16_t q[2][DmaTile<D>::kElems];
+  uint16_t g[2][DmaTile<D>::kElems];
   struct RowStats {
-    float delta[CH];
-    float lse[CH];         // base-2 units
+    float delta[64];
+    float lse[64];         // base-2 units
   } rs[2];                 // one 512-byte direct load fills both arrays of a stage
 };
 
+// FINE: mask blocks of 16 or 32 tokens.  A step's 64 query rows are four pieces of 16 gathered from the next
+// blocks of the tile's list (entries of single blocks, one bit per mask column of the tile), and the
+// tile's 4 or 8 columns are any that are attended by nearly the same rows, so a wavefront's 32 keys are
+// one or two columns and what a lane drops of a piece depends on its column.  (Steps of 32 rows over
+// tiles of adjacent columns, as before, had one stripe column keep three idle ones company.)
+//
 // VARLEN: a packed batch of sequences of different lengths.  A key tile's members are columns of
 // the whole layout, so the workgroup first drops out if none of them exists in its sequence, skips
 // the list entries (query blocks, last first) that lie after the sequence's end, clamps the loads
@@ -79,12 +86,14 @@ struct DkvSmem {
 // STORE: dS, rounded to bf16 as the dK contraction takes it, is also left in the workspace for the dQ
 // launch (launch_dq_gemm), 4 KiB per wavefront and step: [half chunk][16-query slab][key][lane half][8
 // queries in the order the lane holds them], i.e. each B operand as it is, 1 KiB per store instruction.
-template <int D, bool DENSE, int CH, bool VARLEN = false, bool STORE = false>
+template <int D, bool DENSE, bool FINE, bool VARLEN = false, bool STORE = false>
 __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
-  typedef DmaTile<D, CH> Tile;
-  constexpr int QT = CH / 32;
+  typedef DmaTile<D> Tile;
+  typedef PieceTile<D> Piece;
+  constexpr int CH = 64, QT = CH / 32;
+  static_assert(!(DENSE && (FINE || VARLEN)) && !(STORE && (DENSE || FINE || VARLEN)), "forms that exist");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  DkvSmem<D, CH>& sm = *reinterpret_cast<DkvSmem<D, CH>*>(smem_raw);
+  DkvSmem<D>& sm = *reinterpret_cast<DkvSmem<D>*>(smem_raw);
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -94,13 +103,9 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
   if (!map_workgroup_interleaved(blockIdx.x, p.batch * p.heads, T, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
   const int tile = DENSE ? rank : p.kv_tiles.order[h * T + rank];  // dense: first key tiles are longest
-  const int S = DENSE ? kChunk : p.block_size;
-  // 16-token blocks: a list entry is a unit of two query blocks (32 rows, one step) and my 32 key
-  // rows are two adjacent mask columns, so a lane's keep pattern is 2 x 2 bits per wavefront
-  const bool fine = !DENSE && CH == 32 && S == 16;
-  const int Sg = fine ? 32 : S;  // tokens per list entry
-  const int cpb = Sg / CH;  // a power of two: / and % below are a shift and a mask
-  const int cpb_sh = __builtin_ctz(cpb), cpb_m = cpb - 1;
+  const int S = DENSE ? CH : p.block_size;  // FINE: 16 or 32, else 64 or 128
+  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
+  const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-row pieces per list entry
   int row_base = 0, N = p.seqlen;
   if (VARLEN) {
     const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
@@ -108,29 +113,36 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
   }
 
-  // my 32 key rows
-  int kvw0, my_member = 0;
+  // My 32 keys: kvw0 .. kvw0 + 31, or (FINE) keys 0..15 from kvw0 and 16..31 from kvw1.  A group of keys
+  // that does not exist (the layout's last tile, a packed sequence's end) starts at kNoKey.
+  constexpr int kNoKey = 1 << 29;
+  int kvw0, kvw1, my_member = 0;
   bool wave_active;
   if (DENSE) {
     kvw0 = tile * kBwdBN + wave * 32;
+    kvw1 = kvw0 + 16;
     wave_active = kvw0 < N;
   } else {
-    my_member = (wave * 32) / S;  // with 16-token blocks the first of my two (adjacent) columns
     const int32_t* mem = p.kv_tiles.members + (h * T + tile) * p.kv_tiles.group;
     if (VARLEN) {  // the whole workgroup leaves together when none of its columns is in the sequence
       bool any = false;
       for (int m = 0; m < p.kv_tiles.group; ++m) any = any || (mem[m] >= 0 && mem[m] * S < N);
       if (!any) return;
     }
-    const int blk = mem[my_member];
-    kvw0 = blk * S + (wave * 32) % S;
-    wave_active = blk >= 0 && kvw0 < N;
+    my_member = (wave * 32) / S;
+    const int blk0 = mem[my_member], blk1 = mem[(wave * 32 + 16) / S];
+    kvw0 = blk0 < 0 ? kNoKey : blk0 * S + (wave * 32) % S;
+    kvw1 = blk1 < 0 ? kNoKey : blk1 * S + (wave * 32 + 16) % S;
+    wave_active = FINE ? min(kvw0, kvw1) < N : kvw0 < N;
   }
+  // key of row r (0..31) of mine
+  auto key_of = [&](int r) S2_INLINE { return FINE ? (r < 16 ? kvw0 + r : kvw1 + r - 16) : kvw0 + r; };
 
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
-  const uint16_t* qb = p.q + q_off;
-  const uint16_t* gb = p.d_o + q_off;
+  // minus the bias the grouped direct loads put into their lane offsets
+  const uint16_t* qb = p.q + q_off - Piece::kBias / 2;
+  const uint16_t* gb = p.d_o + q_off - Piece::kBias / 2;
   // packed batch: the row statistics are [heads, rows of the tensors]
   const int64_t stats_off = VARLEN ? (int64_t)h * p.seqlen + row_base : ((int64_t)b * p.heads + h) * N;
   const float* lse_b = p.lse2 + stats_off;
@@ -143,94 +155,114 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     ent_lo = p.kv_tiles.ptr[h * T + tile];
     n_ent = p.kv_tiles.ptr[h * T + tile + 1] - ent_lo;
   }
-  const int total = n_ent * cpb;
+  // steps: chunks of an entry, or (FINE) as many as the entries' pieces fill
+  const int total = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent << cpb_sh;
   // where this wavefront's dS of step 0 goes: unit 2 * (global step) + wave / 2, its keys' half of it
   uint16_t* ds_wave = nullptr;
   if (STORE)
     ds_wave = p.ds_store + ((int64_t)b * p.ds_units + (((int64_t)ent_lo << cpb_sh) * 2 + (wave >> 1))) * 4096 + (wave & 1) * 2048;
   EntryList list;
   if (!DENSE) list.init(p.kv_tiles.ent + ent_lo, n_ent, lane);
-  // chunk `it` of the tile's list: its first row, and whether my mask row / column keeps it
-  // `pat` (16-token blocks only): bit 2m + c set when query block c of the unit keeps my column m
-  auto chunk_of = [&](int it, int& q0, bool& keep, int& pat) {
-    pat = 0xF;
+  // FINE: piece pc (0..3) of step j: its first query row, and which of my two groups of 16 keys it attends
+  // (bits 0 and 1; both or neither for 32-token blocks); a list that does not fill its last step repeats
+  // its last block there, attending nothing
+  auto piece_at = [&](int j, int pc, int& row, int& bits) S2_INLINE {
+    const int x = 4 * j + pc;
+    const int i = x >> ppe_sh;
+    const uint32_t e = (uint32_t)list.peek(min(i, n_ent - 1));
+    row = (int)(e >> 16) * S + ((x & ppe_sh) << 4);
+    bits = ppe_sh ? ((e >> wave) & 1) * 3 : (e >> (2 * wave)) & 3;
+    if (i >= n_ent || (VARLEN && row >= N)) bits = 0;
+  };
+  // not FINE: first row of step j, and whether my mask column is kept there
+  auto chunk_at = [&](int j, int& q0, bool& keep) S2_INLINE {
     if (DENSE) {
-      q0 = N - CH - it * CH;  // from the last query chunk down, like the sparse lists
+      q0 = N - CH - j * CH;  // from the last query chunk down, like the sparse lists
       keep = true;
     } else {
-      const int e = list.get((it >> cpb_sh), lane);
-      q0 = (e >> 16) * Sg + (cpb - 1 - (it & cpb_m)) * CH;
-      if (fine) {
-        pat = (e >> (4 * wave)) & 0xF;
-        keep = pat != 0;
-      } else {
-        keep = (e >> my_member) & 1;
-      }
-    }
-  };
-  // first row of chunk it+1, right after chunk_of(it)
-  auto next_chunk_of = [&](int it, int& q0_n) {
-    if (DENSE) {
-      q0_n = N - CH - (it + 1) * CH;
-    } else {
-      const int e = ((it + 1) >> cpb_sh) == (it >> cpb_sh) ? list.get((it >> cpb_sh), lane) : list.peek_next((it >> cpb_sh));
-      q0_n = (e >> 16) * Sg + (cpb - 1 - ((it + 1) & cpb_m)) * CH;
+      const int e = list.peek(j >> cpb_sh);
+      q0 = (e >> 16) * S + (cpb_m - (j & cpb_m)) * CH;
+      keep = (e >> my_member) & 1;
     }
   };
 
-  const typename Tile::Plan plan = Tile::plan(p.q_st, wave, lane);
+  const typename Piece::Plan plan = Piece::plan(p.q_st, lane);
   const uint32_t stats_gap = (uint32_t)((const char*)lse_b - (const char*)delta_b);
   // `ln` is the lane number.  The loop passes a copy the optimiser cannot see through, so that
   // what is derived from it is recomputed each step (a few integer operations) rather than kept in
   // registers across the loop: this kernel has no registers to spare, and a spilled constant costs
   // a wait for all outstanding loads when it is fetched back.
-  auto issue_chunk = [&](int q0, int buf, int ln) {
-    if (VARLEN && q0 + CH > N) {  // ragged end of the sequence: rows past it fetch its last row instead
-      // (a list need not be in descending order, so a chunk that lies wholly after the sequence's end
-      // can turn up anywhere in it: it fetches the last row 64 times and nothing uses it)
-      const int qs = min(q0, N - 1);
-      const typename Tile::Plan pr = Tile::plan_rows(p.q_st, wave, ln, N - qs);
-      Tile::issue(pr, qb + (int64_t)qs * p.q_st, sm.q[buf], wave);
-      Tile::issue(pr, gb + (int64_t)qs * p.q_st, sm.g[buf], wave);
+  auto issue_chunk = [&](int j, int buf, int ln) S2_INLINE {
+    int r[4];  // first row of each piece
+    if constexpr (FINE) {
+#pragma unroll
+      for (int pc = 0; pc < 4; ++pc) {
+        int bits;
+        piece_at(j, pc, r[pc], bits);
+      }
     } else {
-      Tile::issue(plan, qb + (int64_t)q0 * p.q_st, sm.q[buf], wave);
-      Tile::issue(plan, gb + (int64_t)q0 * p.q_st, sm.g[buf], wave);
+      bool keep;
+      chunk_at(j, r[0], keep);
+#pragma unroll
+      for (int pc = 1; pc < 4; ++pc) r[pc] = r[0] + 16 * pc;
     }
-    // CH floats of each array: the first CH/4 lanes fetch delta, the next CH/4 lanes lse, 16 bytes
-    // each, in one direct load issued by the wavefront that has one load fewer than the others in the two tiles
-    constexpr int NL = CH / 4;  // lanes per array, 16 bytes each
-    if (wave == 3 && ln < 2 * NL)
-      dma16(delta_b + (VARLEN && q0 >= N ? 0 : q0), 16 * ln + (ln < NL ? 0u : stats_gap - 16u * NL), lds_addr(&sm.rs[buf]));
+    int row = FINE ? (wave == 0 ? r[0] : wave == 1 ? r[1] : wave == 2 ? r[2] : r[3]) : r[0] + 16 * wave;
+    // Ragged end of a packed sequence: rows past it fetch parts of its last row instead (a list need
+    // not be in descending order, so a piece that lies wholly after the end can turn up anywhere in
+    // it: nothing uses it).
+    typename Piece::Plan pl = plan;
+    if (VARLEN && row + 16 > N) {
+      row = min(row, N - 1);
+      Piece::limit(pl, N - row, p.q_st);
+    }
+    const uint16_t* qg = qb + (int64_t)row * p.q_st;
+    const uint16_t* gg = gb + (int64_t)row * p.q_st;
+    Piece::template issue<0>(pl, qg, sm.q[buf], wave);
+    Piece::template issue<1>(pl, qg, sm.q[buf], wave);
+    Piece::template issue<0>(pl, gg, sm.g[buf], wave);
+    Piece::template issue<1>(pl, gg, sm.g[buf], wave);
+    // 64 floats of each array: lanes 0..15 fetch delta, lanes 16..31 lse, 16 bytes each, in one direct load.
+    // (Where a packed sequence ends inside a piece the rest of it comes from the slack of the workspace
+    // or from the next rows: nothing uses it.)
+    if (wave == 3) {
+      uint32_t off;
+      if constexpr (FINE) {
+        const int pc = (ln >> 2) & 3;
+        int pr = pc == 0 ? r[0] : pc == 1 ? r[1] : pc == 2 ? r[2] : r[3];
+        if (VARLEN) pr = min(pr, N - 1);
+        off = 4 * pr + 16 * (ln & 3) + ((ln & 16) ? stats_gap : 0u);
+      } else {
+        off = 16 * (ln & 15) + ((ln & 16) ? stats_gap : 0u);
+      }
+      if (ln < 32) dma16(FINE ? delta_b : delta_b + (VARLEN && r[0] >= N ? 0 : r[0]), off, lds_addr(&sm.rs[buf]));
+    }
   };
-  // first step: a packed sequence skips the leading chunks of query blocks that lie after its end (most
-  // lists start at the layout's last row; such chunks further on are walked without being used)
+  // first step: a packed sequence skips the leading entries, query blocks that lie after its end (most
+  // lists start at the layout's last row; such blocks further on are walked without being used)
   int it0 = 0;
   if (VARLEN) {
-    for (; it0 < total; ++it0) {
-      int q0, pat;
-      bool keep;
-      chunk_of(it0, q0, keep, pat);
-      if (q0 < N) break;
+    int e = 0;
+    for (; e < n_ent; e += 64) {
+      (void)list.get(e, lane);
+      const uint64_t in = __ballot(e + lane < n_ent && (int)((uint32_t)list.cur >> 16) * S < N);
+      if (in) {
+        e += __builtin_ctzll(in);
+        break;
+      }
     }
+    e = min(e, n_ent - 1);  // (a key of the sequence is attended by its own block at least)
+    (void)list.get(e, lane);
+    it0 = FINE ? (e << ppe_sh) >> 2 : e << cpb_sh;
   }
-  if (it0 < total) {
-    int q0, pat;
-    bool keep;
-    chunk_of(it0, q0, keep, pat);
-    issue_chunk(q0, it0 & 1, lane);
-  }
+  issue_chunk(it0, it0 & 1, lane);
 
   bf16x8 kf[D / 16], vf[D / 16];  // K and V fragments (B operands), lane = key
 #pragma unroll
   for (int kk = 0; kk < D / 16; ++kk) {
-    if (wave_active) {
-      const int64_t o = kv_off + (int64_t)(VARLEN ? min(kvw0 + l32, N - 1) : kvw0 + l32) * p.kv_st + 16 * kk + 8 * half;
-      kf[kk] = *reinterpret_cast<const bf16x8*>(p.k + o);
-      vf[kk] = *reinterpret_cast<const bf16x8*>(p.v + o);
-    } else {
-      kf[kk] = bf16x8{};
-      vf[kk] = bf16x8{};
-    }
+    // (a lane whose key does not exist reads an existing one: every pair of it is masked and nothing is stored)
+    const int64_t o = kv_off + (int64_t)min(key_of(l32), N - 1) * p.kv_st + 16 * kk + 8 * half;
+    kf[kk] = *reinterpret_cast<const bf16x8*>(p.k + o);
+    vf[kk] = *reinterpret_cast<const bf16x8*>(p.v + o);
   }
 
   f32x16 acc_dk[D / 32], acc_dv[D / 32];
@@ -248,41 +280,71 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     const int buf = it & 1;
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    int q0, pat;
-    bool keep;
-    chunk_of(it, q0, keep, pat);
-    if (it + 1 < total) {
-      int q1;
-      next_chunk_of(it, q1);
-      issue_chunk(q1, buf ^ 1, ln);
-    }
+    // keeps the entry window moving (entries of this step on)
+    if (!DENSE) (void)list.get(FINE ? (4 * it) >> ppe_sh : it >> cpb_sh, ln);
+    if (it + 1 < total) issue_chunk(it + 1, buf ^ 1, ln);
+
+    int q0 = 0;
+    bool keep = true;
+    if constexpr (!FINE) chunk_at(it, q0, keep);
 
     int stores = 0;  // dS stores of this step (wave-uniform)
     uint16_t* ds_step = STORE ? ds_wave + (int64_t)it * 8192 : nullptr;
-    if (wave_active && keep && q0 + CH - 1 >= kvw0) {
+    if (wave_active && (FINE || (keep && q0 + CH - 1 >= kvw0))) {
       const uint16_t* qs = sm.q[buf];
       const uint16_t* gs = sm.g[buf];
       const int l32 = ln & 31, half = ln >> 5;
       const int trb = Tile::tr_base(ln);
-      const int key = kvw0 + l32;
-      const int mine = pat >> (2 * (l32 >> 4));  // 16-token blocks: bit c = query block c keeps my key
+      const int key = key_of(l32);
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
+        // Causal mask, and (FINE) blocks my column does not keep: of the 16 query rows of piece u of this half
+        // chunk, row 8 i + 4 half + e is dropped when lim[u] > 8 i + e, a compare with a constant.
+        // Packed batch: it exists iff 8 i + e < left[u].
+        int lim[2], left[2];
         const int qbase = q0 + 32 * qt;
-        if (qbase + 31 < kvw0) continue;  // every query of this half-chunk lies before my keys
-        if (VARLEN && qbase >= N) continue;  // ... or after the end of my sequence
+        if constexpr (FINE) {
+          int r0, r1, b0, b1;
+          piece_at(it, 2 * qt, r0, b0);
+          piece_at(it, 2 * qt + 1, r1, b1);
+          if ((b0 | b1) == 0) continue;  // nothing of it attends my keys
+          const int col = l32 >> 4;
+          lim[0] = (b0 >> col) & 1 ? key - r0 - 4 * half : 64;
+          lim[1] = (b1 >> col) & 1 ? key - r1 - 4 * half : 64;
+          left[0] = N - r0 - 4 * half;
+          left[1] = N - r1 - 4 * half;
+        } else {
+          if (qbase + 31 < kvw0) continue;  // every query of this half-chunk lies before my keys
+          if (VARLEN && qbase >= N) continue;  // ... or after the end of my sequence
+          // away from the diagonal lim = -1 or less and nothing is dropped
+          // (the dense instantiation keeps the plain comparison: with this form the compiler spills there)
+          lim[0] = qbase < kvw0 + 31 ? key - qbase - 4 * half : -32;
+          lim[1] = lim[0] - 16;
+          left[0] = N - qbase - 4 * half;
+          left[1] = left[0] - 16;
+        }
         f32x16 s = f32x16{}, dp = f32x16{};
+        if constexpr (D == 64) {
+          // all eight row fragments are requested before the first MFMA waits for one (left alone, the
+          // compiler requests and awaits them one at a time to save registers: 2 x 16 heads x 4096, 121.5 us
+          // against 107)
+          bf16x8 fq[D / 16], fg[D / 16];
 #pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) s = mfma32(Tile::row_frag(qs, qt, kk, l32, half), kf[kk], s);
+          for (int kk = 0; kk < D / 16; ++kk) fq[kk] = Tile::row_frag(qs, qt, kk, l32, half);
 #pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) dp = mfma32(Tile::row_frag(gs, qt, kk, l32, half), vf[kk], dp);
-        // causal mask: key > qbase + 8g + 4 half + e  <=>  lim > 8g + e, a compare with a constant;
-        // away from the diagonal lim = -1 and nothing is dropped
-        // (the dense instantiation keeps the plain comparison: with this form the compiler spills there)
+          for (int kk = 0; kk < D / 16; ++kk) fg[kk] = Tile::row_frag(gs, qt, kk, l32, half);
+          S2_FENCE();
+#pragma unroll
+          for (int kk = 0; kk < D / 16; ++kk) s = mfma32(fq[kk], kf[kk], s);
+#pragma unroll
+          for (int kk = 0; kk < D / 16; ++kk) dp = mfma32(fg[kk], vf[kk], dp);
+        } else {
+#pragma unroll
+          for (int kk = 0; kk < D / 16; ++kk) s = mfma32(Tile::row_frag(qs, qt, kk, l32, half), kf[kk], s);
+#pragma unroll
+          for (int kk = 0; kk < D / 16; ++kk) dp = mfma32(Tile::row_frag(gs, qt, kk, l32, half), vf[kk], dp);
+        }
         const bool diag = qbase < kvw0 + 31;
-        const int lim = diag ? key - qbase - 4 * half : -1;
-        // packed batch: query row 8g + 4 half + e of the half-chunk exists iff 8g + e < rows_left
-        const int rows_left = VARLEN ? N - qbase - 4 * half : 0;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const int r0 = 32 * qt + 8 * g + 4 * half;
@@ -292,10 +354,10 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
           for (int e = 0; e < 4; ++e) {
             const int r = 4 * g + e;
             float pr = fast_exp2(__builtin_fmaf(s[r], c, -l4[e]));
-            if (DENSE ? (diag && key > q0 + r0 + e) : (lim > 8 * g + e)) pr = 0.f;
-            if (CH == 32 && !((mine >> (g >> 1)) & 1)) pr = 0.f;  // query rows 0..15: block 0, 16..31: block 1
+            if (DENSE ? (diag && key > q0 + r0 + e) : FINE ? (lim[g >> 1] > 8 * (g & 1) + e) : (lim[0] > 8 * g + e)) pr = 0.f;
             float ds = pr * (dp[r] - d4[e]);
-            if (VARLEN && 8 * g + e >= rows_left) {  // a row past the sequence's end: its statistics are not its own
+            // a row past the sequence's end: its statistics are not its own
+            if (VARLEN && (FINE ? 8 * (g & 1) + e >= left[g >> 1] : 8 * g + e >= left[0])) {
               pr = 0.f;
               ds = 0.f;
             }
@@ -336,42 +398,15 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     __syncthreads();
   }
 
-  if (!wave_active || (VARLEN && kvw0 + l32 >= N)) return;
-  if (!VARLEN && CH == 64) {
-    // Whole rows exist: dK and dV go out through LDS (free since the loop's last barrier; each
-    // wavefront uses regions of its own, so no barrier).  A lane holds its row's features four at a
-    // time, and storing them from there touches 32 rows per instruction with 16 bytes each; read back
-    // 16 bytes per lane, row after row, an instruction stores four whole rows.
-    constexpr int RS = D + 8;  // staging row stride (elements)
-    static_assert(4 * 32 * (D + 8) <= 2 * DmaTile<D, CH>::kElems || CH != 64, "the staging rows fit two stages");
-    uint16_t* sk_ = &sm.q[0][0] + wave * 32 * RS;
-    uint16_t* sv_ = &sm.g[0][0] + wave * 32 * RS;
-#pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        bf16x4 wk, wv;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          wk[e] = (__bf16)(acc_dk[dt][4 * g + e] * p.scale);
-          wv[e] = (__bf16)(acc_dv[dt][4 * g + e]);
-        }
-        *reinterpret_cast<bf16x4*>(sk_ + l32 * RS + 32 * dt + 8 * g + 4 * half) = wk;
-        *reinterpret_cast<bf16x4*>(sv_ + l32 * RS + 32 * dt + 8 * g + 4 * half) = wv;
-      }
-    uint16_t* dk_base = p.dk + kv_off + (int64_t)kvw0 * p.kv_st;
-    uint16_t* dv_base = p.dv + kv_off + (int64_t)kvw0 * p.kv_st;
-    constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
-#pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
-      const int r = RPI * i + lane / PPR, piece = lane % PPR;
-      *reinterpret_cast<u32x4*>(dk_base + (int64_t)r * p.kv_st + 8 * piece) = *reinterpret_cast<const u32x4*>(sk_ + r * RS + 8 * piece);
-      *reinterpret_cast<u32x4*>(dv_base + (int64_t)r * p.kv_st + 8 * piece) = *reinterpret_cast<const u32x4*>(sv_ + r * RS + 8 * piece);
-    }
-    return;
-  }
-  uint16_t* dk_row = p.dk + kv_off + (int64_t)(kvw0 + l32) * p.kv_st;
-  uint16_t* dv_row = p.dv + kv_off + (int64_t)(kvw0 + l32) * p.kv_st;
+  if (!wave_active) return;
+  // dK and dV go out through LDS (free since the loop's last barrier; each wavefront uses regions of its
+  // own, so no barrier).  A lane holds its row's features four at a time, and storing them from there
+  // touches 32 rows per instruction with 16 bytes each; read back 16 bytes per lane, row after row, an
+  // instruction stores four whole rows.
+  constexpr int RS = D + 8;  // staging row stride (elements)
+  static_assert(4 * 32 * (D + 8) <= 2 * Tile::kElems, "the staging rows fit two stages");
+  uint16_t* sk_ = &sm.q[0][0] + wave * 32 * RS;
+  uint16_t* sv_ = &sm.g[0][0] + wave * 32 * RS;
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
@@ -382,9 +417,23 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
         wk[e] = (__bf16)(acc_dk[dt][4 * g + e] * p.scale);
         wv[e] = (__bf16)(acc_dv[dt][4 * g + e]);
       }
-      *reinterpret_cast<bf16x4*>(dk_row + 32 * dt + 8 * g + 4 * half) = wk;
-      *reinterpret_cast<bf16x4*>(dv_row + 32 * dt + 8 * g + 4 * half) = wv;
+      *reinterpret_cast<bf16x4*>(sk_ + l32 * RS + 32 * dt + 8 * g + 4 * half) = wk;
+      *reinterpret_cast<bf16x4*>(sv_ + l32 * RS + 32 * dt + 8 * g + 4 * half) = wv;
     }
+  uint16_t* dk_base = p.dk + kv_off;
+  uint16_t* dv_base = p.dv + kv_off;
+  constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int r = RPI * i + lane / PPR, piece = lane % PPR;
+    const u32x4 xk = *reinterpret_cast<const u32x4*>(sk_ + r * RS + 8 * piece);
+    const u32x4 xv = *reinterpret_cast<const u32x4*>(sv_ + r * RS + 8 * piece);
+    const int kr = key_of(r);
+    if ((FINE || VARLEN) && kr >= N) continue;
+    const int64_t o = (int64_t)kr * p.kv_st + 8 * piece;
+    *reinterpret_cast<u32x4*>(dk_base + o) = xk;
+    *reinterpret_cast<u32x4*>(dv_base + o) = xv;
+  }
 }
 
 // A kernel's dynamic LDS limit is a per-device attribute: remember, per device, that it is set.
@@ -406,55 +455,50 @@ hipError_t set_smem(K kernel, size_t bytes, SmemSet& flags) {
   return e;
 }
 
-template <int D, bool DENSE, int CH, bool VARLEN = false>
-hipError_t launch_one(const AttnParams& p, int stages, hipStream_t stream) {
-  static SmemSet dkdv_set;  // zero-initialised
-  hipError_t e = set_smem(&dkdv_kernel<D, DENSE, CH, VARLEN>, sizeof(DkvSmem<D, CH>), dkdv_set);
+template <int D, bool DENSE, bool FINE, bool VARLEN, bool STORE>
+hipError_t launch_dkdv(const AttnParams& p, hipStream_t stream) {
+  static SmemSet set;  // zero-initialised
+  hipError_t e = set_smem(&dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>, sizeof(DkvSmem<D>), set);
   if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(grid_for(p.batch * p.heads, p.kv_tiles.tiles_per_head)),
+                     dim3(kThreads), sizeof(DkvSmem<D>), stream, p);
+  return hipGetLastError();
+}
 
+template <int D>
+hipError_t launch_delta(const AttnParams& p, hipStream_t stream) {
   const int64_t rows = (int64_t)p.batch * p.heads * p.seqlen;
   constexpr int RPB = 256 / (D / 8);
-  const int bh = p.batch * p.heads;
-  if constexpr (D == 128 && !DENSE && CH == 64 && !VARLEN) {
+  hipLaunchKernelGGL((delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t stream) {
+  hipError_t e = hipSuccess;
+  if constexpr (D == 128) {
     if (p.ds_store) {
       // The backward that keeps dS: delta, then dK/dV (5 contractions' worth of work less the dQ one,
       // leaving dS in the workspace), then dQ = scale * dS K - nothing is computed twice.
-      static SmemSet store_set;
-      e = set_smem(&dkdv_kernel<D, false, CH, false, true>, sizeof(DkvSmem<D, CH>), store_set);
-      if (e != hipSuccess) return e;
-      if (stages & kBwdDelta) {
-        hipLaunchKernelGGL((delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, stream, p);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-      }
-      if (stages & kBwdDkDv) {
-        hipLaunchKernelGGL((dkdv_kernel<D, false, CH, false, true>), dim3(grid_for(bh, p.kv_tiles.tiles_per_head)),
-                           dim3(kThreads), sizeof(DkvSmem<D, CH>), stream, p);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-      }
-      if (stages & kBwdDq) e = launch_dq_gemm(p, stream);
+      if (stages & kBwdDelta) e = launch_delta<D>(p, stream);
+      if (e == hipSuccess && (stages & kBwdDkDv)) e = launch_dkdv<D, false, false, false, true>(p, stream);
+      if (e == hipSuccess && (stages & kBwdDq)) e = launch_dq_gemm(p, stream);
       return e;
     }
   }
   // The dQ kernel computes delta itself and leaves it (and LSE in base-2 units) in the workspace,
   // so it runs first and the stand-alone delta kernel only when dQ is not part of the call
   // (a packed batch is always a whole backward).
-  if (!VARLEN && (stages & kBwdDelta) && !(stages & kBwdDq)) {
-    hipLaunchKernelGGL((delta_kernel<D>), dim3((unsigned)((rows + RPB - 1) / RPB)), dim3(256), 0, stream, p);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  if (stages & kBwdDq) {
-    e = launch_dq(p, DENSE, stream);
-    if (e != hipSuccess) return e;
-  }
-  if (stages & kBwdDkDv) {
-    hipLaunchKernelGGL((dkdv_kernel<D, DENSE, CH, VARLEN>), dim3(grid_for(bh, p.kv_tiles.tiles_per_head)),
-                       dim3(kThreads), sizeof(DkvSmem<D, CH>), stream, p);
-    e = hipGetLastError();
-  }
-  return e;
+  if (stages & kBwdDq)
+    e = launch_dq(p, dense, stream);
+  else if (stages & kBwdDelta)
+    e = launch_delta<D>(p, stream);
+  if (e != hipSuccess || !(stages & kBwdDkDv)) return e;
+  if (dense) return launch_dkdv<D, true, false, false, false>(p, stream);
+  const bool fine = p.block_size < 64;
+  if (p.cu_seqlens)
+    return fine ? launch_dkdv<D, false, true, true, false>(p, stream) : launch_dkdv<D, false, false, true, false>(p, stream);
+  return fine ? launch_dkdv<D, false, true, false, false>(p, stream) : launch_dkdv<D, false, false, false, false>(p, stream);
 }
 
 }  // namespace
@@ -462,19 +506,7 @@ hipError_t launch_one(const AttnParams& p, int stages, hipStream_t stream) {
 hipError_t launch_bwd(const AttnParams& params, bool dense, int stages, hipStream_t stream) {
   AttnParams p = params;
   p.map_group = map_group(p.batch * p.heads, (p.q_rows + kBwdBM - 1) / kBwdBM, p.cu_seqlens != nullptr);
-  if (!dense && p.cu_seqlens) {  // packed variable-length batch: a whole backward, sparse layouts only
-    if (p.block_size <= 32)
-      return p.head_dim == 128 ? launch_one<128, false, 32, true>(p, kBwdAll, stream)
-                               : launch_one<64, false, 32, true>(p, kBwdAll, stream);
-    return p.head_dim == 128 ? launch_one<128, false, kChunk, true>(p, kBwdAll, stream)
-                             : launch_one<64, false, kChunk, true>(p, kBwdAll, stream);
-  }
-  // 32-token mask blocks are walked in steps of 32 rows, everything else in steps of 64
-  if (!dense && p.block_size <= 32)
-    return p.head_dim == 128 ? launch_one<128, false, 32>(p, stages, stream) : launch_one<64, false, 32>(p, stages, stream);
-  if (p.head_dim == 128)
-    return dense ? launch_one<128, true, kChunk>(p, stages, stream) : launch_one<128, false, kChunk>(p, stages, stream);
-  return dense ? launch_one<64, true, kChunk>(p, stages, stream) : launch_one<64, false, kChunk>(p, stages, stream);
+  return p.head_dim == 128 ? launch_dim<128>(p, dense, stages, stream) : launch_dim<64>(p, dense, stages, stream);
 }
 
 }  // namespace s2

@@ -111,154 +111,35 @@ __device__ __forceinline__ void dma16(const void* gbase, uint32_t byte_off, uint
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(gbase), "s"(lds_base)
                : "memory", "m0");
 }
-__device__ __forceinline__ void dma4(const void* gbase, uint32_t byte_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(byte_off), "s"(gbase), "s"(lds_base)
-               : "memory", "m0");
-}
-// Up to four loads that share one M0 value.  The instruction's immediate offset is added to the
-// global address AND to the LDS address, so loads whose LDS targets are 1 KiB apart need only
+// Two or three loads that share one M0 value.  The instruction's immediate offset is added to the
+// global address AND to the LDS address, so loads whose LDS targets differ by less than 4 KiB need only
 // one scalar write of M0 (and one wait state) between them; the caller takes the immediate back
-// out of the lane's global offset.  kCount loads, the i-th with immediate 1024 * i.
-template <int kCount>
-__device__ __forceinline__ void dma16_group(const void* gbase, uint32_t lds_base, uint32_t o0, uint32_t o1,
-                                            uint32_t o2, uint32_t o3) {
-  static_assert(kCount >= 1 && kCount <= 4, "immediates 0 .. 3072");
-  if constexpr (kCount == 4)
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %2, %0\n\tglobal_load_lds_dwordx4 %3, %0 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %4, %0 offset:2048\n\tglobal_load_lds_dwordx4 %5, %0 offset:3072"
-                 ::"s"(gbase), "s"(lds_base), "v"(o0), "v"(o1), "v"(o2), "v"(o3)
-                 : "m0");
-  else if constexpr (kCount == 3)
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %2, %0\n\tglobal_load_lds_dwordx4 %3, %0 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %4, %0 offset:2048"
-                 ::"s"(gbase), "s"(lds_base), "v"(o0), "v"(o1), "v"(o2)
-                 : "m0");
-  else if constexpr (kCount == 2)
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %2, %0\n\tglobal_load_lds_dwordx4 %3, %0 offset:1024"
-                 ::"s"(gbase), "s"(lds_base), "v"(o0), "v"(o1)
-                 : "m0");
-  else
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0" ::"s"(gbase), "s"(lds_base), "v"(o0)
-                 : "m0");
+// out of the lane's global offset.
+template <int I0, int I1>
+__device__ __forceinline__ void dma16_group(const void* gbase, uint32_t lds_base, uint32_t o0, uint32_t o1) {
+  static_assert(I0 >= 0 && I1 < 4096, "twelve bits");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\t"
+               "global_load_lds_dwordx4 %2, %0 offset:%4\n\tglobal_load_lds_dwordx4 %3, %0 offset:%5"
+               ::"s"(gbase), "s"(lds_base), "v"(o0), "v"(o1), "n"(I0), "n"(I1)
+               : "m0");
 }
-// One load by the first kLanes lanes only.  EXEC is all ones where this is used (uniform control
-// flow, full wavefronts) and is put back; the scalar instruction between the write of M0 and the load
-// is the wait state M0 needs.
-template <int kLanes>
-__device__ __forceinline__ void dma16_lanes(const void* gbase, uint32_t lds_base, uint32_t off) {
-  static_assert(kLanes > 0 && kLanes < 64, "a part of the wavefront");
-  asm volatile("s_mov_b32 m0, %1\n\ts_bfm_b64 exec, %3, 0\n\tglobal_load_lds_dwordx4 %2, %0\n\ts_mov_b64 exec, -1"
-               ::"s"(gbase), "s"(lds_base), "v"(off), "n"(kLanes)
+template <int I0, int I1, int I2>
+__device__ __forceinline__ void dma16_group(const void* gbase, uint32_t lds_base, uint32_t o0, uint32_t o1, uint32_t o2) {
+  static_assert(I0 >= 0 && I2 < 4096, "twelve bits");
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %0 offset:%5\n\t"
+               "global_load_lds_dwordx4 %3, %0 offset:%6\n\tglobal_load_lds_dwordx4 %4, %0 offset:%7"
+               ::"s"(gbase), "s"(lds_base), "v"(o0), "v"(o1), "v"(o2), "n"(I0), "n"(I1), "n"(I2)
                : "m0");
 }
 #pragma clang diagnostic pop
 
-template <int D, int ROWS = 64, int NW = 4>
+template <int D>
 struct DmaTile {
+  static constexpr int ROWS = 64;
   static constexpr int kStride = (D == 128) ? 152 : 104;  // elements
   static constexpr int kInstr = (ROWS * kStride * 2 + 1023) / 1024;  // wavefront-wide loads per tile
   static constexpr int kBytes = kInstr * 1024;            // the last load may run past the last row
   static constexpr int kElems = kBytes / 2;
-  static constexpr int kPerWave = (kInstr + NW - 1) / NW;  // NW wavefronts share the loads
-
-  struct Plan {
-    uint32_t goff[kPerWave];  // byte offset from the chunk's first row, per load of this lane
-  };
-
-  // Every lane of every load gets a valid address, so that the loads need no branches around them
-  // (a branch would also split the basic block and keep the compiler from scheduling MFMAs and
-  // loads together): a lane that falls on row padding fetches a piece of its row again (it lands
-  // in the padding, which nothing reads), and a wavefront with one load fewer than the others
-  // repeats its last one.
-  __device__ static __forceinline__ Plan plan(int64_t row_stride, int wave, int lane) {
-    Plan pl;
-#pragma unroll
-    for (int n = 0; n < kPerWave; ++n) {
-      const int instr = min(NW * n + wave, kInstr - 1);
-      const int pos = instr * 1024 + lane * 16;
-      int row = pos / (kStride * 2);
-      int piece = (pos - row * kStride * 2) / 16;
-      if (piece >= D / 8) piece -= D / 8;
-      if (row >= ROWS) row = ROWS - 1;  // past the tile: lands in the slack after the last row
-      pl.goff[n] = (uint32_t)(row * row_stride * 2) + 16 * piece;
-    }
-    return pl;
-  }
-
-  // The same for a chunk of which only the first `rows_valid` rows exist (the ragged end of a
-  // sequence): loads of later rows fetch the last existing row instead; nothing may use them.
-  __device__ static __forceinline__ Plan plan_rows(int64_t row_stride, int wave, int lane, int rows_valid) {
-    Plan pl;
-    const int last = max(rows_valid, 1) - 1;
-#pragma unroll
-    for (int n = 0; n < kPerWave; ++n) {
-      const int instr = min(NW * n + wave, kInstr - 1);
-      const int pos = instr * 1024 + lane * 16;
-      int row = pos / (kStride * 2);
-      int piece = (pos - row * kStride * 2) / 16;
-      if (piece >= D / 8) piece -= D / 8;
-      row = min(min(row, ROWS - 1), last);
-      pl.goff[n] = (uint32_t)(row * row_stride * 2) + 16 * piece;
-    }
-    return pl;
-  }
-
-  // One of the kPerWave loads of a chunk, so that a kernel can spread them between MFMAs.
-  // Complete after s_waitcnt vmcnt(0).
-  __device__ static __forceinline__ void issue_one(const Plan& pl, int n, const uint16_t* gbase,
-                                                   const uint16_t* tile, int wave) {
-    const int instr = min(NW * n + wave, kInstr - 1);
-    dma16(gbase, pl.goff[n], lds_addr(tile) + instr * 1024);
-  }
-  // ---- loads dealt to the wavefronts in blocks, issued in groups of up to four per M0 write ----
-  // Wavefront w fetches kBlock consecutive loads of the tile (consecutive kilobytes of LDS),
-  // starting at load min(w * kBlock, kInstr - kBlock): where the blocks do not divide the tile
-  // evenly the last wavefront starts early and fetches a load or two twice (same data, same place)
-  // rather than having a shorter block, so that every wavefront runs the same instructions.  A group
-  // of four shares one M0 value and tells its loads apart by the instruction's immediate offset,
-  // which the hardware adds to the global address as well: the lane offsets of the plan have it
-  // taken out again, plus kBias so that they stay non-negative (the caller passes the chunk's
-  // address minus kBias bytes).
-  static constexpr int kBlock = (kInstr + NW - 1) / NW;
-  static constexpr int kGroups = (kBlock + 3) / 4;
-  static constexpr uint32_t kBias = 3072;
-  struct BlockPlan {
-    uint32_t goff[kBlock];
-  };
-  __device__ static __forceinline__ int block_start(int wave) { return min(wave * kBlock, kInstr - kBlock); }
-  __device__ static __forceinline__ BlockPlan block_plan(int64_t row_stride, int wave, int lane) {
-    BlockPlan pl;
-#pragma unroll
-    for (int n = 0; n < kBlock; ++n) {
-      const int pos = (block_start(wave) + n) * 1024 + lane * 16;
-      int row = pos / (kStride * 2);
-      int piece = (pos - row * kStride * 2) / 16;
-      if (piece >= D / 8) piece -= D / 8;
-      if (row >= ROWS) row = ROWS - 1;  // past the tile: lands in the slack after the last row
-      pl.goff[n] = (uint32_t)(row * row_stride * 2) + 16 * piece + kBias - 1024 * (n & 3);
-    }
-    return pl;
-  }
-  // group G of this wavefront's loads; gbase_biased = address of the chunk's first row minus kBias bytes
-  template <int G>
-  __device__ static __forceinline__ void issue_group(const BlockPlan& pl, const void* gbase_biased, const uint16_t* tile,
-                                                     int wave) {
-    static_assert(G >= 0 && G < kGroups, "group index");
-    constexpr int first = 4 * G;
-    constexpr int count = (kBlock - first) < 4 ? (kBlock - first) : 4;
-    const uint32_t lds = lds_addr(tile) + (block_start(wave) + first) * 1024;
-    dma16_group<count>(gbase_biased, lds, pl.goff[first], pl.goff[first + (count > 1 ? 1 : 0)],
-                       pl.goff[first + (count > 2 ? 2 : 0)], pl.goff[first + (count > 3 ? 3 : 0)]);
-  }
-  // All loads of one chunk.
-  __device__ static __forceinline__ void issue(const Plan& pl, const uint16_t* gbase, const uint16_t* tile,
-                                               int wave) {
-#pragma unroll
-    for (int n = 0; n < kPerWave; ++n) issue_one(pl, n, gbase, tile, wave);
-  }
 
   // row fragment: row = 32*rt + lane%32, features 16*kk + 8*half .. +7
   __device__ static __forceinline__ bf16x8 row_frag(const uint16_t* tile, int rt, int kk, int l32, int half) {
@@ -284,56 +165,54 @@ struct DmaTile {
 
 // ---------------------------------------------------------------------------------------------
 // PieceTile: how the four wavefronts of a workgroup fill a 64-row DmaTile by pieces of 16 rows, one
-// piece each.  Sixteen padded rows are 4864 bytes (D = 128) or 3328 (D = 64), so a piece is a few
-// whole kilobytes and a remainder: the last load of a piece runs with only the lanes that still
-// belong to it (48 or 16 of them).  The four pieces are then back to back - the tile looks exactly
-// as if it had been filled front to back - and where each piece comes from is up to the wavefront
-// that fetches it: one scalar row number.  For mask blocks of 64 or 128 tokens the pieces are
-// consecutive; for 16- and 32-token blocks a chunk is gathered from whatever blocks come next in the
-// tile's list, at no cost per lane.
+// piece each.  Sixteen padded rows are 4864 bytes (D = 128) or 3328 (D = 64), so a piece is four or
+// three whole wavefront-wide loads and one more that ends where the piece ends and fetches the 256 or
+// 768 bytes before its remainder a second time (the same bytes to the same place).  The four pieces
+// are then back to back - the tile looks exactly as if it had been filled front to back - and where
+// each piece comes from is up to the wavefront that fetches it: one scalar row number.  For mask
+// blocks of 64 or 128 tokens the pieces are consecutive; for 16- and 32-token blocks a chunk is
+// gathered from whatever blocks come next in the tile's list, at no cost per lane.
 // ---------------------------------------------------------------------------------------------
 template <int D>
 struct PieceTile {
-  static constexpr int kStride = DmaTile<D>::kStride;              // elements
+  static constexpr int kStride = DmaTile<D>::kStride;   // elements
   static constexpr int kRows = 16;
-  static constexpr int kBytes = kRows * kStride * 2;               // 4864 / 3328
-  static constexpr int kFull = kBytes / 1024;                      // whole wavefront-wide loads: 4 / 3
-  static constexpr int kTailLanes = (kBytes - kFull * 1024) / 16;  // lanes of the last one: 48 / 16
-  static constexpr int kLoads = kFull + 1;
-  static constexpr int kGroups = 2;  // the whole loads (one write of M0), then the last
-  static constexpr uint32_t kBias = 3072;
-  static_assert(kFull >= 1 && kFull <= 4 && kTailLanes > 0 && kTailLanes < 64, "piece = a few whole loads and a remainder");
+  static constexpr int kBytes = kRows * kStride * 2;    // 4864 / 3328
+  static constexpr int kLoads = (kBytes + 1023) / 1024; // 5 / 4
+  static constexpr int kGroups = 2;                     // 3 + 2 / 2 + 2 loads to a write of M0
+  static constexpr uint32_t kBias = 4096;
+  // where load n starts in the piece: the immediate it is issued with
+  __host__ __device__ static constexpr int imm(int n) { return n + 1 < kLoads ? 1024 * n : kBytes - 1024; }
+  static_assert(imm(kLoads - 1) < 4096 && kBytes % 16 == 0, "immediates of twelve bits");
 
   // Byte offset of each of this lane's loads from the piece's first row, plus kBias, minus the
-  // immediate the load is issued with (it is added to the LDS address and to the global one).
+  // immediate (which the instruction adds to the LDS address and to the global one).
   struct Plan {
     uint32_t goff[kLoads];
   };
-  __device__ static constexpr uint32_t imm(int n) { return n < kFull ? 1024u * n : 0u; }
   __device__ static __forceinline__ Plan plan(int64_t row_stride, int lane) {
     Plan pl;
 #pragma unroll
     for (int n = 0; n < kLoads; ++n) {
-      const int pos = n * 1024 + lane * 16;
-      int row = pos / (kStride * 2);
+      const int pos = imm(n) + lane * 16;
+      const int row = pos / (kStride * 2);
       int col = (pos - row * kStride * 2) / 16;
       if (col >= D / 8) col -= D / 8;       // row padding: fetches a part of the row again, nothing reads it
-      if (row >= kRows) row = kRows - 1;    // (lanes the last load is issued without)
       pl.goff[n] = (uint32_t)(row * row_stride * 2) + 16 * col + kBias - imm(n);
     }
     return pl;
   }
   // Group G of the loads of this wavefront's piece into `tile`.  gbase_biased: address of the piece's
-  // first row minus kBias bytes.  All 64 lanes must be active (the last load switches lanes off and
-  // on again by itself).
+  // first row minus kBias bytes.
   template <int G>
   __device__ static __forceinline__ void issue(const Plan& pl, const void* gbase_biased, const uint16_t* tile, int wave) {
     const uint32_t lds = lds_addr(tile) + wave * kBytes;
-    if constexpr (G == 0)
-      dma16_group<kFull>(gbase_biased, lds, pl.goff[0], pl.goff[kFull > 1 ? 1 : 0], pl.goff[kFull > 2 ? 2 : 0],
-                         pl.goff[kFull > 3 ? 3 : 0]);
+    if constexpr (kLoads == 5 && G == 0)
+      dma16_group<imm(0), imm(1), imm(2)>(gbase_biased, lds, pl.goff[0], pl.goff[1], pl.goff[2]);
+    else if constexpr (G == 0)
+      dma16_group<imm(0), imm(1)>(gbase_biased, lds, pl.goff[0], pl.goff[1]);
     else
-      dma16_lanes<kTailLanes>(gbase_biased, lds + kFull * 1024, pl.goff[kFull]);
+      dma16_group<imm(kLoads - 2), imm(kLoads - 1)>(gbase_biased, lds, pl.goff[kLoads - 2], pl.goff[kLoads - 1]);
   }
   // Limits a plan to pieces of which only the first `rows_valid` (>= 1) rows exist: no lane then reads
   // past the last of them (later rows come out as copies of parts of it; nothing may use them).  A plan
@@ -412,8 +291,13 @@ struct EntryList {
 // then all its second longest (map_group chooses).
 __device__ __forceinline__ bool map_workgroup(int wg, int bh_total, int tiles, int group, int& bh, int& rank) {
   const int x = wg & 7, slot = wg >> 3;
-  const int per_xcd = (bh_total + 7) >> 3;  // slots are laid out for the fullest XCD
   const int g = slot / (group * tiles);
+  if (group == 1) {
+    rank = slot - g * tiles;
+    bh = x + 8 * g;
+    return bh < bh_total;
+  }
+  const int per_xcd = (bh_total + 7) >> 3;  // slots are laid out for the fullest XCD
   const int in = slot - g * (group * tiles);
   const int size = min(group, per_xcd - g * group);
   rank = in / size;

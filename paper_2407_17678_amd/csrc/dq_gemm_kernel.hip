@@ -41,7 +41,7 @@ template <int D>
 struct DqGemmSmem {
   union {
     struct {
-      uint16_t k[2][DmaTile<D, 64, 4>::kElems];  // K rows of a chunk (the padded tile of device_util.h), two stages
+      uint16_t k[2][DmaTile<D>::kElems];  // K rows of a chunk (the padded tile of device_util.h), two stages
       unsigned char ds[4][kDsWaveBytes];         // per wavefront: its dS of the current chunk
     } loop;
     float reduce[2][64 * D];  // after the loop: the second key half's sums, per 64-row half of the tile
@@ -54,7 +54,7 @@ struct DqGemmSmem {
 // tracked the compiler's counted waits let the later chunks stay outstanding.
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p) {
-  typedef DmaTile<D, 64, 4> Tile;
+  typedef DmaTile<D> Tile;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   DqGemmSmem<D>& sm = *reinterpret_cast<DqGemmSmem<D>*>(smem_raw);
   constexpr int BM = kBwdBM, DT = D / 32;

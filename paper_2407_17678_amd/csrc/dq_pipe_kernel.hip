@@ -38,13 +38,13 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 template <int D>
 struct DqPipeSmem {
-  uint16_t k[2][DmaTile<D, 64, 4>::kElems];
-  uint16_t v[2][DmaTile<D, 64, 4>::kElems];
+  uint16_t k[2][DmaTile<D>::kElems];
+  uint16_t v[2][DmaTile<D>::kElems];
 };
 
 template <int D, bool DENSE, bool FINE, bool VARLEN>
 __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p) {
-  typedef DmaTile<D, 64, 4> Tile;
+  typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   DqPipeSmem<D>& sm = *reinterpret_cast<DqPipeSmem<D>*>(smem_raw);

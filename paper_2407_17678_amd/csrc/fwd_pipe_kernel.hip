@@ -60,7 +60,7 @@ constexpr float kTau = 8.0f;  // log2 units a score may exceed the reference max
 // stores are guarded per row.
 template <int D, bool DENSE, bool FINE, bool VARLEN>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(const AttnParams p) {
-  typedef DmaTile<D, 64, 4> Tile;
+  typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
   __shared__ __attribute__((aligned(16))) uint16_t sk[2][Tile::kElems];
   __shared__ __attribute__((aligned(16))) uint16_t sv[2][Tile::kElems];
@@ -186,6 +186,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   float mc = 0.f;         // the same times scale * log2(e); 0 while nothing was seen
   float l_run = 0.f;      // sum of the probabilities over my half's key rows
   const float c = p.scale_log2e;
+  const float tau = kTau / c;  // in units of raw scores
   // The lane offsets of my direct loads, for K and for V.  Where a packed sequence ends inside the rows
   // I fetch (VARLEN) they are limited to the rows that exist; the lists ascend, so from then on every
   // piece is such a piece, with fewer and fewer rows.
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     mx = max_halves(mx);
     // (a lane that has seen no key yet has m_ref = -inf: its first score always exceeds that, and while it
     // sees none the difference is not a number, which does not)
-    if (__any((mx - m_ref) * c > kTau)) {
+    if (__any(mx - m_ref > tau)) {
       const float m_new = fmaxf(m_ref, mx);
       const float m_use = (m_new == kNegInf) ? 0.f : m_new;
       const float alpha = fast_exp2((m_ref - m_use) * c);

@@ -48,9 +48,10 @@ struct s2_layout {
   int32_t* d_col_idx = nullptr;
   s2::TileList q_tiles;   // row groups  -> kept KV blocks   (forward, dQ pass)
   s2::TileList kv_tiles;  // column groups -> attending Q blocks (dK/dV pass)
-  // 16-token blocks: the row groups' lists with an entry per block (8 bits of membership) instead of per
-  // unit of two, which is what the kernels that gather their chunks block by block walk.
-  s2::TileList q_block_tiles;
+  // 16-token blocks: the same two with an entry per block (8 bits of membership) instead of per unit of
+  // two, and with key tiles of any eight columns that are attended by nearly the same rows instead of
+  // adjacent ones.  This is what the kernels walk, which gather their chunks block by block.
+  s2::TileList q_block_tiles, kv_block_tiles;
   // Backward that keeps dS (64- and 128-token blocks): the dK/dV pass leaves dS in units of 64
   // queries x 64 keys, unit (2 * step + wavefront pair) of its walk over kv_tiles; dq_units names, for
   // every 64-key chunk of the q_tiles lists and either 64-row half of the query tile, the unit that
