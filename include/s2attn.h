@@ -245,8 +245,10 @@ int s2_attn_fwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
 /* ---- backward (gradient of the above) ---------------------------------------------------- */
 
 /* Given q,k,v,o,lse,d_o writes dq,dk,dv (bf16; fp32 accumulation).  workspace is DEVICE memory
- * of at least s2_attn_bwd_workspace_bytes(...) bytes, 256-byte aligned, contents undefined on
- * entry and exit.  Errors as forward plus WORKSPACE. */
+ * of s2_attn_bwd_workspace_bytes(...) bytes, 256-byte aligned, contents undefined on entry and exit.
+ * (Two floats per row, each array rounded up to 256 bytes, are enough to run: the rest, asked for
+ * where a launch has few key tiles, lets the longest of them be shared between workgroups.)  Errors as
+ * forward plus WORKSPACE. */
 int s2_attn_bwd(const s2_layout* layout, const s2_tensors* t, float scale, void* workspace,
                 size_t workspace_bytes, void* stream);
 size_t s2_attn_bwd_workspace_bytes(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim);

@@ -53,7 +53,8 @@ void free_device_copies(s2_layout* L) {
   if (L->d_row_ptr) (void)hipFree(L->d_row_ptr);
   if (L->d_col_idx) (void)hipFree(L->d_col_idx);
   if (L->d_dq_units) (void)hipFree(L->d_dq_units);
-  L->d_row_ptr = L->d_col_idx = L->d_dq_units = nullptr;
+  if (L->d_kv_split_codes) (void)hipFree(L->d_kv_split_codes);
+  L->d_row_ptr = L->d_col_idx = L->d_dq_units = L->d_kv_split_codes = nullptr;
 }
 
 s2::DevTiles dev_tiles(const s2::TileList& t) {
@@ -189,6 +190,7 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
         s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_block_tiles);
         s2::build_block_tiles(*L, s2::kBwdBN / S, true, L->kv_block_tiles);
       }
+      s2::build_splits(*L, S == 16 ? L->kv_block_tiles : L->kv_tiles);
       s2::build_ds_units(*L);
     } catch (const std::bad_alloc&) {
       st = S2_ERR_OVERFLOW;
@@ -203,7 +205,8 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
     int dev = 0;
     bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->p.block_size == 16 ? L->q_block_tiles : L->q_tiles) &&
               upload_tiles(L->p.block_size == 16 ? L->kv_block_tiles : L->kv_tiles) && upload(L->row_ptr, &L->d_row_ptr) &&
-              upload(L->col_idx, &L->d_col_idx) && upload(L->dq_units, &L->d_dq_units);
+              upload(L->col_idx, &L->d_col_idx) && upload(L->dq_units, &L->d_dq_units) &&
+              upload(L->kv_split_codes, &L->d_kv_split_codes);
     if (!ok) {
       free_device_copies(L);
       delete L;
@@ -306,15 +309,75 @@ int s2_attn_fwd(const s2_layout* layout, const s2_tensors* t, float scale, void*
   return hip_ok(s2::launch_fwd(p, false, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 
+namespace {
+
+size_t round256(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+// The backward's workspace: delta = rowsum(dO * O), a copy of LSE in base-2 units, and - for launches
+// of so few tiles that the longest ones may be cut - a counter per key tile and the sums of the parts.
+struct BwdWorkspace {
+  size_t stats;      // bytes of either of the two arrays
+  size_t count;      // of the counters
+  size_t sums;       // of the sums
+  int64_t slots;     // parts that there is room for
+  size_t required() const { return 2 * stats; }  // without the rest no tile is cut
+  size_t total() const { return 2 * stats + count + sums; }
+};
+BwdWorkspace bwd_workspace(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim) {
+  BwdWorkspace w{};
+  const int64_t rows = (int64_t)batch * heads * seqlen;
+  w.stats = round256((size_t)rows * sizeof(float));
+  const int64_t tiles = (int64_t)batch * heads * ((seqlen + s2::kBwdBN - 1) / s2::kBwdBN);
+  // From 4096 tiles on (eight rounds of the chip's 512 workgroup slots) the longest tile no longer decides.
+  if (tiles < 4096) {
+    w.count = round256((size_t)tiles * sizeof(int32_t));
+    w.slots = std::min<int64_t>(768, 8 * tiles);
+    w.sums = (size_t)w.slots * s2::kBwdBN * head_dim * 2 * sizeof(float);
+  }
+  return w;
+}
+
+}  // namespace
+
 size_t s2_attn_bwd_workspace_bytes(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim) {
-  (void)head_dim;
-  if (batch < 1 || heads < 1 || seqlen < 1) return 0;
-  const size_t rows = (size_t)batch * heads * seqlen;
-  // delta = rowsum(dO * O) and a copy of LSE in base-2 units, 256-byte aligned each
-  return 2 * (((rows * sizeof(float) + 255) / 256) * 256);
+  if (batch < 1 || heads < 1 || seqlen < 1 || head_dim < 1) return 0;
+  return bwd_workspace(batch, heads, seqlen, head_dim).total();
 }
 
 namespace {
+
+// Whether and how to cut the longest key tiles.  A stripe column is attended by every later row, so a head
+// has a few tiles of up to N / 64 steps among many short ones.  With enough (batch, head) pairs the long
+// ones are hidden behind the rest; with few the launch is as long as its longest tile while most
+// of the chip idles.  `even`: the steps a workgroup slot would walk if all were shared out evenly (a tile
+// costs about five steps besides its own, an XCD holds 64 workgroups of head_dim 128 and the
+// equivalent of 80 of 64).  Measured, forward + backward with the longest tile / even = 4.4 (8 heads
+// x 4096): 202 -> 89 us; 2.3 (2 x 16 x 3904): 255 -> 183; 3.0 (16 x 16384): 969 -> 637; 1.5 (2 x 20 x 8192,
+// blocks of 128): 677 -> 616; 1.2 (3 x 16 x 8192): 791 -> 764; 0.88 (4 x 16 x 8192): 999 uncut, 1026 cut.  The
+// best length of a part was 6 to 8, 24, 64, 48 to 64 and 64 steps, that is about 3/4 of `even` plus 3: a
+// part's own cost (its start, 64 KB per 128 keys and 64 features written and read again) against the evenness of the launch.
+void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, unsigned char* workspace) {
+  const double slots = p.head_dim == 128 ? 64 : 80;
+  const double even = ((p.batch * p.heads + 7) / 8) * (L->kv_head_steps + 5.0 * p.kv_tiles.tiles_per_head) / slots;
+  if (L->kv_max_steps <= 1.1 * even) return;
+  const double best = 0.75 * even + 3;
+  const s2::SplitLevel* use = nullptr;
+  double off = 0;
+  for (const s2::SplitLevel& lv : L->kv_levels) {
+    if ((int64_t)p.batch * p.heads * lv.n_items > w.slots || 2 * lv.steps > L->kv_max_steps) continue;
+    const double o = std::max(lv.steps / best, best / lv.steps);
+    if (use && o >= off) continue;
+    use = &lv;
+    off = o;
+  }
+  if (!use) return;
+  p.split_codes = L->d_kv_split_codes + use->offset;
+  p.split_items = use->n_items;
+  p.split_long = use->n_long;
+  p.split_count = reinterpret_cast<int32_t*>(workspace + 2 * w.stats);
+  p.split_sums = reinterpret_cast<float*>(workspace + 2 * w.stats + w.count);
+}
+
 // The backward that keeps dS covers head_dim 128, mask blocks of 64 or 128 tokens (the layout then
 // carries the unit table) and whole 128-row tiles.
 bool keeps_ds(const s2_layout* L, int32_t seqlen, int32_t head_dim) {
@@ -423,20 +486,20 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
   if (st != S2_OK) return st;
   st = check_layout_fits(layout, t);
   if (st != S2_OK) return st;
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
-      workspace_bytes < s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim))
+  const BwdWorkspace w = bwd_workspace(t->batch, t->heads, t->seqlen, t->head_dim);
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < w.required())
     return S2_ERR_WORKSPACE;
   if (!layout_on_current_device(layout)) return S2_ERR_NO_DEVICE;
   s2::AttnParams p = make_params(t, scale);
   p.delta = static_cast<float*>(workspace);
-  p.lse2 = p.delta + s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim) / 8;
+  p.lse2 = p.delta + w.stats / sizeof(float);
   p.block_size = layout->p.block_size;
   set_tiles(p, layout);
+  if (w.slots > 0 && workspace_bytes >= w.total()) choose_split(p, layout, w, static_cast<unsigned char*>(workspace));
   // a workspace large enough to keep dS selects the backward that computes nothing twice
-  const size_t small = s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim);
   if (keeps_ds(layout, t->seqlen, t->head_dim) &&
       workspace_bytes >= s2_attn_bwd_layout_workspace_bytes(layout, t->batch, t->heads, t->seqlen, t->head_dim)) {
-    p.ds_store = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) + small);
+    p.ds_store = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) + w.total());
     p.ds_units = layout->ds_units;
     p.dq_units = layout->d_dq_units;
   }
@@ -468,14 +531,14 @@ int s2_dense_causal_bwd(const s2_tensors* t, float scale, void* workspace, size_
                         void* stream) {
   int st = check_tensors(t, true, scale);
   if (st != S2_OK) return st;
-  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 ||
-      workspace_bytes < s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim))
+  const BwdWorkspace w = bwd_workspace(t->batch, t->heads, t->seqlen, t->head_dim);
+  if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < w.required())
     return S2_ERR_WORKSPACE;
   s2::AttnParams p = make_params(t, scale);
   st = dense_params(t, p);
   if (st != S2_OK) return st;
   p.delta = static_cast<float*>(workspace);
-  p.lse2 = p.delta + s2_attn_bwd_workspace_bytes(t->batch, t->heads, t->seqlen, t->head_dim) / 8;
+  p.lse2 = p.delta + w.stats / sizeof(float);
   return hip_ok(s2::launch_bwd(p, true, s2::kBwdAll, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 

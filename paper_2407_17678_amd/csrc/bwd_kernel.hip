@@ -1,7 +1,7 @@
 // Backward kernels: gradients of block-sparse causal attention (the backward pass that goes with
 // the forward of section 3.2; the paper names it as the less optimised half of its kernels).
 //
-// Two launches (three kernels exist), no atomics, bitwise reproducible:
+// Two launches (three kernels exist), no floating-point atomics, bitwise reproducible:
 //   delta  : delta[t] = sum_d dO[t][d] * O[t][d].  Folded into the dq launch, which holds the dO
 //            fragments anyway; the stand-alone kernel runs only when dK/dV is asked for alone.
 //   dq     : row-stationary, in dq_pipe_kernel.hip (dq_gemm_kernel.hip where dS is kept).  A workgroup
@@ -9,7 +9,10 @@
 //            forward does), recomputing P and forming dS = P * (dP - delta), dQ += scale * dS K.
 //   dkdv   : column-stationary.  A workgroup owns 128 keys - one or two mask columns, paired by
 //            the layout builder so that both are attended by nearly the same query blocks - and
-//            walks the query blocks that keep them: dV += P^T dO, dK += scale * dS^T Q.
+//            walks the query blocks that keep them: dV += P^T dO, dK += scale * dS^T Q.  Where a launch
+//            has few tiles, the longest are cut into parts for several workgroups; the last one to
+//            finish adds the parts up in their order.  dK/dV launch of 2 x 16 heads x 4096 x 64 107 -> 56 us,
+//            2 x 16 x 3904 x 128 163 -> 88, 1 x 16 x 8192 x 128 with 16-token blocks 355 -> 95.
 //
 // Both main kernels keep the stationary operand's MFMA fragments in registers with the lane
 // owning one stationary row, so the recomputed score tile lands in the C layout with the
@@ -55,6 +58,7 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p) {
   }
 #pragma unroll
   for (int m = LPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
+  clear_split_counts(p, blockIdx.x * 256 + tid);
   if (c == 0 && row < rows_total) {
     p.delta[row] = acc;
     p.lse2[row] = p.lse[row] * kLog2e;  // the main kernels want LSE in base-2 units
@@ -62,6 +66,32 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p) {
 }
 
 // ------------------------------------------------------------------------------------ dk, dv
+
+// To and from memory that other workgroups, on any XCD, write and read in the same launch: the sc1 bit is
+// agent scope, past the caches that the XCDs do not share (what a relaxed atomic of that scope compiles
+// to, sixteen bytes at a time).  Base in scalar registers, a lane offset in bytes, an immediate.
+template <int OFF>
+__device__ __forceinline__ void store_agent(void* base, uint32_t lane_off, f32x4 x) {
+  // (the no-op is the wait state a wide store needs before its data registers are written again)
+  asm volatile("global_store_dwordx4 %0, %1, %2 offset:%3 sc1\n\ts_nop 0" ::"v"(lane_off), "v"(x), "s"(base), "n"(OFF) : "memory");
+}
+// sixteen kilobyte-wide loads in flight together, and the wait for them
+__device__ __forceinline__ void load_agent16(const void* base, uint32_t lane_off, f32x4 (&x)[16]) {
+  const char* b0 = static_cast<const char*>(base);
+  asm volatile("global_load_dwordx4 %0, %16, %17 sc1\n\tglobal_load_dwordx4 %1, %16, %17 offset:1024 sc1\n\t"
+               "global_load_dwordx4 %2, %16, %17 offset:2048 sc1\n\tglobal_load_dwordx4 %3, %16, %17 offset:3072 sc1\n\t"
+               "global_load_dwordx4 %4, %16, %18 sc1\n\tglobal_load_dwordx4 %5, %16, %18 offset:1024 sc1\n\t"
+               "global_load_dwordx4 %6, %16, %18 offset:2048 sc1\n\tglobal_load_dwordx4 %7, %16, %18 offset:3072 sc1\n\t"
+               "global_load_dwordx4 %8, %16, %19 sc1\n\tglobal_load_dwordx4 %9, %16, %19 offset:1024 sc1\n\t"
+               "global_load_dwordx4 %10, %16, %19 offset:2048 sc1\n\tglobal_load_dwordx4 %11, %16, %19 offset:3072 sc1\n\t"
+               "global_load_dwordx4 %12, %16, %20 sc1\n\tglobal_load_dwordx4 %13, %16, %20 offset:1024 sc1\n\t"
+               "global_load_dwordx4 %14, %16, %20 offset:2048 sc1\n\tglobal_load_dwordx4 %15, %16, %20 offset:3072 sc1\n\t"
+               "s_waitcnt vmcnt(0)"
+               : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7]),
+                 "=&v"(x[8]), "=&v"(x[9]), "=&v"(x[10]), "=&v"(x[11]), "=&v"(x[12]), "=&v"(x[13]), "=&v"(x[14]), "=&v"(x[15])
+               : "v"(lane_off), "s"(b0), "s"(b0 + 4096), "s"(b0 + 8192), "s"(b0 + 12288)
+               : "memory");
+}
 
 template <int D>
 struct DkvSmem {
@@ -99,10 +129,23 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int T = p.kv_tiles.tiles_per_head;
+  constexpr bool kSplits = !DENSE && !VARLEN;
   int bh, rank;
-  if (!map_workgroup_interleaved(blockIdx.x, p.batch * p.heads, T, bh, rank)) return;
+  if (!map_workgroup_interleaved(blockIdx.x, p.batch * p.heads, kSplits ? p.split_items + T - p.split_long : T, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
-  const int tile = DENSE ? rank : p.kv_tiles.order[h * T + rank];  // dense: first key tiles are longest
+  // which part of which tile, in descending length: the parts of the tiles that are cut, then the others
+  int part = 0, parts = 1, nth = rank;
+  if (kSplits) {
+    if (rank < p.split_items) {
+      const int code = p.split_codes[rank];
+      nth = code & 0xFFFF;
+      part = (code >> 16) & 0xFF;
+      parts = code >> 24;
+    } else {
+      nth = rank - p.split_items + p.split_long;
+    }
+  }
+  const int tile = DENSE ? rank : p.kv_tiles.order[h * T + nth];  // dense: first key tiles are longest
   const int S = DENSE ? CH : p.block_size;  // FINE: 16 or 32, else 64 or 128
   const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
   const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-row pieces per list entry
@@ -154,6 +197,13 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
   } else {
     ent_lo = p.kv_tiles.ptr[h * T + tile];
     n_ent = p.kv_tiles.ptr[h * T + tile + 1] - ent_lo;
+  }
+  if (kSplits && parts > 1) {  // my part: so many entries, or (FINE) so many full steps of entries
+    const int units = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent;
+    const int u0 = units * part / parts, u1 = units * (part + 1) / parts;
+    const int e0 = FINE ? (4 * u0) >> ppe_sh : u0;
+    n_ent = (FINE ? min((4 * u1) >> ppe_sh, n_ent) : u1) - e0;
+    ent_lo += e0;
   }
   // steps: chunks of an entry, or (FINE) as many as the entries' pieces fill
   const int total = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent << cpb_sh;
@@ -254,7 +304,7 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     (void)list.get(e, lane);
     it0 = FINE ? (e << ppe_sh) >> 2 : e << cpb_sh;
   }
-  issue_chunk(it0, it0 & 1, lane);
+  if (!kSplits || total > 0) issue_chunk(it0, it0 & 1, lane);  // (where a head's tile is short for its rank a part may be empty)
 
   bf16x8 kf[D / 16], vf[D / 16];  // K and V fragments (B operands), lane = key
 #pragma unroll
@@ -398,6 +448,55 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     __syncthreads();
   }
 
+  if (kSplits && parts > 1) {
+    // This is a part of a tile: leave my sums in memory, and if the other parts have done so already add
+    // all of them up, in the order of the parts, and go on with the result.
+    constexpr int kTiles = 2 * (D / 32);               // accumulator tiles of a wavefront, dK and dV in turn
+    constexpr int kWaveBytes = kTiles * 4 * 1024;      // [tile][register quad][lane][4 floats]
+    const uint32_t lane_off = 16 * lane;
+    unsigned char* const sums = reinterpret_cast<unsigned char*>(p.split_sums) + ((int64_t)bh * p.split_items + rank) * (4 * kWaveBytes) +
+                                wave * kWaveBytes;
+    auto quad = [](const f32x16& a, int g) S2_INLINE { return f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]}; };
+    static_for<kTiles>([&](auto tc) S2_INLINE {
+      constexpr int t = decltype(tc)::value;
+      const f32x16& a = t & 1 ? acc_dv[t >> 1] : acc_dk[t >> 1];
+      store_agent<0>(sums + 4096 * t, lane_off, quad(a, 0));
+      store_agent<1024>(sums + 4096 * t, lane_off, quad(a, 1));
+      store_agent<2048>(sums + 4096 * t, lane_off, quad(a, 2));
+      store_agent<3072>(sums + 4096 * t, lane_off, quad(a, 3));
+    });
+    wait_all_loads();  // my stores have arrived
+    __syncthreads();
+    int* const flag = reinterpret_cast<int*>(&sm.rs[0]);
+    if (tid == 0) {
+      int32_t* const count = p.split_count + (int64_t)bh * T + nth;
+      const int done = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (done == parts - 1) *count = 0;  // for the next launch; nobody else looks any more
+      *flag = done;
+    }
+    __syncthreads();
+    if (*flag != parts - 1) return;
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) {
+      acc_dk[dt] = f32x16{};
+      acc_dv[dt] = f32x16{};
+    }
+    const unsigned char* from = sums - (int64_t)part * (4 * kWaveBytes);
+#pragma unroll 1
+    for (int i = 0; i < parts; ++i, from += 4 * kWaveBytes) {
+      static_for<kTiles / 4>([&](auto jc) S2_INLINE {
+        constexpr int j = decltype(jc)::value;
+        f32x4 x[16];
+        load_agent16(from + 16384 * j, lane_off, x);
+#pragma unroll
+        for (int n = 0; n < 16; ++n) {
+          f32x16& a = (n >> 2) & 1 ? acc_dv[2 * j + (n >> 3)] : acc_dk[2 * j + (n >> 3)];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[4 * (n & 3) + e] += x[n][e];
+        }
+      });
+    }
+  }
   if (!wave_active) return;
   // dK and dV go out through LDS (free since the loop's last barrier; each wavefront uses regions of its
   // own, so no barrier).  A lane holds its row's features four at a time, and storing them from there
@@ -460,7 +559,7 @@ hipError_t launch_dkdv(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   hipError_t e = set_smem(&dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>, sizeof(DkvSmem<D>), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(grid_for(p.batch * p.heads, p.kv_tiles.tiles_per_head)),
+  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(grid_for(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long)),
                      dim3(kThreads), sizeof(DkvSmem<D>), stream, p);
   return hipGetLastError();
 }

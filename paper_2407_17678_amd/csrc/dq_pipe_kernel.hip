@@ -60,6 +60,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  if (!DENSE && !VARLEN) clear_split_counts(p, blockIdx.x * kThreads + tid);
   const int T = p.q_tiles.tiles_per_head;
   const int T_run = VARLEN ? (p.q_rows + BM - 1) / BM : T;  // packed batch: tiles of the longest length allowed
   int bh, rank;

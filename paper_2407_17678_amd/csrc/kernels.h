@@ -45,6 +45,15 @@ struct AttnParams {
   DevTiles fwd_tiles; // row tiles of the forward kernel -> KV blocks
   DevTiles q_tiles;   // row tiles of the dQ kernel -> KV blocks
   DevTiles kv_tiles;  // column tiles -> Q blocks
+  // Key tiles cut into parts (SplitLevel in layout.h; split_items == 0: none are): the first split_items
+  // items of a head are parts of its first split_long tiles.  The parts' sums go to split_sums, [batch *
+  // heads][item][wavefront][accumulator quad][lane][4] floats, and split_count[batch * heads][tile] counts the
+  // parts that are done: it is zero before the launch (the launch before it, which leaves delta, clears it)
+  // and zero again after.
+  const int32_t* split_codes;
+  float* split_sums;
+  int32_t* split_count;
+  int split_items, split_long;
   // Backward with dS kept (head_dim 128, mask blocks of 64 or 128 tokens): the dK/dV kernel leaves
   // dS = P * (dP - delta), rounded to bf16, in the workspace, in units of 64 queries x 64 keys (8 KiB),
   // unit (2 * step + wavefront pair) of its walk; the dQ launch is then the one contraction dS K over
@@ -53,6 +62,12 @@ struct AttnParams {
   int64_t ds_units;            // units per batch element
   const int32_t* dq_units;     // [dQ list chunk][query half of the 128-row tile]: unit, -1 = none
 };
+
+// Clears the counters of the key tiles that are cut, thread i of a launch that precedes the dK/dV launch
+// (it has at least as many threads as there are tiles).
+__device__ __forceinline__ void clear_split_counts(const AttnParams& p, int i) {
+  if (p.split_items > 0 && i < p.batch * p.heads * p.kv_tiles.tiles_per_head) p.split_count[i] = 0;
+}
 
 struct DecodeParams {
   const uint16_t* q;

@@ -290,6 +290,41 @@ void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& 
   build_lists(L, group, transpose, 1, out);
 }
 
+void build_splits(s2_layout& L, const TileList& kv) {
+  L.kv_levels.clear();
+  L.kv_split_codes.clear();
+  const int H = L.p.num_heads, T = kv.tiles_per_head, S = L.p.block_size;
+  // 64-row steps of a list of n entries (of a block each)
+  auto steps_of = [&](int n) { return (int)(((int64_t)n * S + 63) / 64); };
+  std::vector<int> longest((size_t)T, 0);  // over heads, by rank in the head's order
+  double sum = 0;
+  for (int h = 0; h < H; ++h)
+    for (int k = 0; k < T; ++k) {
+      const size_t t = (size_t)h * T + kv.order[(size_t)h * T + k];
+      const int n = steps_of(kv.ptr[t + 1] - kv.ptr[t]);
+      longest[(size_t)k] = std::max(longest[(size_t)k], n);
+      sum += n;
+    }
+  L.kv_max_steps = longest[0];
+  L.kv_head_steps = sum / H;
+  for (int steps : {4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256}) {
+    if (steps * 3 > longest[0] * 2) break;           // next to nothing to cut
+    if (longest[0] > 64 * steps) continue;           // parts are counted in seven bits
+    if (L.kv_head_steps > 64.0 * 3 * steps) continue;  // one head on an XCD's 64 workgroup slots is longer than that
+    SplitLevel lv;
+    lv.steps = steps;
+    lv.offset = (int)L.kv_split_codes.size();
+    for (int k = 0; k < T && longest[(size_t)k] > steps; ++k) {
+      const int parts = (longest[(size_t)k] + steps - 1) / steps;
+      for (int i = 0; i < parts; ++i) L.kv_split_codes.push_back(k | i << 16 | parts << 24);
+      lv.n_items += parts;
+      ++lv.n_long;
+    }
+    if (lv.n_long > 0xFFFF) return;
+    L.kv_levels.push_back(lv);
+  }
+}
+
 void build_ds_units(s2_layout& L) {
   L.dq_units.clear();
   L.ds_units = 0;

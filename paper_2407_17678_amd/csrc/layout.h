@@ -34,6 +34,17 @@ struct TileList {
   int max_len = 0;
 };
 
+// How the dK/dV launch may cut its longest key tiles into parts that different workgroups walk (their sums
+// are then added by whichever of them is done last).  The lengths of a head's tiles are sorted, so a way
+// of cutting is: the first n_long tiles of every head's order, tile k into as many parts as keep it within
+// `steps` steps for the head where it is longest.
+struct SplitLevel {
+  int steps = 0;    // 64-row steps a part has at most
+  int n_long = 0;   // tiles that are cut
+  int n_items = 0;  // parts they are cut into, over one head
+  int offset = 0;   // first of the level's n_items codes: tile | part << 16 | parts << 24, longest tile first
+};
+
 }  // namespace s2
 
 struct s2_layout {
@@ -52,6 +63,12 @@ struct s2_layout {
   // two, and with key tiles of any eight columns that are attended by nearly the same rows instead of
   // adjacent ones.  This is what the kernels walk, which gather their chunks block by block.
   s2::TileList q_block_tiles, kv_block_tiles;
+  // Of the key tiles the kernels walk: the ways to cut them, and what choosing one takes
+  std::vector<s2::SplitLevel> kv_levels;
+  std::vector<int32_t> kv_split_codes;
+  int32_t* d_kv_split_codes = nullptr;
+  int kv_max_steps = 0;       // longest tile
+  double kv_head_steps = 0;   // steps of all tiles of a head, averaged over heads
   // Backward that keeps dS (64- and 128-token blocks): the dK/dV pass leaves dS in units of 64
   // queries x 64 keys, unit (2 * step + wavefront pair) of its walk over kv_tiles; dq_units names, for
   // every 64-key chunk of the q_tiles lists and either 64-row half of the query tile, the unit that
@@ -74,6 +91,8 @@ int64_t row_blocks(const s2_layout_params& p, int head, int i, int32_t* out, int
 void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out);
 // The same with one partner block per entry whatever the block size (partner index = entry >> 16, unsigned).
 void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& out);
+// Fills kv_levels and what belongs to them from `kv` (the key tiles the kernels walk).
+void build_splits(s2_layout& L, const TileList& kv);
 // Fills dq_units / ds_units from q_tiles and kv_tiles (built before, with 128-row and 128-key tiles).
 void build_ds_units(s2_layout& L);
 }  // namespace s2

@@ -1,0 +1,87 @@
+"""The dK/dV launch with its longest key tiles cut into parts that different workgroups walk (chosen when a
+launch has few tiles, by the room in the workspace): against the fp64 oracle at the usual 2e-2 relative
+L2, bit for bit repeatable though the parts finish in any order, the same through the stage calls when
+the dK/dV launch runs several times on one delta, and close to the uncut result of the smallest workspace.
+One pattern has a column that every row of one head attends while the other heads keep their diagonal
+only, so that parts of their tiles are empty."""
+
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import s2_oracle as orc
+from paper_2407_17678_amd import binding as B
+from paper_2407_17678_amd import synth
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # D, S, heads, batch, blocks, local, stride (0: the one-column pattern), keep dS
+    (64, 64, 4, 1, 8, 2, 4, False),       # parts of four steps
+    (64, 16, 3, 1, 64, 2, 16, False),
+    (64, 128, 2, 2, 12, 1, 4, False),
+    (128, 64, 2, 1, 33, 2, 8, False),     # an odd number of blocks
+    (128, 64, 3, 1, 32, 3, 8, True),
+    (128, 32, 2, 2, 40, 2, 8, False),
+    (128, 16, 9, 1, 66, 3, 16, False),    # the last step of a list not full
+    (128, 128, 2, 1, 12, 1, 4, True),
+    (128, 64, 3, 1, 32, 1, 0, False),
+    (128, 64, 3, 1, 32, 1, 0, True),
+    (64, 16, 3, 1, 128, 1, 0, False),
+]
+
+
+def _mask(H, Bk, B_l, stride):
+    if stride:
+        return orc.block_mask(H, Bk, B_l, stride)
+    M = np.zeros((H, Bk, Bk), dtype=bool)
+    M[:, np.arange(Bk), np.arange(Bk)] = True
+    M[1, :, 0] = True
+    return M
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "D%d_S%d_H%d_b%d_B%d_L%d_V%d_%s" % (c[:7] + ("keep" if c[7] else "again",)))
+def test_cut_tiles(case):
+    D, S, H, batch, Bk, B_l, stride, keep_ds = case
+    N = Bk * S
+    w = dataclasses.replace(synth.WORKLOADS["tiny" if D == 64 else "1p3b_8k"], block_size=S)
+    print("cut tiles case", case, flush=True)
+    bits = synth.train_inputs(w, heads=H, batch=batch, seqlen=N)
+    q, k, v, g = (G.to_dev(x) for x in bits)
+    M = _mask(H, Bk, B_l, stride)
+    row_ptr, col_idx, _, _ = orc.compressed_layout(M)
+    lay = B.s2_layout_from_csr(H, Bk, S, row_ptr, col_idx)
+    o = torch.empty_like(q)
+    lse = torch.empty((batch, H, N), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, w.scale)
+    size = B.s2_attn_bwd_layout_workspace_bytes if keep_ds else lambda lay, *s: B.s2_attn_bwd_workspace_bytes(*s)
+    ws = torch.full((size(lay, batch, H, N, D),), 0xFF, dtype=torch.uint8, device="cuda")
+    runs = []
+    for _ in range(3):
+        grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+        ws[:] = 0xFF
+        B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, w.scale, ws)
+        runs.append(grads)
+    grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+    ws[:] = 0xFF
+    # (delta comes from the launch that a whole backward takes it from, so that it is the same to the bit)
+    for stage in (B.BWD_DELTA if keep_ds else B.BWD_DQ, B.BWD_DKDV, B.BWD_DKDV, B.BWD_DKDV):
+        B.s2_attn_bwd_stages(lay, q, k, v, o, lse, g, *grads, w.scale, ws, stage)
+    # two floats per row: nothing is cut
+    small = [torch.full_like(q, float("nan")) for _ in range(3)]
+    least = 2 * ((batch * H * N * 4 + 255) // 256 * 256)
+    B.s2_attn_bwd(lay, q, k, v, o, lse, g, *small, w.scale, ws[:least])
+    torch.cuda.synchronize()
+    ref = orc.attention_backward(*(G.bits_f64(x) for x in bits), M, S, w.scale)
+    for i, n in enumerate(("dq", "dk", "dv")):
+        for b in range(batch):
+            for h in range(H):
+                assert G.rel_l2(G.to_f64(runs[0][i])[b, h], ref[i][b, h]) <= 2e-2, (n, b, h)
+        assert all(torch.equal(runs[0][i], r[i]) for r in runs[1:]), n
+        # (the sums differ in the order of their fp32 additions, dQ also in whether dS is formed twice: at
+        # most bf16 roundings, 2^-9 of an element each way)
+        assert G.rel_l2(G.to_f64(small[i]), G.to_f64(runs[0][i])) <= 5e-3, n
+    assert torch.equal(grads[1], runs[0][1]) and torch.equal(grads[2], runs[0][2])
