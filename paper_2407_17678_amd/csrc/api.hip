@@ -48,8 +48,6 @@ void free_tiles(s2::TileList& t) {
 void free_device_copies(s2_layout* L) {
   free_tiles(L->q_tiles);
   free_tiles(L->kv_tiles);
-  free_tiles(L->q_block_tiles);
-  free_tiles(L->kv_block_tiles);
   if (L->d_row_ptr) (void)hipFree(L->d_row_ptr);
   if (L->d_col_idx) (void)hipFree(L->d_col_idx);
   if (L->d_dq_units) (void)hipFree(L->d_dq_units);
@@ -70,9 +68,8 @@ s2::DevTiles dev_tiles(const s2::TileList& t) {
 
 // The lists the row-tile and key-tile kernels walk.
 void set_tiles(s2::AttnParams& p, const s2_layout* L) {
-  const bool by_block = L->p.block_size == 16;
-  p.fwd_tiles = p.q_tiles = dev_tiles(by_block ? L->q_block_tiles : L->q_tiles);
-  p.kv_tiles = dev_tiles(by_block ? L->kv_block_tiles : L->kv_tiles);
+  p.fwd_tiles = p.q_tiles = dev_tiles(L->q_tiles);
+  p.kv_tiles = dev_tiles(L->kv_tiles);
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -184,13 +181,9 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
     try {
       const int S = L->p.block_size;
       static_assert(s2::kFwdBM == s2::kBwdBM, "forward and dQ walk the same lists");
-      s2::build_tiles(*L, s2::kBwdBM / S, false, L->q_tiles);
-      s2::build_tiles(*L, s2::kBwdBN / S, true, L->kv_tiles);
-      if (S == 16) {
-        s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_block_tiles);
-        s2::build_block_tiles(*L, s2::kBwdBN / S, true, L->kv_block_tiles);
-      }
-      s2::build_splits(*L, S == 16 ? L->kv_block_tiles : L->kv_tiles);
+      s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_tiles);
+      s2::build_block_tiles(*L, s2::kBwdBN / S, true, L->kv_tiles);
+      s2::build_splits(*L);
       s2::build_ds_units(*L);
     } catch (const std::bad_alloc&) {
       st = S2_ERR_OVERFLOW;
@@ -203,8 +196,7 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
   int ndev = 0;
   if (hipGetDeviceCount(&ndev) == hipSuccess && ndev > 0) {
     int dev = 0;
-    bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->p.block_size == 16 ? L->q_block_tiles : L->q_tiles) &&
-              upload_tiles(L->p.block_size == 16 ? L->kv_block_tiles : L->kv_tiles) && upload(L->row_ptr, &L->d_row_ptr) &&
+    bool ok = hip_ok(hipGetDevice(&dev)) && upload_tiles(L->q_tiles) && upload_tiles(L->kv_tiles) && upload(L->row_ptr, &L->d_row_ptr) &&
               upload(L->col_idx, &L->d_col_idx) && upload(L->dq_units, &L->d_dq_units) &&
               upload(L->kv_split_codes, &L->d_kv_split_codes);
     if (!ok) {
@@ -277,7 +269,18 @@ int s2_layout_get(const s2_layout* L, s2_layout_view* out) {
 int s2_layout_get_tiles(const s2_layout* L, int which, s2_tile_view* out) {
   if (!L || !out) return S2_ERR_NULL;
   if (which != S2_TILES_FWD && which != S2_TILES_DQ && which != S2_TILES_DKDV) return S2_ERR_BAD_PARAM;
-  const s2::TileList& t = which == S2_TILES_DKDV ? L->kv_tiles : L->q_tiles;
+  const bool by_unit = L->p.block_size < 32;
+  if (by_unit) {
+    try {
+      std::call_once(L->shown_once, [L] {
+        s2::build_tiles(*L, s2::kBwdBM / L->p.block_size, false, L->shown_q);
+        s2::build_tiles(*L, s2::kBwdBN / L->p.block_size, true, L->shown_kv);
+      });
+    } catch (const std::bad_alloc&) {
+      return S2_ERR_OVERFLOW;
+    }
+  }
+  const s2::TileList& t = which == S2_TILES_DKDV ? (by_unit ? L->shown_kv : L->kv_tiles) : by_unit ? L->shown_q : L->q_tiles;
   out->ptr = t.ptr.data();
   out->ent = t.ent.data();
   out->order = t.order.data();

@@ -290,7 +290,8 @@ void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& 
   build_lists(L, group, transpose, 1, out);
 }
 
-void build_splits(s2_layout& L, const TileList& kv) {
+void build_splits(s2_layout& L) {
+  const TileList& kv = L.kv_tiles;
   L.kv_levels.clear();
   L.kv_split_codes.clear();
   const int H = L.p.num_heads, T = kv.tiles_per_head, S = L.p.block_size;

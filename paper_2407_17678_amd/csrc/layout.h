@@ -1,6 +1,7 @@
 // Internal: host-side layout handle shared by the layout builder and the launch code.
 #pragma once
 #include <cstdint>
+#include <mutex>
 #include <vector>
 
 #include "../../include/s2attn.h"
@@ -59,10 +60,11 @@ struct s2_layout {
   int32_t* d_col_idx = nullptr;
   s2::TileList q_tiles;   // row groups  -> kept KV blocks   (forward, dQ pass)
   s2::TileList kv_tiles;  // column groups -> attending Q blocks (dK/dV pass)
-  // 16-token blocks: the same two with an entry per block (8 bits of membership) instead of per unit of
-  // two, and with key tiles of any eight columns that are attended by nearly the same rows instead of
-  // adjacent ones.  This is what the kernels walk, which gather their chunks block by block.
-  s2::TileList q_block_tiles, kv_block_tiles;
+  // With 16-token blocks both hold an entry per block (8 bits of membership), and the key tiles any eight
+  // columns that are attended by nearly the same rows: the kernels gather their chunks block by block.
+  // s2_layout_get_tiles shows such lists by unit of two blocks instead, built when they are first asked for.
+  mutable std::once_flag shown_once;
+  mutable s2::TileList shown_q, shown_kv;
   // Of the key tiles the kernels walk: the ways to cut them, and what choosing one takes
   std::vector<s2::SplitLevel> kv_levels;
   std::vector<int32_t> kv_split_codes;
@@ -91,8 +93,8 @@ int64_t row_blocks(const s2_layout_params& p, int head, int i, int32_t* out, int
 void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out);
 // The same with one partner block per entry whatever the block size (partner index = entry >> 16, unsigned).
 void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& out);
-// Fills kv_levels and what belongs to them from `kv` (the key tiles the kernels walk).
-void build_splits(s2_layout& L, const TileList& kv);
+// Fills kv_levels and what belongs to them from kv_tiles (entries of single blocks).
+void build_splits(s2_layout& L);
 // Fills dq_units / ds_units from q_tiles and kv_tiles (built before, with 128-row and 128-key tiles).
 void build_ds_units(s2_layout& L);
 }  // namespace s2
