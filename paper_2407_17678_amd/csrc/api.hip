@@ -584,18 +584,26 @@ int check_pattern(const s2_layout_params* lp, const s2_layout* layout, int heads
   return S2_OK;
 }
 
-// Split count when the caller leaves it to the library: the public default (enough workgroups to
-// fill the chip; it also sizes the workspace, so never more than that), cut down so that a
-// workgroup still has about a dozen 64-token units of the longest row to walk: with fewer, its four
-// wavefronts mostly idle and the reduce kernel merges partials for nothing.
-int choose_splits(const s2_layout_params* lp, const s2_layout* layout, int nseq, int heads, int max_len) {
-  int splits = s2_attn_decode_default_splits(nseq, heads, max_len);
+// Split count when the caller leaves it to the library; never more than the public default, which also
+// sizes the workspace.  A trip of a workgroup's four wavefronts through four 64-token units takes about 2 us
+// however few workgroups there are, the merging launch 2 us more.  Below 256 (sequence, head) pairs the chip
+// is not full and the trips count: about 512 workgroups, down to one trip each (32 pairs of 32768 tokens, 48
+// units: 18.1 us in three splits, 14.3 in twelve; of 8192 tokens, 23 units: 18.5 us in one, 9.3 in six; 128
+// pairs: 35.0 us in three, 32.2 in four, 35.7 in eight); up to two trips one split is as good (8 pairs, 6
+// units: 5.8 us, 7.5 in two).  With more pairs the cache's bytes count, and splits must be worth their
+// partials: a dozen units each at least (512 pairs, 19 units: 52.5 us in one split, 60 in two).
+int choose_splits(const s2_layout_params* lp, const s2_layout* layout, int nseq, int heads, int head_dim, int max_len,
+                  size_t workspace_bytes) {
+  const int splits = s2_attn_decode_default_splits(nseq, heads, max_len);
   const int S = lp->block_size;
-  int64_t blocks = layout ? layout->max_row_blocks : s2::row_blocks(*lp, 0, (max_len - 1) / S, nullptr, 0);
+  const int64_t blocks = layout ? layout->max_row_blocks : s2::row_blocks(*lp, 0, (max_len - 1) / S, nullptr, 0);
   const int64_t units = blocks * S / 64;  // 64-token units of work in the longest row
-  const int64_t cap = units / 12 < 1 ? 1 : units / 12;
-  if (splits > cap) splits = (int)cap;
-  return splits;
+  const int64_t pairs = (int64_t)nseq * heads;
+  const int64_t cap = pairs >= 256 ? units / 12 : units <= 8 ? 1 : std::min<int64_t>((units + 3) / 4, 512 / pairs);
+  int n = (int)std::max<int64_t>(1, std::min<int64_t>(splits, cap));
+  // a workspace that holds the partials of units / 12 splits is enough
+  while (n > 1 && 12 * (int64_t)n > units && s2_attn_decode_workspace_bytes(nseq, heads, head_dim, max_len, n) > workspace_bytes) --n;
+  return n;
 }
 
 void set_pattern(s2::DecodeParams& p, const s2_layout_params* lp, const s2_layout* layout) {
@@ -628,7 +636,7 @@ int decode_contiguous(const s2_layout_params* lp, const s2_layout* layout, const
   if (!aligned16(a->q) || !aligned16(a->k_cache) || !aligned16(a->v_cache) || !aligned16(a->o) ||
       (reinterpret_cast<uintptr_t>(a->seq_lens) & 3u) != 0)
     return S2_ERR_ALIGN;
-  const int splits = a->num_splits > 0 ? a->num_splits : choose_splits(lp, layout, a->nseq, a->heads, a->max_len);
+  const int splits = a->num_splits > 0 ? a->num_splits : choose_splits(lp, layout, a->nseq, a->heads, a->head_dim, a->max_len, workspace_bytes);
   const size_t need = s2_attn_decode_workspace_bytes(a->nseq, a->heads, a->head_dim, a->max_len, splits);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return S2_ERR_WORKSPACE;
@@ -677,7 +685,7 @@ int decode_paged(const s2_layout_params* lp, const s2_layout* layout, const s2_p
       (reinterpret_cast<uintptr_t>(a->block_table) & 3u) != 0 ||
       (reinterpret_cast<uintptr_t>(a->missing) & 3u) != 0)
     return S2_ERR_ALIGN;
-  const int splits = a->num_splits > 0 ? a->num_splits : choose_splits(lp, layout, a->nseq, a->heads, max_len);
+  const int splits = a->num_splits > 0 ? a->num_splits : choose_splits(lp, layout, a->nseq, a->heads, a->head_dim, max_len, workspace_bytes);
   const size_t need = s2_attn_decode_workspace_bytes(a->nseq, a->heads, a->head_dim, max_len, splits);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < need)
     return S2_ERR_WORKSPACE;

@@ -262,25 +262,56 @@ __global__ __launch_bounds__(256, 2) void decode_split_kernel(const DecodeParams
   }
 }
 
+// Merges the splits of one (sequence, head).  What it costs is latency (a launch of few bytes), so the first
+// partials are requested together with the (max, sum) pairs, one split to a lane, and groups of D / 4 lanes
+// each add up the splits of their own.
 template <int D>
-__global__ __launch_bounds__(D) void decode_reduce_kernel(const DecodeParams p) {
-  const int bh = blockIdx.x, d = threadIdx.x;
-  const float cl = p.scale_log2e;
-  const float* ml = p.part_ml + (int64_t)bh * p.num_splits * 2;
-  float m = kNegInf;
-  for (int s = 0; s < p.num_splits; ++s) m = fmaxf(m, ml[2 * s]);
-  float l = 0.f, a = 0.f;
-  for (int s = 0; s < p.num_splits; ++s) {
-    const float ms = ml[2 * s];
-    if (ms == kNegInf) continue;  // empty split
-    const float wgt = fast_exp2((ms - m) * cl);
-    l += ml[2 * s + 1] * wgt;
-    a += p.part_acc[((int64_t)bh * p.num_splits + s) * D + d] * wgt;
+__global__ __launch_bounds__(256) void decode_reduce_kernel(const DecodeParams p) {
+  constexpr int LPR = D / 4;      // lanes covering one partial
+  constexpr int NG = 256 / LPR;   // partials covered by the workgroup at a time
+  constexpr int NP = 4;           // partials a group requests at a time
+  __shared__ f32x4 sh[NG][LPR];
+  const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int g = tid / LPR, c = tid % LPR, n = p.num_splits;
+  const f32x4* part = reinterpret_cast<const f32x4*>(p.part_acc) + (int64_t)bh * n * LPR + c;
+  const float* ml = p.part_ml + (int64_t)bh * n * 2;
+  f32x4 x[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) x[i] = part[(int64_t)min(g + NG * i, n - 1) * LPR];
+  const float ms = lane < n ? ml[2 * lane] : kNegInf;
+  const float ls = lane < n ? ml[2 * lane + 1] : 0.f;
+  float m = ms;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+  // (an empty split weighs nothing)
+  const float wgt = ms == kNegInf ? 0.f : fast_exp2((ms - m) * p.scale_log2e);
+  float l = ls * wgt;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) l += __shfl_xor(l, d, 64);
+  f32x4 a = f32x4{};
+  for (int s0 = 0;;) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int s = s0 + g + NG * i;
+      const float w = __shfl(wgt, s & 63, 64);
+      if (s < n) a += x[i] * w;
+    }
+    s0 += NG * NP;
+    if (s0 >= n) break;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) x[i] = part[(int64_t)min(s0 + g + NG * i, n - 1) * LPR];
   }
+  sh[g][c] = a;
+  __syncthreads();
+  if (tid >= LPR) return;
+#pragma unroll
+  for (int i = 1; i < NG; ++i) a += sh[i][c];
   // l == 0 only when nothing was attended: a paged cache with every kept block missing
-  const __bf16 out = (__bf16)(l > 0.f ? a / l : 0.f);
-  p.o[(int64_t)bh * D + d] = *reinterpret_cast<const uint16_t*>(&out);
-  if (d == 0 && p.lse) p.lse[bh] = l > 0.f ? m * p.scale + __logf(l) : kNegInf;
+  bf16x4 out;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out[e] = (__bf16)(l > 0.f ? a[e] / l : 0.f);
+  *reinterpret_cast<bf16x4*>(p.o + (int64_t)bh * D + 4 * c) = out;
+  if (tid == 0 && p.lse) p.lse[bh] = l > 0.f ? m * p.scale + __logf(l) : kNegInf;
 }
 
 template <int D>
@@ -299,7 +330,7 @@ hipError_t launch_one(const DecodeParams& p, hipStream_t stream) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.num_splits == 1) return e;  // a single split writes the result itself
-  hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(bh), dim3(D), 0, stream, p);
+  hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(bh), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 

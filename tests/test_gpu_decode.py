@@ -80,3 +80,36 @@ def test_decode_independent_of_split_count_and_head_base():
     o, lse = _run(w, qb, kcb, vcb, lens, 4096, 4, params=p)
     O, LSE = _oracle(w, qb, kcb, vcb, lens, dense=True)
     assert G.o_excess(o, O) <= 0 and np.abs(lse - LSE).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("name", ["7b_decode", "tiny"])        # head_dim 128 and 64
+@pytest.mark.parametrize("splits", [8, 31, 32, 33, 64])        # a merge asks for 32 (D = 128) or 64 (D = 64) splits at a time
+def test_decode_merges_any_number_of_splits(name, splits):
+    w = synth.WORKLOADS[name]
+    max_len = 2500                                             # up to 40 units of work, so that some splits are empty
+    lens = np.array([1, 65, 1000, max_len], dtype=np.int32)
+    qb, kcb, vcb, lens = synth.decode_inputs_small(w, len(lens), 3, max_len, lengths=lens)
+    p = B.layout_params(3, 1, w.block_size, 1, 0, 0, 0, 1)     # dense: every block is kept
+    o, lse = _run(w, qb, kcb, vcb, lens, max_len, splits, params=p)
+    O, LSE = _oracle(w, qb, kcb, vcb, lens, dense=True)
+    assert G.o_excess(o, O) <= 0 and np.abs(lse - LSE).max() <= LSE_TOL
+
+
+@pytest.mark.parametrize("nseq,heads,max_len", [(1, 4, 512), (1, 4, 600), (1, 4, 2500), (3, 43, 1500), (4, 64, 1500)])
+def test_decode_splits_left_to_the_library(nseq, heads, max_len):
+    # one split up to 8 units of work, then one to every four units, as many as 512 workgroups, and from 256
+    # (sequence, head) pairs on one to every twelve units
+    w = synth.WORKLOADS["7b_decode"]
+    qb, kcb, vcb, lens = synth.decode_inputs_small(w, nseq, heads, max_len, lengths=np.full(nseq, max_len, dtype=np.int32))
+    p = B.layout_params(heads, 1, w.block_size, 1, 0, 0, 0, 1)
+    o, lse = _run(w, qb, kcb, vcb, lens, max_len, 0, params=p)
+    o1, lse1 = _run(w, qb, kcb, vcb, lens, max_len, 1, params=p)
+    assert np.abs(o - o1).max() <= 2 ** -7 and np.abs(lse - lse1).max() <= 1e-5
+    # a workspace for a split to every twelve units is taken as well
+    units = -(-max_len // 64)
+    few = max(1, min(units // 12, B.s2_attn_decode_default_splits(nseq, heads, max_len)))
+    small = torch.empty(B.s2_attn_decode_workspace_bytes(nseq, heads, w.head_dim, max_len, few), dtype=torch.uint8, device="cuda")
+    q, kc, vc = (G.to_dev(x) for x in (qb, kcb, vcb))
+    o2 = torch.empty_like(q)
+    B.s2_attn_decode(p, q, kc, vc, torch.from_numpy(lens).cuda(), o2, None, w.scale, small, max_len)
+    assert np.abs(G.to_f64(o2) - o1).max() <= 2 ** -7
