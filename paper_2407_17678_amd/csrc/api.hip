@@ -585,13 +585,16 @@ int check_pattern(const s2_layout_params* lp, const s2_layout* layout, int heads
 }
 
 // Split count when the caller leaves it to the library; never more than the public default, which also
-// sizes the workspace.  A trip of a workgroup's four wavefronts through four 64-token units takes about 2 us
-// however few workgroups there are, the merging launch 2 us more.  Below 256 (sequence, head) pairs the chip
-// is not full and the trips count: about 512 workgroups, down to one trip each (32 pairs of 32768 tokens, 48
-// units: 18.1 us in three splits, 14.3 in twelve; of 8192 tokens, 23 units: 18.5 us in one, 9.3 in six; 128
-// pairs: 35.0 us in three, 32.2 in four, 35.7 in eight); up to two trips one split is as good (8 pairs, 6
-// units: 5.8 us, 7.5 in two).  With more pairs the cache's bytes count, and splits must be worth their
-// partials: a dozen units each at least (512 pairs, 19 units: 52.5 us in one split, 60 in two).
+// sizes the workspace.  A trip of a workgroup's wavefronts, a 64-token unit each, takes 1.5 to 2 us however few
+// workgroups there are, the second launch that merges splits 2 to 3 us.  While all of a call's workgroups are of
+// eight wavefronts and fit the chip at once, one split is best up to three trips (five at head_dim 64,
+// whose units are half as large), then as many as still fit, down to one trip each: 32 pairs of 19 units 11.1 us
+// in one split, 11.5 in two; of 31 units 16.3 in one, 11.2 in four; 75 pairs of 34 units 14.2, 12.5 in three, 16.1 in
+// four.  Where only one fits but leaves a third of the chip idle, three splits of four wavefronts share it better
+// (160 pairs of 95 units 60.1 us in one, 55.4; of 47 units 29.8, 28.5; 192 pairs: 71.8, 78.6).  Above that, up to 256
+// pairs, one split of four wavefronts (240 pairs of 31 units 28.1 us, 29.5 in two).  With more pairs the cache's bytes
+// count, and splits must be worth their partials: a dozen units each at least (512 pairs, 19 units: 33.5 us in
+// one split, 37.0 in two).
 int choose_splits(const s2_layout_params* lp, const s2_layout* layout, int nseq, int heads, int head_dim, int max_len,
                   size_t workspace_bytes) {
   const int splits = s2_attn_decode_default_splits(nseq, heads, max_len);
@@ -599,7 +602,15 @@ int choose_splits(const s2_layout_params* lp, const s2_layout* layout, int nseq,
   const int64_t blocks = layout ? layout->max_row_blocks : s2::row_blocks(*lp, 0, (max_len - 1) / S, nullptr, 0);
   const int64_t units = blocks * S / 64;  // 64-token units of work in the longest row
   const int64_t pairs = (int64_t)nseq * heads;
-  const int64_t cap = pairs >= 256 ? units / 12 : units <= 8 ? 1 : std::min<int64_t>((units + 3) / 4, 512 / pairs);
+  int64_t cap;
+  if (pairs > s2::decode_wide_groups(S, 1)) {
+    cap = pairs < 256 ? 1 : units / 12;
+  } else if (units <= (head_dim == 128 ? 24 : 40)) {
+    cap = 1;
+  } else {
+    cap = std::min<int64_t>((units + 7) / 8, s2::decode_wide_groups(S, 2) / pairs);
+    if (cap == 1 && S != 16 && 3 * pairs <= 512) cap = 3;
+  }
   int n = (int)std::max<int64_t>(1, std::min<int64_t>(splits, cap));
   // a workspace that holds the partials of units / 12 splits is enough
   while (n > 1 && 12 * (int64_t)n > units && s2_attn_decode_workspace_bytes(nseq, heads, head_dim, max_len, n) > workspace_bytes) --n;

@@ -11,7 +11,7 @@
 // by offset into a contiguous cache; nothing else changes, since a page is one contiguous block.
 //
 // Split-KV: the list of 64-token units of one (sequence, head) is cut into num_splits pieces, one
-// workgroup each; the four wavefronts of a workgroup take units round-robin and merge their
+// workgroup each; the four or eight wavefronts of a workgroup take units round-robin and merge their
 // (max, sum, accumulator) through LDS; a second kernel merges the splits.  With one split per
 // (sequence, head) the first kernel writes the result itself and the second is not launched.
 #include <hip/hip_runtime.h>
@@ -72,14 +72,16 @@ __device__ inline RowBlocks row_blocks(const DecodeParams& p, int head, int i) {
 // GATHER: the instantiation for 16-token blocks, where a unit of work is four consecutive kept blocks
 // of the row's list side by side, so that every load still fetches rows the query attends (a 16-token
 // block on its own would fill a quarter of the 64 rows a unit loads).
-template <int D, bool PAGED, bool GATHER>
-__global__ __launch_bounds__(256, 2) void decode_split_kernel(const DecodeParams p) {
+//
+// W: wavefronts of a workgroup, each with a unit in flight (128 data registers, so two to a SIMD).
+template <int D, bool PAGED, bool GATHER, int W>
+__global__ __launch_bounds__(64 * W, 2) void decode_split_kernel(const DecodeParams p) {
   constexpr int LPR = D / 8;     // lanes covering one row
   constexpr int RPI = 64 / LPR;  // rows covered by one wavefront-wide load
   constexpr int NI = 64 / RPI;   // loads per 64-token unit
 
-  __shared__ float sh_m[4], sh_l[4];
-  __shared__ float sh_acc[4][D];
+  __shared__ float sh_m[W], sh_l[W];
+  __shared__ float sh_acc[W][D];
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int c = lane % LPR, g = lane / LPR;
@@ -118,7 +120,7 @@ __global__ __launch_bounds__(256, 2) void decode_split_kernel(const DecodeParams
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 
-  for (int u = u_lo + wave; u < u_hi; u += 4) {
+  for (int u = u_lo + wave; u < u_hi; u += W) {
     bf16x8 kr[NI], vr[NI];
     bool live[NI];  // GATHER: whether my row of load n is a token the query attends
     int tok0 = 0, tok_end = 0;
@@ -236,11 +238,13 @@ __global__ __launch_bounds__(256, 2) void decode_split_kernel(const DecodeParams
   }
   __syncthreads();
   if (tid < D) {
-    float m = fmaxf(fmaxf(sh_m[0], sh_m[1]), fmaxf(sh_m[2], sh_m[3]));
+    float m = sh_m[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) m = fmaxf(m, sh_m[w]);
     float l = 0.f, a = 0.f;
     if (m > kNegInf) {
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
+      for (int w = 0; w < W; ++w) {
         const float wgt = fast_exp2((sh_m[w] - m) * cl);  // exp2(-inf) = 0 for an idle wavefront
         l += sh_l[w] * wgt;
         a += sh_acc[w][tid] * wgt;
@@ -314,20 +318,28 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(const DecodeParams p
   if (tid == 0 && p.lse) p.lse[bh] = l > 0.f ? m * p.scale + __logf(l) : kNegInf;
 }
 
+template <int D, int W>
+void launch_split(const DecodeParams& p, hipStream_t stream) {
+  const dim3 grid(p.nseq * p.heads * p.num_splits), block(64 * W);
+  if (p.block_size == 16) {
+    if (p.block_table)
+      hipLaunchKernelGGL((decode_split_kernel<D, true, true, W>), grid, block, 0, stream, p);
+    else
+      hipLaunchKernelGGL((decode_split_kernel<D, false, true, W>), grid, block, 0, stream, p);
+  } else if (p.block_table) {
+    hipLaunchKernelGGL((decode_split_kernel<D, true, false, W>), grid, block, 0, stream, p);
+  } else {
+    hipLaunchKernelGGL((decode_split_kernel<D, false, false, W>), grid, block, 0, stream, p);
+  }
+}
+
 template <int D>
 hipError_t launch_one(const DecodeParams& p, hipStream_t stream) {
   const int bh = p.nseq * p.heads;
-  const dim3 grid(bh * p.num_splits);
-  if (p.block_size == 16) {
-    if (p.block_table)
-      hipLaunchKernelGGL((decode_split_kernel<D, true, true>), grid, dim3(256), 0, stream, p);
-    else
-      hipLaunchKernelGGL((decode_split_kernel<D, false, true>), grid, dim3(256), 0, stream, p);
-  } else if (p.block_table) {
-    hipLaunchKernelGGL((decode_split_kernel<D, true, false>), grid, dim3(256), 0, stream, p);
-  } else {
-    hipLaunchKernelGGL((decode_split_kernel<D, false, false>), grid, dim3(256), 0, stream, p);
-  }
+  if (bh * p.num_splits <= decode_wide_groups(p.block_size, p.num_splits))
+    launch_split<D, 8>(p, stream);
+  else
+    launch_split<D, 4>(p, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.num_splits == 1) return e;  // a single split writes the result itself
   hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(bh), dim3(256), 0, stream, p);

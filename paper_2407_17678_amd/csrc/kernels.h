@@ -102,6 +102,13 @@ hipError_t launch_bwd(const AttnParams& p, bool dense, int stages, hipStream_t s
 hipError_t launch_dq(const AttnParams& p, bool dense, hipStream_t stream);
 // The dQ launch of the backward that keeps dS: dQ = scale * dS K over the stored units.
 hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream);
+// The most workgroups of a decode call that are of eight wavefronts instead of four.  One to a compute unit,
+// they keep twice the units of a (sequence, head) in flight: 32 pairs of 16 units in one split 13.2 -> 9.8 us, 19
+// units 15.8 -> 11.1; 64 pairs of 34 units in three splits 13.2 -> 11.3.  A grid with more of them brings no
+// more loads and ends less evenly (192 pairs of 16 units 12.4 and 12.3, 240 pairs 14.6 and 15.1), except that with
+// 16-token blocks, whose loads wait for more addresses, eight stay ahead while the chip holds all (256 pairs of
+// 17 units 21.2 -> 18.2, 384 pairs 27.0 -> 29.2), and so do the splits of longer rows (96 x 2, 31 units: 14.6 and 14.5).
+constexpr int decode_wide_groups(int block_size, int splits) { return block_size == 16 || splits > 1 ? 256 : 192; }
 hipError_t launch_decode(const DecodeParams& p, hipStream_t stream);
 
 }  // namespace s2

@@ -1,5 +1,7 @@
 """GPU parity of the split-KV decode kernels against the fp64 oracle (through the C ABI)."""
 
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -95,16 +97,22 @@ def test_decode_merges_any_number_of_splits(name, splits):
     assert G.o_excess(o, O) <= 0 and np.abs(lse - LSE).max() <= LSE_TOL
 
 
-@pytest.mark.parametrize("nseq,heads,max_len", [(1, 4, 512), (1, 4, 600), (1, 4, 2500), (3, 43, 1500), (4, 64, 1500)])
-def test_decode_splits_left_to_the_library(nseq, heads, max_len):
-    # one split up to 8 units of work, then one to every four units, as many as 512 workgroups, and from 256
-    # (sequence, head) pairs on one to every twelve units
-    w = synth.WORKLOADS["7b_decode"]
+@pytest.mark.parametrize("nseq,heads,max_len,S", [(1, 4, 512, 64), (1, 4, 600, 64), (1, 4, 1536, 64), (1, 4, 2500, 64), (3, 43, 1500, 64),
+                                                  (3, 43, 2500, 64), (3, 64, 100, 64), (1, 193, 1600, 64), (4, 64, 1500, 64),
+                                                  (4, 64, 520, 16), (1, 257, 520, 16)])
+def test_decode_splits_left_to_the_library(nseq, heads, max_len, S):
+    # one split up to 24 units of work, then one to every eight units, as many as 256 workgroups (or three,
+    # where that is one); above 192 (sequence, head) pairs, or 256 with 16-token blocks, four wavefronts to a
+    # workgroup instead of eight and one split, from 256 on one to every twelve units
+    w = dataclasses.replace(synth.WORKLOADS["7b_decode"], block_size=S)
     qb, kcb, vcb, lens = synth.decode_inputs_small(w, nseq, heads, max_len, lengths=np.full(nseq, max_len, dtype=np.int32))
     p = B.layout_params(heads, 1, w.block_size, 1, 0, 0, 0, 1)
     o, lse = _run(w, qb, kcb, vcb, lens, max_len, 0, params=p)
     o1, lse1 = _run(w, qb, kcb, vcb, lens, max_len, 1, params=p)
     assert np.abs(o - o1).max() <= 2 ** -7 and np.abs(lse - lse1).max() <= 1e-5
+    few_heads = [x[:, :5] for x in (qb, kcb, vcb)]
+    O, LSE = _oracle(dataclasses.replace(w, heads=5), *few_heads, lens, dense=True)
+    assert G.o_excess(o[:, :5], O) <= 0 and np.abs(lse[:, :5] - LSE).max() <= LSE_TOL
     # a workspace for a split to every twelve units is taken as well
     units = -(-max_len // 64)
     few = max(1, min(units // 12, B.s2_attn_decode_default_splits(nseq, heads, max_len)))
