@@ -319,12 +319,16 @@ __device__ __forceinline__ bool map_workgroup_interleaved(int wg, int bh_total, 
 // How many pairs of an XCD to take at a time.  One after the other leaves the longest tiles of the last
 // pair for the end of the launch, which counts when an XCD's 64 workgroup slots go round only a few
 // times: forward / dQ of 2 x 16 heads x 4096 x 64 36.1 / 46.6 us one by one, 32.9 / 42.6 in fours; dense 32
-// heads x 8192 542 / 781 and 518 / 731; packed 8 x 32 heads of 200 to 8192 rows 351 / 481 and 348 / 476.
+// heads x 8192 542 / 781 and 518 / 731.
 // From about eight rounds on the tail is nothing, while four heads' stripes then share an L2: 32 heads x
 // 32768 the same both ways, 32 heads x 131072 (2 MB of stripes a head) 5.90 ms one by one, 6.06 in fours.
-// (Eight at a time, or all: the same as four, packed batches up to 3 % slower.)
+// Pairs of a packed batch are of different lengths and go one after the other: neighbouring workgroups of an
+// XCD go to its four shader engines in turn, so with four pairs side by side each engine had the tiles of
+// one, and the launch waited for the engine with the longest sequence.  Forward / dQ of 20 x 5 heads x up to
+// 8832 x 128 197.7 / 277.4 us in fours, 119.2 / 166.5 one by one; 11 x 10 heads x 64 87.7 / 107.7 and 61.2 / 76.8;
+// 8 x 32 heads of 200 to 8192 rows 330.8 / 448.4 and 331.6 / 454.1.
 __host__ inline int map_group(int bh_total, int tiles, bool packed) {
-  return packed || (int64_t)((bh_total + 7) / 8) * tiles <= 8 * 64 ? 4 : 1;
+  return !packed && (int64_t)((bh_total + 7) / 8) * tiles <= 8 * 64 ? 4 : 1;
 }
 __host__ __device__ inline int grid_for(int bh_total, int tiles) { return 8 * ((bh_total + 7) / 8) * tiles; }
 
