@@ -470,9 +470,7 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     int* const flag = reinterpret_cast<int*>(&sm.rs[0]);
     if (tid == 0) {
       int32_t* const count = p.split_count + (int64_t)bh * T + nth;
-      const int done = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (done == parts - 1) *count = 0;  // for the next launch; nobody else looks any more
-      *flag = done;
+      *flag = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (*flag != parts - 1) return;
@@ -572,6 +570,17 @@ hipError_t launch_delta(const AttnParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// The counters of the cut key tiles for a dK/dV launch that is not preceded by delta or dQ in its own call: what
+// an earlier call left there is not known (it may have had a smaller workspace).
+__global__ __launch_bounds__(256) void clear_counts_kernel(const AttnParams p) { clear_split_counts(p, blockIdx.x * 256 + threadIdx.x); }
+
+hipError_t launch_clear_counts(const AttnParams& p, hipStream_t stream) {
+  if (p.split_items == 0) return hipSuccess;
+  const int tiles = p.batch * p.heads * p.kv_tiles.tiles_per_head;
+  hipLaunchKernelGGL(clear_counts_kernel, dim3((tiles + 255) / 256), dim3(256), 0, stream, p);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t stream) {
   hipError_t e = hipSuccess;
@@ -579,7 +588,10 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
     if (p.ds_store) {
       // The backward that keeps dS: delta, then dK/dV (5 contractions' worth of work less the dQ one,
       // leaving dS in the workspace), then dQ = scale * dS K - nothing is computed twice.
-      if (stages & kBwdDelta) e = launch_delta<D>(p, stream);
+      if (stages & kBwdDelta)
+        e = launch_delta<D>(p, stream);
+      else if (stages & kBwdDkDv)
+        e = launch_clear_counts(p, stream);
       if (e == hipSuccess && (stages & kBwdDkDv)) e = launch_dkdv<D, false, false, false, true>(p, stream);
       if (e == hipSuccess && (stages & kBwdDq)) e = launch_dq_gemm(p, stream);
       return e;
@@ -592,6 +604,8 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
     e = launch_dq(p, dense, stream);
   else if (stages & kBwdDelta)
     e = launch_delta<D>(p, stream);
+  else
+    e = launch_clear_counts(p, stream);
   if (e != hipSuccess || !(stages & kBwdDkDv)) return e;
   if (dense) return launch_dkdv<D, true, false, false, false>(p, stream);
   const bool fine = p.block_size < 64;

@@ -48,8 +48,8 @@ struct AttnParams {
   // Key tiles cut into parts (SplitLevel in layout.h; split_items == 0: none are): the first split_items
   // items of a head are parts of its first split_long tiles.  The parts' sums go to split_sums, [batch *
   // heads][item][wavefront][accumulator quad][lane][4] floats, and split_count[batch * heads][tile] counts the
-  // parts that are done: it is zero before the launch (the launch before it, which leaves delta, clears it)
-  // and zero again after.
+  // parts that are done: it is zero before the launch (the launch before it clears it: the one that leaves delta, or one
+  // of its own where the call has none of those).
   const int32_t* split_codes;
   float* split_sums;
   int32_t* split_count;

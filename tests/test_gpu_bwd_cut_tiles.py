@@ -85,3 +85,33 @@ def test_cut_tiles(case):
         # most bf16 roundings, 2^-9 of an element each way)
         assert G.rel_l2(G.to_f64(small[i]), G.to_f64(runs[0][i])) <= 5e-3, n
     assert torch.equal(grads[1], runs[0][1]) and torch.equal(grads[2], runs[0][2])
+
+
+@pytest.mark.parametrize("keep_ds", [False, True])
+def test_a_dkdv_call_clears_its_own_counters(keep_ds):
+    # delta by a call whose workspace is too small for any tile to be cut, dK/dV by one with the room for it on
+    # the same memory: the counters, which the first call does not know of, still hold what was there before
+    D, S, H, batch, Bk = 128, 64, 3, 1, 32
+    N = Bk * S
+    w = dataclasses.replace(synth.WORKLOADS["1p3b_8k"], block_size=S)
+    q, k, v, g = (G.to_dev(x) for x in synth.train_inputs(w, heads=H, batch=batch, seqlen=N))
+    row_ptr, col_idx, _, _ = orc.compressed_layout(orc.block_mask(H, Bk, 3, 8))
+    lay = B.s2_layout_from_csr(H, Bk, S, row_ptr, col_idx)
+    o = torch.empty_like(q)
+    lse = torch.empty((batch, H, N), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, w.scale)
+    bytes_ = B.s2_attn_bwd_layout_workspace_bytes(lay, batch, H, N, D) if keep_ds else B.s2_attn_bwd_workspace_bytes(batch, H, N, D)
+    least = 2 * ((batch * H * N * 4 + 255) // 256 * 256)
+    stage = B.BWD_DELTA if keep_ds else B.BWD_DQ
+    results = []
+    for fill in (0xFF, 0x00, 0x01):
+        for first in (least, bytes_):
+            ws = torch.full((bytes_,), fill, dtype=torch.uint8, device="cuda")
+            grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+            B.s2_attn_bwd_stages(lay, q, k, v, o, lse, g, *grads, w.scale, ws[:first], stage)
+            B.s2_attn_bwd_stages(lay, q, k, v, o, lse, g, *grads, w.scale, ws, B.BWD_DKDV)
+            results.append(grads[1:])
+    torch.cuda.synchronize()
+    for r in results:
+        assert torch.equal(r[0], results[1][0]) and torch.equal(r[1], results[1][1])
+    assert torch.isfinite(results[1][0].float()).all()
