@@ -585,35 +585,48 @@ int check_pattern(const s2_layout_params* lp, const s2_layout* layout, int heads
 }
 
 // Split count when the caller leaves it to the library; never more than the public default, which also
-// sizes the workspace.  A trip of a workgroup's wavefronts, a 64-token unit each, takes 1.5 to 2 us however few
-// workgroups there are, the second launch that merges splits 2 to 3 us.  While all of a call's workgroups are of
-// eight wavefronts and fit the chip at once, one split is best up to three trips (five at head_dim 64,
-// whose units are half as large), then as many as still fit, down to one trip each: 32 pairs of 19 units 11.1 us
-// in one split, 11.5 in two; of 31 units 16.3 in one, 11.2 in four; 75 pairs of 34 units 14.2, 12.5 in three, 16.1 in
-// four.  Where only one fits but leaves a third of the chip idle, three splits of four wavefronts share it better
-// (160 pairs of 95 units 60.1 us in one, 55.4; of 47 units 29.8, 28.5; 192 pairs: 71.8, 78.6).  Above that, up to 256
-// pairs, one split of four wavefronts (240 pairs of 31 units 28.1 us, 29.5 in two).  With more pairs the cache's bytes
-// count, and splits must be worth their partials: a dozen units each at least (512 pairs, 19 units: 33.5 us in
-// one split, 37.0 in two).
+// sizes the workspace.  A trip of a workgroup's wavefronts, a unit each (64 tokens, or a block of 32), takes 1.5 to 2 us
+// however few workgroups there are, the second launch that merges splits 2 to 3 us.  Three ranges:
+//  - All of a call's workgroups are of eight wavefronts and fit the chip at once: one split is best up to three trips
+//    (four at head_dim 64), then as many as still fit, down to one trip each: 32 pairs of 19 units 11.1 us in one
+//    split, 11.5 in two; of 31 units 16.3 in one, 11.2 in four; 75 pairs of 34 units 14.2, 12.5 in three, 16.1 in four.
+//    Where only one fits but leaves a third of the chip idle, three splits of four wavefronts share it better (160 pairs of 95
+//    units 60.1 us in one, 55.4; of 47 units 29.8, 28.5; 192 pairs: 71.8, 78.6).  Long rows of many pairs are cut
+//    into pieces of 24 units though not all fit: sequences of different lengths even out better, and equal ones lose
+//    little.  From 384 units on where two fit (four in blocks of 32, whose units are half as large), from 512 where
+//    one does: 96 pairs of 128 to 512 units x 128 179 us in two splits, 163 in eight, all of 384 203 and 206; 80 pairs of 256
+//    to 1024 32-token units x 64 101 in three, 82 in twelve; 180 pairs of 128 to 512 x 128 370 in one, 350 in six.
+//  - Above that, up to 255 pairs: one split of four wavefronts while rows are short, then pieces of a dozen units.  At
+//    head_dim 128 from 256 units on (200 pairs of 64 to 256 units 204 us in one split, 179 in six, all of 384 411 and 414, but
+//    all of 128 139 and 148), at 64 from 96 (all of 128 89 and 83, of 64 34 and 39), in blocks of 32 from 64 (of 64 x 128
+//    47 in one, 39 in two; of 256 to 1024 x 64 470 in one, 176 in six).
+//  - With more pairs the cache's bytes count, and splits must be worth their partials: a dozen units each at least (512
+//    pairs, 19 units: 33.5 us in one split, 37.0 in two).
 int choose_splits(const s2_layout_params* lp, const s2_layout* layout, int nseq, int heads, int head_dim, int max_len,
                   size_t workspace_bytes) {
   const int splits = s2_attn_decode_default_splits(nseq, heads, max_len);
   const int S = lp->block_size;
   const int64_t blocks = layout ? layout->max_row_blocks : s2::row_blocks(*lp, 0, (max_len - 1) / S, nullptr, 0);
-  const int64_t units = blocks * S / 64;  // 64-token units of work in the longest row
+  const int64_t units64 = blocks * S / 64;                // 64 tokens each
+  const int64_t units = S == 32 ? blocks : units64;       // as the kernel counts them, in the longest row
   const int64_t pairs = (int64_t)nseq * heads;
   int64_t cap;
-  if (pairs > s2::decode_wide_groups(S, 1)) {
-    cap = pairs < 256 ? 1 : units / 12;
-  } else if (units <= (head_dim == 128 ? 24 : 40)) {
+  const int64_t fit = s2::decode_wide_groups(S, 2) / pairs;  // splits of eight wavefronts that fit
+  if (pairs >= 256 && pairs > s2::decode_wide_groups(S, 1)) {
+    cap = units64 / 12;
+  } else if (pairs > s2::decode_wide_groups(S, 1)) {
+    cap = units >= (S == 32 ? 64 : head_dim == 64 ? 96 : 256) ? units / 12 : 1;
+  } else if (units <= (head_dim == 128 ? 24 : 32)) {
     cap = 1;
+  } else if (fit <= (S == 32 ? 4 : 2) && units >= (fit == 1 && S != 32 ? 512 : 384)) {
+    cap = units / 24;
   } else {
-    cap = std::min<int64_t>((units + 7) / 8, s2::decode_wide_groups(S, 2) / pairs);
+    cap = std::min<int64_t>((units + 7) / 8, fit);
     if (cap == 1 && S != 16 && 3 * pairs <= 512) cap = 3;
   }
   int n = (int)std::max<int64_t>(1, std::min<int64_t>(splits, cap));
-  // a workspace that holds the partials of units / 12 splits is enough
-  while (n > 1 && 12 * (int64_t)n > units && s2_attn_decode_workspace_bytes(nseq, heads, head_dim, max_len, n) > workspace_bytes) --n;
+  // a workspace that holds the partials of a split to every 768 tokens is enough
+  while (n > 1 && 12 * (int64_t)n > units64 && s2_attn_decode_workspace_bytes(nseq, heads, head_dim, max_len, n) > workspace_bytes) --n;
   return n;
 }
 

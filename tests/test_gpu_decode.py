@@ -121,3 +121,26 @@ def test_decode_splits_left_to_the_library(nseq, heads, max_len, S):
     o2 = torch.empty_like(q)
     B.s2_attn_decode(p, q, kc, vc, torch.from_numpy(lens).cuda(), o2, None, w.scale, small, max_len)
     assert np.abs(G.to_f64(o2) - o1).max() <= 2 ** -7
+
+
+@pytest.mark.parametrize("nseq,heads,max_len,S,D,splits", [
+    (1, 4, 1536, 64, 128, 1), (1, 4, 1600, 64, 128, 2), (1, 4, 2048, 64, 64, 1), (1, 4, 2112, 64, 64, 3),  # up to 24 / 32 units, then one to every eight
+    (4, 20, 2048, 32, 64, 2),                                # a unit is a block where blocks are of 32 tokens
+    (4, 30, 4096, 64, 128, 2), (5, 32, 4096, 64, 128, 3),    # as many as fit; three where one would
+    (3, 32, 24512, 64, 64, 2), (3, 32, 24576, 64, 64, 11),   # from 384 units on one to every 24, whether or not they fit, ...
+    (5, 30, 32704, 16, 64, 1), (5, 30, 32768, 16, 64, 7), (2, 40, 12288, 32, 64, 12),  # ... from 512 where one fits
+    (10, 20, 6080, 64, 64, 1), (10, 20, 6144, 64, 64, 6),    # 193 to 255 pairs: one, then one to every twelve
+    (10, 20, 8192, 64, 128, 1), (10, 20, 2016, 32, 64, 1), (10, 20, 2048, 32, 64, 2),
+    (10, 30, 2048, 64, 128, 2), (10, 30, 1472, 64, 128, 1),  # more pairs: one to every twelve units
+])
+def test_decode_split_count_left_to_the_library(nseq, heads, max_len, S, D, splits):
+    # every split leaves D + 2 floats of a (sequence, head) in the workspace (one split leaves nothing)
+    w = synth.WORKLOADS["7b_decode"]
+    q = torch.ones((nseq, heads, D), dtype=torch.bfloat16, device="cuda")
+    kv = torch.ones((nseq, heads, max_len, D), dtype=torch.bfloat16, device="cuda")
+    ws = torch.full((B.s2_attn_decode_workspace_bytes(nseq, heads, D, max_len) // 4,), 77.25, dtype=torch.float32, device="cuda")
+    o = torch.empty_like(q)
+    p = B.layout_params(heads, 1, S, 1, 0, 0, 0, 1)  # dense: every block is kept
+    B.s2_attn_decode(p, q, kv, kv, torch.full((nseq,), max_len, dtype=torch.int32, device="cuda"), o, None, w.scale, ws, max_len)
+    assert int((ws != 77.25).sum()) == (0 if splits == 1 else nseq * heads * splits * (D + 2))
+    assert torch.equal(o, q)
