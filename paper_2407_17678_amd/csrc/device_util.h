@@ -247,6 +247,35 @@ __device__ __forceinline__ void wait_loads_but() {
   asm volatile("" ::: "memory");
 }
 
+// Writes 32 rows of results, accumulated as acc[feature tile] with a lane's row in lane % 32, times mul, as
+// bf16.  They go out through LDS (`stage`: 32 * (D + 8) elements that are this wavefront's own, so no barrier): a lane
+// holds its row's features four at a time, and storing them from there would touch 32 rows per instruction
+// with 16 bytes each; read back 16 bytes per lane, row after row, an instruction stores four whole rows.
+// GUARD: only the first `rows` rows exist.
+template <int D, bool GUARD>
+__device__ __forceinline__ void store_rows(const f32x16 (&acc)[D / 32], float mul, uint16_t* stage, uint16_t* base, int64_t row_stride,
+                                           int rows, int lane) {
+  constexpr int RS = D + 8;  // staging row stride (elements): 8-byte writes of a row group spread over the banks
+  static_assert(4 * 32 * RS <= 2 * DmaTile<D>::kElems, "four wavefronts' rows fit two stages");
+  const int l32 = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      bf16x4 w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[dt][4 * g + e] * mul);
+      *reinterpret_cast<bf16x4*>(stage + l32 * RS + 32 * dt + 8 * g + 4 * half) = w;
+    }
+  constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int r = RPI * i + lane / PPR, piece = lane % PPR;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(stage + r * RS + 8 * piece);
+    if (!GUARD || r < rows) *reinterpret_cast<u32x4*>(base + (int64_t)r * row_stride + 8 * piece) = x;
+  }
+}
+
 // A tile's entry list, held in registers: lane i of the wavefront keeps entry 64*b + i of the
 // current batch of 64 entries, and the next batch is fetched one batch ahead, so the main loops
 // read their block index with v_readlane instead of waiting on global memory every iteration.

@@ -30,13 +30,12 @@
 //   * the direct loads of a tile are issued four to a write of M0 (their LDS targets are told apart
 //     by the instruction's immediate offset).
 //
-// One loop serves both head sizes, every block size and ragged ends.  Against the phase-by-phase kernel
-// that head_dim 64, blocks below 64 tokens and partial 128-row tiles used to run (per launch): 2 x 16
-// heads x 4096 x 64, blocks of 64: 38.3 -> 36.0 us; 2 x 16 x 3904 x 128 (61 blocks): 53.7 -> 48.8 us;
-// 1 x 16 x 8192 x 128, blocks of 16: 64.0 -> 54.5 us; a packed batch of 8 sequences of 200 to 8192 rows x 32
-// heads: 367 us in two launches -> 348 us in one.  What bounds it: with many steps per tile the matrix and
-// vector pipes (head_dim 128 about 1.05 PFLOP/s; at 64 the vector work per MFMA doubles), with few the
-// latency of a tile's start and end (about 12 us of a workgroup slot against 1.6 us per step).
+// One loop serves both head sizes, blocks of 64 and 128 tokens and ragged ends (blocks of 16 and 32:
+// fwd_gather_kernel.hip).  Against the phase-by-phase kernel that head_dim 64 and partial 128-row tiles used to
+// run (per launch): 2 x 16 heads x 4096 x 64, blocks of 64: 38.3 -> 36.0 us; 2 x 16 x 3904 x 128 (61 blocks): 53.7 -> 48.8 us; a
+// packed batch of 8 sequences of 200 to 8192 rows x 32 heads: 367 us in two launches -> 348 us in one.  What bounds it: with
+// many steps per tile the matrix and vector pipes (head_dim 128 about 1.05 PFLOP/s; at 64 the vector work per MFMA
+// doubles), with few the latency of a tile's start and end (about 12 us of a workgroup slot against 1.6 us per step).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -53,16 +52,11 @@ namespace {
 constexpr float kNegInf = -__builtin_inff();
 constexpr float kTau = 8.0f;  // log2 units a score may exceed a lazily moved reference maximum by
 
-// FINE: mask blocks of 16 or 32 tokens.  A step's 64 keys are then four pieces of 16 gathered from the
-// next blocks of the tile's list (entries of single blocks, with one bit per mask row of the tile), so
-// such masks run the same loop with full chunks, at the same rate, as blocks of 64 tokens; a wavefront's 32
-// rows are one or two mask rows, and a piece that not all of them keep whole is masked lane by lane.
-//
 // VARLEN: a packed batch of sequences of different lengths.  A workgroup finds its sequence's rows in
 // cu_seqlens and treats them as a sequence of its own.  In its last, partial tile no lane fetches past
 // the sequence's last token (keys after it lie after every query, which the causal mask drops) and
 // stores are guarded per row.
-template <int D, bool DENSE, bool FINE, bool VARLEN>
+template <int D, bool DENSE, bool VARLEN>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(const AttnParams p) {
   typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
@@ -77,7 +71,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // LDS fragments are requested kLead MFMAs ahead (3 to 7 measure the same at D = 128; at D = 64 three keep a
   // wavefront at 168 registers, so that three fit a SIMD)
   constexpr int kLead = D == 128 ? 5 : 3, kRing = kLead + 1;
-  static_assert(!(DENSE && (FINE || VARLEN)), "the dense form walks 64-key blocks of whole sequences");
+  static_assert(!(DENSE && VARLEN), "the dense form walks 64-key blocks of whole sequences");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -101,9 +95,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     if (rank >= T_seq) return;
     tile = T_seq - 1 - rank;
   }
-  const int S = DENSE ? CH : p.block_size;  // FINE: 16 or 32, else 64 or 128
+  const int S = DENSE ? CH : p.block_size;  // 64 or 128
   const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
-  const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-key pieces per list entry
   const int qw0 = tile * BM + wave * MW;    // first query row of this wavefront (sequence position)
   const int ql0 = qw0 - p.q_row0;           // the same as a row of q / o / lse
   const bool wave_on = ql0 < n_q;           // whether I have query rows at all
@@ -122,8 +115,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     ent_lo = p.fwd_tiles.ptr[h * T + tile];
     n_ent = p.fwd_tiles.ptr[h * T + tile + 1] - ent_lo;
   }
-  // steps: chunks of an entry, or (FINE) as many as the entries' pieces fill
-  const int total = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent << cpb_sh;
+  const int total = n_ent << cpb_sh;  // steps: chunks of the entries
   if (total <= 0) return;
   EntryList list;
   if (!DENSE) list.init(p.fwd_tiles.ent + ent_lo, n_ent, lane);
@@ -136,50 +128,24 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   for (int kk = 0; kk < KK; ++kk)
     qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + q_off + (int64_t)q_lane * p.q_st + 16 * kk + 8 * half);
 
-  // FINE: piece pc (0..3) of step j: its first key row, and which of my two groups of 16 query rows keep
-  // it (bits 0 and 1; both or neither for 32-token blocks)
-  auto piece_at = [&](int j, int pc, int& row, int& bits) S2_INLINE {
-    const int x = 4 * j + pc;
-    const int i = x >> ppe_sh;
-    const uint32_t e = (uint32_t)list.peek(min(i, n_ent - 1));
-    row = (int)(e >> 16) * S + ((x & ppe_sh) << 4);
-    bits = ppe_sh ? ((e >> wave) & 1) * 3 : (e >> (2 * wave)) & 3;
-    if (i >= n_ent) bits = 0;
-  };
   // Step j of the tile's list (clamped to the last one): the first key row of the 16 that I fetch;
   // whether I have anything to compute there (my mask rows keep some of it, and not every key lies
   // after every one of my queries); and whether some of it has to be masked for me.
   auto chunk_at = [&](int j, int& row, bool& act, bool& masked) S2_INLINE {
     const bool inside = j < total;
     j = min(j, total - 1);
-    if constexpr (FINE) {
-      int all = 0xFF, any = 0, last = 0;
-      row = 0;
-#pragma unroll
-      for (int pc = 0; pc < 4; ++pc) {
-        int r, bits;
-        piece_at(j, pc, r, bits);
-        all &= bits | ~3;
-        any |= bits;
-        if (pc == wave) row = r;
-        last = r;
-      }
-      act = inside && wave_on && any != 0;
-      masked = all != 0xFF || last + 15 > qw0;
+    int kv0;
+    bool keep = true;
+    if (DENSE) {
+      kv0 = j * CH;
     } else {
-      int kv0;
-      bool keep = true;
-      if (DENSE) {
-        kv0 = j * CH;
-      } else {
-        const int e = list.peek(j >> cpb_sh);
-        kv0 = (e >> 16) * S + (j & cpb_m) * CH;
-        keep = (e >> my_member) & 1;
-      }
-      row = kv0 + 16 * wave;
-      act = inside && wave_on && keep && kv0 <= qw0 + MW - 1;
-      masked = kv0 + CH - 1 > qw0;
+      const int e = list.peek(j >> cpb_sh);
+      kv0 = (e >> 16) * S + (j & cpb_m) * CH;
+      keep = (e >> my_member) & 1;
     }
+    row = kv0 + 16 * wave;
+    act = inside && wave_on && keep && kv0 <= qw0 + MW - 1;
+    masked = kv0 + CH - 1 > qw0;
     if (VARLEN) row = min(row, N - 1);
   };
 
@@ -191,7 +157,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   float l_run = 0.f;      // sum of the probabilities over my half's key rows
   const float c = p.scale_log2e;
   // how far a score may exceed the reference maximum before it is moved (raw scores; see the top of this file)
-  const bool lazy_ref = D == 128 && !FINE && (VARLEN ? (tile + 1) * BM <= N : p.q_rows % BM == 0);
+  const bool lazy_ref = D == 128 && (VARLEN ? (tile + 1) * BM <= N : p.q_rows % BM == 0);
   const float tau = lazy_ref ? kTau / c : 0.f;
   // The lane offsets of my direct loads, for K and for V.  Where a packed sequence ends inside the rows
   // I fetch (VARLEN) they are limited to the rows that exist; the lists ascend, so from then on every
@@ -272,22 +238,14 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // element index reached after slot sl: five elements every four slots, or (D = 64) three a slot
   constexpr int kPace = D == 128 ? 40 : 48;
   auto p_upto = [](int sl) S2_INLINE { return (kPace * (sl + 1)) / NS; };
-  // drops what my query does not see of step j: keys after it and (FINE) pieces its mask row does not keep
+  // drops what my query does not see of step j: keys after it
   auto mask_step = [&](f32x16 (&sn)[2], int j) S2_INLINE {
     const int qpos = qw0 + l32;
 #pragma unroll
     for (int pc = 0; pc < 4; ++pc) {
-      int row, bits = 3;
-      if constexpr (FINE) {
-        piece_at(j, pc, row, bits);
-      } else if (DENSE) {
-        row = j * CH + 16 * pc;
-      } else {
-        row = (list.peek(j >> cpb_sh) >> 16) * S + (j & cpb_m) * CH + 16 * pc;
-      }
-      // how many of the piece's keys I see, counted from the first one my half of the wavefront holds
-      int lim = qpos - row + 1 - 4 * half;
-      if (FINE && !((bits >> (l32 >> 4)) & 1)) lim = -4;
+      const int row = (DENSE ? j * CH : (list.peek(j >> cpb_sh) >> 16) * S + (j & cpb_m) * CH) + 16 * pc;
+      // how many of these 16 keys I see, counted from the first one my half of the wavefront holds
+      const int lim = qpos - row + 1 - 4 * half;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (8 * (i >> 2) + (i & 3) >= lim) sn[pc >> 1][8 * (pc & 1) + i] = kNegInf;
@@ -430,7 +388,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
       static_for<2 * NG>([&](auto dc) S2_INLINE { step_dma(dc); });
     }
     // keeps the entry window moving (entries of step it+1 on)
-    if (!DENSE) (void)list.get(FINE ? min((4 * (it + 1)) >> ppe_sh, n_ent - 1) : min(it + 1, total - 1) >> cpb_sh, lane);
+    if (!DENSE) (void)list.get(min(it + 1, total - 1) >> cpb_sh, lane);
     act_c = act_n;
     row_n = row_nn;
     act_n = act_nn;
@@ -447,33 +405,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   if (it < total) step(it, s[0], s[1]);
 
   // ------------------------------------------------------------------ epilogue
-  // O = acc / l goes out through LDS (free since the loop's last barrier; each wavefront uses a
-  // region of its own, so no barrier): a lane holds its row's features four at a time, and storing
-  // them from there would touch 32 rows per instruction with 16 bytes each; read back 16 bytes per
-  // lane, row after row, an instruction stores four whole rows.
   if (!wave_on) return;
   const float l_tot = sum_halves(l_run);
-  const float inv = 1.0f / l_tot;
-  constexpr int RS = D + 8;  // staging row stride (elements): 8-byte writes of a row group spread over the banks
-  uint16_t* stage = sk[0] + wave * MW * RS;
-  static_assert(4 * MW * RS <= 2 * Tile::kElems, "the staging rows fit the K stages");
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      bf16x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[dt][4 * g + e] * inv);
-      *reinterpret_cast<bf16x4*>(stage + l32 * RS + 32 * dt + 8 * g + 4 * half) = w;
-    }
-  uint16_t* obase = p.o + q_off + (int64_t)ql0 * p.q_st;
-  constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
-#pragma unroll
-  for (int i = 0; i < MW / RPI; ++i) {
-    const int r = RPI * i + lane / PPR, piece = lane % PPR;
-    const u32x4 x = *reinterpret_cast<const u32x4*>(stage + r * RS + 8 * piece);
-    if (!VARLEN || ql0 + r < n_q) *reinterpret_cast<u32x4*>(obase + (int64_t)r * p.q_st + 8 * piece) = x;
-  }
+  store_rows<D, VARLEN>(acc, 1.0f / l_tot, sk[0] + wave * MW * (D + 8), p.o + q_off + (int64_t)ql0 * p.q_st, p.q_st, n_q - ql0, lane);
   const int64_t lse_row = VARLEN ? (int64_t)h * p.seqlen + row_base + ql0 + l32  // [heads, rows of the tensors]
                                  : ((int64_t)b * p.heads + h) * p.q_rows + ql0 + l32;
   if (half == 0 && (!VARLEN || ql0 + l32 < n_q)) p.lse[lse_row] = m_ref * p.scale + __logf(l_tot);
@@ -482,17 +416,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
 template <int D>
 hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
   const dim3 grid(grid_for(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM)), block(kThreads);
-  const bool fine = !dense && p.block_size < 64;
   if (dense)
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, true, false, false>), grid, block, 0, stream, p);
-  else if (p.cu_seqlens && fine)
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true, true>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, true, false>), grid, block, 0, stream, p);
   else if (p.cu_seqlens)
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false, true>), grid, block, 0, stream, p);
-  else if (fine)
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true, false>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true>), grid, block, 0, stream, p);
   else
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false, false>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 
@@ -501,6 +430,7 @@ hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
 hipError_t launch_fwd(const AttnParams& params, bool dense, hipStream_t stream) {
   AttnParams p = params;
   p.map_group = map_group(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM, p.cu_seqlens != nullptr);
+  if (!dense && p.block_size < 64) return launch_fwd_gather(p, stream);
   return p.head_dim == 128 ? launch_one<128>(p, dense, stream) : launch_one<64>(p, dense, stream);
 }
 

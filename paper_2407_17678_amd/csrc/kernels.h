@@ -95,6 +95,8 @@ struct DecodeParams {
 
 // Each returns the hipError_t of the launch (hipGetLastError after the launch).
 hipError_t launch_fwd(const AttnParams& p, bool dense, hipStream_t stream);
+// The launch of it for mask blocks of 16 and 32 tokens (map_group set).
+hipError_t launch_fwd_gather(const AttnParams& p, hipStream_t stream);
 // `stages` selects which of the three backward launches run: 1 = delta, 2 = dK/dV, 4 = dQ.
 constexpr int kBwdDelta = 1, kBwdDkDv = 2, kBwdDq = 4, kBwdAll = 7;
 hipError_t launch_bwd(const AttnParams& p, bool dense, int stages, hipStream_t stream);

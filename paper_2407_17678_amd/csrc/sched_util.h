@@ -49,15 +49,19 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t addr, int byte_off) {
 __device__ __forceinline__ f32x4 lds_read_f32x4(uint32_t addr, int byte_off) {
   return *S2_LDS_PTR(f32x4, addr + byte_off);
 }
-// transposed fragment (see DmaTile::tr_frag): two ds_read_b64_tr_b16, the second 8 rows further on
-__device__ __forceinline__ u32x4 lds_read_tr(uint32_t addr, int byte_off, int row_bytes) {
+// transposed fragment (see DmaTile::tr_frag): two ds_read_b64_tr_b16, the second 8 rows further on ...
+__device__ __forceinline__ u32x4 lds_read_tr2(uint32_t addr_lo, uint32_t addr_hi, int off_lo, int off_hi) {
   typedef short s16x4_ __attribute__((ext_vector_type(4)));
   typedef short s16x8_ __attribute__((ext_vector_type(8)));
   typedef __attribute__((address_space(3))) s16x4_* tr_ptr;
-  const s16x4_ lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(uintptr_t)(addr + byte_off));
-  const s16x4_ hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(uintptr_t)(addr + byte_off + 8 * row_bytes));
+  const s16x4_ lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(uintptr_t)(addr_lo + off_lo));
+  const s16x4_ hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(uintptr_t)(addr_hi + off_hi));
   const s16x8_ both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(u32x4, both);
+}
+// ... of the same tile
+__device__ __forceinline__ u32x4 lds_read_tr(uint32_t addr, int byte_off, int row_bytes) {
+  return lds_read_tr2(addr, addr, byte_off, byte_off + 8 * row_bytes);
 }
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
