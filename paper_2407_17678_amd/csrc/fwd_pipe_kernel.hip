@@ -27,8 +27,8 @@
 //     row's largest probability is then 1, which rounding to bf16 leaves alone, and O of short rows is
 //     closer to the exact result (relative error of O against 64 bits, exact and lazy: 2 x 4 heads x 4096 x
 //     64, blocks of 64 2.10e-3 and 2.20e-3; 8192 x 128, blocks of 16 2.12e-3 and 2.25e-3);
-//   * the direct loads of a tile are issued four to a write of M0 (their LDS targets are told apart
-//     by the instruction's immediate offset).
+//   * the direct loads of a tile are issued two or three to a write of M0 (their LDS targets are told
+//     apart by the instruction's immediate offset).
 //
 // One loop serves both head sizes, blocks of 64 and 128 tokens and ragged ends (blocks of 16 and 32:
 // fwd_gather_kernel.hip).  Against the phase-by-phase kernel that head_dim 64 and partial 128-row tiles used to
@@ -60,10 +60,11 @@ template <int D, bool DENSE, bool VARLEN>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(const AttnParams p) {
   typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
-  __shared__ __attribute__((aligned(16))) uint16_t sk[2][Tile::kElems];
-  __shared__ __attribute__((aligned(16))) uint16_t sv[2][Tile::kElems];
+  __shared__ __attribute__((aligned(16))) uint16_t tiles[4][Tile::kElems];  // two stages of K, two of V
+  uint16_t (*const sk)[Tile::kElems] = tiles, (*const sv)[Tile::kElems] = tiles + 2;
   constexpr int BM = kFwdBM, MW = 32, CH = 64;
   constexpr int KK = D / 16, DT = D / 32;
+  constexpr int RB = Tile::kStride * 2;  // bytes per tile row
   constexpr int NQK = 2 * KK;  // MFMAs of the score contraction per step
   constexpr int NPV = 4 * DT;  // MFMAs of the second contraction per step
   constexpr int NS = NQK + NPV;
@@ -173,11 +174,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   auto dma_v = [&](auto gc, const uint16_t* base, const uint16_t* stage) S2_INLINE {
     Piece::template issue<decltype(gc)::value>(VARLEN ? plan_v : plan_k, base, stage, wave);
   };
-  const int trb = Tile::tr_base(lane);
+  // lane parts of the addresses the fragments are read at
+  const uint32_t k_lane = lds_addr(tiles) + l32 * RB + 16 * half, v_lane = lds_addr(tiles) + 2 * Tile::tr_base(lane);
 
   // scores [parity of the step][32-key half].  Zero to begin with: the registers of a step this
   // wavefront skips are still run through the exponential (with a shift of -inf) when the next step
-  // is its own, so they must never hold a NaN; after a step they hold its probabilities.
+  // is its own, so they must not hold a NaN; after a step they hold its probabilities.
   f32x16 s[2][2];
 #pragma unroll
   for (int i = 0; i < 4; ++i) s[i >> 1][i & 1] = f32x16{};
@@ -188,11 +190,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // the MFMA that uses it.
   // fragment f: K fragment (kk = f / 2, key half f % 2) for f < NQK, else V^T fragment f - NQK
   // (group (f - NQK) / DT = key half, 16-key slab; feature tile (f - NQK) % DT)
-  auto frag_load = [&](int f, const uint16_t* ks, const uint16_t* vs, bf16x8 (&fr)[kRing]) S2_INLINE {
+  auto frag_load = [&](int f, uint32_t ks, uint32_t vs, bf16x8 (&fr)[kRing]) S2_INLINE {
     if (f < NQK)
-      fr[f % kRing] = Tile::row_frag(ks, f & 1, f >> 1, l32, half);
+      fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(ks, 32 * (f & 1) * RB + 32 * (f >> 1)));
     else
-      fr[f % kRing] = Tile::tr_frag(vs, (f - NQK) % DT, (f - NQK) / DT, trb);
+      fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read_tr(vs, 16 * ((f - NQK) / DT) * RB + 64 * ((f - NQK) % DT), RB));
   };
   // MFMA n of the score contraction of a step: kk = n / 2, key half = n % 2; fragment n
   auto qk_mfma = [&](int n, f32x16 (&sn)[2], const bf16x8 (&fr)[kRing]) S2_INLINE {
@@ -289,8 +291,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // ------------------------------------------------------------------ prologue
   // A step this wavefront has nothing to compute in (its mask row drops the block, or every key
   // lies after its queries) runs through the same instruction stream when the step before or
-  // after it is its own, with its scores kept out of the maximum and its probabilities forced to
-  // zero; two such steps in a row are skipped.
+  // after it is its own (see `step`); two such steps in a row are skipped.
   int row_n, row_nn;  // the key rows I fetch of the next step and the one after it
   bool act_c, act_n, act_nn, masked_c, masked_n, masked_nn;
   {
@@ -311,10 +312,10 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   if (act_c) {
     bf16x8 fr[kRing];
 #pragma unroll
-    for (int f = 0; f < kLead; ++f) frag_load(f, sk[0], sv[0], fr);
+    for (int f = 0; f < kLead; ++f) frag_load(f, k_lane, 0, fr);
     static_for<NQK>([&](auto nc) S2_INLINE {
       constexpr int n = decltype(nc)::value;
-      if constexpr (n + kLead < NQK) frag_load(n + kLead, sk[0], sv[0], fr);
+      if constexpr (n + kLead < NQK) frag_load(n + kLead, k_lane, 0, fr);
       qk_mfma(n, s[0], fr);
       S2_FENCE();
     });
@@ -332,8 +333,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   auto step = [&](int it, f32x16 (&sc)[2], f32x16 (&sn)[2]) S2_INLINE {
     const int par = it & 1;
     chunk_at(it + 2, row_nn, act_nn, masked_nn);
-    const uint16_t* ks = sk[par ^ 1];
-    const uint16_t* vs = sv[par];
+    // Where one of the two steps is not mine its scores stay out of the maximum and its probabilities are 0,
+    // and the rows of the other one stand in for its own: whatever the rows hold that I do not attend, the scores
+    // are finite (so that the probabilities are 0) and nothing of them is accumulated.
+    uint32_t ks = k_lane + (uint32_t)Tile::kBytes * (act_n ? par ^ 1 : 2 + par);
+    uint32_t vs = v_lane + (uint32_t)Tile::kBytes * (act_c ? 2 + par : par ^ 1);
+    asm volatile("" : "+v"(ks), "+v"(vs));
     // group d of this step's direct loads: 0..NG-1 for K(it+2), into the stage K(it) was in, then
     // V(it+1), into the stage V(it-1) was in
     const uint16_t* kg = kb + (int64_t)row_nn * p.kv_st;

@@ -60,7 +60,7 @@ def _seeded():
     _gen.manual_seed(5)
 
 
-FORMS = [(64, 16), (64, 32), (128, 16), (128, 32)]
+FORMS = [(64, 16), (64, 32), (64, 64), (64, 128), (128, 16), (128, 32), (128, 64), (128, 128)]
 
 
 @pytest.mark.parametrize("D,S", FORMS)
