@@ -11,7 +11,7 @@
 //   * the order is written out, one MFMA per slot with its share of the vector work, LDS reads and
 //     direct loads, and fenced so that the compiler keeps it (see sched_util.h for the measurements
 //     behind this); the A operands pass through a ring of registers requested a few MFMAs ahead;
-//   * the direct loads of a tile are issued four to a write of M0.
+//   * the direct loads of a tile are issued two or three to a write of M0.
 //
 // Head_dim 64, mask blocks below 64 tokens (FINE: chunks gathered from 16-key pieces) and ragged ends
 // (VARLEN) are the same loop, as in the forward.  Against the phase-by-phase kernel that these used to run,
@@ -111,27 +111,30 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
     bits = ppe_sh ? ((e >> wave) & 1) * 3 : (e >> (2 * wave)) & 3;
     if (i >= n_ent) bits = 0;
   };
-  // Chunk j of the tile's list (clamped to the last one): the first key row of the 16 that I fetch, and
+  const uint32_t late_from = (uint32_t)(qw0 >> (4 + ppe_sh)) << 16;  // FINE: entries from my first row's block on
+  // Chunk j of the tile's list: the first key row of the 16 that I fetch (past the end any that exist), and
   // for either 32-key half whether I have anything to compute in it (bit kt: my mask rows keep some of
-  // it and not every key lies after every one of my queries) and whether some of it has to be masked
-  // for me (bit 2 + kt).
+  // it and not every key lies after every one of my queries), whether some of it has to be masked
+  // for me (bit 2 + kt) and (FINE) which of its pieces are mine (bits 4 + 2 * kt and 5 + 2 * kt).
   auto chunk_at = [&](int j, int& row, int& state) S2_INLINE {
     const bool inside = j < total;
-    j = min(j, total - 1);
     state = 0;
     if constexpr (FINE) {
-      row = 0;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        int r0, r1, b0, b1;
-        piece_at(j, 2 * kt, r0, b0);
-        piece_at(j, 2 * kt + 1, r1, b1);
-        if (wave == 2 * kt) row = r0;
-        if (wave == 2 * kt + 1) row = r1;
-        if (b0 | b1) state |= 1 << kt;
-        if ((b0 & b1) != 3 || r1 + 15 > qw0) state |= 4 << kt;
+      // every lane's entry at once (0 after the end of the list: kept by nobody), then the chunk's bits
+      const int i0 = (4 * j) >> ppe_sh;
+      const int src = (i0 >> 6) != list.batch ? list.nxt : list.cur;  // a chunk's entries are of one batch
+      const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane(src, (i0 + (wave >> ppe_sh)) & 63);
+      row = (int)(mine >> 16) * S + ((wave & ppe_sh) << 4);
+      const int bits = ppe_sh ? ((src >> wave) & 1) * 3 : (src >> (2 * wave)) & 3;
+      const uint64_t any = __ballot(bits != 0), whole = __ballot(bits == 3) & ~__ballot((uint32_t)src >= late_from);
+      int on = (int)(any >> (i0 & 63)) & 15, all = (int)(whole >> (i0 & 63)) & 15;
+      if (ppe_sh) {  // two pieces to an entry
+        on = ((on & 1) | ((on & 2) << 1)) * 3;
+        all = ((all & 1) | ((all & 2) << 1)) * 3;
       }
+      state = (on & 3 ? 1 : 0) | (on & 12 ? 2 : 0) | ((all & 3) != 3 ? 4 : 0) | ((all & 12) != 12 ? 8 : 0) | on << 4;
     } else {
+      j = min(j, total - 1);
       int kv0;
       bool keep = true;
       if (DENSE) {
@@ -202,7 +205,9 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x16{};
   const float c = p.scale_log2e;
-  const int trb = Tile::tr_base(lane);
+  // lane parts of the addresses the fragments are read at (stage 0 of K; V lies v_from_k further on)
+  const uint32_t k_lane = lds_addr(sm.k[0]) + l32 * RB + 16 * half, tr_lane = lds_addr(sm.k[0]) + 2 * Tile::tr_base(lane);
+  constexpr uint32_t v_from_k = sizeof(sm.k);
 
   // Scores of a 32-key half: register r is key 8 * (r / 4) + 4 * half + r % 4 of the half, lane % 32
   // the query.  sc holds S, then P in place; dp holds dP, then dS in place.
@@ -233,14 +238,14 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   };
 
   bool act_cur = false;  // whether the half whose P is in sc[parity] is mine
+  int on_cur = 3;        // FINE: which of its pieces are
 
   // ------------------------------------------------------------------ prologue
   wait_all_loads();
   __syncthreads();
   // S, dP and P of the first half, one after the other
   {
-    const uint32_t k_row = lds_addr(sm.k[0]) + l32 * RB + 16 * half;
-    const uint32_t v_row = lds_addr(sm.v[0]) + l32 * RB + 16 * half;
+    const uint32_t k_row = k_lane, v_row = k_lane + v_from_k;
     sc[0] = f32x16{};
     dp = f32x16{};
 #pragma unroll
@@ -249,10 +254,16 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
       dp = mfma32(__builtin_bit_cast(bf16x8, lds_read16(v_row, 32 * kk)), gf[kk], dp);
     }
     act_cur = state_c & 1;
+    on_cur = (state_c >> 4) & 3;
     if (state_c & 4) mask_half(sc[0], 0, 0);
     const float l0 = act_cur ? lse_l : __builtin_inff();
 #pragma unroll
     for (int r = 0; r < 16; ++r) sc[0][r] = fast_exp2(__builtin_fmaf(sc[0][r], c, -l0));
+    if (!act_cur || (FINE && on_cur != 3)) {  // (what does not come from a piece of mine may not be a number)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (!act_cur || !((on_cur >> (r >> 3)) & 1)) sc[0][r] = dp[r] = 0.f;
+    }
   }
 
   // ------------------------------------------------------------------ one half step
@@ -265,18 +276,32 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
     const bool act_n = (state_x >> KTN) & 1, masked_n = (state_x >> (2 + KTN)) & 1;
     // Neither this half nor the next is mine (mask row drops them, or their keys lie after my
     // queries): nothing to compute; the next half's P and dP are zero.  One of the two being mine
-    // runs the whole stream (the other's probabilities are zero through lse = +inf).
+    // runs the whole stream (the other's probabilities are zero through lse = +inf), with its rows standing in for
+    // the other's: whatever the rows hold that I do not attend, S and dP are finite and dS exactly 0.  Likewise
+    // (FINE) the piece that is mine for one of the same half that is not.
     const bool act_this = act_cur;
+    const int on_this = on_cur, on_n = (state_x >> (4 + 2 * KTN)) & 3;
     act_cur = act_n;
+    on_cur = on_n;
     if (!act_this && !act_n) {
       sc[PAR ^ 1] = f32x16{};
       dp = f32x16{};
       return;
     }
-    uint32_t k_row = lds_addr(sm.k[stn]) + l32 * RB + 16 * half + 32 * KTN * RB;
-    uint32_t v_row = lds_addr(sm.v[stn]) + l32 * RB + 16 * half + 32 * KTN * RB;
-    uint32_t k_tr = lds_addr(sm.k[stc]) + 2 * trb + 32 * KT * RB;
+    const uint32_t from_n = stn * (uint32_t)Tile::kBytes + 32 * KTN * RB, from_this = stc * (uint32_t)Tile::kBytes + 32 * KT * RB;
+    const uint32_t row_off = act_n ? from_n : from_this, tr_off = act_this ? from_this : from_n;
+    uint32_t k_row = k_lane + row_off, k_tr = tr_lane + tr_off, k_tr1 = k_tr;
+    if constexpr (FINE) {
+      const int on_r = act_n ? on_n : on_this, on_t = act_this ? on_this : on_n;
+      if (on_r != 3) k_row += (on_r == 1 ? 0 : 16 * RB) - (l32 >> 4) * 16 * RB;
+      if (on_t != 3) {
+        if (on_t == 2) k_tr += 16 * RB;
+        k_tr1 = k_tr - 16 * RB;
+      }
+    }
+    uint32_t v_row = k_row + v_from_k;
     asm volatile("" : "+v"(k_row), "+v"(v_row), "+v"(k_tr));
+    if constexpr (FINE) asm volatile("" : "+v"(k_tr1));
     bf16x8 fr[kRing];
     // fragment f of the half step, in the order the MFMAs use them: KK row fragments of the next
     // half's K, KK transposed fragments of this half's K (16-key slab, feature tile), KK row fragments
@@ -286,7 +311,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
       if constexpr (f < KK)
         fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(k_row, 32 * f));
       else if constexpr (f < 2 * KK)
-        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read_tr(k_tr, 16 * ((f - KK) / DT) * RB + 64 * ((f - KK) % DT), RB));
+        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read_tr(FINE && f - KK >= DT ? k_tr1 : k_tr, 16 * ((f - KK) / DT) * RB + 64 * ((f - KK) % DT), RB));
       else
         fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(v_row, 32 * (f - 2 * KK)));
     };

@@ -111,3 +111,59 @@ def test_forward_packed(D, S):
         v1[:, :, hit.cuda()] = value
         o1, lse1 = fwd(k1, v1)
         assert torch.equal(o1[clean], o[clean]) and torch.equal(lse1[clean], lse[clean])
+
+
+def _forward(lay, q, k, v, scale):
+    o, lse = torch.empty_like(q), torch.empty(q.shape[:3], dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, scale)
+    return o, lse
+
+
+@pytest.mark.parametrize("D,S", FORMS)
+@pytest.mark.parametrize("density", [0.15, 0.5])
+def test_dq(D, S, density):
+    H, Bk = 3, 12 if S == 128 else 1152 // S + (S == 64)
+    M, lay, bad, scale = _setup(D, S, H, Bk, density, 12 * D + S)
+    N = Bk * S
+    q, k, v, g = (_rand(1, H, N, D) for _ in range(4))
+    clean = _clean_rows(M, bad, S)
+    o, lse = _forward(lay, q, k, v, scale)
+    ws = torch.empty(B.s2_attn_bwd_workspace_bytes(1, H, N, D), dtype=torch.uint8, device="cuda")
+
+    def dq(k, v):
+        grads = [torch.empty_like(q) for _ in range(3)]
+        B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, scale, ws)
+        return grads[0][0].cpu()
+
+    want = dq(k, v)
+    for values in ((NAN,), (POS, NEG)):
+        assert torch.equal(dq(_poison(k, bad, S, values), _poison(v, bad, S, values))[clean], want[clean])
+
+
+@pytest.mark.parametrize("D,S", FORMS)
+def test_dq_packed(D, S):
+    H, Bk = 2, 768 // S
+    M, lay, bad, scale = _setup(D, S, H, Bk, 0.3, 13 * D + S)
+    lens = [768, 700, 39, 333]
+    total = sum(lens)
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device="cuda")
+    q, k, v, g = (_rand(1, H, total, D) for _ in range(4))
+    rows = _clean_rows(M, bad, S)
+    clean = torch.cat([rows[:, :n] for n in lens], 1)
+    where = torch.cat([torch.arange(n) for n in lens])
+    hit = torch.isin(where // S, torch.from_numpy(np.asarray(bad))).cuda()
+    o, lse = torch.empty_like(q), torch.empty((H, total), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd_varlen(lay, q, k, v, o, lse, cu, 768, scale)
+    ws = torch.empty(B.s2_attn_bwd_varlen_workspace_bytes(H, total, D), dtype=torch.uint8, device="cuda")
+
+    def dq(k, v):
+        grads = [torch.empty_like(q) for _ in range(3)]
+        B.s2_attn_bwd_varlen(lay, q, k, v, o, lse, g, *grads, cu, 768, scale, ws)
+        return grads[0][0].cpu()
+
+    want = dq(k, v)
+    for value in (NAN, POS):
+        k1, v1 = k.clone(), v.clone()
+        k1[:, :, hit] = value
+        v1[:, :, hit] = value
+        assert torch.equal(dq(k1, v1)[clean], want[clean])
