@@ -168,18 +168,15 @@ int s2_layout_get(const s2_layout* layout, s2_layout_view* out);
 /* The work lists the kernels walk, for inspection (section 3.2's Merge-Q: one 128-row query tile
  * serves `group` fine mask rows; its mirror image for key tiles).  HOST pointers into the handle.
  * For head h and tile t the list is ent[ptr[h*T + t] .. ptr[h*T + t + 1]), each entry
- * (unit << 16) | bits: `unit` is a partner block, or with 16-token blocks a pair of adjacent
- * partner blocks (blocks_per_unit = 2), and bit r*blocks_per_unit + c says that member r of the
- * tile keeps block unit*blocks_per_unit + c.  Row tiles (which = S2_TILES_FWD, S2_TILES_DQ): member
+ * (unit << 16) | bits, read as an unsigned number: `unit` is a partner block and bit r says that member r of
+ * the tile keeps it.  Row tiles (which = S2_TILES_FWD, S2_TILES_DQ): member
  * r is block row t*group + r, partners are KV block columns, ascending.  Column tiles
  * (S2_TILES_DKDV): member r is block column members[(h*T + t)*group + r] (-1 = none), partners are
  * query block rows, descending - except that where a head has eight or more column tiles of one
  * length n, each attending one unbroken run of rows (the local-window tiles), such a tile starts at
  * its row that is a multiple of n and goes down from there, wrapping round to the run's last row, so
  * that tiles running side by side read the same query block at the same time.  order[h*T + k] is the
- * k-th tile of head h by descending length.  With 16-token blocks the kernels walk the same pattern
- * block by block (an entry per block; key tiles of any columns that nearly the same rows attend); what is
- * shown here are its lists by unit.  Errors: NULL, BAD_PARAM (which). */
+ * k-th tile of head h by descending length.  Errors: NULL, BAD_PARAM (which). */
 enum { S2_TILES_FWD = 0, S2_TILES_DQ = 1, S2_TILES_DKDV = 2 };
 typedef struct {
   const int32_t* ptr;      /* [H*T + 1]                              */
@@ -188,7 +185,7 @@ typedef struct {
   const int32_t* members;  /* [H*T*group]                            */
   int32_t tiles_per_head;  /* T                                      */
   int32_t group;           /* members per tile                       */
-  int32_t blocks_per_unit; /* 1, or 2 with 16-token blocks           */
+  int32_t blocks_per_unit; /* 1: an entry is one block               */
 } s2_tile_view;
 int s2_layout_get_tiles(const s2_layout* layout, int which, s2_tile_view* out);
 

@@ -181,8 +181,8 @@ int finish_layout(s2_layout* L, int st, s2_layout** out) {
     try {
       const int S = L->p.block_size;
       static_assert(s2::kFwdBM == s2::kBwdBM, "forward and dQ walk the same lists");
-      s2::build_block_tiles(*L, s2::kBwdBM / S, false, L->q_tiles);
-      s2::build_block_tiles(*L, s2::kBwdBN / S, true, L->kv_tiles);
+      s2::build_tiles(*L, s2::kBwdBM / S, false, L->q_tiles);
+      s2::build_tiles(*L, s2::kBwdBN / S, true, L->kv_tiles);
       s2::build_splits(*L);
       s2::build_ds_units(*L);
     } catch (const std::bad_alloc&) {
@@ -269,25 +269,14 @@ int s2_layout_get(const s2_layout* L, s2_layout_view* out) {
 int s2_layout_get_tiles(const s2_layout* L, int which, s2_tile_view* out) {
   if (!L || !out) return S2_ERR_NULL;
   if (which != S2_TILES_FWD && which != S2_TILES_DQ && which != S2_TILES_DKDV) return S2_ERR_BAD_PARAM;
-  const bool by_unit = L->p.block_size < 32;
-  if (by_unit) {
-    try {
-      std::call_once(L->shown_once, [L] {
-        s2::build_tiles(*L, s2::kBwdBM / L->p.block_size, false, L->shown_q);
-        s2::build_tiles(*L, s2::kBwdBN / L->p.block_size, true, L->shown_kv);
-      });
-    } catch (const std::bad_alloc&) {
-      return S2_ERR_OVERFLOW;
-    }
-  }
-  const s2::TileList& t = which == S2_TILES_DKDV ? (by_unit ? L->shown_kv : L->kv_tiles) : by_unit ? L->shown_q : L->q_tiles;
+  const s2::TileList& t = which == S2_TILES_DKDV ? L->kv_tiles : L->q_tiles;
   out->ptr = t.ptr.data();
   out->ent = t.ent.data();
   out->order = t.order.data();
   out->members = t.members.data();
   out->tiles_per_head = t.tiles_per_head;
   out->group = t.group;
-  out->blocks_per_unit = L->p.block_size < 32 ? 32 / L->p.block_size : 1;
+  out->blocks_per_unit = 1;
   return S2_OK;
 }
 

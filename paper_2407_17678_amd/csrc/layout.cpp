@@ -194,9 +194,7 @@ int build_from_csr(int num_heads, int num_blocks, int block_size, const int32_t*
 // column tiles of one length that a head must have before they walk their rows in step (see below)
 constexpr int kRotateMinTiles = 8;
 
-namespace {
-// sub: partner blocks per entry
-void build_lists(const s2_layout& L, int group, bool transpose, int sub, TileList& out) {
+void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
   const int H = L.p.num_heads, B = L.p.num_blocks;
   const std::vector<int32_t>& ptr = transpose ? L.col_ptr : L.row_ptr;
   const std::vector<int32_t>& idx = transpose ? L.row_idx : L.col_idx;
@@ -215,8 +213,7 @@ void build_lists(const s2_layout& L, int group, bool transpose, int sub, TileLis
     // which blocks go together: rows stay in order; columns are sorted by how many rows keep
     // them (longest first, ties by index) so that stripe columns pair up with stripe columns
     std::iota(seq.begin(), seq.end(), 0);
-    // (with 16-token blocks members stay adjacent, which the kernel relies on for its key rows)
-    if (transpose && group > 1 && sub == 1)
+    if (transpose && group > 1)
       std::stable_sort(seq.begin(), seq.end(),
                        [&](int a, int b) { return hp0[a + 1] - hp0[a] > hp0[b + 1] - hp0[b]; });
     for (int t = 0; t < T; ++t) {
@@ -232,12 +229,12 @@ void build_lists(const s2_layout& L, int group, bool transpose, int sub, TileLis
       for (;;) {  // k-way merge of ascending lists
         int best = std::numeric_limits<int>::max();
         for (int r = 0; r < n_members; ++r)
-          if (cur[r] < end[r]) best = std::min(best, (int)idx[cur[r]] / sub);
+          if (cur[r] < end[r]) best = std::min(best, (int)idx[cur[r]]);
         if (best == std::numeric_limits<int>::max()) break;
         int bits = 0;
         for (int r = 0; r < n_members; ++r)
-          while (cur[r] < end[r] && idx[cur[r]] / sub == best) {
-            bits |= 1 << (r * sub + idx[cur[r]] % sub);
+          if (cur[r] < end[r] && idx[cur[r]] == best) {
+            bits |= 1 << r;
             ++cur[r];
           }
         out.ent.push_back((int32_t)(((uint32_t)best << 16) | (uint32_t)bits));
@@ -277,17 +274,6 @@ void build_lists(const s2_layout& L, int group, bool transpose, int sub, TileLis
     const int32_t* hp = out.ptr.data() + (size_t)h * T;
     std::stable_sort(ord, ord + T, [&](int a, int b) { return hp[a + 1] - hp[a] > hp[b + 1] - hp[b]; });
   }
-}
-
-}  // namespace
-
-void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
-  // an entry covers partners in units of at least 32 tokens: two blocks of 16
-  build_lists(L, group, transpose, L.p.block_size < 32 ? 32 / L.p.block_size : 1, out);
-}
-
-void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
-  build_lists(L, group, transpose, 1, out);
 }
 
 void build_splits(s2_layout& L) {

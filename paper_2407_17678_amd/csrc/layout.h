@@ -1,7 +1,6 @@
 // Internal: host-side layout handle shared by the layout builder and the launch code.
 #pragma once
 #include <cstdint>
-#include <mutex>
 #include <vector>
 
 #include "../../include/s2attn.h"
@@ -10,18 +9,16 @@ namespace s2 {
 
 // Merged tile list: groups of `group` block rows (or block columns) share one list of partner
 // blocks; each entry packs (partner_index << 16) | membership_bits, bit r set when member r of
-// the group keeps that partner.  With 16-token blocks a partner is a UNIT of two adjacent blocks
-// (the kernels step through partners 32 tokens at a time at least) and bit 2r + c says that
-// member r keeps block c of the unit.  This is the Merge-Q idea of section 3.2 (one large tile serves
+// the group keeps that partner.  This is the Merge-Q idea of section 3.2 (one large tile serves
 // several fine-grained mask rows) and its mirror image for key tiles.  Row groups are
 // consecutive rows.  Column groups are formed from columns with similar partner sets (a stripe
 // column is attended by every later row, its neighbours only by the local window), so members
-// of a column group need not be adjacent: `members` names them (they are adjacent for 16-token
-// blocks, where a wavefront's 32 key rows span two members).
-constexpr int kMaxListUnits = 1 << 15;  // partner indices take the 15 bits above the membership bits
+// of a column group need not be adjacent: `members` names them.  A partner index takes all of the upper
+// sixteen bits (with 16-token blocks there are up to 65536 of them): read entries unsigned.
+constexpr int kMaxListUnits = 1 << 15;  // blocks of a layout, or pairs of 16-token blocks
 
 struct TileList {
-  int group = 0;                 // members per tile (1..8; members x blocks per unit <= 16 bits)
+  int group = 0;                 // members per tile (1..8)
   int tiles_per_head = 0;        // ceil(B / group)
   std::vector<int32_t> ptr;      // [H*tiles_per_head + 1]
   std::vector<int32_t> ent;      // packed entries; partner ascending inside a row tile,
@@ -60,11 +57,6 @@ struct s2_layout {
   int32_t* d_col_idx = nullptr;
   s2::TileList q_tiles;   // row groups  -> kept KV blocks   (forward, dQ pass)
   s2::TileList kv_tiles;  // column groups -> attending Q blocks (dK/dV pass)
-  // With 16-token blocks both hold an entry per block (8 bits of membership), and the key tiles any eight
-  // columns that are attended by nearly the same rows: the kernels gather their chunks block by block.
-  // s2_layout_get_tiles shows such lists by unit of two blocks instead, built when they are first asked for.
-  mutable std::once_flag shown_once;
-  mutable s2::TileList shown_q, shown_kv;
   // Of the key tiles the kernels walk: the ways to cut them, and what choosing one takes
   std::vector<s2::SplitLevel> kv_levels;
   std::vector<int32_t> kv_split_codes;
@@ -91,8 +83,6 @@ int build_from_csr(int num_heads, int num_blocks, int block_size, const int32_t*
 int64_t row_blocks(const s2_layout_params& p, int head, int i, int32_t* out, int64_t capacity);
 // Merge `group` consecutive rows (transpose=false) or columns (transpose=true).
 void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out);
-// The same with one partner block per entry whatever the block size (partner index = entry >> 16, unsigned).
-void build_block_tiles(const s2_layout& L, int group, bool transpose, TileList& out);
 // Fills kv_levels and what belongs to them from kv_tiles (entries of single blocks).
 void build_splits(s2_layout& L);
 // Fills dq_units / ds_units from q_tiles and kv_tiles (built before, with 128-row and 128-key tiles).

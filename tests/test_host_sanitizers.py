@@ -14,6 +14,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2407_17678_amd", "csrc")
 
 DRIVER = r"""
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -22,6 +23,7 @@ DRIVER = r"""
 #include "config.h"
 
 static int fails = 0;
+static size_t levels_seen = 0;
 #define CHECK(c) do { if (!(c)) { std::printf("FAILED %s line %d\n", #c, __LINE__); ++fails; } } while (0)
 
 static void exercise(const s2_layout_params& p) {
@@ -48,6 +50,34 @@ static void exercise(const s2_layout_params& p) {
   CHECK((int)t.ptr.size() == H * t.tiles_per_head + 1 && t.ptr.back() == (int32_t)t.ent.size());
   s2::build_tiles(L, s2::kBwdBN / S > 0 ? s2::kBwdBN / S : 1, true, t);
   CHECK((int)t.members.size() == H * t.tiles_per_head * t.group);
+  // the ways to cut the longest key tiles: the codes of a level are the parts 0 .. parts - 1 of the tiles
+  // 0 .. n_long - 1 of every head's order, as many as keep the longest head's tile within the level's steps
+  s2::build_tiles(L, s2::kBwdBN / S, true, L.kv_tiles);
+  s2::build_splits(L);
+  {
+    const s2::TileList& kv = L.kv_tiles;
+    const int T = kv.tiles_per_head;
+    std::vector<int> longest(T, 0);
+    for (int h = 0; h < H; ++h)
+      for (int k = 0; k < T; ++k) {
+        const int t = h * T + kv.order[(size_t)h * T + k];
+        longest[k] = std::max(longest[k], ((kv.ptr[t + 1] - kv.ptr[t]) * S + 63) / 64);
+      }
+    CHECK(L.kv_max_steps == longest[0]);
+    size_t at = 0;
+    for (const s2::SplitLevel& lv : L.kv_levels) {
+      CHECK((size_t)lv.offset == at && lv.n_long >= 1 && lv.n_long <= T);
+      for (int k = 0; k < lv.n_long; ++k) {
+        const int parts = (longest[k] + lv.steps - 1) / lv.steps;
+        CHECK(parts >= 2 && parts <= 64);
+        for (int i = 0; i < parts; ++i, ++at) CHECK(at < L.kv_split_codes.size() && L.kv_split_codes[at] == (k | i << 16 | parts << 24));
+      }
+      CHECK(at == (size_t)(lv.offset + lv.n_items));
+      CHECK(lv.n_long == T || longest[lv.n_long] <= lv.steps);
+    }
+    CHECK(at == L.kv_split_codes.size());
+    levels_seen += L.kv_levels.size();
+  }
   // the unit table of the backward that keeps dS (64- and 128-token blocks)
   if (S >= 64) {
     s2::build_tiles(L, s2::kBwdBM / S, false, L.q_tiles);
@@ -89,6 +119,13 @@ int main() {
     p.stride = rng() % 12;
     p.window_blocks = (rng() % 3 == 0) ? 1 + rng() % 40 : 0;
     p.dense = (rng() % 10 == 0);
+    exercise(p);
+  }
+  CHECK(levels_seen > 50);
+  // more 16-token blocks than a signed partner index could name
+  {
+    s2_layout_params p{};
+    p.num_heads = 1; p.num_blocks = 40000; p.block_size = 16; p.local_blocks = 2; p.stride = 0;
     exercise(p);
   }
   // rejected inputs: a status, never a crash or an out-of-bounds access

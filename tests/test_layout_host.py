@@ -469,6 +469,33 @@ def test_work_lists_hold_exactly_the_mask(S):
     assert B.lib().s2_layout_get_tiles(None, 0, C.byref(v)) == -1
 
 
+def test_work_lists_of_16_token_blocks():
+    # what is shown is what the kernels walk: an entry per block, key tiles of any eight columns (the stripe columns,
+    # which every later row attends, go together), and partner indices that need all sixteen bits
+    lay = B.s2_layout_build(B.layout_params(2, 64, 16, 2, 8))
+    kv = B.s2_layout_get_tiles(lay, B.TILES_DKDV)
+    assert kv["group"] == 8 and kv["blocks_per_unit"] == 1
+    for h in range(2):
+        longest = int(kv["order"][h * kv["tiles_per_head"]])
+        mem = kv["members"][(h * kv["tiles_per_head"] + longest) * 8:][:8]
+        assert [int(m) for m in mem] == list(range(h, 64, 8))
+    Bk = 40000
+    lay = B.s2_layout_build(B.layout_params(1, Bk, 16, 3, 0))
+    i = np.arange(Bk)
+    want = np.sort(np.concatenate([i[d:] * Bk + i[:Bk - d] for d in range(3)]))
+    for which in (B.TILES_FWD, B.TILES_DKDV):
+        t = B.s2_layout_get_tiles(lay, which)
+        ent = np.asarray(t["ent"]).view(np.uint32).astype(np.int64)
+        tile = np.repeat(np.arange(t["tiles_per_head"]), np.diff(np.asarray(t["ptr"])))
+        got = []
+        for r in range(8):
+            has = (ent >> r) & 1 == 1
+            member = np.asarray(t["members"]).reshape(-1, 8)[tile[has], r].astype(np.int64) if which == B.TILES_DKDV else tile[has] * 8 + r
+            partner = ent[has] >> 16
+            got.append(partner * Bk + member if which == B.TILES_DKDV else member * Bk + partner)
+        assert np.array_equal(np.sort(np.concatenate(got)), want)
+
+
 @pytest.mark.parametrize("S", [64, 128])
 def test_ds_unit_table(S):
     # the backward that keeps dS: every 64 x 64 piece of a kept block that holds a causal pair has one
