@@ -103,11 +103,15 @@ struct DkvSmem {
   } rs[2];                 // one 512-byte direct load fills both arrays of a stage
 };
 
-// FINE: mask blocks of 16 or 32 tokens.  A step's 64 query rows are four pieces of 16 gathered from the next
-// blocks of the tile's list (entries of single blocks, one bit per mask column of the tile), and the
-// tile's 4 or 8 columns are any that are attended by nearly the same rows, so a wavefront's 32 keys are
-// one or two columns and what a lane drops of a piece depends on its column.  (Steps of 32 rows over
-// tiles of adjacent columns, as before, had one stripe column keep three idle ones company.)
+// FINE: mask blocks of 16 or 32 tokens (0: larger ones).  A step's 64 query rows are four pieces of 16
+// gathered from the next blocks of the tile's list (entries of single blocks, one bit per mask column of
+// the tile), and the tile's 4 or 8 columns are any that are attended by nearly the same rows, so a
+// wavefront's 32 keys are one or two columns and what a lane drops of a piece depends on its column.
+// (Steps of 32 rows over tiles of adjacent columns, as before, had one stripe column keep three idle ones
+// company.)  A 32-row half that none of them attends is left out.  With blocks of 16 a half is two blocks
+// and a wavefront two columns: a row that is not a number reaches dK and dV of both columns if either of the
+// half's blocks attends either (keeping it from them, by zeros for dS and the other block's rows, was built and
+// cost 10 to 18 %: spilled registers at head_dim 128, the selects at 64).
 //
 // VARLEN: a packed batch of sequences of different lengths.  A key tile's members are columns of
 // the whole layout, so the workgroup first drops out if none of them exists in its sequence, skips
@@ -116,12 +120,14 @@ struct DkvSmem {
 // STORE: dS, rounded to bf16 as the dK contraction takes it, is also left in the workspace for the dQ
 // launch (launch_dq_gemm), 4 KiB per wavefront and step: [half chunk][16-query slab][key][lane half][8
 // queries in the order the lane holds them], i.e. each B operand as it is, 1 KiB per store instruction.
-template <int D, bool DENSE, bool FINE, bool VARLEN = false, bool STORE = false>
-__global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
+template <int D, bool DENSE, int FINE, bool VARLEN = false, bool STORE = false>
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const AttnParams p) {
   typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
   constexpr int CH = 64, QT = CH / 32;
   static_assert(!(DENSE && (FINE || VARLEN)) && !(STORE && (DENSE || FINE || VARLEN)), "forms that exist");
+  static_assert(FINE == 0 || FINE == 16 || FINE == 32, "blocks that are gathered");
+  constexpr int PPE = FINE == 32 ? 2 : 1, EPC = 4 / PPE;  // FINE: 16-row pieces of a list entry, entries of a step
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   DkvSmem<D>& sm = *reinterpret_cast<DkvSmem<D>*>(smem_raw);
 
@@ -146,9 +152,8 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     }
   }
   const int tile = DENSE ? rank : p.kv_tiles.order[h * T + nth];  // dense: first key tiles are longest
-  const int S = DENSE ? CH : p.block_size;  // FINE: 16 or 32, else 64 or 128
+  const int S = DENSE ? CH : FINE ? FINE : p.block_size;
   const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
-  const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-row pieces per list entry
   int row_base = 0, N = p.seqlen;
   if (VARLEN) {
     const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
@@ -156,7 +161,7 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
   }
 
-  // My 32 keys: kvw0 .. kvw0 + 31, or (FINE) keys 0..15 from kvw0 and 16..31 from kvw1.  A group of keys
+  // My 32 keys: kvw0 .. kvw0 + 31, or (blocks of 16) keys 0..15 from kvw0 and 16..31 from kvw1.  A group of keys
   // that does not exist (the layout's last tile, a packed sequence's end) starts at kNoKey.
   constexpr int kNoKey = 1 << 29;
   int kvw0, kvw1, my_member = 0;
@@ -176,10 +181,10 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     const int blk0 = mem[my_member], blk1 = mem[(wave * 32 + 16) / S];
     kvw0 = blk0 < 0 ? kNoKey : blk0 * S + (wave * 32) % S;
     kvw1 = blk1 < 0 ? kNoKey : blk1 * S + (wave * 32 + 16) % S;
-    wave_active = FINE ? min(kvw0, kvw1) < N : kvw0 < N;
+    wave_active = FINE == 16 ? min(kvw0, kvw1) < N : kvw0 < N;
   }
   // key of row r (0..31) of mine
-  auto key_of = [&](int r) S2_INLINE { return FINE ? (r < 16 ? kvw0 + r : kvw1 + r - 16) : kvw0 + r; };
+  auto key_of = [&](int r) S2_INLINE { return FINE == 16 ? (r < 16 ? kvw0 + r : kvw1 + r - 16) : kvw0 + r; };
 
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
@@ -199,31 +204,23 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     n_ent = p.kv_tiles.ptr[h * T + tile + 1] - ent_lo;
   }
   if (kSplits && parts > 1) {  // my part: so many entries, or (FINE) so many full steps of entries
-    const int units = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent;
+    const int units = FINE ? (n_ent + EPC - 1) / EPC : n_ent;
     const int u0 = units * part / parts, u1 = units * (part + 1) / parts;
-    const int e0 = FINE ? (4 * u0) >> ppe_sh : u0;
-    n_ent = (FINE ? min((4 * u1) >> ppe_sh, n_ent) : u1) - e0;
+    const int e0 = FINE ? EPC * u0 : u0;
+    n_ent = (FINE ? min(EPC * u1, n_ent) : u1) - e0;
     ent_lo += e0;
   }
   // steps: chunks of an entry, or (FINE) as many as the entries' pieces fill
-  const int total = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent << cpb_sh;
+  const int total = FINE ? (n_ent + EPC - 1) / EPC : n_ent << cpb_sh;
   // where this wavefront's dS of step 0 goes: unit 2 * (global step) + wave / 2, its keys' half of it
   uint16_t* ds_wave = nullptr;
   if (STORE)
     ds_wave = p.ds_store + ((int64_t)b * p.ds_units + (((int64_t)ent_lo << cpb_sh) * 2 + (wave >> 1))) * 4096 + (wave & 1) * 2048;
   EntryList list;
   if (!DENSE) list.init(p.kv_tiles.ent + ent_lo, n_ent, lane);
-  // FINE: piece pc (0..3) of step j: its first query row, and which of my two groups of 16 keys it attends
-  // (bits 0 and 1; both or neither for 32-token blocks); a list that does not fill its last step repeats
-  // its last block there, attending nothing
-  auto piece_at = [&](int j, int pc, int& row, int& bits) S2_INLINE {
-    const int x = 4 * j + pc;
-    const int i = x >> ppe_sh;
-    const uint32_t e = (uint32_t)list.peek(min(i, n_ent - 1));
-    row = (int)(e >> 16) * S + ((x & ppe_sh) << 4);
-    bits = ppe_sh ? ((e >> wave) & 1) * 3 : (e >> (2 * wave)) & 3;
-    if (i >= n_ent || (VARLEN && row >= N)) bits = 0;
-  };
+  // FINE: the entries of step j, in lanes EPC * j % 64 and on (0 after the end of the list: attends nobody)
+  auto entries_at = [&](int j) S2_INLINE { return ((EPC * j) >> 6) != list.batch ? list.nxt : list.cur; };
+  auto entry = [&](int src, int i) S2_INLINE { return (uint32_t)__builtin_amdgcn_readlane(src, i & 63); };
   // not FINE: first row of step j, and whether my mask column is kept there
   auto chunk_at = [&](int j, int& q0, bool& keep) S2_INLINE {
     if (DENSE) {
@@ -243,20 +240,15 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
   // registers across the loop: this kernel has no registers to spare, and a spilled constant costs
   // a wait for all outstanding loads when it is fetched back.
   auto issue_chunk = [&](int j, int buf, int ln) S2_INLINE {
-    int r[4];  // first row of each piece
+    int q0 = 0, src = 0, row;
     if constexpr (FINE) {
-#pragma unroll
-      for (int pc = 0; pc < 4; ++pc) {
-        int bits;
-        piece_at(j, pc, r[pc], bits);
-      }
+      src = entries_at(j);
+      row = (int)(entry(src, EPC * j + wave / PPE) >> 16) * FINE + 16 * (wave % PPE);
     } else {
       bool keep;
-      chunk_at(j, r[0], keep);
-#pragma unroll
-      for (int pc = 1; pc < 4; ++pc) r[pc] = r[0] + 16 * pc;
+      chunk_at(j, q0, keep);
+      row = q0 + 16 * wave;
     }
-    int row = FINE ? (wave == 0 ? r[0] : wave == 1 ? r[1] : wave == 2 ? r[2] : r[3]) : r[0] + 16 * wave;
     // Ragged end of a packed sequence: rows past it fetch parts of its last row instead (a list need
     // not be in descending order, so a piece that lies wholly after the end can turn up anywhere in
     // it: nothing uses it).
@@ -278,13 +270,16 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
       uint32_t off;
       if constexpr (FINE) {
         const int pc = (ln >> 2) & 3;
+        int r[4];  // first row of each piece
+#pragma unroll
+        for (int n = 0; n < 4; ++n) r[n] = (int)(entry(src, EPC * j + n / PPE) >> 16) * FINE + 16 * (n % PPE);
         int pr = pc == 0 ? r[0] : pc == 1 ? r[1] : pc == 2 ? r[2] : r[3];
         if (VARLEN) pr = min(pr, N - 1);
         off = 4 * pr + 16 * (ln & 3) + ((ln & 16) ? stats_gap : 0u);
       } else {
         off = 16 * (ln & 15) + ((ln & 16) ? stats_gap : 0u);
       }
-      if (ln < 32) dma16(FINE ? delta_b : delta_b + (VARLEN && r[0] >= N ? 0 : r[0]), off, lds_addr(&sm.rs[buf]));
+      if (ln < 32) dma16(FINE ? delta_b : delta_b + (VARLEN && q0 >= N ? 0 : q0), off, lds_addr(&sm.rs[buf]));
     }
   };
   // first step: a packed sequence skips the leading entries, query blocks that lie after its end (most
@@ -302,7 +297,7 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     }
     e = min(e, n_ent - 1);  // (a key of the sequence is attended by its own block at least)
     (void)list.get(e, lane);
-    it0 = FINE ? (e << ppe_sh) >> 2 : e << cpb_sh;
+    it0 = FINE ? e / EPC : e << cpb_sh;
   }
   if (!kSplits || total > 0) issue_chunk(it0, it0 & 1, lane);  // (where a head's tile is short for its rank a part may be empty)
 
@@ -331,7 +326,7 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     // keeps the entry window moving (entries of this step on)
-    if (!DENSE) (void)list.get(FINE ? (4 * it) >> ppe_sh : it >> cpb_sh, ln);
+    if (!DENSE) (void)list.get(FINE ? EPC * it : it >> cpb_sh, ln);
     if (it + 1 < total) issue_chunk(it + 1, buf ^ 1, ln);
 
     int q0 = 0;
@@ -346,6 +341,15 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
       const int l32 = ln & 31, half = ln >> 5;
       const int trb = Tile::tr_base(ln);
       const int key = key_of(l32);
+      // FINE: which pieces of the step attend keys of mine, from every lane's entry at once
+      int src = 0;
+      uint32_t on4 = 0;
+      if constexpr (FINE) {
+        src = entries_at(it);
+        uint64_t any = __ballot(FINE == 32 ? ((src >> wave) & 1) != 0 : ((src >> (2 * wave)) & 3) != 0);
+        if (VARLEN) any &= __ballot((uint32_t)src < (uint32_t)((N + FINE - 1) / FINE) << 16);
+        on4 = (uint32_t)(any >> ((EPC * it) & 63));
+      }
 #pragma unroll
       for (int qt = 0; qt < QT; ++qt) {
         // Causal mask, and (FINE) blocks my column does not keep: of the 16 query rows of piece u of this half
@@ -354,15 +358,20 @@ __global__ __launch_bounds__(kThreads, 2) void dkdv_kernel(const AttnParams p) {
         int lim[2], left[2];
         const int qbase = q0 + 32 * qt;
         if constexpr (FINE) {
-          int r0, r1, b0, b1;
-          piece_at(it, 2 * qt, r0, b0);
-          piece_at(it, 2 * qt + 1, r1, b1);
-          if ((b0 | b1) == 0) continue;  // nothing of it attends my keys
-          const int col = l32 >> 4;
-          lim[0] = (b0 >> col) & 1 ? key - r0 - 4 * half : 64;
-          lim[1] = (b1 >> col) & 1 ? key - r1 - 4 * half : 64;
+          if (((on4 >> (2 * qt / PPE)) & (FINE == 32 ? 1 : 3)) == 0) continue;  // nothing of it attends my keys
+          const uint32_t e0 = entry(src, EPC * it + (FINE == 32 ? qt : 2 * qt));
+          const int r0 = (int)(e0 >> 16) * FINE;
+          lim[0] = key - r0 - 4 * half;
+          lim[1] = lim[0] - 16;
           left[0] = N - r0 - 4 * half;
-          left[1] = N - r1 - 4 * half;
+          left[1] = left[0] - 16;
+          if constexpr (FINE == 16) {
+            const uint32_t e1 = entry(src, EPC * it + 2 * qt + 1);
+            const int r1 = (int)(e1 >> 16) * FINE, mine = 2 * wave + (l32 >> 4);
+            lim[0] = (e0 >> mine) & 1 ? lim[0] : 64;
+            lim[1] = (e1 >> mine) & 1 ? key - r1 - 4 * half : 64;
+            left[1] = N - r1 - 4 * half;
+          }
         } else {
           if (qbase + 31 < kvw0) continue;  // every query of this half-chunk lies before my keys
           if (VARLEN && qbase >= N) continue;  // ... or after the end of my sequence
@@ -552,7 +561,7 @@ hipError_t set_smem(K kernel, size_t bytes, SmemSet& flags) {
   return e;
 }
 
-template <int D, bool DENSE, bool FINE, bool VARLEN, bool STORE>
+template <int D, bool DENSE, int FINE, bool VARLEN, bool STORE>
 hipError_t launch_dkdv(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   hipError_t e = set_smem(&dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>, sizeof(DkvSmem<D>), set);
@@ -592,7 +601,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
         e = launch_delta<D>(p, stream);
       else if (stages & kBwdDkDv)
         e = launch_clear_counts(p, stream);
-      if (e == hipSuccess && (stages & kBwdDkDv)) e = launch_dkdv<D, false, false, false, true>(p, stream);
+      if (e == hipSuccess && (stages & kBwdDkDv)) e = launch_dkdv<D, false, 0, false, true>(p, stream);
       if (e == hipSuccess && (stages & kBwdDq)) e = launch_dq_gemm(p, stream);
       return e;
     }
@@ -607,11 +616,15 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
   else
     e = launch_clear_counts(p, stream);
   if (e != hipSuccess || !(stages & kBwdDkDv)) return e;
-  if (dense) return launch_dkdv<D, true, false, false, false>(p, stream);
-  const bool fine = p.block_size < 64;
-  if (p.cu_seqlens)
-    return fine ? launch_dkdv<D, false, true, true, false>(p, stream) : launch_dkdv<D, false, false, true, false>(p, stream);
-  return fine ? launch_dkdv<D, false, true, false, false>(p, stream) : launch_dkdv<D, false, false, false, false>(p, stream);
+  if (dense) return launch_dkdv<D, true, 0, false, false>(p, stream);
+  if (p.cu_seqlens) {
+    if (p.block_size == 16) return launch_dkdv<D, false, 16, true, false>(p, stream);
+    if (p.block_size == 32) return launch_dkdv<D, false, 32, true, false>(p, stream);
+    return launch_dkdv<D, false, 0, true, false>(p, stream);
+  }
+  if (p.block_size == 16) return launch_dkdv<D, false, 16, false, false>(p, stream);
+  if (p.block_size == 32) return launch_dkdv<D, false, 32, false, false>(p, stream);
+  return launch_dkdv<D, false, 0, false, false>(p, stream);
 }
 
 }  // namespace

@@ -1,7 +1,7 @@
 """What a mask row does not keep does not reach its results, whatever it holds: blocks of K and V (for dK and dV: of
 q and dO) are overwritten with NaN and infinities, and the rows that keep none of them come out bit for bit as with
 the clean tensors.  With 16-token blocks a wavefront's 32 rows are two mask rows, which share this: the rows that
-count are those of pairs of which neither keeps a poisoned block."""
+count are those of pairs of which neither keeps a poisoned block (dK and dV: see _clean_columns)."""
 
 import numpy as np
 import pytest
@@ -167,3 +167,82 @@ def test_dq_packed(D, S):
         k1[:, :, hit] = value
         v1[:, :, hit] = value
         assert torch.equal(dq(k1, v1)[clean], want[clean])
+
+
+def _clean_columns(lay, M, bad, S):
+    """[H, keys]: keys that no poisoned query block attends.  With 16-token blocks dK and dV are formed for two columns
+    of a key tile and from two blocks of its list at a time, which share this."""
+    H, Bk, _ = M.shape
+    hit = M[:, bad, :].any(1)
+    if S == 16:
+        kv = B.s2_layout_get_tiles(lay, B.TILES_DKDV)
+        T = kv["tiles_per_head"]
+        for h in range(H):
+            for t in range(T):
+                ent = np.asarray(kv["ent"][kv["ptr"][h * T + t]:kv["ptr"][h * T + t + 1]]).view(np.uint32)
+                mem = np.asarray(kv["members"][(h * T + t) * 8:(h * T + t + 1) * 8])
+                for i in range(0, len(ent), 2):
+                    half = ent[i:i + 2]
+                    if not np.isin(half >> 16, bad).any():
+                        continue
+                    bits = int(np.bitwise_or.reduce(half)) & 0xFF
+                    for w in range(4):
+                        if (bits >> (2 * w)) & 3:
+                            hit[h, [m for m in mem[2 * w:2 * w + 2] if m >= 0]] = True
+    return torch.from_numpy(~np.repeat(hit, S, axis=1))
+
+
+@pytest.mark.parametrize("D,S,keep_ds", [f + (False,) for f in FORMS] + [(128, 64, True), (128, 128, True)])
+@pytest.mark.parametrize("density", [0.1, 0.5])
+def test_dk_dv(D, S, keep_ds, density):
+    H, Bk = 3, 12 if S == 128 else 1152 // S
+    M, lay, bad, scale = _setup(D, S, H, Bk, density, 14 * D + S)
+    N = Bk * S
+    q, k, v, g = (_rand(1, H, N, D) for _ in range(4))
+    clean = _clean_columns(lay, M, bad, S)
+    assert clean.any()
+    o, lse = _forward(lay, q, k, v, scale)
+    ws = torch.empty(B.s2_attn_bwd_layout_workspace_bytes(lay, 1, H, N, D) if keep_ds else B.s2_attn_bwd_workspace_bytes(1, H, N, D),
+                     dtype=torch.uint8, device="cuda")
+
+    def bwd(q, g):
+        grads = [torch.empty_like(q) for _ in range(3)]
+        B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, scale, ws)
+        return grads[1][0].cpu(), grads[2][0].cpu()
+
+    want = bwd(q, g)
+    for values in ((NAN,), (POS, NEG)):
+        got = bwd(_poison(q, bad, S, values), _poison(g, bad, S, values))
+        for a, b in zip(got, want):
+            assert torch.equal(a[clean], b[clean])
+
+
+@pytest.mark.parametrize("D,S", FORMS)
+def test_dk_dv_packed(D, S):
+    H, Bk = 2, 768 // S
+    M, lay, bad, scale = _setup(D, S, H, Bk, 0.15, 15 * D + S)
+    lens = [768, 700, 39, 333]
+    total = sum(lens)
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device="cuda")
+    q, k, v, g = (_rand(1, H, total, D) for _ in range(4))
+    keys = _clean_columns(lay, M, bad, S)
+    clean = torch.cat([keys[:, :n] for n in lens], 1)
+    assert clean.any()
+    where = torch.cat([torch.arange(n) for n in lens])
+    hit = torch.isin(where // S, torch.from_numpy(np.asarray(bad))).cuda()
+    o, lse = torch.empty_like(q), torch.empty((H, total), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd_varlen(lay, q, k, v, o, lse, cu, 768, scale)
+    ws = torch.empty(B.s2_attn_bwd_varlen_workspace_bytes(H, total, D), dtype=torch.uint8, device="cuda")
+
+    def bwd(q, g):
+        grads = [torch.empty_like(q) for _ in range(3)]
+        B.s2_attn_bwd_varlen(lay, q, k, v, o, lse, g, *grads, cu, 768, scale, ws)
+        return grads[1][0].cpu(), grads[2][0].cpu()
+
+    want = bwd(q, g)
+    for value in (NAN, POS):
+        q1, g1 = q.clone(), g.clone()
+        q1[:, :, hit] = value
+        g1[:, :, hit] = value
+        for a, b in zip(bwd(q1, g1), want):
+            assert torch.equal(a[clean], b[clean])
