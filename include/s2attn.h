@@ -244,7 +244,8 @@ int s2_attn_fwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
 /* Given q,k,v,o,lse,d_o writes dq,dk,dv (bf16; fp32 accumulation).  workspace is DEVICE memory
  * of s2_attn_bwd_workspace_bytes(...) bytes, 256-byte aligned, contents undefined on entry and exit.
  * (Two floats per row, each array rounded up to 256 bytes, are enough to run: the rest, asked for
- * where a launch has few key tiles, lets the longest of them be shared between workgroups.)  Errors as
+ * where a launch has fewer than 4096 key tiles, up to 96 MiB, lets the longest of them be shared between
+ * workgroups.  So the size does not grow with the shape throughout.)  Errors as
  * forward plus WORKSPACE. */
 int s2_attn_bwd(const s2_layout* layout, const s2_tensors* t, float scale, void* workspace,
                 size_t workspace_bytes, void* stream);
@@ -258,7 +259,8 @@ size_t s2_attn_bwd_workspace_bytes(int32_t batch, int32_t heads, int32_t seqlen,
  * dQ = scale * dS K over it.  Same results to rounding (dQ then takes the same bf16 dS that dK takes),
  * bitwise repeatable like the other path.  Covers head_dim 128, mask blocks of 64 or 128 tokens and
  * seqlen a multiple of 128; for any other call the value equals s2_attn_bwd_workspace_bytes and the
- * other path runs.  Which path a call takes is decided by workspace_bytes alone. */
+ * other path runs.  Which path a call takes is decided by workspace_bytes alone: the two floats per row and the
+ * dS units are enough to keep dS, the rest of the value is what s2_attn_bwd_workspace_bytes adds. */
 size_t s2_attn_bwd_layout_workspace_bytes(const s2_layout* layout, int32_t batch, int32_t heads,
                                           int32_t seqlen, int32_t head_dim);
 
@@ -292,6 +294,8 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
 int s2_dense_causal_fwd(const s2_tensors* t, float scale, void* stream);
 int s2_dense_causal_bwd(const s2_tensors* t, float scale, void* workspace, size_t workspace_bytes,
                         void* stream);
+/* What s2_dense_causal_bwd needs (it cuts no tiles; the size of s2_attn_bwd_workspace_bytes does as well). */
+size_t s2_dense_causal_bwd_workspace_bytes(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim);
 
 /* ---- decode (section 4.1: one step against the cache) ------------------------------------ */
 

@@ -85,7 +85,7 @@ class PagedDecodeArgs(C.Structure):
 EXPORTS = (
     "s2_layout_build", "s2_layout_from_csr", "s2_layout_destroy", "s2_layout_get", "s2_layout_get_tiles", "s2_layout_get_ds_units", "s2_attn_fwd", "s2_attn_fwd_rows", "s2_attn_fwd_varlen", "s2_attn_bwd_varlen",
     "s2_attn_bwd_varlen_workspace_bytes", "s2_attn_bwd",
-    "s2_attn_bwd_workspace_bytes", "s2_attn_bwd_layout_workspace_bytes", "s2_attn_bwd_stages", "s2_dense_causal_fwd", "s2_dense_causal_bwd", "s2_attn_decode",
+    "s2_attn_bwd_workspace_bytes", "s2_attn_bwd_layout_workspace_bytes", "s2_attn_bwd_stages", "s2_dense_causal_fwd", "s2_dense_causal_bwd", "s2_dense_causal_bwd_workspace_bytes", "s2_attn_decode",
     "s2_attn_decode_workspace_bytes", "s2_attn_decode_default_splits", "s2_attn_decode_static", "s2_attn_decode_paged",
     "s2_kv_resident_blocks", "s2_attn_decode_layout", "s2_attn_decode_paged_layout",
     "s2_layout_resident_blocks", "s2_probe_scratch_bytes", "s2_probe_mfma", "s2_probe_read", "s2_probe_atomic_add", "s2_status_string",
@@ -123,6 +123,8 @@ def lib():
                                      C.c_int, C.c_void_p]
     L.s2_attn_bwd_workspace_bytes.argtypes = [C.c_int32] * 4
     L.s2_attn_bwd_workspace_bytes.restype = C.c_size_t
+    L.s2_dense_causal_bwd_workspace_bytes.argtypes = [C.c_int32] * 4
+    L.s2_dense_causal_bwd_workspace_bytes.restype = C.c_size_t
     L.s2_attn_bwd_layout_workspace_bytes.argtypes = [C.c_void_p] + [C.c_int32] * 4
     L.s2_attn_bwd_layout_workspace_bytes.restype = C.c_size_t
     L.s2_dense_causal_fwd.argtypes = [C.POINTER(Tensors), C.c_float, C.c_void_p]
@@ -333,6 +335,10 @@ def s2_attn_bwd_stages(layout, q, k, v, o, lse, d_o, dq, dk, dv, scale, workspac
     _check(lib().s2_attn_bwd_stages(layout.handle, C.byref(t), scale, _ptr(workspace),
                                     workspace.numel() * workspace.element_size(), stages,
                                     _stream_ptr(stream)), "s2_attn_bwd_stages")
+
+
+def s2_dense_causal_bwd_workspace_bytes(batch, heads, seqlen, head_dim):
+    return lib().s2_dense_causal_bwd_workspace_bytes(batch, heads, seqlen, head_dim)
 
 
 def s2_dense_causal_fwd(q, k, v, o, lse, scale, stream=None):

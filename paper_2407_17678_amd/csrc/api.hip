@@ -115,7 +115,7 @@ int check_tensors(const s2_tensors* t, bool need_bwd, float scale) {
   for (int64_t s : strides)
     if (s < 0 || (s & 7) != 0) return S2_ERR_ALIGN;
   if (t->q_stride_t < t->head_dim || t->kv_stride_t < t->head_dim) return S2_ERR_ALIGN;
-  // the kernels address the 64 rows of a chunk with unsigned 32-bit byte offsets
+  // the kernels address the 16 rows of a piece with unsigned 32-bit byte offsets
   if (t->q_stride_t > (1 << 24) || t->kv_stride_t > (1 << 24)) return S2_ERR_SHAPE;
   const void* ptrs[9] = {t->q, t->k, t->v, t->o, t->lse, t->d_o, t->dq, t->dk, t->dv};
   for (int i = 0; i < (need_bwd ? 9 : 5); ++i)
@@ -305,25 +305,28 @@ namespace {
 
 size_t round256(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
-// The backward's workspace: delta = rowsum(dO * O), a copy of LSE in base-2 units, and - for launches
-// of so few tiles that the longest ones may be cut - a counter per key tile and the sums of the parts.
+// The backward's workspace: delta = rowsum(dO * O) and a copy of LSE in base-2 units; then dS, where it is kept;
+// then, for launches of so few tiles that the longest ones may be cut, a counter per key tile and the sums of the
+// parts.  Without the last nothing is cut, without room for dS it is not kept, and neither depends on the other.
 struct BwdWorkspace {
-  size_t stats;      // bytes of either of the two arrays
+  size_t stats;      // bytes of either of the first two arrays
   size_t count;      // of the counters
   size_t sums;       // of the sums
   int64_t slots;     // parts that there is room for
-  size_t required() const { return 2 * stats; }  // without the rest no tile is cut
-  size_t total() const { return 2 * stats + count + sums; }
+  size_t required() const { return 2 * stats; }
+  size_t cut() const { return count + sums; }
 };
 BwdWorkspace bwd_workspace(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim) {
   BwdWorkspace w{};
   const int64_t rows = (int64_t)batch * heads * seqlen;
   w.stats = round256((size_t)rows * sizeof(float));
-  const int64_t tiles = (int64_t)batch * heads * ((seqlen + s2::kBwdBN - 1) / s2::kBwdBN);
-  // From 4096 tiles on (eight rounds of the chip's 512 workgroup slots) the longest tile no longer decides.
-  if (tiles < 4096) {
+  const int64_t per_head = (seqlen + s2::kBwdBN - 1) / s2::kBwdBN, tiles = (int64_t)batch * heads * per_head;
+  // From 4096 tiles on (eight rounds of the chip's 512 workgroup slots) the longest tile no longer decides.  (head_dim
+  // is not checked here: the query has never done so, and no call takes one that is neither 64 nor 128.)
+  if (tiles < 4096 && head_dim > 0) {
     w.count = round256((size_t)tiles * sizeof(int32_t));
-    w.slots = std::min<int64_t>(768, 8 * tiles);
+    // no tile is longer than all of its head's rows, two 64-row steps to a tile, and no part shorter than four steps
+    w.slots = std::min<int64_t>(768, tiles * std::min<int64_t>(8, (2 * per_head + 3) / 4));
     w.sums = (size_t)w.slots * s2::kBwdBN * head_dim * 2 * sizeof(float);
   }
   return w;
@@ -332,8 +335,9 @@ BwdWorkspace bwd_workspace(int32_t batch, int32_t heads, int32_t seqlen, int32_t
 }  // namespace
 
 size_t s2_attn_bwd_workspace_bytes(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim) {
-  if (batch < 1 || heads < 1 || seqlen < 1 || head_dim < 1) return 0;
-  return bwd_workspace(batch, heads, seqlen, head_dim).total();
+  if (batch < 1 || heads < 1 || seqlen < 1) return 0;
+  const BwdWorkspace w = bwd_workspace(batch, heads, seqlen, head_dim);
+  return w.required() + w.cut();
 }
 
 namespace {
@@ -348,7 +352,7 @@ namespace {
 // blocks of 128): 677 -> 616; 1.2 (3 x 16 x 8192): 791 -> 764; 0.88 (4 x 16 x 8192): 999 uncut, 1026 cut.  The
 // best length of a part was 6 to 8, 24, 64, 48 to 64 and 64 steps, that is about 3/4 of `even` plus 3: a
 // part's own cost (its start, 64 KB per 128 keys and 64 features written and read again) against the evenness of the launch.
-void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, unsigned char* workspace) {
+void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, unsigned char* room) {
   const double slots = p.head_dim == 128 ? 64 : 80;
   const double even = ((p.batch * p.heads + 7) / 8) * (L->kv_head_steps + 5.0 * p.kv_tiles.tiles_per_head) / slots;
   if (L->kv_max_steps <= 1.1 * even) return;
@@ -366,8 +370,8 @@ void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, 
   p.split_codes = L->d_kv_split_codes + use->offset;
   p.split_items = use->n_items;
   p.split_long = use->n_long;
-  p.split_count = reinterpret_cast<int32_t*>(workspace + 2 * w.stats);
-  p.split_sums = reinterpret_cast<float*>(workspace + 2 * w.stats + w.count);
+  p.split_count = reinterpret_cast<int32_t*>(room);
+  p.split_sums = reinterpret_cast<float*>(room + w.count);
 }
 
 // The backward that keeps dS covers head_dim 128, mask blocks of 64 or 128 tokens (the layout then
@@ -487,14 +491,19 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
   p.lse2 = p.delta + w.stats / sizeof(float);
   p.block_size = layout->p.block_size;
   set_tiles(p, layout);
-  if (w.slots > 0 && workspace_bytes >= w.total()) choose_split(p, layout, w, static_cast<unsigned char*>(workspace));
-  // a workspace large enough to keep dS selects the backward that computes nothing twice
-  if (keeps_ds(layout, t->seqlen, t->head_dim) &&
-      workspace_bytes >= s2_attn_bwd_layout_workspace_bytes(layout, t->batch, t->heads, t->seqlen, t->head_dim)) {
-    p.ds_store = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(workspace) + w.total());
+  unsigned char* const ws = static_cast<unsigned char*>(workspace);
+  size_t used = w.required();
+  // Room for dS selects the backward that computes nothing twice.  Where there is room for dS or for cutting
+  // tiles but not for both, the workspace is of the size asked for cutting alone if that is the larger of the two.
+  const size_t ds_bytes = (size_t)t->batch * (size_t)layout->ds_units * 8192;
+  if (keeps_ds(layout, t->seqlen, t->head_dim) && workspace_bytes >= used + ds_bytes &&
+      (workspace_bytes >= used + ds_bytes + w.cut() || workspace_bytes < used + w.cut() || ds_bytes > w.cut())) {
+    p.ds_store = reinterpret_cast<uint16_t*>(ws + used);
     p.ds_units = layout->ds_units;
     p.dq_units = layout->d_dq_units;
+    used += ds_bytes;
   }
+  if (w.slots > 0 && workspace_bytes >= used + w.cut()) choose_split(p, layout, w, ws + used);
   return hip_ok(s2::launch_bwd(p, false, stages, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 
@@ -532,6 +541,11 @@ int s2_dense_causal_bwd(const s2_tensors* t, float scale, void* workspace, size_
   p.delta = static_cast<float*>(workspace);
   p.lse2 = p.delta + w.stats / sizeof(float);
   return hip_ok(s2::launch_bwd(p, true, s2::kBwdAll, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
+}
+
+size_t s2_dense_causal_bwd_workspace_bytes(int32_t batch, int32_t heads, int32_t seqlen, int32_t head_dim) {
+  if (batch < 1 || heads < 1 || seqlen < 1) return 0;
+  return bwd_workspace(batch, heads, seqlen, head_dim).required();
 }
 
 int32_t s2_attn_decode_default_splits(int32_t nseq, int32_t heads, int32_t max_len) {

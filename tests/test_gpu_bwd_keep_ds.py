@@ -202,3 +202,32 @@ def test_random_case(case):
         for b in range(batch):
             for h in range(H):
                 assert G.rel_l2(got[b, h], ref[b, h]) <= GRAD_TOL, (n, b, h)
+
+
+@pytest.mark.parametrize("heads,seqlen,local", [(4, 1024, 2), (12, 4096, 16)])  # dS smaller and larger than the room to cut tiles
+def test_room_for_ds_alone_keeps_it(heads, seqlen, local):
+    w = dataclasses.replace(synth.WORKLOADS["1p3b_8k"], local_blocks=local)
+    q, k, v, g = (G.to_dev(x) for x in synth.train_inputs(w, heads=heads, batch=1, seqlen=seqlen))
+    lay = B.s2_layout_build(B.layout_params(heads, seqlen // w.block_size, w.block_size, local, w.stride))
+    o, lse = torch.empty_like(q), torch.empty((1, heads, seqlen), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, w.scale)
+    stats = 2 * ((heads * seqlen * 4 + 255) // 256 * 256)
+    plain = B.s2_attn_bwd_workspace_bytes(1, heads, seqlen, 128)
+    ds = B.s2_attn_bwd_layout_workspace_bytes(lay, 1, heads, seqlen, 128) - plain
+    assert (ds > plain - stats) == (local == 16)
+
+    def dq(size):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+        grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+        B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, w.scale, ws)
+        return grads[0], ws
+
+    kept, _ = dq(plain + ds)
+    again, _ = dq(stats)
+    assert not torch.equal(kept, again)  # (dQ from the bf16 dS, or from scores formed a second time)
+    for size in (stats + ds, stats + ds + 256):
+        got, ws = dq(size)
+        assert torch.equal(got, kept) and not (ws[stats:stats + 8192] == 0xFF).all()
+    # the plain size, and what is no more than it, recomputes
+    for size in (plain, stats + 256):
+        assert torch.equal(dq(size)[0], again)

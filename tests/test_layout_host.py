@@ -567,3 +567,22 @@ def test_ds_unit_table(S):
     assert B.s2_attn_bwd_layout_workspace_bytes(lay, 3, 4, 8 * S, 64) == B.s2_attn_bwd_workspace_bytes(3, 4, 8 * S, 64)
     assert B.s2_attn_bwd_layout_workspace_bytes(lay, 3, 5, 8 * S, 128) == B.s2_attn_bwd_workspace_bytes(3, 5, 8 * S, 128)
     assert B.s2_attn_bwd_layout_workspace_bytes(lay, 3, 4, 4 * S, 128) == B.s2_attn_bwd_workspace_bytes(3, 4, 4 * S, 128)
+
+
+def test_backward_workspace_sizes():
+    stats = lambda rows: 2 * ((rows * 4 + 255) // 256 * 256)
+    # two floats a row is what any call needs and all that the dense pair asks for
+    for batch, heads, seqlen, D in ((1, 4, 512, 64), (2, 16, 3904, 128), (1, 32, 8192, 128), (4, 16, 8192, 128)):
+        assert B.s2_dense_causal_bwd_workspace_bytes(batch, heads, seqlen, D) == stats(batch * heads * seqlen)
+        assert B.s2_attn_bwd_workspace_bytes(batch, heads, seqlen, D) >= stats(batch * heads * seqlen)
+    assert B.s2_dense_causal_bwd_workspace_bytes(0, 4, 512, 64) == 0
+    # the head size has never been checked by the query
+    assert B.s2_attn_bwd_workspace_bytes(1, 4, 512, 0) == stats(4 * 512)
+    # room to cut tiles: a counter per key tile, and 64 KiB (head_dim 64) or 128 KiB a part; of the parts no more than the
+    # steps of a head's rows, two to a key tile, make at four a part, eight a tile, or 768 in all
+    part = {64: 65536, 128: 131072}
+    for batch, heads, seqlen, D, parts in ((1, 4, 512, 64, 4 * 4 * 2), (1, 4, 128, 64, 4), (1, 2, 2048, 128, 2 * 16 * 8), (2, 16, 3904, 128, 768)):
+        tiles = batch * heads * (-(-seqlen // 128))
+        assert B.s2_attn_bwd_workspace_bytes(batch, heads, seqlen, D) == \
+            stats(batch * heads * seqlen) + (tiles * 4 + 255) // 256 * 256 + parts * part[D]
+    assert B.s2_attn_bwd_workspace_bytes(4, 16, 8192, 128) == stats(4 * 16 * 8192)  # 4096 tiles: none is cut
