@@ -43,6 +43,16 @@ def _mask(H, Bk, B_l, stride):
     return M
 
 
+def _counters_and_sums(ws, lay, batch, H, N, D, keep_ds):
+    """The part of the workspace that cut tiles use, behind the statistics and (kept) dS."""
+    off = 2 * ((batch * H * N * 4 + 255) // 256 * 256)
+    if keep_ds:
+        off += B.s2_attn_bwd_layout_workspace_bytes(lay, batch, H, N, D) - B.s2_attn_bwd_workspace_bytes(batch, H, N, D)
+    tiles = batch * H * (-(-N // 128))
+    end = off + (4 * tiles + 255) // 256 * 256
+    return ws[off:off + 4 * tiles].view(torch.int32), ws[end:]
+
+
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "D%d_S%d_H%d_b%d_B%d_L%d_V%d_%s" % (c[:7] + ("keep" if c[7] else "again",)))
 def test_cut_tiles(case):
     D, S, H, batch, Bk, B_l, stride, keep_ds = case
@@ -65,6 +75,9 @@ def test_cut_tiles(case):
         ws[:] = 0xFF
         B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, w.scale, ws)
         runs.append(grads)
+        # the workspace shows that tiles were cut: a counter has counted parts, and sums have been written
+        count, sums = _counters_and_sums(ws, lay, batch, H, N, D, keep_ds)
+        assert 2 <= int(count.max()) <= 64 and int(count.min()) >= 0 and bool((sums != 0xFF).any())
     grads = [torch.full_like(q, float("nan")) for _ in range(3)]
     ws[:] = 0xFF
     # (delta comes from the launch that a whole backward takes it from, so that it is the same to the bit)
@@ -115,3 +128,20 @@ def test_a_dkdv_call_clears_its_own_counters(keep_ds):
     for r in results:
         assert torch.equal(r[0], results[1][0]) and torch.equal(r[1], results[1][1])
     assert torch.isfinite(results[1][0].float()).all()
+
+
+@pytest.mark.parametrize("D,S", [(64, 64), (128, 32)])
+def test_short_tiles_stay_whole(D, S):
+    # a local window of one block: no key tile is long enough to be cut, and the room for it stays untouched
+    H, Bk = 3, 1024 // S
+    N = Bk * S
+    w = dataclasses.replace(synth.WORKLOADS["tiny" if D == 64 else "1p3b_8k"], block_size=S)
+    q, k, v, g = (G.to_dev(x) for x in synth.train_inputs(w, heads=H, batch=1, seqlen=N))
+    lay = B.s2_layout_build(B.layout_params(H, Bk, S, 1, 0))
+    o, lse = torch.empty_like(q), torch.empty((1, H, N), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, w.scale)
+    ws = torch.full((B.s2_attn_bwd_workspace_bytes(1, H, N, D),), 0xFF, dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(q) for _ in range(3)]
+    B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, w.scale, ws)
+    count, sums = _counters_and_sums(ws, lay, 1, H, N, D, False)
+    assert int(count.max()) == -1 and bool((sums == 0xFF).all())

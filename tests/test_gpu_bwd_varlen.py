@@ -120,9 +120,8 @@ def test_varlen_backward_agrees_with_the_fixed_length_backward():
 
 def test_varlen_seeded_sweep_around_the_tile_size():
     """Random packed batches for head_dim 128 and blocks of 64 and 128 tokens, lengths drawn around the
-    multiples of 128: whole 128-row tiles and a sequence's partial last tile are computed by different
-    kernels (forward and dQ alike), so lengths of exactly k * 128, one more, one less, below 128 and zero
-    all occur, with random local-window and stride parameters."""
+    multiples of 128, where a sequence's partial last tile begins: lengths of exactly k * 128, one more, one
+    less, below 128 and zero all occur, with random local-window and stride parameters."""
     rng = np.random.default_rng(2024)
     for case in range(10):
         S = int(rng.choice([64, 128]))
@@ -142,11 +141,27 @@ def test_varlen_seeded_sweep_around_the_tile_size():
         _check(bits, cu, M, S, w.scale, out, int(cu[-1]))
 
 
+@pytest.mark.parametrize("D,S", [(64, 16), (64, 32), (64, 128), (128, 16), (128, 32)])
+def test_varlen_short_sequences_in_a_long_layout(D, S):
+    """Sequences from one token to the whole of a layout whose lists are longer than the 64 entries held at a time
+    (16- and 32-token blocks), so that the entries after a short sequence's end, which its key tiles skip, are in other
+    batches of 64 than the ones they use, and a wavefront's columns lie far apart, one of them past the end."""
+    rng = np.random.default_rng(100 * D + S)
+    H, Bk = 2, 2560 // S
+    M = np.tril(rng.random((H, Bk, Bk)) < 0.7)
+    M[:, np.arange(Bk), np.arange(Bk)] = True
+    w = dataclasses.replace(synth.WORKLOADS["tiny" if D == 64 else "1p3b_8k"], block_size=S)
+    lens = [2560, 1, S, 2 * S + 1, 700, 0, 129, 1290]
+    print("varlen long layout case D", D, "S", S, flush=True)
+    bits, cu, M, out = _run(w, H, lens, Bk, M=M, extra_rows=3)
+    _check(bits, cu, M, S, w.scale, out, int(cu[-1]))
+
+
 def test_varlen_row_offsets_that_make_no_sense_stay_inside_the_tensors():
     """cu_seqlens is a device array the host cannot check: negative entries, entries far beyond the tensors,
     decreasing ones.  The kernels cut every sequence to the rows that exist and to max_seqlen, so such a call
     must complete, leave the rows no (cut) sequence owns alone, and still compute the sequences that are in
-    order and overlap nothing - forward and backward, on the path with the whole-tile kernels."""
+    order and overlap nothing - forward and backward."""
     w = dataclasses.replace(synth.WORKLOADS["1p3b_8k"], local_blocks=2, stride=3)
     H, Bk, S, D = 2, 8, w.block_size, w.head_dim
     total, max_len = 1600, Bk * S

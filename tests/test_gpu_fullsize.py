@@ -257,8 +257,7 @@ def test_7b_prefill_varlen_full():
     rng = np.random.default_rng(4)
     for sq, L in enumerate(lens.tolist()):
         lo = int(cu[sq])
-        # (whole 128-row tiles and the partial last tile are computed by different kernels: both sides of
-        # that line are in the sample)
+        # (both sides of the line between the whole 128-row tiles and the partial last one are in the sample)
         rows = sorted({0, S - 1, S, L // 2, (L // S) * S - 1, min((L // S) * S, L - 1), L - 2, L - 1,
                        (L // 128) * 128 - 1, min((L // 128) * 128, L - 1)} |
                       set(int(x) for x in rng.integers(0, L, size=6)))

@@ -82,9 +82,9 @@ def test_varlen_custom_pattern():
 
 
 def test_varlen_rows_agree_with_the_fixed_length_forward():
-    # The two entry points may run differently scheduled kernels (the fixed-length one has a fast
-    # path for whole 128-row tiles), so they agree to rounding, not bit for bit: O within one bf16
-    # ulp of each other (and 1e-2), LSE within 1e-5.
+    # The two entry points may treat a sequence's whole tiles differently (the reference maximum is moved
+    # lazily or not), so they agree to rounding, not bit for bit: O within one bf16 ulp of each other (and 1e-2), LSE
+    # within 1e-5.
     # each sequence on its own through s2_attn_fwd (lengths it accepts: whole blocks)
     w = dataclasses.replace(synth.WORKLOADS["1p3b_8k"], block_size=64, local_blocks=2, stride=3)
     H, Bk, S = 3, 12, 64
