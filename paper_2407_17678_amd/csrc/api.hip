@@ -68,7 +68,7 @@ s2::DevTiles dev_tiles(const s2::TileList& t) {
 
 // The lists the row-tile and key-tile kernels walk.
 void set_tiles(s2::AttnParams& p, const s2_layout* L) {
-  p.fwd_tiles = p.q_tiles = dev_tiles(L->q_tiles);
+  p.q_tiles = dev_tiles(L->q_tiles);
   p.kv_tiles = dev_tiles(L->kv_tiles);
 }
 
@@ -352,15 +352,19 @@ namespace {
 // blocks of 128): 677 -> 616; 1.2 (3 x 16 x 8192): 791 -> 764; 0.88 (4 x 16 x 8192): 999 uncut, 1026 cut.  The
 // best length of a part was 6 to 8, 24, 64, 48 to 64 and 64 steps, that is about 3/4 of `even` plus 3: a
 // part's own cost (its start, 64 KB per 128 keys and 64 features written and read again) against the evenness of the launch.
+// Where all tiles start at once they must still do so when cut: 52 heads x 800 x 128 in blocks of 32, 49 workgroups for
+// an XCD's 64 slots uncut and 84 cut, forward and backward 78 us uncut, 90 cut; 42 heads, 42 and 54, 66 and 54.
 void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, unsigned char* room) {
   const double slots = p.head_dim == 128 ? 64 : 80;
-  const double even = ((p.batch * p.heads + 7) / 8) * (L->kv_head_steps + 5.0 * p.kv_tiles.tiles_per_head) / slots;
+  const int pairs = (p.batch * p.heads + 7) / 8, T = p.kv_tiles.tiles_per_head;  // (batch, head) pairs of an XCD
+  const double even = pairs * (L->kv_head_steps + 5.0 * T) / slots;
   if (L->kv_max_steps <= 1.1 * even) return;
   const double best = 0.75 * even + 3;
   const s2::SplitLevel* use = nullptr;
   double off = 0;
   for (const s2::SplitLevel& lv : L->kv_levels) {
     if ((int64_t)p.batch * p.heads * lv.n_items > w.slots || 2 * lv.steps > L->kv_max_steps) continue;
+    if (pairs * T <= slots && pairs * (T + lv.n_items - lv.n_long) > slots) continue;
     const double o = std::max(lv.steps / best, best / lv.steps);
     if (use && o >= off) continue;
     use = &lv;
@@ -510,8 +514,6 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
 static int dense_params(const s2_tensors* t, s2::AttnParams& p) {
   if (t->seqlen % 128 != 0) return S2_ERR_SHAPE;
   p.block_size = s2::kChunk;
-  p.fwd_tiles.tiles_per_head = (t->seqlen + s2::kFwdBM - 1) / s2::kFwdBM;
-  p.fwd_tiles.group = s2::kFwdBM / s2::kChunk;
   p.q_tiles.tiles_per_head = t->seqlen / s2::kBwdBM;
   p.q_tiles.group = s2::kBwdBM / s2::kChunk;
   p.kv_tiles.tiles_per_head = t->seqlen / s2::kBwdBN;

@@ -57,14 +57,14 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_gather_kernel(
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-  const int T = p.fwd_tiles.tiles_per_head;      // tiles of the whole sequence (indexes the lists)
+  const int T = p.q_tiles.tiles_per_head;      // tiles of the whole sequence (indexes the lists)
   const int T_run = (p.q_rows + BM - 1) / BM;    // tiles this launch computes
   int bh, rank;
   if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, p.map_group, bh, rank)) return;
   const int b = bh / p.heads, h = bh - b * p.heads;
   // longest tiles first: by the layout's order for a whole sequence, else simply last row first
   const bool whole = !VARLEN && p.q_row0 == 0 && T_run == T;
-  int tile = whole ? p.fwd_tiles.order[h * T + rank] : p.q_row0 / BM + (T_run - 1 - rank);
+  int tile = whole ? p.q_tiles.order[h * T + rank] : p.q_row0 / BM + (T_run - 1 - rank);
   // my sequence's length, its query rows in this call, and the rows of the tensors before it
   int N = p.seqlen, n_q = p.q_rows, row_base = 0;
   if (VARLEN) {
@@ -86,12 +86,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_gather_kernel(
   const uint16_t* kb = p.k + kv_off - Piece::kBias / 2;
   const uint16_t* vb = p.v + kv_off - Piece::kBias / 2;
 
-  const int ent_lo = p.fwd_tiles.ptr[h * T + tile];
-  const int n_ent = p.fwd_tiles.ptr[h * T + tile + 1] - ent_lo;
+  const int ent_lo = p.q_tiles.ptr[h * T + tile];
+  const int n_ent = p.q_tiles.ptr[h * T + tile + 1] - ent_lo;
   const int total = (n_ent + EPC - 1) / EPC;  // chunks
   if (total <= 0) return;
   EntryList list;
-  list.init(p.fwd_tiles.ent + ent_lo, n_ent, lane);
+  list.init(p.q_tiles.ent + ent_lo, n_ent, lane);
 
   // Q^T fragments stay in registers for the whole tile (B operands of the score MFMAs); a lane without
   // a row of its own reads the last row, its result is never stored

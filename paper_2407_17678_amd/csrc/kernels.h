@@ -42,8 +42,7 @@ struct AttnParams {
   float scale;        // softmax scale
   float scale_log2e;  // scale * log2(e)
   int block_size;     // S (sparse path); 64 on the dense path
-  DevTiles fwd_tiles; // row tiles of the forward kernel -> KV blocks
-  DevTiles q_tiles;   // row tiles of the dQ kernel -> KV blocks
+  DevTiles q_tiles;   // row tiles of the forward and dQ kernels -> KV blocks
   DevTiles kv_tiles;  // column tiles -> Q blocks
   // Key tiles cut into parts (SplitLevel in layout.h; split_items == 0: none are): the first split_items
   // items of a head are parts of its first split_long tiles.  The parts' sums go to split_sums, [batch *
