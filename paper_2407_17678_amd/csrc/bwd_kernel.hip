@@ -233,6 +233,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     }
   };
 
+  // FINE: the largest entry whose query block begins before my sequence's end
+  const uint32_t last_ent = FINE && VARLEN ? ((uint32_t)((N + FINE - 1) / max(FINE, 1) - 1) << 16) | 0xFFFFu : 0;
   const typename Piece::Plan plan = Piece::plan(p.q_st, lane);
   const uint32_t stats_gap = (uint32_t)((const char*)lse_b - (const char*)delta_b);
   // `ln` is the lane number.  The loop passes a copy the optimiser cannot see through, so that
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
       if constexpr (FINE) {
         src = entries_at(it);
         uint64_t any = __ballot(FINE == 32 ? ((src >> wave) & 1) != 0 : ((src >> (2 * wave)) & 3) != 0);
-        if (VARLEN) any &= __ballot((uint32_t)src < (uint32_t)((N + FINE - 1) / FINE) << 16);
+        if (VARLEN) any &= __ballot((uint32_t)src <= last_ent);
         on4 = (uint32_t)(any >> ((EPC * it) & 63));
       }
 #pragma unroll

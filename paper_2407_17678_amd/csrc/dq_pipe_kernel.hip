@@ -16,7 +16,7 @@
 // Head_dim 64, mask blocks below 64 tokens (FINE: chunks gathered from 16-key pieces) and ragged ends
 // (VARLEN) are the same loop, as in the forward.  Against the phase-by-phase kernel that these used to run,
 // per launch: 2 x 16 heads x 4096 x 64, blocks of 64: 50.1 -> 45.9 us; 2 x 16 x 3904 x 128 (61 blocks):
-// 73.3 -> 65.2 us; 1 x 16 x 8192 x 128, blocks of 16: 84.2 -> 71.3 us; a packed batch of 8 sequences of 200 to
+// 73.3 -> 65.2 us; 1 x 16 x 8192 x 128, blocks of 16: 84.2 -> 70 us; a packed batch of 8 sequences of 200 to
 // 8192 rows x 32 heads: 497 us in two launches -> 478 us in one.  It is bound as the forward is: by the
 // matrix pipe and the vector work beside it over long lists, by a tile's start and end over short ones.
 #include <hip/hip_runtime.h>

@@ -157,6 +157,31 @@ def test_varlen_short_sequences_in_a_long_layout(D, S):
     _check(bits, cu, M, S, w.scale, out, int(cu[-1]))
 
 
+def test_varlen_the_longest_sequence_of_16_token_blocks():
+    # 65536 blocks, the most a layout takes: partner indices use all sixteen bits
+    S, Bk, D = 16, 65536, 64
+    N = S * Bk
+    lay = B.s2_layout_build(B.layout_params(1, Bk, S, 2, 0))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    q, k, v, g = (torch.empty((1, 1, N, D), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(4))
+    o, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(4))
+    lse = torch.empty((1, N), dtype=torch.float32, device="cuda")
+    cu = torch.tensor([0, N], dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.s2_attn_bwd_varlen_workspace_bytes(1, N, D), dtype=torch.uint8, device="cuda")
+    B.s2_attn_fwd_varlen(lay, q, k, v, o, lse, cu, N, D ** -0.5)
+    B.s2_attn_bwd_varlen(lay, q, k, v, o, lse, g, dq, dk, dv, cu, N, D ** -0.5, ws)
+    # a local window of two blocks: the first and the last 320 rows but their margins, as sequences of their own
+    M = orc.block_mask(1, 20, 2, 0)
+    for lo in (0, N - 320):
+        f = lambda x: G.to_f64(x[0, :, lo:lo + 320])[None]
+        ref = orc.attention_backward(f(q), f(k), f(v), f(g), M, S, D ** -0.5)
+        rows = slice(0, 288) if lo == 0 else slice(32, 320)
+        assert G.o_excess(f(o)[0, :, rows], ref[3][0, :, rows]) <= 0
+        for n, t, want in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
+            assert G.rel_l2(f(t)[0, :, rows], want[0, :, rows]) <= GRAD_TOL, (n, lo)
+
+
 def test_varlen_row_offsets_that_make_no_sense_stay_inside_the_tensors():
     """cu_seqlens is a device array the host cannot check: negative entries, entries far beyond the tensors,
     decreasing ones.  The kernels cut every sequence to the rows that exist and to max_seqlen, so such a call
