@@ -185,8 +185,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   for (int i = 0; i < 4; ++i) s[i >> 1][i & 1] = f32x16{};
 
   // ------------------------------------------------------------------ pieces of a step
-  // The A operands of a step's 32 MFMAs - 16 row fragments of K, then 16 transposed fragments of
-  // V - pass through one ring of kRing registers sets, each requested from LDS kLead slots before
+  // The A operands of a step's MFMAs (head_dim 128: 16 row fragments of K, then 16 transposed fragments
+  // of V; half as many at 64) pass through one ring of kRing registers sets, each requested from LDS kLead slots before
   // the MFMA that uses it.
   // fragment f: K fragment (kk = f / 2, key half f % 2) for f < NQK, else V^T fragment f - NQK
   // (group (f - NQK) / DT = key half, 16-key slab; feature tile (f - NQK) % DT)

@@ -29,8 +29,8 @@ struct AttnParams {
   float* delta;  // workspace: rowsum(dO * O), [batch, heads, seqlen]
   float* lse2;   // workspace: lse * log2(e), [batch, heads, seqlen]
   int batch, heads, seqlen, head_dim;
-  // forward only: q, o, lse hold q_rows rows, local row r being sequence position q_row0 + r
-  // (the whole sequence: q_row0 = 0, q_rows = seqlen)
+  // q, o, lse hold q_rows rows, local row r being sequence position q_row0 + r (the whole sequence,
+  // as in every backward of a fixed length: q_row0 = 0, q_rows = seqlen)
   int q_row0, q_rows;
   // packed variable-length batch (nullptr = every sequence has seqlen rows):
   // sequence b owns rows cu_seqlens[b] .. cu_seqlens[b+1]-1 of q, k, v, o and lse; then batch is
