@@ -148,6 +148,8 @@ s2::AttnParams make_params(const s2_tensors* t, float scale) {
   p.kv_st = t->kv_stride_t;
   p.scale = scale;
   p.scale_log2e = scale * 1.4426950408889634f;
+  // (clamped so that lse / scale stays finite where no score is beyond 2^100)
+  p.neg_inv_scale = -1.0f / fmaxf(scale, 4e-38f);
   return p;
 }
 
@@ -305,7 +307,7 @@ namespace {
 
 size_t round256(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
-// The backward's workspace: delta = rowsum(dO * O) and a copy of LSE in base-2 units; then dS, where it is kept;
+// The backward's workspace: the row statistics -delta = -rowsum(dO * O) and -lse / scale; then dS, where it is kept;
 // then, for launches of so few tiles that the longest ones may be cut, a counter per key tile and the sums of the
 // parts.  Without the last nothing is cut, without room for dS it is not kept, and neither depends on the other.
 struct BwdWorkspace {
@@ -443,7 +445,7 @@ int s2_attn_fwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
 size_t s2_attn_bwd_varlen_workspace_bytes(int32_t heads, int32_t rows, int32_t head_dim) {
   (void)head_dim;
   if (heads < 1 || rows < 1) return 0;
-  // delta and base-2 LSE per (head, row), plus one chunk of slack each: the dK/dV kernel fetches the
+  // the two row statistics per (head, row), plus one chunk of slack each: the dK/dV kernel fetches the
   // statistics of a whole 64-row chunk even where a sequence ends inside it
   const size_t floats = (size_t)heads * rows + 64;
   return 2 * (((floats * sizeof(float) + 255) / 256) * 256);
@@ -469,8 +471,8 @@ int s2_attn_bwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   p.cu_seqlens = cu_seqlens;
   p.block_size = layout->p.block_size;
   set_tiles(p, layout);
-  p.delta = static_cast<float*>(workspace);
-  p.lse2 = p.delta + need / 8;
+  p.neg_delta = static_cast<float*>(workspace);
+  p.neg_lse = p.neg_delta + need / 8;
   // one grid slot per (sequence, head, tile): query tiles of the longest length allowed, key tiles of the layout
   const int64_t pairs = 8 * (((int64_t)num_seqs * t->heads + 7) / 8);
   const int64_t slots = pairs * std::max<int64_t>((max_seqlen + s2::kBwdBM - 1) / s2::kBwdBM, layout->kv_tiles.tiles_per_head);
@@ -491,8 +493,8 @@ int s2_attn_bwd_stages(const s2_layout* layout, const s2_tensors* t, float scale
     return S2_ERR_WORKSPACE;
   if (!layout_on_current_device(layout)) return S2_ERR_NO_DEVICE;
   s2::AttnParams p = make_params(t, scale);
-  p.delta = static_cast<float*>(workspace);
-  p.lse2 = p.delta + w.stats / sizeof(float);
+  p.neg_delta = static_cast<float*>(workspace);
+  p.neg_lse = p.neg_delta + w.stats / sizeof(float);
   p.block_size = layout->p.block_size;
   set_tiles(p, layout);
   unsigned char* const ws = static_cast<unsigned char*>(workspace);
@@ -540,8 +542,8 @@ int s2_dense_causal_bwd(const s2_tensors* t, float scale, void* workspace, size_
   s2::AttnParams p = make_params(t, scale);
   st = dense_params(t, p);
   if (st != S2_OK) return st;
-  p.delta = static_cast<float*>(workspace);
-  p.lse2 = p.delta + w.stats / sizeof(float);
+  p.neg_delta = static_cast<float*>(workspace);
+  p.neg_lse = p.neg_delta + w.stats / sizeof(float);
   return hip_ok(s2::launch_bwd(p, true, s2::kBwdAll, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 

@@ -20,6 +20,15 @@
 // without leaving the lane (see device_util.h).  The streamed 64-row chunk is brought in by
 // direct global -> LDS loads (double buffered) and read in both operand forms from the one
 // row-major tile: row fragments (k = feature) and LDS transpose reads (k = token).
+//
+// The dK/dV loop is written out one MFMA per slot (see sched_util.h): for 32 query rows S, dP, dV and dK one after the
+// other, the exponentials under dP and the first half of dV, dS = P * dP under the second half of dV and the first of dK,
+// each LDS fragment requested three MFMAs ahead of its use through a ring that goes on from one half step to the next.  Left to the compiler
+// every MFMA waited for the read issued right before it, since at 192 registers of accumulators and K / V fragments it keeps no second
+// fragment.  Room for the ring comes from what no longer has registers: the row statistics are read straight into the accumulators (S begins at
+// -lse / scale, dP at -delta), the lane offsets of the direct loads lie in LDS (head_dim 128), and what derives from the lane number is
+// formed where it is used.  dK/dV launch, before and now: 1 x 32 heads x 32768 x 128 1.980 -> 1.855 ms (2.262 -> 2.172 where it
+// keeps dS), dense 32 x 8192 x 128 0.98 -> 0.89 ms, 4 x 32 x 8192 x 64 0.639 -> 0.617 ms.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -32,8 +41,6 @@
 namespace s2 {
 
 namespace {
-
-constexpr float kLog2e = 1.4426950408889634f;
 
 // ------------------------------------------------------------------------------------ delta
 
@@ -60,8 +67,8 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p) {
   for (int m = LPR / 2; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
   clear_split_counts(p, blockIdx.x * 256 + tid);
   if (c == 0 && row < rows_total) {
-    p.delta[row] = acc;
-    p.lse2[row] = p.lse[row] * kLog2e;  // the main kernels want LSE in base-2 units
+    p.neg_delta[row] = -acc;
+    p.neg_lse[row] = p.lse[row] * p.neg_inv_scale;
   }
 }
 
@@ -93,14 +100,43 @@ __device__ __forceinline__ void load_agent16(const void* base, uint32_t lane_off
                : "memory");
 }
 
+// The lane number, computed where it is asked for: nothing derived from it is kept in a register between two calls.
+__device__ __forceinline__ int lane_now() {
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  return ln;
+}
+
+// x stays where AT >= lim (keep_from) or AT < lim (keep_below), else it becomes `gone`.  Written out so that it costs no register but
+// its operands: left to itself the compiler keeps the compares of a whole tile at hand, and `gone` over the whole kernel.
+// (The no-op is the wait between a vector write of vcc and its use as a select.)
+template <int AT>
+__device__ __forceinline__ float keep_from(float x, int lim, float gone) {
+  asm volatile("v_cmp_ge_i32 vcc, %2, %1\n\ts_nop 1\n\tv_cndmask_b32 %0, %3, %0, vcc" : "+v"(x) : "v"(lim), "n"(AT), "v"(gone) : "vcc");
+  return x;
+}
+template <int AT>
+__device__ __forceinline__ float keep_below(float x, int lim, float gone) {
+  asm volatile("v_cmp_lt_i32 vcc, %2, %1\n\ts_nop 1\n\tv_cndmask_b32 %0, %3, %0, vcc" : "+v"(x) : "v"(lim), "n"(AT), "v"(gone) : "vcc");
+  return x;
+}
+template <uint32_t BITS>
+__device__ __forceinline__ float constant_now() {
+  float x;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "n"((int)BITS));
+  return x;
+}
+constexpr uint32_t kNegInfBits = 0xFF800000u;
+
 template <int D>
 struct DkvSmem {
   uint16_t q[2][DmaTile<D>::kElems];
   uint16_t g[2][DmaTile<D>::kElems];
   struct RowStats {
-    float delta[64];
-    float lse[64];         // base-2 units
+    float neg_delta[64];
+    float neg_lse[64];
   } rs[2];                 // one 512-byte direct load fills both arrays of a stage
+  uint32_t goff[D == 128 ? PieceTile<D>::kLoads : 1][64];  // D = 128: the lane offsets of the direct loads
 };
 
 // FINE: mask blocks of 16 or 32 tokens (0: larger ones).  A step's 64 query rows are four pieces of 16
@@ -124,7 +160,12 @@ template <int D, bool DENSE, int FINE, bool VARLEN = false, bool STORE = false>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const AttnParams p) {
   typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
-  constexpr int CH = 64, QT = CH / 32;
+  constexpr int CH = 64;
+  constexpr int KK = D / 16, DT = D / 32;
+  constexpr int RB = Tile::kStride * 2;                       // bytes per tile row
+  constexpr int G_OFF = 2 * Tile::kBytes;                     // dO stages lie after the Q stages
+  constexpr int kLead = 3, kRing = 4;
+  static_assert((4 * KK) % kRing == 0, "the ring goes on from half to half");
   static_assert(!(DENSE && (FINE || VARLEN)) && !(STORE && (DENSE || FINE || VARLEN)), "forms that exist");
   static_assert(FINE == 0 || FINE == 16 || FINE == 32, "blocks that are gathered");
   constexpr int PPE = FINE == 32 ? 2 : 1, EPC = 4 / PPE;  // FINE: 16-row pieces of a list entry, entries of a step
@@ -193,8 +234,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   const uint16_t* gb = p.d_o + q_off - Piece::kBias / 2;
   // packed batch: the row statistics are [heads, rows of the tensors]
   const int64_t stats_off = VARLEN ? (int64_t)h * p.seqlen + row_base : ((int64_t)b * p.heads + h) * N;
-  const float* lse_b = p.lse2 + stats_off;
-  const float* delta_b = p.delta + stats_off;
+  const float* lse_b = p.neg_lse + stats_off;
+  const float* delta_b = p.neg_delta + stats_off;
 
   int ent_lo = 0, n_ent;
   if (DENSE) {
@@ -241,7 +282,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   // what is derived from it is recomputed each step (a few integer operations) rather than kept in
   // registers across the loop: this kernel has no registers to spare, and a spilled constant costs
   // a wait for all outstanding loads when it is fetched back.
-  auto issue_chunk = [&](int j, int buf, int ln) S2_INLINE {
+  auto issue_chunk = [&](const typename Piece::Plan& plan, int j, int buf, int ln) S2_INLINE {
     int q0 = 0, src = 0, row;
     if constexpr (FINE) {
       src = entries_at(j);
@@ -301,7 +342,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     (void)list.get(e, lane);
     it0 = FINE ? e / EPC : e << cpb_sh;
   }
-  if (!kSplits || total > 0) issue_chunk(it0, it0 & 1, lane);  // (where a head's tile is short for its rank a part may be empty)
+  if (!kSplits || total > 0) issue_chunk(plan, it0, it0 & 1, lane);  // (where a head's tile is short for its rank a part may be empty)
 
   bf16x8 kf[D / 16], vf[D / 16];  // K and V fragments (B operands), lane = key
 #pragma unroll
@@ -319,17 +360,29 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     acc_dv[dt] = f32x16{};
   }
   const float c = p.scale_log2e;
+  if (D == 128 && wave == 0) {
+#pragma unroll
+    for (int n = 0; n < Piece::kLoads; ++n) sm.goff[n][lane] = plan.goff[n];
+  }
 
   wait_all_loads();
   __syncthreads();
 
   for (int it = it0; it < total; ++it) {
     const int buf = it & 1;
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
+    const int ln = lane_now();
     // keeps the entry window moving (entries of this step on)
     if (!DENSE) (void)list.get(FINE ? EPC * it : it >> cpb_sh, ln);
-    if (it + 1 < total) issue_chunk(it + 1, buf ^ 1, ln);
+    if (it + 1 < total) {
+      typename Piece::Plan pl;
+      if constexpr (D == 128) {
+#pragma unroll
+        for (int n = 0; n < Piece::kLoads; ++n) pl.goff[n] = sm.goff[n][ln];
+      } else {
+        pl = plan;
+      }
+      issue_chunk(pl, it + 1, buf ^ 1, ln);
+    }
 
     int q0 = 0;
     bool keep = true;
@@ -337,115 +390,190 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
 
     int stores = 0;  // dS stores of this step (wave-uniform)
     uint16_t* ds_step = STORE ? ds_wave + (int64_t)it * 8192 : nullptr;
-    if (wave_active && (FINE || (keep && q0 + CH - 1 >= kvw0))) {
-      const uint16_t* qs = sm.q[buf];
-      const uint16_t* gs = sm.g[buf];
-      const int l32 = ln & 31, half = ln >> 5;
-      const int trb = Tile::tr_base(ln);
-      const int key = key_of(l32);
-      // FINE: which pieces of the step attend keys of mine, from every lane's entry at once
-      int src = 0;
-      uint32_t on4 = 0;
-      if constexpr (FINE) {
+    // which of the step's 32-row halves hold something for my keys: qt0 .. qt1 - 1
+    int qt0 = 0, qt1 = 0, src = 0;
+    if constexpr (FINE) {
+      if (wave_active) {
+        // which pieces of the step attend keys of mine, from every lane's entry at once
         src = entries_at(it);
         uint64_t any = __ballot(FINE == 32 ? ((src >> wave) & 1) != 0 : ((src >> (2 * wave)) & 3) != 0);
         if (VARLEN) any &= __ballot((uint32_t)src <= last_ent);
-        on4 = (uint32_t)(any >> ((EPC * it) & 63));
+        const uint32_t on4 = (uint32_t)(any >> ((EPC * it) & 63));
+        qt0 = (on4 & (FINE == 32 ? 1 : 3)) ? 0 : 1;
+        qt1 = (on4 & (FINE == 32 ? 2 : 12)) ? 2 : 1;
       }
+    } else if (wave_active && keep) {
+      qt0 = q0 + 31 < kvw0 ? 1 : 0;  // (every query of the half lies before my keys)
+      qt1 = q0 + CH - 1 < kvw0 ? 0 : 2;
+      if (VARLEN) qt1 = q0 >= N ? 0 : q0 + 32 >= N ? min(qt1, 1) : qt1;  // ... or after the end of my sequence
+    }
+    qt0 = __builtin_amdgcn_readfirstlane(qt0);
+    qt1 = __builtin_amdgcn_readfirstlane(qt1);
+    if (qt0 < qt1) {
+      const uint32_t stage = lds_addr(sm.q[0]) + buf * (uint32_t)Tile::kBytes;
+      uint32_t row_a, tr_a;
+      {
+        const int ln = lane_now();
+        row_a = stage + (ln & 31) * RB + 16 * (ln >> 5) + qt0 * 32 * RB;
+        tr_a = stage + 2 * Tile::tr_base(ln) + qt0 * 32 * RB;
+        asm volatile("" : "+v"(row_a), "+v"(tr_a));
+      }
+      // VARLEN: `gone` where a row of piece u of the half, which begins at row r, lies past the sequence's end
+      auto drop_past_end = [&](auto gone, auto uc, f32x16& a, int r) S2_INLINE {
+        constexpr int u = decltype(uc)::value;
+        const int left = N - r - 4 * (lane_now() >> 5);
+        const float drop = constant_now<decltype(gone)::value>();
+        static_for<8>([&](auto ic) S2_INLINE {
+          constexpr int i = decltype(ic)::value;
+          a[8 * u + i] = keep_below<8 * (i >> 2) + (i & 3)>(a[8 * u + i], left, drop);
+        });
+      };
+      // where a half's statistics are (the lane's rows of them)
+      auto stats_at = [&](int qt) S2_INLINE {
+        uint32_t a = lds_addr(&sm.rs[0]) + buf * (uint32_t)sizeof(sm.rs[0]) + 128 * qt + 16 * (lane_now() >> 5);
+        asm volatile("" : "+v"(a));
+        return a;
+      };
+      bf16x8 fr[kRing];
+      f32x16 s, dp;  // S, then P in place; dP, then dS in place
+      // fragment f of a half, in the order the MFMAs use them; those after the last are the first of the next half
+      auto frag_load = [&](auto fc) S2_INLINE {
+        constexpr int f = decltype(fc)::value;
+        u32x4 x;
+        if constexpr (f < KK)
+          x = lds_read16(row_a, 32 * f);
+        else if constexpr (f < 2 * KK)
+          x = lds_read16(row_a, G_OFF + 32 * (f - KK));
+        else if constexpr (f < 3 * KK)
+          x = lds_read_tr(tr_a, G_OFF + 16 * ((f - 2 * KK) / DT) * RB + 64 * ((f - 2 * KK) % DT), RB);
+        else if constexpr (f < 4 * KK)
+          x = lds_read_tr(tr_a, 16 * ((f - 3 * KK) / DT) * RB + 64 * ((f - 3 * KK) % DT), RB);
+        else
+          x = lds_read16(row_a, 32 * (f - 4 * KK));
+        fr[f % kRing] = __builtin_bit_cast(bf16x8, x);
+      };
+      auto stats_load = [&](f32x16& x, int g, uint32_t addr, int off) S2_INLINE {
+        const f32x4 v4 = lds_read_f32x4(addr, off + 32 * g);
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt) {
-        // Causal mask, and (FINE) blocks my column does not keep: of the 16 query rows of piece u of this half
-        // chunk, row 8 i + 4 half + e is dropped when lim[u] > 8 i + e, a compare with a constant.
-        // Packed batch: it exists iff 8 i + e < left[u].
-        int lim[2], left[2];
+        for (int e = 0; e < 4; ++e) x[4 * g + e] = v4[e];
+      };
+      uint32_t st_a = stats_at(qt0);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) stats_load(s, g, st_a, 256);
+      static_for<kLead>([&](auto fc) S2_INLINE { frag_load(fc); });
+#pragma unroll
+      for (int g = 0; g < 4; ++g) stats_load(dp, g, st_a, 0);
+#pragma unroll 1
+      for (int qt = qt0; qt < qt1; ++qt) {
+        const int more = qt + 1 < qt1 ? 1 : 0;
+        // Of the 16 query rows of piece u of this half, row 8 i + 4 half + e is dropped when it lies before the lane's key or
+        // (FINE) my column does not keep the piece.
         const int qbase = q0 + 32 * qt;
+        bool masked, ragged = false;
+        int r0 = qbase, r1 = qbase + 16;
+        uint32_t e0 = ~0u, e1 = ~0u;
         if constexpr (FINE) {
-          if (((on4 >> (2 * qt / PPE)) & (FINE == 32 ? 1 : 3)) == 0) continue;  // nothing of it attends my keys
-          const uint32_t e0 = entry(src, EPC * it + (FINE == 32 ? qt : 2 * qt));
-          const int r0 = (int)(e0 >> 16) * FINE;
-          lim[0] = key - r0 - 4 * half;
-          lim[1] = lim[0] - 16;
-          left[0] = N - r0 - 4 * half;
-          left[1] = left[0] - 16;
+          e0 = entry(src, EPC * it + (FINE == 32 ? qt : 2 * qt));
+          r0 = (int)(e0 >> 16) * FINE;
+          r1 = r0 + 16;
           if constexpr (FINE == 16) {
-            const uint32_t e1 = entry(src, EPC * it + 2 * qt + 1);
-            const int r1 = (int)(e1 >> 16) * FINE, mine = 2 * wave + (l32 >> 4);
-            lim[0] = (e0 >> mine) & 1 ? lim[0] : 64;
-            lim[1] = (e1 >> mine) & 1 ? key - r1 - 4 * half : 64;
-            left[1] = N - r1 - 4 * half;
+            e1 = entry(src, EPC * it + 2 * qt + 1);
+            r1 = (int)(e1 >> 16) * FINE;
           }
+          masked = min(r0, r1) < (FINE == 16 ? max(kvw0, kvw1) + 15 : kvw0 + 31);
+          if (FINE == 16) masked = masked || (((e0 & e1) >> (2 * wave)) & 3) != 3;
         } else {
-          if (qbase + 31 < kvw0) continue;  // every query of this half-chunk lies before my keys
-          if (VARLEN && qbase >= N) continue;  // ... or after the end of my sequence
-          // away from the diagonal lim = -1 or less and nothing is dropped
-          // (the dense instantiation keeps the plain comparison: with this form the compiler spills there)
-          lim[0] = qbase < kvw0 + 31 ? key - qbase - 4 * half : -32;
-          lim[1] = lim[0] - 16;
-          left[0] = N - qbase - 4 * half;
-          left[1] = left[0] - 16;
+          masked = qbase < kvw0 + 31;
         }
-        f32x16 s = f32x16{}, dp = f32x16{};
-        if constexpr (D == 64) {
-          // all eight row fragments are requested before the first MFMA waits for one (left alone, the
-          // compiler requests and awaits them one at a time to save registers: 2 x 16 heads x 4096, 121.5 us
-          // against 107)
-          bf16x8 fq[D / 16], fg[D / 16];
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) fq[kk] = Tile::row_frag(qs, qt, kk, l32, half);
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) fg[kk] = Tile::row_frag(gs, qt, kk, l32, half);
-          S2_FENCE();
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) s = mfma32(fq[kk], kf[kk], s);
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) dp = mfma32(fg[kk], vf[kk], dp);
-        } else {
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) s = mfma32(Tile::row_frag(qs, qt, kk, l32, half), kf[kk], s);
-#pragma unroll
-          for (int kk = 0; kk < D / 16; ++kk) dp = mfma32(Tile::row_frag(gs, qt, kk, l32, half), vf[kk], dp);
-        }
-        const bool diag = qbase < kvw0 + 31;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int r0 = 32 * qt + 8 * g + 4 * half;
-          const f32x4 l4 = *reinterpret_cast<const f32x4*>(&sm.rs[buf].lse[r0]);
-          const f32x4 d4 = *reinterpret_cast<const f32x4*>(&sm.rs[buf].delta[r0]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int r = 4 * g + e;
-            float pr = fast_exp2(__builtin_fmaf(s[r], c, -l4[e]));
-            if (DENSE ? (diag && key > q0 + r0 + e) : FINE ? (lim[g >> 1] > 8 * (g & 1) + e) : (lim[0] > 8 * g + e)) pr = 0.f;
-            float ds = pr * (dp[r] - d4[e]);
-            // a row past the sequence's end: its statistics are not its own
-            if (VARLEN && (FINE ? 8 * (g & 1) + e >= left[g >> 1] : 8 * g + e >= left[0])) {
-              pr = 0.f;
-              ds = 0.f;
+        if (VARLEN) ragged = max(r0, r1) + 16 > N;
+        u32x4 pb[2], dsb[2];
+        S2_FENCE();
+        static_for<4 * KK>([&](auto nc) S2_INLINE {
+          constexpr int n = decltype(nc)::value;
+          if constexpr (n + kLead == 4 * KK) {
+            row_a += more * (32 * RB);
+            asm volatile("" : "+v"(row_a));
+          }
+          frag_load(std::integral_constant<int, n + kLead>{});
+          if constexpr (n < KK)
+            s = mfma32(fr[n % kRing], kf[n], s);
+          else if constexpr (n < 2 * KK)
+            dp = mfma32(fr[n % kRing], vf[n - KK], dp);
+          else if constexpr (n < 3 * KK)
+            acc_dv[(n - 2 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, pb[(n - 2 * KK) / DT]), acc_dv[(n - 2 * KK) % DT]);
+          else
+            acc_dk[(n - 3 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[(n - 3 * KK) / DT]), acc_dk[(n - 3 * KK) % DT]);
+          // P
+          constexpr int RS = 16 / KK, M0 = KK + 1, D0 = 2 * KK + 1;
+          if constexpr (n == M0) {
+            if (masked) {
+              const int ln = lane_now(), l32 = ln & 31, half = ln >> 5;
+              const int key = key_of(l32);
+              const float drop = constant_now<kNegInfBits>();
+              static_for<2>([&](auto uc) S2_INLINE {
+                constexpr int u = decltype(uc)::value;
+                int lim = key - (u ? r1 : r0) - 4 * half;
+                if constexpr (FINE == 16) lim = ((u ? e1 : e0) >> (2 * wave + (l32 >> 4))) & 1 ? lim : 64;
+                static_for<8>([&](auto ic) S2_INLINE {
+                  constexpr int i = decltype(ic)::value;
+                  s[8 * u + i] = keep_from<8 * (i >> 2) + (i & 3)>(s[8 * u + i], lim, drop);
+                });
+              });
             }
-            s[r] = pr;
-            dp[r] = ds;
+            if constexpr (VARLEN) {
+              if (ragged) {
+                drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 0>{}, s, r0);
+                drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 1>{}, s, r1);
+              }
+            }
           }
-        }
+          if constexpr (n >= M0 && n < M0 + KK) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const bf16x8 pb = pack8(s[8 * u + 0], s[8 * u + 1], s[8 * u + 2], s[8 * u + 3], s[8 * u + 4],
-                                  s[8 * u + 5], s[8 * u + 6], s[8 * u + 7]);
-          const bf16x8 dsb = pack8(dp[8 * u + 0], dp[8 * u + 1], dp[8 * u + 2], dp[8 * u + 3], dp[8 * u + 4],
-                                   dp[8 * u + 5], dp[8 * u + 6], dp[8 * u + 7]);
-          if constexpr (STORE) {
-            const uint32_t off = 16u * (2 * l32 + half) + 1024u * (2 * qt + u);
-            // non-temporal: written once here and read by a later launch, it should not push the Q / dO
-            // blocks this kernel re-reads out of L2
-            __builtin_nontemporal_store(__builtin_bit_cast(u32x4, dsb),
-                                        reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(ds_step) + off));
-            ++stores;
+            for (int r = RS * (n - M0); r < RS * (n - M0 + 1); ++r) s[r] *= c;
           }
+          if constexpr (n >= M0 + 1 && n < M0 + 1 + KK) {
 #pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt) {
-            acc_dv[dt] = mfma32(Tile::tr_frag(gs, dt, 2 * qt + u, trb), pb, acc_dv[dt]);
-            acc_dk[dt] = mfma32(Tile::tr_frag(qs, dt, 2 * qt + u, trb), dsb, acc_dk[dt]);
+            for (int r = RS * (n - M0 - 1); r < RS * (n - M0); ++r) s[r] = fast_exp2(s[r]);
           }
-        }
+          constexpr int PK0 = M0 + 1 + KK / 2 < 2 * KK - 1 ? M0 + 1 + KK / 2 : 2 * KK - 1;
+          constexpr int PK1 = M0 + 1 + KK < 2 * KK + DT - 1 ? M0 + 1 + KK : 2 * KK + DT - 1;
+          if constexpr (n == PK0 || n == PK1) {
+            constexpr int u = n == PK0 ? 0 : 1;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pb[u][i] = pack2(s[8 * u + 2 * i], s[8 * u + 2 * i + 1]);
+          }
+          // dS
+          if constexpr (n >= D0 && n < D0 + KK) {
+#pragma unroll
+            for (int r = RS * (n - D0); r < RS * (n - D0 + 1); ++r) dp[r] *= s[r];
+          }
+          constexpr int DK0 = D0 + KK / 2 < 3 * KK - 1 ? D0 + KK / 2 : 3 * KK - 1;
+          constexpr int DK1 = D0 + KK < 3 * KK + DT - 1 ? D0 + KK : 3 * KK + DT - 1;
+          if constexpr (n == DK0 || n == DK1) {
+            constexpr int u = n == DK0 ? 0 : 1;
+            if constexpr (VARLEN) {
+              if (ragged) drop_past_end(std::integral_constant<uint32_t, 0>{}, std::integral_constant<int, u>{}, dp, u ? r1 : r0);  // (their statistics are not their own)
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dsb[u][i] = pack2(dp[8 * u + 2 * i], dp[8 * u + 2 * i + 1]);
+            if constexpr (STORE) {
+              const int ln = lane_now();
+              const uint32_t off = 16u * (2 * (ln & 31) + (ln >> 5)) + 1024u * u;
+              // non-temporal: written once here and read by a later launch, it should not push the Q / dO
+              // blocks this kernel re-reads out of L2
+              __builtin_nontemporal_store(dsb[u], reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(ds_step + 1024 * qt) + off));
+            }
+          }
+          // the next half's statistics, where its contractions begin
+          if constexpr (n == 4 * KK - 5) st_a = stats_at(qt + more);
+          if constexpr (n >= 4 * KK - 4) {
+            stats_load(s, n - (4 * KK - 4), st_a, 256);
+            stats_load(dp, n - (4 * KK - 4), st_a, 0);
+          }
+          S2_FENCE();
+        });
+        if (STORE) stores += 2;
+        tr_a += 32 * RB;
       }
     }
 
@@ -464,7 +592,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     // all of them up, in the order of the parts, and go on with the result.
     constexpr int kTiles = 2 * (D / 32);               // accumulator tiles of a wavefront, dK and dV in turn
     constexpr int kWaveBytes = kTiles * 4 * 1024;      // [tile][register quad][lane][4 floats]
-    const uint32_t lane_off = 16 * lane;
+    const uint32_t lane_off = 16 * lane_now();
     unsigned char* const sums = reinterpret_cast<unsigned char*>(p.split_sums) + ((int64_t)bh * p.split_items + rank) * (4 * kWaveBytes) +
                                 wave * kWaveBytes;
     auto quad = [](const f32x16& a, int g) S2_INLINE { return f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]}; };
@@ -479,7 +607,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     wait_all_loads();  // my stores have arrived
     __syncthreads();
     int* const flag = reinterpret_cast<int*>(&sm.rs[0]);
-    if (tid == 0) {
+    if (wave == 0 && lane_off == 0) {
       int32_t* const count = p.split_count + (int64_t)bh * T + nth;
       *flag = __hip_atomic_fetch_add(count, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -512,6 +640,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   // touches 32 rows per instruction with 16 bytes each; read back 16 bytes per lane, row after row, an
   // instruction stores four whole rows.
   constexpr int RS = D + 8;  // staging row stride (elements)
+  const int ln_out = lane_now();
   static_assert(4 * 32 * (D + 8) <= 2 * Tile::kElems, "the staging rows fit two stages");
   uint16_t* sk_ = &sm.q[0][0] + wave * 32 * RS;
   uint16_t* sv_ = &sm.g[0][0] + wave * 32 * RS;
@@ -525,15 +654,15 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
         wk[e] = (__bf16)(acc_dk[dt][4 * g + e] * p.scale);
         wv[e] = (__bf16)(acc_dv[dt][4 * g + e]);
       }
-      *reinterpret_cast<bf16x4*>(sk_ + l32 * RS + 32 * dt + 8 * g + 4 * half) = wk;
-      *reinterpret_cast<bf16x4*>(sv_ + l32 * RS + 32 * dt + 8 * g + 4 * half) = wv;
+      *reinterpret_cast<bf16x4*>(sk_ + (ln_out & 31) * RS + 32 * dt + 8 * g + 4 * (ln_out >> 5)) = wk;
+      *reinterpret_cast<bf16x4*>(sv_ + (ln_out & 31) * RS + 32 * dt + 8 * g + 4 * (ln_out >> 5)) = wv;
     }
   uint16_t* dk_base = p.dk + kv_off;
   uint16_t* dv_base = p.dv + kv_off;
   constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
 #pragma unroll
   for (int i = 0; i < 32 / RPI; ++i) {
-    const int r = RPI * i + lane / PPR, piece = lane % PPR;
+    const int r = RPI * i + ln_out / PPR, piece = ln_out % PPR;
     const u32x4 xk = *reinterpret_cast<const u32x4*>(sk_ + r * RS + 8 * piece);
     const u32x4 xv = *reinterpret_cast<const u32x4*>(sv_ + r * RS + 8 * piece);
     const int kr = key_of(r);
@@ -608,7 +737,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
       return e;
     }
   }
-  // The dQ kernel computes delta itself and leaves it (and LSE in base-2 units) in the workspace,
+  // The dQ kernel computes delta itself and leaves the row statistics in the workspace,
   // so it runs first and the stand-alone delta kernel only when dQ is not part of the call
   // (a packed batch is always a whole backward).
   if (stages & kBwdDq)

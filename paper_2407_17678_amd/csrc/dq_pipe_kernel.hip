@@ -2,7 +2,7 @@
 // Same tiles, lists, staging and orientation as the forward (fwd_pipe_kernel.hip) - a workgroup owns 128
 // query rows, a wavefront 32 of them, and walks the 64-key chunks of the KV blocks its mask rows keep,
 // recomputing P and forming dS = P * (dP - delta), dQ += scale * dS K; it also computes
-// delta = rowsum(dO * O) and leaves it, with LSE in base-2 units, in the workspace for the dK/dV
+// delta = rowsum(dO * O) and leaves the row statistics in the workspace for the dK/dV
 // kernel - with a hand-scheduled inner loop:
 //
 //   * it runs in half chunks of 32 keys, skewed by one half: S and dP of the next half are computed
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
 
   // Q^T and dO^T fragments (B operands), lane = query; delta = rowsum(dO * O) of my query from the
   // dO fragments (my half of the row's features, then the two halves added), written out with LSE
-  // in base-2 units for the dK/dV kernel, which runs after this one.  A lane without a row of its own
+  // as the dK/dV kernel, which runs after this one, wants them.  A lane without a row of its own
   // reads the last row; nothing of it is stored.
   bf16x8 qf[KK], gf[KK];
   float part = 0.f;
@@ -197,8 +197,8 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
                                   : ((int64_t)b * p.heads + h) * N + my_row;
   const float lse_l = p.lse[stat_row] * kLog2e;
   if (half == 0 && qw0 + l32 < N) {
-    p.delta[stat_row] = delta_l;
-    p.lse2[stat_row] = lse_l;
+    p.neg_delta[stat_row] = -delta_l;
+    p.neg_lse[stat_row] = p.lse[stat_row] * p.neg_inv_scale;
   }
 
   f32x16 acc[DT];

@@ -26,8 +26,10 @@ struct AttnParams {
   uint16_t* dq;
   uint16_t* dk;
   uint16_t* dv;
-  float* delta;  // workspace: rowsum(dO * O), [batch, heads, seqlen]
-  float* lse2;   // workspace: lse * log2(e), [batch, heads, seqlen]
+  // Workspace, [batch, heads, seqlen] each: what the dK/dV kernel's accumulators begin with, so that the score contraction ends
+  // at S - lse / scale (P = exp2 of it times scale * log2(e)) and the other at dP - delta
+  float* neg_delta;  // -rowsum(dO * O)
+  float* neg_lse;    // -lse / scale
   int batch, heads, seqlen, head_dim;
   // q, o, lse hold q_rows rows, local row r being sequence position q_row0 + r (the whole sequence,
   // as in every backward of a fixed length: q_row0 = 0, q_rows = seqlen)
@@ -41,6 +43,7 @@ struct AttnParams {
   int64_t kv_sb, kv_sh, kv_st;
   float scale;        // softmax scale
   float scale_log2e;  // scale * log2(e)
+  float neg_inv_scale;  // -1 / scale (backward)
   int block_size;     // S (sparse path); 64 on the dense path
   DevTiles q_tiles;   // row tiles of the forward and dQ kernels -> KV blocks
   DevTiles kv_tiles;  // column tiles -> Q blocks
@@ -99,7 +102,7 @@ hipError_t launch_fwd_gather(const AttnParams& p, hipStream_t stream);
 // `stages` selects which of the three backward launches run: 1 = delta, 2 = dK/dV, 4 = dQ.
 constexpr int kBwdDelta = 1, kBwdDkDv = 2, kBwdDq = 4, kBwdAll = 7;
 hipError_t launch_bwd(const AttnParams& p, bool dense, int stages, hipStream_t stream);
-// The dQ launch that recomputes S and dP (it also leaves delta and base-2 LSE in the workspace).
+// The dQ launch that recomputes S and dP (it also leaves the row statistics in the workspace).
 hipError_t launch_dq(const AttnParams& p, bool dense, hipStream_t stream);
 // The dQ launch of the backward that keeps dS: dQ = scale * dS K over the stored units.
 hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream);
