@@ -23,12 +23,13 @@
 //
 // The dK/dV loop is written out one MFMA per slot (see sched_util.h): for 32 query rows S, dP, dV and dK one after the
 // other, the exponentials under dP and the first half of dV, dS = P * dP under the second half of dV and the first of dK,
-// each LDS fragment requested three MFMAs ahead of its use through a ring that goes on from one half step to the next.  Left to the compiler
+// each LDS fragment requested three MFMAs ahead of its use through a ring that goes on from one half step to the next,
+// across the barrier too: it lies before the last three MFMAs of a step.  Left to the compiler
 // every MFMA waited for the read issued right before it, since at 192 registers of accumulators and K / V fragments it keeps no second
 // fragment.  Room for the ring comes from what no longer has registers: the row statistics are read straight into the accumulators (S begins at
 // -lse / scale, dP at -delta), the lane offsets of the direct loads lie in LDS (head_dim 128), and what derives from the lane number is
-// formed where it is used.  dK/dV launch, before and now: 1 x 32 heads x 32768 x 128 1.980 -> 1.855 ms (2.262 -> 2.172 where it
-// keeps dS), dense 32 x 8192 x 128 0.98 -> 0.89 ms, 4 x 32 x 8192 x 64 0.639 -> 0.617 ms.
+// formed where it is used.  dK/dV launch, before, with the slots, and with the ring going across the barrier: 1 x 32 heads x 32768 x 128
+// 1.980, 1.872, 1.820 ms (2.262, 2.195, 2.157 where it keeps dS), 4 x 32 x 8192 x 64 0.639, 0.625, 0.603 ms.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -166,6 +167,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   constexpr int G_OFF = 2 * Tile::kBytes;                     // dO stages lie after the Q stages
   constexpr int kLead = 3, kRing = 4;
   static_assert((4 * KK) % kRing == 0, "the ring goes on from half to half");
+  constexpr int kTr = 2 * KK - kLead;                         // the slot that requests the first transposed fragment
   static_assert(!(DENSE && (FINE || VARLEN)) && !(STORE && (DENSE || FINE || VARLEN)), "forms that exist");
   static_assert(FINE == 0 || FINE == 16 || FINE == 32, "blocks that are gathered");
   constexpr int PPE = FINE == 32 ? 2 : 1, EPC = 4 / PPE;  // FINE: 16-row pieces of a list entry, entries of a step
@@ -282,8 +284,10 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   // what is derived from it is recomputed each step (a few integer operations) rather than kept in
   // registers across the loop: this kernel has no registers to spare, and a spilled constant costs
   // a wait for all outstanding loads when it is fetched back.
+  const int wave_of = wave;
   auto issue_chunk = [&](const typename Piece::Plan& plan, int j, int buf, int ln) S2_INLINE {
     int q0 = 0, src = 0, row;
+    const int wave = __builtin_amdgcn_readfirstlane(wave_of);  // (into a scalar register again: the compiler may hold it in a vector one)
     if constexpr (FINE) {
       src = entries_at(j);
       row = (int)(entry(src, EPC * j + wave / PPE) >> 16) * FINE + 16 * (wave % PPE);
@@ -365,11 +369,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     for (int n = 0; n < Piece::kLoads; ++n) sm.goff[n][lane] = plan.goff[n];
   }
 
-  wait_all_loads();
-  __syncthreads();
-
-  for (int it = it0; it < total; ++it) {
-    const int buf = it & 1;
+  // The walk is one sequence of half steps of 32 query rows: half qt (up to qt1 - 1) of step it, whose first row is q0 (not FINE) or
+  // whose entries are in src.
+  int it = __builtin_amdgcn_readfirstlane(it0) - 1, qt = 0, qt1 = 0, q0 = 0, src = 0, stores = 0;  // stores: dS stores since the last direct loads
+  // opens step it: requests the chunk of the step after it into the other stage, and finds the halves that hold something for my keys
+  auto open_step = [&]() S2_INLINE {
     const int ln = lane_now();
     // keeps the entry window moving (entries of this step on)
     if (!DENSE) (void)list.get(FINE ? EPC * it : it >> cpb_sh, ln);
@@ -381,210 +385,215 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
       } else {
         pl = plan;
       }
-      issue_chunk(pl, it + 1, buf ^ 1, ln);
+      issue_chunk(pl, it + 1, (it + 1) & 1, ln);
     }
-
-    int q0 = 0;
-    bool keep = true;
-    if constexpr (!FINE) chunk_at(it, q0, keep);
-
-    int stores = 0;  // dS stores of this step (wave-uniform)
-    uint16_t* ds_step = STORE ? ds_wave + (int64_t)it * 8192 : nullptr;
-    // which of the step's 32-row halves hold something for my keys: qt0 .. qt1 - 1
-    int qt0 = 0, qt1 = 0, src = 0;
+    stores = 0;
+    int lo = 0, hi = 0;
     if constexpr (FINE) {
-      if (wave_active) {
-        // which pieces of the step attend keys of mine, from every lane's entry at once
-        src = entries_at(it);
-        uint64_t any = __ballot(FINE == 32 ? ((src >> wave) & 1) != 0 : ((src >> (2 * wave)) & 3) != 0);
-        if (VARLEN) any &= __ballot((uint32_t)src <= last_ent);
-        const uint32_t on4 = (uint32_t)(any >> ((EPC * it) & 63));
-        qt0 = (on4 & (FINE == 32 ? 1 : 3)) ? 0 : 1;
-        qt1 = (on4 & (FINE == 32 ? 2 : 12)) ? 2 : 1;
-      }
-    } else if (wave_active && keep) {
-      qt0 = q0 + 31 < kvw0 ? 1 : 0;  // (every query of the half lies before my keys)
-      qt1 = q0 + CH - 1 < kvw0 ? 0 : 2;
-      if (VARLEN) qt1 = q0 >= N ? 0 : q0 + 32 >= N ? min(qt1, 1) : qt1;  // ... or after the end of my sequence
+      // which pieces of the step attend keys of mine, from every lane's entry at once
+      src = entries_at(it);
+      uint64_t any = __ballot(FINE == 32 ? ((src >> wave) & 1) != 0 : ((src >> (2 * wave)) & 3) != 0);
+      if (VARLEN) any &= __ballot((uint32_t)src <= last_ent);
+      const uint32_t on4 = (uint32_t)(any >> ((EPC * it) & 63));
+      lo = (on4 & (FINE == 32 ? 1 : 3)) ? 0 : 1;
+      hi = !wave_active ? 0 : (on4 & (FINE == 32 ? 2 : 12)) ? 2 : 1;
+    } else {
+      bool keep;
+      chunk_at(it, q0, keep);
+      lo = q0 + 31 < kvw0 ? 1 : 0;  // (every query of the half lies before my keys)
+      hi = !wave_active || !keep || q0 + CH - 1 < kvw0 ? 0 : 2;
+      if (VARLEN) hi = q0 >= N ? 0 : q0 + 32 >= N ? min(hi, 1) : hi;  // ... or after the end of my sequence
     }
-    qt0 = __builtin_amdgcn_readfirstlane(qt0);
-    qt1 = __builtin_amdgcn_readfirstlane(qt1);
-    if (qt0 < qt1) {
-      const uint32_t stage = lds_addr(sm.q[0]) + buf * (uint32_t)Tile::kBytes;
-      uint32_t row_a, tr_a;
-      {
-        const int ln = lane_now();
-        row_a = stage + (ln & 31) * RB + 16 * (ln >> 5) + qt0 * 32 * RB;
-        tr_a = stage + 2 * Tile::tr_base(ln) + qt0 * 32 * RB;
-        asm volatile("" : "+v"(row_a), "+v"(tr_a));
-      }
-      // VARLEN: `gone` where a row of piece u of the half, which begins at row r, lies past the sequence's end
-      auto drop_past_end = [&](auto gone, auto uc, f32x16& a, int r) S2_INLINE {
-        constexpr int u = decltype(uc)::value;
-        const int left = N - r - 4 * (lane_now() >> 5);
-        const float drop = constant_now<decltype(gone)::value>();
-        static_for<8>([&](auto ic) S2_INLINE {
-          constexpr int i = decltype(ic)::value;
-          a[8 * u + i] = keep_below<8 * (i >> 2) + (i & 3)>(a[8 * u + i], left, drop);
-        });
-      };
-      // where a half's statistics are (the lane's rows of them)
-      auto stats_at = [&](int qt) S2_INLINE {
-        uint32_t a = lds_addr(&sm.rs[0]) + buf * (uint32_t)sizeof(sm.rs[0]) + 128 * qt + 16 * (lane_now() >> 5);
-        asm volatile("" : "+v"(a));
-        return a;
-      };
-      bf16x8 fr[kRing];
-      f32x16 s, dp;  // S, then P in place; dP, then dS in place
-      // fragment f of a half, in the order the MFMAs use them; those after the last are the first of the next half
-      auto frag_load = [&](auto fc) S2_INLINE {
-        constexpr int f = decltype(fc)::value;
-        u32x4 x;
-        if constexpr (f < KK)
-          x = lds_read16(row_a, 32 * f);
-        else if constexpr (f < 2 * KK)
-          x = lds_read16(row_a, G_OFF + 32 * (f - KK));
-        else if constexpr (f < 3 * KK)
-          x = lds_read_tr(tr_a, G_OFF + 16 * ((f - 2 * KK) / DT) * RB + 64 * ((f - 2 * KK) % DT), RB);
-        else if constexpr (f < 4 * KK)
-          x = lds_read_tr(tr_a, 16 * ((f - 3 * KK) / DT) * RB + 64 * ((f - 3 * KK) % DT), RB);
-        else
-          x = lds_read16(row_a, 32 * (f - 4 * KK));
-        fr[f % kRing] = __builtin_bit_cast(bf16x8, x);
-      };
-      auto stats_load = [&](f32x16& x, int g, uint32_t addr, int off) S2_INLINE {
-        const f32x4 v4 = lds_read_f32x4(addr, off + 32 * g);
+    qt = __builtin_amdgcn_readfirstlane(lo);
+    qt1 = __builtin_amdgcn_readfirstlane(hi);
+  };
+  // Goes on to the next half (false: there is none), through the barrier where that is in another step: by then the next chunk has
+  // landed and every wavefront has read what it needs of this one.  Exactly one barrier a step, whatever I have to do in it.
+  auto next_half = [&]() S2_INLINE {
+    if (++qt < qt1) return true;
+    do {
+      // (this step's dS stores, issued after its loads, may stay in flight)
+      if (STORE && stores == 4)
+        wait_loads_but<4>();
+      else if (STORE && stores == 2)
+        wait_loads_but<2>();
+      else
+        wait_loads_but<0>();
+      wait_lds();
+      __syncthreads();
+      it = __builtin_amdgcn_readfirstlane(it + 1);
+      if (it >= total) return false;
+      open_step();
+    } while (qt >= qt1);
+    return true;
+  };
+  wait_all_loads();
+  bool more = next_half();  // (after the last half the loop still requests fragments, from inside the stages, that nothing uses)
+  if (more) {
+    uint32_t row_a, tr_a, st_a;
+    // where the lane finds its rows of the half's tiles and statistics
+    auto aim_rows = [&]() S2_INLINE {
+      const int ln = lane_now(), buf = it & 1;
+      row_a = lds_addr(sm.q[0]) + buf * (uint32_t)Tile::kBytes + qt * 32 * RB + (ln & 31) * RB + 16 * (ln >> 5);
+      st_a = lds_addr(&sm.rs[0]) + buf * (uint32_t)sizeof(sm.rs[0]) + 128 * qt + 16 * (ln >> 5);
+      asm volatile("" : "+v"(row_a), "+v"(st_a));
+    };
+    auto aim_tr = [&]() S2_INLINE {
+      tr_a = lds_addr(sm.q[0]) + (it & 1) * (uint32_t)Tile::kBytes + qt * 32 * RB + 2 * Tile::tr_base(lane_now());
+      asm volatile("" : "+v"(tr_a));
+    };
+    // VARLEN: `gone` where a row of piece u of the half, which begins at row r, lies past the sequence's end
+    auto drop_past_end = [&](auto gone, auto uc, f32x16& a, int r) S2_INLINE {
+      constexpr int u = decltype(uc)::value;
+      const int left = N - r - 4 * (lane_now() >> 5);
+      const float drop = constant_now<decltype(gone)::value>();
+      static_for<8>([&](auto ic) S2_INLINE {
+        constexpr int i = decltype(ic)::value;
+        a[8 * u + i] = keep_below<8 * (i >> 2) + (i & 3)>(a[8 * u + i], left, drop);
+      });
+    };
+    bf16x8 fr[kRing];
+    f32x16 s, dp;  // S, then P in place; dP, then dS in place
+    // fragment f of a half, in the order the MFMAs use them; those after the last are the first of the next half
+    auto frag_load = [&](auto fc) S2_INLINE {
+      constexpr int f = decltype(fc)::value;
+      u32x4 x;
+      if constexpr (f < KK)
+        x = lds_read16(row_a, 32 * f);
+      else if constexpr (f < 2 * KK)
+        x = lds_read16(row_a, G_OFF + 32 * (f - KK));
+      else if constexpr (f < 3 * KK)
+        x = lds_read_tr(tr_a, G_OFF + 16 * ((f - 2 * KK) / DT) * RB + 64 * ((f - 2 * KK) % DT), RB);
+      else if constexpr (f < 4 * KK)
+        x = lds_read_tr(tr_a, 16 * ((f - 3 * KK) / DT) * RB + 64 * ((f - 3 * KK) % DT), RB);
+      else
+        x = lds_read16(row_a, 32 * (f - 4 * KK));
+      fr[f % kRing] = __builtin_bit_cast(bf16x8, x);
+    };
+    auto stats_load = [&](f32x16& x, int g, uint32_t addr, int off) S2_INLINE {
+      const f32x4 v4 = lds_read_f32x4(addr, off + 32 * g);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * g + e] = v4[e];
-      };
-      uint32_t st_a = stats_at(qt0);
+      for (int e = 0; e < 4; ++e) x[4 * g + e] = v4[e];
+    };
+    auto stats_all = [&](int g) S2_INLINE {
+      stats_load(s, g, st_a, 256);
+      stats_load(dp, g, st_a, 0);
+    };
+    aim_rows();
 #pragma unroll
-      for (int g = 0; g < 4; ++g) stats_load(s, g, st_a, 256);
-      static_for<kLead>([&](auto fc) S2_INLINE { frag_load(fc); });
+    for (int g = 0; g < 4; ++g) stats_load(s, g, st_a, 256);
+    static_for<kLead>([&](auto fc) S2_INLINE { frag_load(fc); });
 #pragma unroll
-      for (int g = 0; g < 4; ++g) stats_load(dp, g, st_a, 0);
-#pragma unroll 1
-      for (int qt = qt0; qt < qt1; ++qt) {
-        const int more = qt + 1 < qt1 ? 1 : 0;
-        // Of the 16 query rows of piece u of this half, row 8 i + 4 half + e is dropped when it lies before the lane's key or
-        // (FINE) my column does not keep the piece.
-        const int qbase = q0 + 32 * qt;
-        bool masked, ragged = false;
-        int r0 = qbase, r1 = qbase + 16;
-        uint32_t e0 = ~0u, e1 = ~0u;
-        if constexpr (FINE) {
-          e0 = entry(src, EPC * it + (FINE == 32 ? qt : 2 * qt));
-          r0 = (int)(e0 >> 16) * FINE;
-          r1 = r0 + 16;
-          if constexpr (FINE == 16) {
-            e1 = entry(src, EPC * it + 2 * qt + 1);
-            r1 = (int)(e1 >> 16) * FINE;
-          }
-          masked = min(r0, r1) < (FINE == 16 ? max(kvw0, kvw1) + 15 : kvw0 + 31);
-          if (FINE == 16) masked = masked || (((e0 & e1) >> (2 * wave)) & 3) != 3;
-        } else {
-          masked = qbase < kvw0 + 31;
+    for (int g = 0; g < 4; ++g) stats_load(dp, g, st_a, 0);
+    do {
+      // Of the 16 query rows of piece u of this half, row 8 i + 4 half + e is dropped when it lies before the lane's key or
+      // (FINE) my column does not keep the piece.
+      const int qbase = q0 + 32 * qt;
+      bool masked, ragged = false;
+      int r0 = qbase, r1 = qbase + 16;
+      uint32_t e0 = ~0u, e1 = ~0u;
+      if constexpr (FINE) {
+        e0 = entry(src, EPC * it + (FINE == 32 ? qt : 2 * qt));
+        r0 = (int)(e0 >> 16) * FINE;
+        r1 = r0 + 16;
+        if constexpr (FINE == 16) {
+          e1 = entry(src, EPC * it + 2 * qt + 1);
+          r1 = (int)(e1 >> 16) * FINE;
         }
-        if (VARLEN) ragged = max(r0, r1) + 16 > N;
-        u32x4 pb[2], dsb[2];
-        S2_FENCE();
-        static_for<4 * KK>([&](auto nc) S2_INLINE {
-          constexpr int n = decltype(nc)::value;
-          if constexpr (n + kLead == 4 * KK) {
-            row_a += more * (32 * RB);
-            asm volatile("" : "+v"(row_a));
-          }
-          frag_load(std::integral_constant<int, n + kLead>{});
-          if constexpr (n < KK)
-            s = mfma32(fr[n % kRing], kf[n], s);
-          else if constexpr (n < 2 * KK)
-            dp = mfma32(fr[n % kRing], vf[n - KK], dp);
-          else if constexpr (n < 3 * KK)
-            acc_dv[(n - 2 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, pb[(n - 2 * KK) / DT]), acc_dv[(n - 2 * KK) % DT]);
-          else
-            acc_dk[(n - 3 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[(n - 3 * KK) / DT]), acc_dk[(n - 3 * KK) % DT]);
-          // P
-          constexpr int RS = 16 / KK, M0 = KK + 1, D0 = 2 * KK + 1;
-          if constexpr (n == M0) {
-            if (masked) {
-              const int ln = lane_now(), l32 = ln & 31, half = ln >> 5;
-              const int key = key_of(l32);
-              const float drop = constant_now<kNegInfBits>();
-              static_for<2>([&](auto uc) S2_INLINE {
-                constexpr int u = decltype(uc)::value;
-                int lim = key - (u ? r1 : r0) - 4 * half;
-                if constexpr (FINE == 16) lim = ((u ? e1 : e0) >> (2 * wave + (l32 >> 4))) & 1 ? lim : 64;
-                static_for<8>([&](auto ic) S2_INLINE {
-                  constexpr int i = decltype(ic)::value;
-                  s[8 * u + i] = keep_from<8 * (i >> 2) + (i & 3)>(s[8 * u + i], lim, drop);
-                });
-              });
-            }
-            if constexpr (VARLEN) {
-              if (ragged) {
-                drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 0>{}, s, r0);
-                drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 1>{}, s, r1);
-              }
-            }
-          }
-          if constexpr (n >= M0 && n < M0 + KK) {
-#pragma unroll
-            for (int r = RS * (n - M0); r < RS * (n - M0 + 1); ++r) s[r] *= c;
-          }
-          if constexpr (n >= M0 + 1 && n < M0 + 1 + KK) {
-#pragma unroll
-            for (int r = RS * (n - M0 - 1); r < RS * (n - M0); ++r) s[r] = fast_exp2(s[r]);
-          }
-          constexpr int PK0 = M0 + 1 + KK / 2 < 2 * KK - 1 ? M0 + 1 + KK / 2 : 2 * KK - 1;
-          constexpr int PK1 = M0 + 1 + KK < 2 * KK + DT - 1 ? M0 + 1 + KK : 2 * KK + DT - 1;
-          if constexpr (n == PK0 || n == PK1) {
-            constexpr int u = n == PK0 ? 0 : 1;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pb[u][i] = pack2(s[8 * u + 2 * i], s[8 * u + 2 * i + 1]);
-          }
-          // dS
-          if constexpr (n >= D0 && n < D0 + KK) {
-#pragma unroll
-            for (int r = RS * (n - D0); r < RS * (n - D0 + 1); ++r) dp[r] *= s[r];
-          }
-          constexpr int DK0 = D0 + KK / 2 < 3 * KK - 1 ? D0 + KK / 2 : 3 * KK - 1;
-          constexpr int DK1 = D0 + KK < 3 * KK + DT - 1 ? D0 + KK : 3 * KK + DT - 1;
-          if constexpr (n == DK0 || n == DK1) {
-            constexpr int u = n == DK0 ? 0 : 1;
-            if constexpr (VARLEN) {
-              if (ragged) drop_past_end(std::integral_constant<uint32_t, 0>{}, std::integral_constant<int, u>{}, dp, u ? r1 : r0);  // (their statistics are not their own)
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) dsb[u][i] = pack2(dp[8 * u + 2 * i], dp[8 * u + 2 * i + 1]);
-            if constexpr (STORE) {
-              const int ln = lane_now();
-              const uint32_t off = 16u * (2 * (ln & 31) + (ln >> 5)) + 1024u * u;
-              // non-temporal: written once here and read by a later launch, it should not push the Q / dO
-              // blocks this kernel re-reads out of L2
-              __builtin_nontemporal_store(dsb[u], reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(ds_step + 1024 * qt) + off));
-            }
-          }
-          // the next half's statistics, where its contractions begin
-          if constexpr (n == 4 * KK - 5) st_a = stats_at(qt + more);
-          if constexpr (n >= 4 * KK - 4) {
-            stats_load(s, n - (4 * KK - 4), st_a, 256);
-            stats_load(dp, n - (4 * KK - 4), st_a, 0);
-          }
-          S2_FENCE();
-        });
-        if (STORE) stores += 2;
-        tr_a += 32 * RB;
+        masked = min(r0, r1) < (FINE == 16 ? max(kvw0, kvw1) + 15 : kvw0 + 31);
+        if (FINE == 16) masked = masked || (((e0 & e1) >> (2 * wave)) & 3) != 3;
+      } else {
+        masked = qbase < kvw0 + 31;
       }
-    }
-
-    // the next chunk has landed; this step's dS stores, issued after its loads, may stay in flight
-    if (STORE && stores == 4)
-      wait_loads_but<4>();
-    else if (STORE && stores == 2)
-      wait_loads_but<2>();
-    else
-      wait_all_loads();
-    __syncthreads();
+      if (VARLEN) ragged = max(r0, r1) + 16 > N;
+      u32x4 pb[2], dsb[2];
+      S2_FENCE();
+      static_for<4 * KK>([&](auto nc) S2_INLINE {
+        constexpr int n = decltype(nc)::value;
+        if constexpr (n == kTr) aim_tr();
+        // every fragment of this half is requested: on to the next one
+        if constexpr (n + kLead == 4 * KK) {
+          more = next_half();
+          aim_rows();
+        }
+        frag_load(std::integral_constant<int, n + kLead>{});
+        if constexpr (n < KK)
+          s = mfma32(fr[n % kRing], kf[n], s);
+        else if constexpr (n < 2 * KK)
+          dp = mfma32(fr[n % kRing], vf[n - KK], dp);
+        else if constexpr (n < 3 * KK)
+          acc_dv[(n - 2 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, pb[(n - 2 * KK) / DT]), acc_dv[(n - 2 * KK) % DT]);
+        else
+          acc_dk[(n - 3 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[(n - 3 * KK) / DT]), acc_dk[(n - 3 * KK) % DT]);
+        // P
+        constexpr int RS = 16 / KK, M0 = KK + 1, D0 = 2 * KK + 1;
+        if constexpr (n == M0) {
+          if (masked) {
+            const int ln = lane_now(), l32 = ln & 31, half = ln >> 5;
+            const int key = key_of(l32);
+            const float drop = constant_now<kNegInfBits>();
+            static_for<2>([&](auto uc) S2_INLINE {
+              constexpr int u = decltype(uc)::value;
+              int lim = key - (u ? r1 : r0) - 4 * half;
+              if constexpr (FINE == 16) lim = ((u ? e1 : e0) >> (2 * wave + (l32 >> 4))) & 1 ? lim : 64;
+              static_for<8>([&](auto ic) S2_INLINE {
+                constexpr int i = decltype(ic)::value;
+                s[8 * u + i] = keep_from<8 * (i >> 2) + (i & 3)>(s[8 * u + i], lim, drop);
+              });
+            });
+          }
+          if constexpr (VARLEN) {
+            if (ragged) {
+              drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 0>{}, s, r0);
+              drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 1>{}, s, r1);
+            }
+          }
+        }
+        if constexpr (n >= M0 && n < M0 + KK) {
+#pragma unroll
+          for (int r = RS * (n - M0); r < RS * (n - M0 + 1); ++r) s[r] *= c;
+        }
+        if constexpr (n >= M0 + 1 && n < M0 + 1 + KK) {
+#pragma unroll
+          for (int r = RS * (n - M0 - 1); r < RS * (n - M0); ++r) s[r] = fast_exp2(s[r]);
+          asm volatile("" : "+v"(s));
+        }
+        constexpr int PK0 = M0 + 1 + KK / 2 < 2 * KK - 1 ? M0 + 1 + KK / 2 : 2 * KK - 1;
+        constexpr int PK1 = M0 + 1 + KK < 2 * KK + DT - 1 ? M0 + 1 + KK : 2 * KK + DT - 1;
+        if constexpr (n == PK0 || n == PK1) {
+          constexpr int u = n == PK0 ? 0 : 1;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pb[u][i] = pack2(s[8 * u + 2 * i], s[8 * u + 2 * i + 1]);
+        }
+        // dS
+        if constexpr (n >= D0 && n < D0 + KK) {
+#pragma unroll
+          for (int r = RS * (n - D0); r < RS * (n - D0 + 1); ++r) dp[r] *= s[r];
+        }
+        constexpr int DK0 = D0 + KK / 2 < 3 * KK - 1 ? D0 + KK / 2 : 3 * KK - 1;
+        constexpr int DK1 = D0 + KK < 3 * KK + DT - 1 ? D0 + KK : 3 * KK + DT - 1;
+        if constexpr (n == DK0 || n == DK1) {
+          constexpr int u = n == DK0 ? 0 : 1;
+          if constexpr (VARLEN) {
+            if (ragged) drop_past_end(std::integral_constant<uint32_t, 0>{}, std::integral_constant<int, u>{}, dp, u ? r1 : r0);  // (their statistics are not their own)
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) dsb[u][i] = pack2(dp[8 * u + 2 * i], dp[8 * u + 2 * i + 1]);
+          if constexpr (STORE) {
+            const int ln = lane_now();
+            const uint32_t off = 16u * (2 * (ln & 31) + (ln >> 5)) + 1024u * u;
+            // non-temporal: written once here and read by a later launch, it should not push the Q / dO
+            // blocks this kernel re-reads out of L2
+            __builtin_nontemporal_store(dsb[u], reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(ds_wave + (int64_t)it * 8192 + 1024 * qt) + off));
+            ++stores;
+          }
+        }
+        // the next half's statistics, where its contractions begin
+        if constexpr (n >= 4 * KK - 3) stats_all(n - (4 * KK - 3));
+        if constexpr (n == 4 * KK - 1) stats_all(3);
+        S2_FENCE();
+      });
+    } while (more);
   }
 
   if (kSplits && parts > 1) {

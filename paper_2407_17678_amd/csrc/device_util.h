@@ -247,6 +247,13 @@ __device__ __forceinline__ void wait_loads_but() {
   asm volatile("" ::: "memory");
 }
 
+// What this wavefront has asked of the LDS has arrived.
+__device__ __forceinline__ void wait_lds() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));  // lgkmcnt(0); vmcnt and expcnt at their maxima: no wait
+  asm volatile("" ::: "memory");
+}
+
 // Writes 32 rows of results, accumulated as acc[feature tile] with a lane's row in lane % 32, times mul, as
 // bf16.  They go out through LDS (`stage`: 32 * (D + 8) elements that are this wavefront's own, so no barrier): a lane
 // holds its row's features four at a time, and storing them from there would touch 32 rows per instruction
