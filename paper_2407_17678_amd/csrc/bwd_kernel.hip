@@ -21,15 +21,20 @@
 // direct global -> LDS loads (double buffered) and read in both operand forms from the one
 // row-major tile: row fragments (k = feature) and LDS transpose reads (k = token).
 //
-// The dK/dV loop is written out one MFMA per slot (see sched_util.h): for 32 query rows S, dP, dV and dK one after the
-// other, the exponentials under dP and the first half of dV, dS = P * dP under the second half of dV and the first of dK,
-// each LDS fragment requested three MFMAs ahead of its use through a ring that goes on from one half step to the next,
-// across the barrier too: it lies before the last three MFMAs of a step.  Left to the compiler
+// The dK/dV loop is written out fragment by fragment, one slot and two MFMAs each (see sched_util.h): for 32 query rows S, dP, dV and dK one
+// after the other, the exponentials under dP, dS = P * dP under dV, each LDS fragment requested three slots ahead of its use through a ring
+// that goes on from one half step to the next, across the barrier too: it lies before the last three slots of a step.  Left to the compiler
 // every MFMA waited for the read issued right before it, since at 192 registers of accumulators and K / V fragments it keeps no second
 // fragment.  Room for the ring comes from what no longer has registers: the row statistics are read straight into the accumulators (S begins at
-// -lse / scale, dP at -delta), the lane offsets of the direct loads lie in LDS (head_dim 128), and what derives from the lane number is
+// -lse / scale, dP at -delta), the lane offsets of the direct loads lie in LDS, and what derives from the lane number is
 // formed where it is used.  dK/dV launch, before, with the slots, and with the ring going across the barrier: 1 x 32 heads x 32768 x 128
 // 1.980, 1.872, 1.820 ms (2.262, 2.195, 2.157 where it keeps dS), 4 x 32 x 8192 x 64 0.639, 0.625, 0.603 ms.
+//
+// What bounds it then is power: the chip's clock falls from 2.4 GHz to about 1.6 under it (GRBM_GUI_ACTIVE).  A loop of nothing but
+// 32x32x16 MFMAs on random operands sustains 1.75 PFLOP/s at 1.76 GHz, one of 16x16x32 MFMAs 2.06 at 2.07, and with one 16-byte LDS read to 32
+// cycles of either 1.59 and 1.81: hence the smaller shape, whose fragments of 16 rows also leave the LDS fewer bank conflicts (ChunkTile).
+// Same launches, 32x32x16 and 16x16x32: 1.820 and 1.740 ms (2.157 and 2.070 keeping dS), 4 x 32 x 8192 x 64 603 and 511 us, 3 x 20 x 8192 x
+// 64 with 32-token blocks 171 and 152.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -101,13 +106,6 @@ __device__ __forceinline__ void load_agent16(const void* base, uint32_t lane_off
                : "memory");
 }
 
-// The lane number, computed where it is asked for: nothing derived from it is kept in a register between two calls.
-__device__ __forceinline__ int lane_now() {
-  int ln;
-  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-  return ln;
-}
-
 // x stays where AT >= lim (keep_from) or AT < lim (keep_below), else it becomes `gone`.  Written out so that it costs no register but
 // its operands: left to itself the compiler keeps the compares of a whole tile at hand, and `gone` over the whole kernel.
 // (The no-op is the wait between a vector write of vcc and its use as a select.)
@@ -131,13 +129,13 @@ constexpr uint32_t kNegInfBits = 0xFF800000u;
 
 template <int D>
 struct DkvSmem {
-  uint16_t q[2][DmaTile<D>::kElems];
-  uint16_t g[2][DmaTile<D>::kElems];
+  uint16_t q[2][ChunkTile<D>::kElems];
+  uint16_t g[2][ChunkTile<D>::kElems];
   struct RowStats {
     float neg_delta[64];
     float neg_lse[64];
   } rs[2];                 // one 512-byte direct load fills both arrays of a stage
-  uint32_t goff[D == 128 ? PieceTile<D>::kLoads : 1][64];  // D = 128: the lane offsets of the direct loads
+  uint32_t goff[PieceTile<D, ChunkTile<D>>::kLoads][64];  // the lane offsets of the direct loads
 };
 
 // FINE: mask blocks of 16 or 32 tokens (0: larger ones).  A step's 64 query rows are four pieces of 16
@@ -159,13 +157,16 @@ struct DkvSmem {
 // queries in the order the lane holds them], i.e. each B operand as it is, 1 KiB per store instruction.
 template <int D, bool DENSE, int FINE, bool VARLEN = false, bool STORE = false>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const AttnParams p) {
-  typedef DmaTile<D> Tile;
-  typedef PieceTile<D> Piece;
+  typedef ChunkTile<D> Tile;
+  typedef PieceTile<D, Tile> Piece;
   constexpr int CH = 64;
-  constexpr int KK = D / 16, DT = D / 32;
-  constexpr int RB = Tile::kStride * 2;                       // bytes per tile row
+  constexpr int KS = D / 32;                                  // 32-feature steps of the S and dP contractions
+  constexpr int FT = D / 16;                                  // 16-feature tiles of dK and dV
+  constexpr int KK = D / 16;                                  // fragments of each contraction, two MFMAs each
+  static_assert(2 * KS == KK && FT == KK, "two 16-row tiles by KS steps; one 32-row slab by FT tiles");
+  constexpr int RB = Tile::RB;                                // bytes per tile row
   constexpr int G_OFF = 2 * Tile::kBytes;                     // dO stages lie after the Q stages
-  constexpr int kLead = 3, kRing = 4;
+  constexpr int kLead = VARLEN ? 2 : 3, kRing = 4;            // (packed batches have no room for three; the same time)
   static_assert((4 * KK) % kRing == 0, "the ring goes on from half to half");
   constexpr int kTr = 2 * KK - kLead;                         // the slot that requests the first transposed fragment
   static_assert(!(DENSE && (FINE || VARLEN)) && !(STORE && (DENSE || FINE || VARLEN)), "forms that exist");
@@ -176,7 +177,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int lane = tid & 63;
   const int T = p.kv_tiles.tiles_per_head;
   constexpr bool kSplits = !DENSE && !VARLEN;
   int bh, rank;
@@ -306,10 +307,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     }
     const uint16_t* qg = qb + (int64_t)row * p.q_st;
     const uint16_t* gg = gb + (int64_t)row * p.q_st;
-    Piece::template issue<0>(pl, qg, sm.q[buf], wave);
-    Piece::template issue<1>(pl, qg, sm.q[buf], wave);
-    Piece::template issue<0>(pl, gg, sm.g[buf], wave);
-    Piece::template issue<1>(pl, gg, sm.g[buf], wave);
+    static_for<Piece::kGroups>([&](auto gc) S2_INLINE { Piece::template issue<decltype(gc)::value>(pl, qg, sm.q[buf], wave); });
+    static_for<Piece::kGroups>([&](auto gc) S2_INLINE { Piece::template issue<decltype(gc)::value>(pl, gg, sm.g[buf], wave); });
     // 64 floats of each array: lanes 0..15 fetch delta, lanes 16..31 lse, 16 bytes each, in one direct load.
     // (Where a packed sequence ends inside a piece the rest of it comes from the slack of the workspace
     // or from the next rows: nothing uses it.)
@@ -348,30 +347,35 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   }
   if (!kSplits || total > 0) issue_chunk(plan, it0, it0 & 1, lane);  // (where a head's tile is short for its rank a part may be empty)
 
-  bf16x8 kf[D / 16], vf[D / 16];  // K and V fragments (B operands), lane = key
+  // K and V fragments (B operands) [32-feature step][16-key tile], lane % 16 = key of the tile
+  bf16x8 kf[KS][2], vf[KS][2];
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
+  for (int nt = 0; nt < 2; ++nt) {
     // (a lane whose key does not exist reads an existing one: every pair of it is masked and nothing is stored)
-    const int64_t o = kv_off + (int64_t)min(key_of(l32), N - 1) * p.kv_st + 16 * kk + 8 * half;
-    kf[kk] = *reinterpret_cast<const bf16x8*>(p.k + o);
-    vf[kk] = *reinterpret_cast<const bf16x8*>(p.v + o);
+    const int64_t row = kv_off + (int64_t)min(key_of(16 * nt + (lane & 15)), N - 1) * p.kv_st + 8 * (lane >> 4);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      kf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.k + row + 32 * kk);
+      vf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.v + row + 32 * kk);
+    }
   }
 
-  f32x16 acc_dk[D / 32], acc_dv[D / 32];
+  // dK and dV, transposed [16-feature tile][16-key tile]: lane % 16 = key, register r = feature 4 * (lane / 16) + r
+  f32x4 acc_dk[FT][2], acc_dv[FT][2];
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt) {
-    acc_dk[dt] = f32x16{};
-    acc_dv[dt] = f32x16{};
-  }
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) acc_dk[ft][nt] = acc_dv[ft][nt] = f32x4{};
   const float c = p.scale_log2e;
-  if (D == 128 && wave == 0) {
+  if (wave == 0) {
 #pragma unroll
     for (int n = 0; n < Piece::kLoads; ++n) sm.goff[n][lane] = plan.goff[n];
   }
 
   // The walk is one sequence of half steps of 32 query rows: half qt (up to qt1 - 1) of step it, whose first row is q0 (not FINE) or
-  // whose entries are in src.
-  int it = __builtin_amdgcn_readfirstlane(it0) - 1, qt = 0, qt1 = 0, q0 = 0, src = 0, stores = 0;  // stores: dS stores since the last direct loads
+  // whose entries are in ents.
+  uint32_t ents[EPC] = {};
+  int it = __builtin_amdgcn_readfirstlane(it0) - 1, qt = 0, qt1 = 0, q0 = 0, stores = 0;  // stores: dS stores since the last direct loads
   // opens step it: requests the chunk of the step after it into the other stage, and finds the halves that hold something for my keys
   auto open_step = [&]() S2_INLINE {
     const int ln = lane_now();
@@ -379,19 +383,17 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     if (!DENSE) (void)list.get(FINE ? EPC * it : it >> cpb_sh, ln);
     if (it + 1 < total) {
       typename Piece::Plan pl;
-      if constexpr (D == 128) {
 #pragma unroll
-        for (int n = 0; n < Piece::kLoads; ++n) pl.goff[n] = sm.goff[n][ln];
-      } else {
-        pl = plan;
-      }
+      for (int n = 0; n < Piece::kLoads; ++n) pl.goff[n] = sm.goff[n][ln];
       issue_chunk(pl, it + 1, (it + 1) & 1, ln);
     }
     stores = 0;
     int lo = 0, hi = 0;
     if constexpr (FINE) {
       // which pieces of the step attend keys of mine, from every lane's entry at once
-      src = entries_at(it);
+      const int src = entries_at(it);
+#pragma unroll
+      for (int i = 0; i < EPC; ++i) ents[i] = entry(src, EPC * it + i);
       uint64_t any = __ballot(FINE == 32 ? ((src >> wave) & 1) != 0 : ((src >> (2 * wave)) & 3) != 0);
       if (VARLEN) any &= __ballot((uint32_t)src <= last_ent);
       const uint32_t on4 = (uint32_t)(any >> ((EPC * it) & 63));
@@ -434,79 +436,76 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     // where the lane finds its rows of the half's tiles and statistics
     auto aim_rows = [&]() S2_INLINE {
       const int ln = lane_now(), buf = it & 1;
-      row_a = lds_addr(sm.q[0]) + buf * (uint32_t)Tile::kBytes + qt * 32 * RB + (ln & 31) * RB + 16 * (ln >> 5);
-      st_a = lds_addr(&sm.rs[0]) + buf * (uint32_t)sizeof(sm.rs[0]) + 128 * qt + 16 * (ln >> 5);
+      row_a = lds_addr(sm.q[0]) + buf * (uint32_t)Tile::kBytes + qt * 32 * RB + Tile::row_lane(ln);
+      st_a = lds_addr(&sm.rs[0]) + buf * (uint32_t)sizeof(sm.rs[0]) + 128 * qt + 16 * (ln >> 4);
       asm volatile("" : "+v"(row_a), "+v"(st_a));
     };
     auto aim_tr = [&]() S2_INLINE {
-      tr_a = lds_addr(sm.q[0]) + (it & 1) * (uint32_t)Tile::kBytes + qt * 32 * RB + 2 * Tile::tr_base(lane_now());
+      tr_a = lds_addr(sm.q[0]) + (it & 1) * (uint32_t)Tile::kBytes + qt * 32 * RB + Tile::tr_lane(lane_now());
       asm volatile("" : "+v"(tr_a));
     };
-    // VARLEN: `gone` where a row of piece u of the half, which begins at row r, lies past the sequence's end
-    auto drop_past_end = [&](auto gone, auto uc, f32x16& a, int r) S2_INLINE {
-      constexpr int u = decltype(uc)::value;
-      const int left = N - r - 4 * (lane_now() >> 5);
-      const float drop = constant_now<decltype(gone)::value>();
-      static_for<8>([&](auto ic) S2_INLINE {
-        constexpr int i = decltype(ic)::value;
-        a[8 * u + i] = keep_below<8 * (i >> 2) + (i & 3)>(a[8 * u + i], left, drop);
-      });
-    };
     bf16x8 fr[kRing];
-    f32x16 s, dp;  // S, then P in place; dP, then dS in place
+    // [16-row tile m][16-key tile nt]: lane % 16 = key, register r = row 4 * (lane / 16) + r
+    f32x4 s[2][2], dp[2][2];    // S, then P in place; dP, then dS in place
+    f32x4 st_s[2], st_d[2];     // what S and dP begin with: the statistics of the lane's rows
     // fragment f of a half, in the order the MFMAs use them; those after the last are the first of the next half
     auto frag_load = [&](auto fc) S2_INLINE {
       constexpr int f = decltype(fc)::value;
       u32x4 x;
       if constexpr (f < KK)
-        x = lds_read16(row_a, 32 * f);
+        x = lds_read16(row_a, Tile::row_off(f & 1, f >> 1));
       else if constexpr (f < 2 * KK)
-        x = lds_read16(row_a, G_OFF + 32 * (f - KK));
+        x = lds_read16(row_a, G_OFF + Tile::row_off((f - KK) & 1, (f - KK) >> 1));
       else if constexpr (f < 3 * KK)
-        x = lds_read_tr(tr_a, G_OFF + 16 * ((f - 2 * KK) / DT) * RB + 64 * ((f - 2 * KK) % DT), RB);
+        x = lds_read_tr(tr_a, G_OFF + Tile::tr_off(0, f - 2 * KK), 2 * RB);
       else if constexpr (f < 4 * KK)
-        x = lds_read_tr(tr_a, 16 * ((f - 3 * KK) / DT) * RB + 64 * ((f - 3 * KK) % DT), RB);
+        x = lds_read_tr(tr_a, Tile::tr_off(0, f - 3 * KK), 2 * RB);
       else
-        x = lds_read16(row_a, 32 * (f - 4 * KK));
+        x = lds_read16(row_a, Tile::row_off((f - 4 * KK) & 1, (f - 4 * KK) >> 1));
       fr[f % kRing] = __builtin_bit_cast(bf16x8, x);
     };
-    auto stats_load = [&](f32x16& x, int g, uint32_t addr, int off) S2_INLINE {
-      const f32x4 v4 = lds_read_f32x4(addr, off + 32 * g);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) x[4 * g + e] = v4[e];
-    };
-    auto stats_all = [&](int g) S2_INLINE {
-      stats_load(s, g, st_a, 256);
-      stats_load(dp, g, st_a, 0);
+    auto stats_load = [&](int m) S2_INLINE {
+      st_s[m] = lds_read_f32x4(st_a, 256 + 64 * m);
+      st_d[m] = lds_read_f32x4(st_a, 64 * m);
     };
     aim_rows();
-#pragma unroll
-    for (int g = 0; g < 4; ++g) stats_load(s, g, st_a, 256);
+    stats_load(0);
+    stats_load(1);
     static_for<kLead>([&](auto fc) S2_INLINE { frag_load(fc); });
-#pragma unroll
-    for (int g = 0; g < 4; ++g) stats_load(dp, g, st_a, 0);
     do {
-      // Of the 16 query rows of piece u of this half, row 8 i + 4 half + e is dropped when it lies before the lane's key or
-      // (FINE) my column does not keep the piece.
-      const int qbase = q0 + 32 * qt;
-      bool masked, ragged = false;
-      int r0 = qbase, r1 = qbase + 16;
-      uint32_t e0 = ~0u, e1 = ~0u;
+      // row of tile m's first row, and (FINE) the list entry it comes from
+      int row[2] = {q0 + 32 * qt, q0 + 32 * qt + 16};
+      uint32_t ent[2] = {~0u, ~0u};
       if constexpr (FINE) {
-        e0 = entry(src, EPC * it + (FINE == 32 ? qt : 2 * qt));
-        r0 = (int)(e0 >> 16) * FINE;
-        r1 = r0 + 16;
-        if constexpr (FINE == 16) {
-          e1 = entry(src, EPC * it + 2 * qt + 1);
-          r1 = (int)(e1 >> 16) * FINE;
-        }
-        masked = min(r0, r1) < (FINE == 16 ? max(kvw0, kvw1) + 15 : kvw0 + 31);
-        if (FINE == 16) masked = masked || (((e0 & e1) >> (2 * wave)) & 3) != 3;
-      } else {
-        masked = qbase < kvw0 + 31;
+        ent[0] = qt ? ents[EPC / 2] : ents[0];
+        ent[1] = FINE == 32 ? ent[0] : qt ? ents[EPC - 1] : ents[1];
+        row[0] = (int)(ent[0] >> 16) * FINE;
+        row[1] = FINE == 32 ? row[0] + 16 : (int)(ent[1] >> 16) * FINE;
       }
-      if (VARLEN) ragged = max(r0, r1) + 16 > N;
-      u32x4 pb[2], dsb[2];
+      // some pair of the half is dropped: its query lies before its key or (blocks of 16) my column does not keep the piece
+      bool masked = min(row[0], row[1]) < (FINE == 16 ? max(kvw0, kvw1) + 15 : kvw0 + 31);
+      if (FINE == 16) masked = masked || (((ent[0] & ent[1]) >> (2 * wave)) & 3) != 3;
+      const bool ragged = VARLEN && max(row[0], row[1]) + 16 > N;
+      u32x4 pb[2], dsb[2];  // P and dS as B operands [16-key tile]
+      // element x (0..15) of s or dp, in the order of the B operands: tile [(x >> 2) & 1][x >> 3], register x & 3
+      auto elem = [](f32x4 (&a)[2][2], int x) S2_INLINE -> float { return a[(x >> 2) & 1][x >> 3][x & 3]; };
+      auto pack_operand = [&](f32x4 (&a)[2][2], int nt) S2_INLINE {
+        return u32x4{pack2(elem(a, 8 * nt), elem(a, 8 * nt + 1)), pack2(elem(a, 8 * nt + 2), elem(a, 8 * nt + 3)),
+                     pack2(elem(a, 8 * nt + 4), elem(a, 8 * nt + 5)), pack2(elem(a, 8 * nt + 6), elem(a, 8 * nt + 7))};
+      };
+      // VARLEN: `gone` where a row lies past the sequence's end
+      auto drop_past_end = [&](auto gone, f32x4 (&a)[2][2]) S2_INLINE {
+        const float drop = constant_now<decltype(gone)::value>();
+        const int g4 = 4 * (lane_now() >> 4);
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int left = N - row[m] - g4;
+          S2_FENCE();
+#pragma unroll
+          for (int nt = 0; nt < 2; ++nt)
+            static_for<4>([&](auto rc) S2_INLINE { a[m][nt][decltype(rc)::value] = keep_below<decltype(rc)::value>(a[m][nt][decltype(rc)::value], left, drop); });
+        }
+      };
       S2_FENCE();
       static_for<4 * KK>([&](auto nc) S2_INLINE {
         constexpr int n = decltype(nc)::value;
@@ -517,80 +516,82 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
           aim_rows();
         }
         frag_load(std::integral_constant<int, n + kLead>{});
-        if constexpr (n < KK)
-          s = mfma32(fr[n % kRing], kf[n], s);
-        else if constexpr (n < 2 * KK)
-          dp = mfma32(fr[n % kRing], vf[n - KK], dp);
-        else if constexpr (n < 3 * KK)
-          acc_dv[(n - 2 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, pb[(n - 2 * KK) / DT]), acc_dv[(n - 2 * KK) % DT]);
-        else
-          acc_dk[(n - 3 * KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[(n - 3 * KK) / DT]), acc_dk[(n - 3 * KK) % DT]);
-        // P
-        constexpr int RS = 16 / KK, M0 = KK + 1, D0 = 2 * KK + 1;
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+          if constexpr (n < KK) {
+            constexpr int m = n & 1, kk = n >> 1;
+            s[m][nt] = mfma16(fr[n % kRing], kf[kk][nt], kk == 0 ? st_s[m] : s[m][nt]);
+          } else if constexpr (n < 2 * KK) {
+            constexpr int m = n & 1, kk = (n - KK) >> 1;
+            dp[m][nt] = mfma16(fr[n % kRing], vf[kk][nt], kk == 0 ? st_d[m] : dp[m][nt]);
+          } else if constexpr (n < 3 * KK) {
+            acc_dv[n - 2 * KK][nt] = mfma16(fr[n % kRing], __builtin_bit_cast(bf16x8, pb[nt]), acc_dv[n - 2 * KK][nt]);
+          } else {
+            acc_dk[n - 3 * KK][nt] = mfma16(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[nt]), acc_dk[n - 3 * KK][nt]);
+          }
+        }
+        constexpr int M0 = KK + 1, D0 = 2 * KK + 1;
         if constexpr (n == M0) {
           if (masked) {
-            const int ln = lane_now(), l32 = ln & 31, half = ln >> 5;
-            const int key = key_of(l32);
+            const int ln = lane_now(), l16 = ln & 15, g4 = 4 * (ln >> 4);
             const float drop = constant_now<kNegInfBits>();
-            static_for<2>([&](auto uc) S2_INLINE {
-              constexpr int u = decltype(uc)::value;
-              int lim = key - (u ? r1 : r0) - 4 * half;
-              if constexpr (FINE == 16) lim = ((u ? e1 : e0) >> (2 * wave + (l32 >> 4))) & 1 ? lim : 64;
-              static_for<8>([&](auto ic) S2_INLINE {
-                constexpr int i = decltype(ic)::value;
-                s[8 * u + i] = keep_from<8 * (i >> 2) + (i & 3)>(s[8 * u + i], lim, drop);
-              });
-            });
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+              for (int nt = 0; nt < 2; ++nt) {
+                const int key0 = FINE == 16 && nt ? kvw1 : kvw0 + 16 * nt;
+                if (FINE == 16 && !((ent[m] >> (2 * wave + nt)) & 1)) {  // the tile is a block my column does not keep
+                  s[m][nt] = f32x4{drop, drop, drop, drop};
+                } else if (FINE != 16 || row[m] < key0 + 15) {
+                  const int lim = key0 + l16 - row[m] - g4;
+                  S2_FENCE();
+                  static_for<4>([&](auto rc) S2_INLINE { s[m][nt][decltype(rc)::value] = keep_from<decltype(rc)::value>(s[m][nt][decltype(rc)::value], lim, drop); });
+                }
+              }
           }
-          if constexpr (VARLEN) {
-            if (ragged) {
-              drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 0>{}, s, r0);
-              drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, std::integral_constant<int, 1>{}, s, r1);
-            }
-          }
+          if (ragged) drop_past_end(std::integral_constant<uint32_t, kNegInfBits>{}, s);
         }
-        if constexpr (n >= M0 && n < M0 + KK) {
+        // P: scaled in slots M0 .., the exponential a slot behind, all of it before dV begins
+        constexpr int NP = KK - 2;
+        auto upto = [](int i) { return i < 0 ? 0 : i >= NP ? 16 : (16 * i + NP - 1) / NP; };
+        if constexpr (n >= M0 && n < M0 + NP) {
 #pragma unroll
-          for (int r = RS * (n - M0); r < RS * (n - M0 + 1); ++r) s[r] *= c;
+          for (int x = upto(n - M0); x < upto(n - M0 + 1); ++x) s[(x >> 2) & 1][x >> 3][x & 3] *= c;
         }
-        if constexpr (n >= M0 + 1 && n < M0 + 1 + KK) {
+        if constexpr (n > M0 && n <= M0 + NP) {
 #pragma unroll
-          for (int r = RS * (n - M0 - 1); r < RS * (n - M0); ++r) s[r] = fast_exp2(s[r]);
-          asm volatile("" : "+v"(s));
+          for (int x = upto(n - M0 - 1); x < upto(n - M0); ++x) s[(x >> 2) & 1][x >> 3][x & 3] = fast_exp2(s[(x >> 2) & 1][x >> 3][x & 3]);
         }
-        constexpr int PK0 = M0 + 1 + KK / 2 < 2 * KK - 1 ? M0 + 1 + KK / 2 : 2 * KK - 1;
-        constexpr int PK1 = M0 + 1 + KK < 2 * KK + DT - 1 ? M0 + 1 + KK : 2 * KK + DT - 1;
-        if constexpr (n == PK0 || n == PK1) {
-          constexpr int u = n == PK0 ? 0 : 1;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) pb[u][i] = pack2(s[8 * u + 2 * i], s[8 * u + 2 * i + 1]);
+        static_assert(M0 + NP == 2 * KK - 1, "P is complete in the slot before dV begins");
+        if constexpr (n == 2 * KK - 1) {
+          pb[0] = pack_operand(s, 0);
+          pb[1] = pack_operand(s, 1);
         }
-        // dS
-        if constexpr (n >= D0 && n < D0 + KK) {
+        // dS under dV
+        constexpr int ND = KK - 1;
+        auto dupto = [](int i) { return i >= ND ? 16 : (16 * i + ND - 1) / ND; };
+        if constexpr (n >= D0 && n < D0 + ND) {
 #pragma unroll
-          for (int r = RS * (n - D0); r < RS * (n - D0 + 1); ++r) dp[r] *= s[r];
+          for (int x = dupto(n - D0); x < dupto(n - D0 + 1); ++x) dp[(x >> 2) & 1][x >> 3][x & 3] *= s[(x >> 2) & 1][x >> 3][x & 3];
+          asm volatile("" : "+v"(dp[0][0]), "+v"(dp[0][1]), "+v"(dp[1][0]), "+v"(dp[1][1]));
         }
-        constexpr int DK0 = D0 + KK / 2 < 3 * KK - 1 ? D0 + KK / 2 : 3 * KK - 1;
-        constexpr int DK1 = D0 + KK < 3 * KK + DT - 1 ? D0 + KK : 3 * KK + DT - 1;
-        if constexpr (n == DK0 || n == DK1) {
-          constexpr int u = n == DK0 ? 0 : 1;
-          if constexpr (VARLEN) {
-            if (ragged) drop_past_end(std::integral_constant<uint32_t, 0>{}, std::integral_constant<int, u>{}, dp, u ? r1 : r0);  // (their statistics are not their own)
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) dsb[u][i] = pack2(dp[8 * u + 2 * i], dp[8 * u + 2 * i + 1]);
+        if constexpr (n == 3 * KK - 1) {
+          if (ragged) drop_past_end(std::integral_constant<uint32_t, 0>{}, dp);  // (their statistics are not their own)
+          dsb[0] = pack_operand(dp, 0);
+          dsb[1] = pack_operand(dp, 1);
           if constexpr (STORE) {
-            const int ln = lane_now();
-            const uint32_t off = 16u * (2 * (ln & 31) + (ln >> 5)) + 1024u * u;
+            const uint32_t off = 64u * (lane_now() & 15) + 16u * (lane_now() >> 4);
+            unsigned char* const unit = reinterpret_cast<unsigned char*>(ds_wave + (int64_t)it * 8192 + 1024 * qt);
             // non-temporal: written once here and read by a later launch, it should not push the Q / dO
             // blocks this kernel re-reads out of L2
-            __builtin_nontemporal_store(dsb[u], reinterpret_cast<u32x4*>(reinterpret_cast<unsigned char*>(ds_wave + (int64_t)it * 8192 + 1024 * qt) + off));
-            ++stores;
+            __builtin_nontemporal_store(dsb[0], reinterpret_cast<u32x4*>(unit + off));
+            __builtin_nontemporal_store(dsb[1], reinterpret_cast<u32x4*>(unit + 1024 + off));
+            stores += 2;
           }
         }
         // the next half's statistics, where its contractions begin
-        if constexpr (n >= 4 * KK - 3) stats_all(n - (4 * KK - 3));
-        if constexpr (n == 4 * KK - 1) stats_all(3);
+        if constexpr (n == 4 * KK - kLead) stats_load(0);
+        if constexpr (n == 4 * KK - kLead + 1) stats_load(1);
         S2_FENCE();
       });
     } while (more);
@@ -599,19 +600,17 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   if (kSplits && parts > 1) {
     // This is a part of a tile: leave my sums in memory, and if the other parts have done so already add
     // all of them up, in the order of the parts, and go on with the result.
-    constexpr int kTiles = 2 * (D / 32);               // accumulator tiles of a wavefront, dK and dV in turn
-    constexpr int kWaveBytes = kTiles * 4 * 1024;      // [tile][register quad][lane][4 floats]
+    constexpr int kTiles = FT;                         // of four accumulator quads each: dK and dV of a 16-feature tile
+    constexpr int kWaveBytes = kTiles * 4 * 1024;      // [feature tile][dK, dV][16-key tile][lane][4 floats]
     const uint32_t lane_off = 16 * lane_now();
     unsigned char* const sums = reinterpret_cast<unsigned char*>(p.split_sums) + ((int64_t)bh * p.split_items + rank) * (4 * kWaveBytes) +
                                 wave * kWaveBytes;
-    auto quad = [](const f32x16& a, int g) S2_INLINE { return f32x4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]}; };
     static_for<kTiles>([&](auto tc) S2_INLINE {
-      constexpr int t = decltype(tc)::value;
-      const f32x16& a = t & 1 ? acc_dv[t >> 1] : acc_dk[t >> 1];
-      store_agent<0>(sums + 4096 * t, lane_off, quad(a, 0));
-      store_agent<1024>(sums + 4096 * t, lane_off, quad(a, 1));
-      store_agent<2048>(sums + 4096 * t, lane_off, quad(a, 2));
-      store_agent<3072>(sums + 4096 * t, lane_off, quad(a, 3));
+      constexpr int ft = decltype(tc)::value;
+      store_agent<0>(sums + 4096 * ft, lane_off, acc_dk[ft][0]);
+      store_agent<1024>(sums + 4096 * ft, lane_off, acc_dk[ft][1]);
+      store_agent<2048>(sums + 4096 * ft, lane_off, acc_dv[ft][0]);
+      store_agent<3072>(sums + 4096 * ft, lane_off, acc_dv[ft][1]);
     });
     wait_all_loads();  // my stores have arrived
     __syncthreads();
@@ -623,10 +622,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     __syncthreads();
     if (*flag != parts - 1) return;
 #pragma unroll
-    for (int dt = 0; dt < D / 32; ++dt) {
-      acc_dk[dt] = f32x16{};
-      acc_dv[dt] = f32x16{};
-    }
+    for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) acc_dk[ft][nt] = acc_dv[ft][nt] = f32x4{};
     const unsigned char* from = sums - (int64_t)part * (4 * kWaveBytes);
 #pragma unroll 1
     for (int i = 0; i < parts; ++i, from += 4 * kWaveBytes) {
@@ -636,9 +634,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
         load_agent16(from + 16384 * j, lane_off, x);
 #pragma unroll
         for (int n = 0; n < 16; ++n) {
-          f32x16& a = (n >> 2) & 1 ? acc_dv[2 * j + (n >> 3)] : acc_dk[2 * j + (n >> 3)];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) a[4 * (n & 3) + e] += x[n][e];
+          f32x4& a = n & 2 ? acc_dv[4 * j + (n >> 2)][n & 1] : acc_dk[4 * j + (n >> 2)][n & 1];
+          a += x[n];
         }
       });
     }
@@ -654,17 +651,18 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   uint16_t* sk_ = &sm.q[0][0] + wave * 32 * RS;
   uint16_t* sv_ = &sm.g[0][0] + wave * 32 * RS;
 #pragma unroll
-  for (int dt = 0; dt < D / 32; ++dt)
+  for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int nt = 0; nt < 2; ++nt) {
       bf16x4 wk, wv;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        wk[e] = (__bf16)(acc_dk[dt][4 * g + e] * p.scale);
-        wv[e] = (__bf16)(acc_dv[dt][4 * g + e]);
+        wk[e] = (__bf16)(acc_dk[ft][nt][e] * p.scale);
+        wv[e] = (__bf16)(acc_dv[ft][nt][e]);
       }
-      *reinterpret_cast<bf16x4*>(sk_ + (ln_out & 31) * RS + 32 * dt + 8 * g + 4 * (ln_out >> 5)) = wk;
-      *reinterpret_cast<bf16x4*>(sv_ + (ln_out & 31) * RS + 32 * dt + 8 * g + 4 * (ln_out >> 5)) = wv;
+      const int at = (16 * nt + (ln_out & 15)) * RS + 16 * ft + 4 * (ln_out >> 4);
+      *reinterpret_cast<bf16x4*>(sk_ + at) = wk;
+      *reinterpret_cast<bf16x4*>(sv_ + at) = wv;
     }
   uint16_t* dk_base = p.dk + kv_off;
   uint16_t* dv_base = p.dv + kv_off;

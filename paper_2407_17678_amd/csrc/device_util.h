@@ -30,6 +30,15 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// v_mfma_f32_16x16x32_bf16 (g = lane / 16):
+//   A (16 x 32): lane holds row (lane % 16), the 8 k-values of its g.  B (32 x 16): column (lane % 16), likewise.
+//   C/D (16 x 16, 4 floats): lane holds column (lane % 16); register r is row 4 * g + r.
+// Two C tiles one below the other (32 rows) are, as a B operand of 32 k-values, four registers each: the lane's k-values are
+// rows {4 * g + 0..3, 16 + 4 * g + 0..3}, and ChunkTile::tr_lane fetches the matching A operand in that order.
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // x of this lane combined with x of the lane 32 positions away (the other half of the wavefront).
@@ -164,6 +173,27 @@ struct DmaTile {
 };
 
 // ---------------------------------------------------------------------------------------------
+// ChunkTile: the tile that goes with the 16x16x32 MFMA.  Its fragments are read as 16 rows x 64 bytes (k = feature) or, by the
+// transpose read, 16 rows x 32 bytes, and for these one row stride serves both: 72 dwords (D = 128) or 40 (D = 64), 8 modulo 32.  Measured on
+// gfx950, eight wavefronts on a compute unit, cycles an instruction (row reads, transpose reads): 72 dwords 2.0 and 2.5, 76 dwords 4.0 and 3.7, 64
+// dwords 16 and 12; the same at 40 and 52.  (The 32x32x16 fragments at DmaTile's 76: 2.0 and 3.7.)
+// ---------------------------------------------------------------------------------------------
+template <int D>
+struct ChunkTile {
+  static constexpr int kStride = (D == 128) ? 144 : 80;  // elements
+  static constexpr int RB = 2 * kStride;                 // bytes
+  static constexpr int kBytes = 64 * RB;                 // a whole number of wavefront-wide loads
+  static constexpr int kElems = kBytes / 2;
+  // Row fragment: 16-row tile m, features 32 * kk + 8 * g .. + 7 of row lane % 16, at row_lane(lane) + row_off(m, kk)
+  __device__ static __forceinline__ uint32_t row_lane(int lane) { return (lane & 15) * RB + 16 * (lane >> 4); }
+  static constexpr int row_off(int m, int kk) { return 16 * m * RB + 64 * kk; }
+  // Transposed fragment: feature 16 * ft + lane % 16 of the rows {4 * g + 0..3, 16 + 4 * g + 0..3} of 32-row slab u: two transpose
+  // reads (see above) at tr_lane(lane) + tr_off(u, ft), the second 16 rows further on
+  __device__ static __forceinline__ uint32_t tr_lane(int lane) { return (4 * (lane >> 4) + ((lane & 15) >> 2)) * RB + 8 * (lane & 3); }
+  static constexpr int tr_off(int u, int ft) { return 32 * u * RB + 32 * ft; }
+};
+
+// ---------------------------------------------------------------------------------------------
 // PieceTile: how the four wavefronts of a workgroup fill a 64-row DmaTile by pieces of 16 rows, one
 // piece each.  Sixteen padded rows are 4864 bytes (D = 128) or 3328 (D = 64), so a piece is four or
 // three whole wavefront-wide loads and one more that ends where the piece ends and fetches the 256 or
@@ -173,13 +203,13 @@ struct DmaTile {
 // blocks of 64 or 128 tokens the pieces are consecutive; for 16- and 32-token blocks a chunk is
 // gathered from whatever blocks come next in the tile's list, at no cost per lane.
 // ---------------------------------------------------------------------------------------------
-template <int D>
+template <int D, class TILE = DmaTile<D>>
 struct PieceTile {
-  static constexpr int kStride = DmaTile<D>::kStride;   // elements
+  static constexpr int kStride = TILE::kStride;         // elements
   static constexpr int kRows = 16;
   static constexpr int kBytes = kRows * kStride * 2;    // 4864 / 3328
   static constexpr int kLoads = (kBytes + 1023) / 1024; // 5 / 4
-  static constexpr int kGroups = 2;                     // 3 + 2 / 2 + 2 loads to a write of M0
+  static constexpr int kGroups = kLoads == 3 ? 1 : 2;   // 3 + 2 / 2 + 2 / 3 loads to a write of M0
   static constexpr uint32_t kBias = 4096;
   // where load n starts in the piece: the immediate it is issued with
   __host__ __device__ static constexpr int imm(int n) { return n + 1 < kLoads ? 1024 * n : kBytes - 1024; }
@@ -207,7 +237,7 @@ struct PieceTile {
   template <int G>
   __device__ static __forceinline__ void issue(const Plan& pl, const void* gbase_biased, const uint16_t* tile, int wave) {
     const uint32_t lds = lds_addr(tile) + wave * kBytes;
-    if constexpr (kLoads == 5 && G == 0)
+    if constexpr (kLoads != 4 && G == 0)
       dma16_group<imm(0), imm(1), imm(2)>(gbase_biased, lds, pl.goff[0], pl.goff[1], pl.goff[2]);
     else if constexpr (G == 0)
       dma16_group<imm(0), imm(1)>(gbase_biased, lds, pl.goff[0], pl.goff[1]);

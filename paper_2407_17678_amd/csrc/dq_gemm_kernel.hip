@@ -16,8 +16,8 @@
 // per unmasked pair and 128 flop against it).
 //
 // dS in the workspace: units of 64 queries x 64 keys, 8 KiB each, found through AttnParams::dq_units;
-// inside a unit [32-key half][32-query half][16-query slab][key][lane half][8 queries as the writing
-// lane held them: 4 * half + 0..3, then 8 + 4 * half + 0..3].
+// inside a unit [32-key half][32-query half][key][g = 0..3][8 queries as the writing lane held them: 4 * g + 0..3, then
+// 16 + 4 * g + 0..3].
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -31,17 +31,16 @@ namespace s2 {
 
 namespace {
 
-// One wavefront's dS of a chunk in LDS: four 1 KiB pieces (32-query half t, 16-query slab u of it), piece
-// (t, u) at t * 1024 + u * kDsSlabStride.  The 128 odd bytes put the two slabs half a bank row apart, so
-// that the four 16-lane groups of a transpose read (slab, lane half) fall on different banks.
-constexpr int kDsSlabStride = 2 * 1024 + 128;
-constexpr int kDsWaveBytes = 2 * kDsSlabStride;
+// One wavefront's dS of a chunk in LDS as it lies in the unit, 64 bytes a key, but 4 keys (256 bytes) at every kDsQuadStride: the
+// four 16-lane groups of a transpose read, 4 keys each, then fall on different banks (each touches 8 of every 16 bytes).
+constexpr int kDsQuadStride = 256 + 32;
+constexpr int kDsWaveBytes = 16 * kDsQuadStride;
 
 template <int D>
 struct DqGemmSmem {
   union {
     struct {
-      uint16_t k[2][DmaTile<D>::kElems];  // K rows of a chunk (the padded tile of device_util.h), two stages
+      uint16_t k[2][ChunkTile<D>::kElems];  // K rows of a chunk, two stages
       unsigned char ds[4][kDsWaveBytes];         // per wavefront: its dS of the current chunk
     } loop;
     float reduce[2][64 * D];  // after the loop: the second key half's sums, per 64-row half of the tile
@@ -54,15 +53,15 @@ struct DqGemmSmem {
 // tracked the compiler's counted waits let the later chunks stay outstanding.
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p) {
-  typedef DmaTile<D> Tile;
+  typedef ChunkTile<D> Tile;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   DqGemmSmem<D>& sm = *reinterpret_cast<DqGemmSmem<D>*>(smem_raw);
-  constexpr int BM = kBwdBM, DT = D / 32;
+  constexpr int BM = kBwdBM, FT = D / 16;
   static_assert(D == 128, "a chunk's K rows are 4 x 16 bytes per lane of the workgroup");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   const int T = p.q_tiles.tiles_per_head;
   int bh, rank;
   if (!map_workgroup(blockIdx.x, p.batch * p.heads, T, p.map_group, bh, rank)) return;
@@ -113,48 +112,47 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
 #pragma unroll
     for (int i = 0; i < 4; ++i) f.ds[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ug + 1024 * i));
   };
-  // piece i of the run is (32-query half i / 2, slab i % 2)
+  // lane i of a run's kilobyte holds 16 bytes of key i / 4
+  const uint32_t ds_loff = (lane >> 4) * kDsQuadStride + l16 * 16;
   auto stash = [&](const Fetch& f, int stage, int unit) S2_INLINE {
     uint16_t* kt = sm.loop.k[stage] + k_loff;
 #pragma unroll
     for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(kt + 16 * i * Tile::kStride) = f.k[i];
     if (unit < 0) return;
-    unsigned char* dw = sm.loop.ds[wave] + lane * 16;
+    unsigned char* dw = sm.loop.ds[wave] + ds_loff;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(dw + 1024 * (i >> 1) + kDsSlabStride * (i & 1)) = f.ds[i];
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(dw + 4 * i * kDsQuadStride) = f.ds[i];
   };
 
-  f32x16 acc[2][DT];  // [32-query half][feature tile]
+  f32x4 acc[FT][4];  // dQ transposed [16-feature tile][16-query tile of my 64]
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) acc[t][dt] = f32x16{};
-  const int trb = Tile::tr_base(lane);
-  // lane part of a dS transpose read: group g = lane / 16 reads slab g % 2 for lane half g / 2; lane
-  // 4 e + q of a group supplies key 4 (g / 2) + e, queries 4 q .. 4 q + 3 of the slab, which the writer's
-  // lane half q % 2 holds as its first (q < 2) or second four
-  const int g16 = lane >> 4, e4 = (lane & 15) >> 2, q4 = lane & 3;
-  const uint32_t ds_trb = lds_addr(sm.loop.ds[wave]) + (g16 & 1) * kDsSlabStride + (4 * (g16 >> 1) + e4) * 32 + (q4 & 1) * 16 + (q4 >> 1) * 8;
+    for (int nq = 0; nq < 4; ++nq) acc[ft][nq] = f32x4{};
+  const uint32_t tr_lane = lds_addr(sm.loop.k[0]) + Tile::tr_lane(lane) + Tile::tr_off(khalf, 0);
+  // lane part of a dS transpose read: lane 4 e + q of group g supplies key 4 g + e, queries 4 q .. 4 q + 3 of a 16-query tile,
+  // which lie in the key's 16 bytes of (the writer's) group q, the first or second eight of them by the tile's parity
+  const uint32_t ds_lane = lds_addr(sm.loop.ds[wave]) + g * kDsQuadStride + (l16 >> 2) * 64 + (l16 & 3) * 16;
 
   auto multiply = [&](int kv0, int unit, int stage) S2_INLINE {
     if (unit < 0) return;
-    const uint16_t* ks = sm.loop.k[stage];
-    const int kb32 = kv0 + 32 * khalf;  // my first key
     // keys all after the first 32 queries: the dK/dV kernel skipped that quarter, nothing was stored
     // (the unit exists, so they are not after the second 32)
-    const bool first = kb32 <= q0;
+    const bool first = kv0 + 32 * khalf <= q0;
+    bf16x8 ds[4];
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl) {  // 16-key slab of my 32 keys
-      const u32x4 r1 = lds_read_tr(ds_trb, 1024 + 512 * sl, 32);
-      u32x4 r0 = lds_read_tr(ds_trb, 512 * sl, 32);
-      if (!first) r0 = u32x4{0u, 0u, 0u, 0u};  // what LDS holds there is not dS: that quarter counts as zero
-      const bf16x8 d0 = __builtin_bit_cast(bf16x8, r0), d1 = __builtin_bit_cast(bf16x8, r1);
+    for (int nq = 0; nq < 4; ++nq) {
+      // (the second four of the lane's keys are 16 keys further on)
+      u32x4 r = lds_read_tr(ds_lane, (nq >> 1) * 8 * kDsQuadStride + 8 * (nq & 1), kDsQuadStride / 2);
+      if (nq < 2 && !first) r = u32x4{0u, 0u, 0u, 0u};  // what LDS holds there is not dS: that quarter counts as zero
+      ds[nq] = __builtin_bit_cast(bf16x8, r);
+    }
+    const uint32_t kt = tr_lane + stage * (uint32_t)Tile::kBytes;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const bf16x8 kf = Tile::tr_frag(ks, dt, 2 * khalf + sl, trb);
-        acc[0][dt] = mfma32(kf, d0, acc[0][dt]);
-        acc[1][dt] = mfma32(kf, d1, acc[1][dt]);
-      }
+    for (int ft = 0; ft < FT; ++ft) {
+      const bf16x8 kf = __builtin_bit_cast(bf16x8, lds_read_tr(kt, Tile::tr_off(0, ft), 2 * Tile::RB));
+#pragma unroll
+      for (int nq = 0; nq < 4; ++nq) acc[ft][nq] = mfma16(kf, ds[nq], acc[ft][nq]);
     }
   };
 
@@ -196,20 +194,20 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
   float* red = sm.reduce[qhalf] + lane;
   if (khalf == 1) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+      for (int nq = 0; nq < 4; ++nq)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) red[((t * DT + dt) * 16 + r) * 64] = acc[t][dt][r];
+        for (int r = 0; r < 4; ++r) red[((ft * 4 + nq) * 4 + r) * 64] = acc[ft][nq][r];
   }
   __syncthreads();
   if (khalf == 1) return;
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int nq = 0; nq < 4; ++nq)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[t][dt][r] += red[((t * DT + dt) * 16 + r) * 64];
+      for (int r = 0; r < 4; ++r) acc[ft][nq][r] += red[((ft * 4 + nq) * 4 + r) * 64];
 
   // dQ = scale * acc goes out through LDS (my half of the reduction buffer, which only I read, after my
   // own reads of it), whole rows per store instruction
@@ -217,16 +215,14 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
   uint16_t* stage = reinterpret_cast<uint16_t*>(sm.reduce[qhalf]);
   static_assert(64 * RS * 2 <= 64 * D * 4, "the staging rows fit the reduction buffer");
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
+  for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+    for (int nq = 0; nq < 4; ++nq) {
+      bf16x4 w;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        bf16x4 w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[t][dt][4 * g + e] * p.scale);
-        *reinterpret_cast<bf16x4*>(stage + (32 * t + l32) * RS + 32 * dt + 8 * g + 4 * half) = w;
-      }
+      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[ft][nq][e] * p.scale);
+      *reinterpret_cast<bf16x4*>(stage + (16 * nq + l16) * RS + 16 * ft + 4 * g) = w;
+    }
   uint16_t* obase = p.dq + q_off + (int64_t)q0 * p.q_st;
 #pragma unroll
   for (int i = 0; i < 64 / 4; ++i) {

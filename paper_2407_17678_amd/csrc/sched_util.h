@@ -64,6 +64,13 @@ __device__ __forceinline__ u32x4 lds_read_tr(uint32_t addr, int byte_off, int ro
   return lds_read_tr2(addr, addr, byte_off, byte_off + 8 * row_bytes);
 }
 
+// The lane number, computed where it is asked for: nothing derived from it is kept in a register between two calls.
+__device__ __forceinline__ int lane_now() {
+  int ln;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+  return ln;
+}
+
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pack2(float lo, float hi) {
   bf16x2 w;
