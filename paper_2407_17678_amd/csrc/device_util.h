@@ -11,7 +11,7 @@
 // C-layout tile be fed back as a B operand without moving data between lanes: registers
 // 8u..8u+7 of a C tile are, for the lane's half, the rows {16u + 4*half + 0..3,
 // 16u + 8 + 4*half + 0..3}; the matching A operand is fetched from LDS in exactly that order
-// (see DmaTile::tr_frag).
+// (see DmaTile::tr_base).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -64,13 +64,12 @@ __device__ __forceinline__ float sum_halves(float x) {
   return a + b;
 }
 
-// Eight floats -> eight bf16 (round to nearest even, hardware conversion on gfx950).
-__device__ __forceinline__ bf16x8 pack8(float a0, float a1, float a2, float a3, float a4, float a5,
-                                        float a6, float a7) {
-  bf16x8 r;
-  r[0] = (__bf16)a0; r[1] = (__bf16)a1; r[2] = (__bf16)a2; r[3] = (__bf16)a3;
-  r[4] = (__bf16)a4; r[5] = (__bf16)a5; r[6] = (__bf16)a6; r[7] = (__bf16)a7;
-  return r;
+// The same with the lane 16 positions away (v_permlane16_swap exchanges the odd rows of 16 lanes of one register with the even
+// rows of another), and so over the four lanes that hold one column of a 16x16 tile.
+__device__ __forceinline__ float sum_groups(float x) {
+  float even = sum_halves(x), odd = even;
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(even), "+v"(odd));
+  return even + odd;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -150,25 +149,10 @@ struct DmaTile {
   static constexpr int kBytes = kInstr * 1024;            // the last load may run past the last row
   static constexpr int kElems = kBytes / 2;
 
-  // row fragment: row = 32*rt + lane%32, features 16*kk + 8*half .. +7
-  __device__ static __forceinline__ bf16x8 row_frag(const uint16_t* tile, int rt, int kk, int l32, int half) {
-    return *reinterpret_cast<const bf16x8*>(tile + (32 * rt + l32) * kStride + 16 * kk + 8 * half);
-  }
-
-  // lane-dependent part of a transposed fragment's address (elements)
+  // lane-dependent part of a transposed fragment's address (elements): features 32*ft + lane%32 of 16 tokens in C-layout k order
   __device__ static __forceinline__ int tr_base(int lane) {
     const int g = lane >> 4, e = (lane & 15) >> 2, q = lane & 3;
     return (4 * (g >> 1) + e) * kStride + 16 * (g & 1) + 4 * q;
-  }
-  // transposed fragment: features 32*ft + lane%32, the 16 tokens of `slab` in C-layout k order
-  __device__ static __forceinline__ bf16x8 tr_frag(const uint16_t* tile, int ft, int slab, int trb) {
-    typedef __attribute__((address_space(3))) s16x4* lds_ptr;
-    const uint16_t* p = tile + trb + 16 * slab * kStride + 32 * ft;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 8 * kStride));
-    typedef short s16x8 __attribute__((ext_vector_type(8)));
-    const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8, both);
   }
 };
 
@@ -194,9 +178,9 @@ struct ChunkTile {
 };
 
 // ---------------------------------------------------------------------------------------------
-// PieceTile: how the four wavefronts of a workgroup fill a 64-row DmaTile by pieces of 16 rows, one
-// piece each.  Sixteen padded rows are 4864 bytes (D = 128) or 3328 (D = 64), so a piece is four or
-// three whole wavefront-wide loads and one more that ends where the piece ends and fetches the 256 or
+// PieceTile: how the four wavefronts of a workgroup fill a 64-row tile by pieces of 16 rows, one
+// piece each.  Sixteen padded rows are 4864 bytes (DmaTile, D = 128) or 3328 (64), 4608 or 2560 (ChunkTile), so a piece is
+// some whole wavefront-wide loads and one more that ends where the piece ends and fetches the 256 to
 // 768 bytes before its remainder a second time (the same bytes to the same place).  The four pieces
 // are then back to back - the tile looks exactly as if it had been filled front to back - and where
 // each piece comes from is up to the wavefront that fetches it: one scalar row number.  For mask
@@ -207,8 +191,8 @@ template <int D, class TILE = DmaTile<D>>
 struct PieceTile {
   static constexpr int kStride = TILE::kStride;         // elements
   static constexpr int kRows = 16;
-  static constexpr int kBytes = kRows * kStride * 2;    // 4864 / 3328
-  static constexpr int kLoads = (kBytes + 1023) / 1024; // 5 / 4
+  static constexpr int kBytes = kRows * kStride * 2;
+  static constexpr int kLoads = (kBytes + 1023) / 1024; // 5 / 4 (DmaTile), 5 / 3 (ChunkTile)
   static constexpr int kGroups = kLoads == 3 ? 1 : 2;   // 3 + 2 / 2 + 2 / 3 loads to a write of M0
   static constexpr uint32_t kBias = 4096;
   // where load n starts in the piece: the immediate it is issued with

@@ -8,9 +8,9 @@
 //   * it runs in half chunks of 32 keys, skewed by one half: S and dP of the next half are computed
 //     around the dQ MFMAs of this one, with this half's dS arithmetic under the former and the next
 //     half's exponentials under the latter;
-//   * the order is written out, one MFMA per slot with its share of the vector work, LDS reads and
-//     direct loads, and fenced so that the compiler keeps it (see sched_util.h for the measurements
-//     behind this); the A operands pass through a ring of registers requested a few MFMAs ahead;
+//   * the order is written out, one fragment and two 16x16x32 MFMAs per slot with their share of the vector work and LDS reads,
+//     and fenced so that the compiler keeps it (see sched_util.h for the measurements
+//     behind this); the A operands pass through a ring of registers requested a few slots ahead;
 //   * the direct loads of a tile are issued two or three to a write of M0.
 //
 // Head_dim 64, mask blocks below 64 tokens (FINE: chunks gathered from 16-key pieces) and ragged ends
@@ -18,7 +18,11 @@
 // per launch: 2 x 16 heads x 4096 x 64, blocks of 64: 50.1 -> 45.9 us; 2 x 16 x 3904 x 128 (61 blocks):
 // 73.3 -> 65.2 us; 1 x 16 x 8192 x 128, blocks of 16: 84.2 -> 70 us; a packed batch of 8 sequences of 200 to
 // 8192 rows x 32 heads: 497 us in two launches -> 478 us in one.  It is bound as the forward is: by the
-// matrix pipe and the vector work beside it over long lists, by a tile's start and end over short ones.
+// matrix pipe and the vector work beside it over long lists, by a tile's start and end over short ones.  The 16x16x32 shape (less power
+// to a flop and fewer bank conflicts, see bwd_kernel.hip), dP's contraction beginning at -delta instead of a subtraction a pair, and no chunk
+// fetched past a list's end, together: 1 x 32 x 32768 x 128 1.438 -> 1.385 ms, 4 x 32 x 8192 x 64 457 -> 425 us, 3 x 20 x 8192 x 64 with 32-token
+// blocks 138 -> 129, 2 x 16 x 3904 x 128 61.0 -> 59.2.  (One rolled loop of half steps whose ring goes on across the barriers, as in dK/dV,
+// was built: the same over long lists, 6 to 15 % slower over short ones, where its scalar work is not hidden.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -38,28 +42,29 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 template <int D>
 struct DqPipeSmem {
-  uint16_t k[2][DmaTile<D>::kElems];
-  uint16_t v[2][DmaTile<D>::kElems];
+  uint16_t k[2][ChunkTile<D>::kElems];
+  uint16_t v[2][ChunkTile<D>::kElems];
 };
 
 template <int D, bool DENSE, bool FINE, bool VARLEN>
-__global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p) {
-  typedef DmaTile<D> Tile;
-  typedef PieceTile<D> Piece;
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dq_pipe_kernel(const AttnParams p) {
+  typedef ChunkTile<D> Tile;
+  typedef PieceTile<D, Tile> Piece;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   DqPipeSmem<D>& sm = *reinterpret_cast<DqPipeSmem<D>*>(smem_raw);
   constexpr int BM = kBwdBM, MW = 32, CH = 64;
-  constexpr int KK = D / 16, DT = D / 32;
+  constexpr int KS = D / 32, FT = D / 16;  // 32-feature steps of S and dP, 16-feature tiles of dQ
+  constexpr int KK = D / 16;               // fragments of each contraction, two MFMAs each
+  static_assert(2 * KS == KK && FT == KK, "two 16-key tiles by KS steps; one 32-key slab by FT tiles");
   constexpr int NG = Piece::kGroups;
-  constexpr int RB = Tile::kStride * 2;  // bytes per tile row
-  constexpr int kSlots = 3 * KK;         // MFMAs (and fragments) per half step: KK of S, 2 * DT of dQ, KK of dP
-  constexpr int kLead = D == 128 ? 5 : 3, kRing = kLead + 1;  // (at D = 128 3 to 7 measure the same)
-  static_assert(2 * DT == KK, "the dQ part is as long as the S and dP parts");
+  constexpr int RB = Tile::RB;             // bytes per tile row
+  constexpr int kSlots = 3 * KK;           // fragments per half step: KK of S, KK of dQ, KK of dP
+  constexpr int kLead = D == 128 ? 5 : 3, kRing = kLead + 1;
   static_assert(!(DENSE && (FINE || VARLEN)), "the dense form walks 64-key blocks of whole sequences");
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   if (!DENSE && !VARLEN) clear_split_counts(p, blockIdx.x * kThreads + tid);
   const int T = p.q_tiles.tiles_per_head;
   const int T_run = VARLEN ? (p.q_rows + BM - 1) / BM : T;  // packed batch: tiles of the longest length allowed
@@ -163,9 +168,9 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
     const uint16_t* kg = kb + (int64_t)row * p.kv_st;
     const uint16_t* vg = vb + (int64_t)row * p.kv_st;
     static_for<NG>([&](auto gc) S2_INLINE {
-      constexpr int g = decltype(gc)::value;
-      Piece::template issue<g>(plan, kg, sm.k[stage], wave);
-      Piece::template issue<g>(plan, vg, sm.v[stage], wave);
+      constexpr int n = decltype(gc)::value;
+      Piece::template issue<n>(plan, kg, sm.k[stage], wave);
+      Piece::template issue<n>(plan, vg, sm.v[stage], wave);
     });
   };
   int row_n, state_c, state_n;
@@ -180,60 +185,93 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   // dO fragments (my half of the row's features, then the two halves added), written out with LSE
   // as the dK/dV kernel, which runs after this one, wants them.  A lane without a row of its own
   // reads the last row; nothing of it is stored.
-  bf16x8 qf[KK], gf[KK];
-  float part = 0.f;
-  const int my_row = min(qw0 + l32, N - 1);
+  // [32-feature step][16-query tile nt]
+  bf16x8 qf[KS][2], gf[KS][2];
+  float delta_l[2], lse_l[2];
+  {
+    bf16x8 of[KS][2];
+    int64_t stat_row[2];
+    // (all loads first: a wait between them would be a second trip to memory at every tile's start)
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    const int64_t o = q_off + (int64_t)my_row * p.q_st + 16 * kk + 8 * half;
-    qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + o);
-    gf[kk] = *reinterpret_cast<const bf16x8*>(p.d_o + o);
-    const bf16x8 of = *reinterpret_cast<const bf16x8*>(p.o + o);
+    for (int nt = 0; nt < 2; ++nt) {
+      const int my_row = min(qw0 + 16 * nt + l16, N - 1);
+      const int64_t at = q_off + (int64_t)my_row * p.q_st + 8 * g;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)gf[kk][e], (float)of[e], part);
-  }
-  const float delta_l = sum_halves(part);
-  const int64_t stat_row = VARLEN ? (int64_t)h * p.seqlen + row_base + my_row  // [heads, rows of the tensors]
-                                  : ((int64_t)b * p.heads + h) * N + my_row;
-  const float lse_l = p.lse[stat_row] * kLog2e;
-  if (half == 0 && qw0 + l32 < N) {
-    p.neg_delta[stat_row] = -delta_l;
-    p.neg_lse[stat_row] = p.lse[stat_row] * p.neg_inv_scale;
+      for (int kk = 0; kk < KS; ++kk) {
+        qf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.q + at + 32 * kk);
+        gf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.d_o + at + 32 * kk);
+        of[kk][nt] = *reinterpret_cast<const bf16x8*>(p.o + at + 32 * kk);
+      }
+      stat_row[nt] = VARLEN ? (int64_t)h * p.seqlen + row_base + my_row  // [heads, rows of the tensors]
+                            : ((int64_t)b * p.heads + h) * N + my_row;
+      lse_l[nt] = p.lse[stat_row[nt]];
+    }
+    S2_FENCE();
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+      float part = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)gf[kk][nt][e], (float)of[kk][nt][e], part);
+      delta_l[nt] = sum_groups(part);
+    }
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) {
+      if (g == 0 && qw0 + 16 * nt + l16 < N) {
+        p.neg_delta[stat_row[nt]] = -delta_l[nt];
+        p.neg_lse[stat_row[nt]] = lse_l[nt] * p.neg_inv_scale;
+      }
+      lse_l[nt] *= kLog2e;
+    }
   }
 
-  f32x16 acc[DT];
+  f32x4 acc[FT][2];  // dQ transposed [16-feature tile][16-query tile]: lane % 16 = query, register r = feature 4 * g + r
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x16{};
+  for (int ft = 0; ft < FT; ++ft)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) acc[ft][nt] = f32x4{};
+  // what the dP contraction begins with, so that it ends at dP - delta (a subtraction less a pair)
+  f32x4 dp0[2];
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) dp0[nt] = f32x4{-delta_l[nt], -delta_l[nt], -delta_l[nt], -delta_l[nt]};
   const float c = p.scale_log2e;
   // lane parts of the addresses the fragments are read at (stage 0 of K; V lies v_from_k further on)
-  const uint32_t k_lane = lds_addr(sm.k[0]) + l32 * RB + 16 * half, tr_lane = lds_addr(sm.k[0]) + 2 * Tile::tr_base(lane);
+  const uint32_t k_lane = lds_addr(sm.k[0]) + Tile::row_lane(lane), tr_lane = lds_addr(sm.k[0]) + Tile::tr_lane(lane);
   constexpr uint32_t v_from_k = sizeof(sm.k);
 
-  // Scores of a 32-key half: register r is key 8 * (r / 4) + 4 * half + r % 4 of the half, lane % 32
-  // the query.  sc holds S, then P in place; dp holds dP, then dS in place.
-  f32x16 sc[2], dp;  // sc[parity of the half]
-  u32x4 dsb[2];      // dS of this half as B operands [16-key slab]
+  // Scores of a 32-key half [16-key tile m][16-query tile nt]: register r is key 4 * g + r of the tile, lane % 16 the query.
+  // sc holds S, then P in place; dp holds dP - delta, then dS in place.
+  f32x4 sc[2][2][2], dp[2][2];  // sc[parity of the half]
+  u32x4 dsb[2];                 // dS of this half as B operands [16-query tile]
+  // element x (0..15), in the order of the B operands
+#define S2_AT(a, x) (a)[((x) >> 2) & 1][(x) >> 3][(x) & 3]
 
-  // Drops what my query does not see of half kt of chunk j: keys after it and (FINE) pieces its mask row
+  // Drops what my queries do not see of half kt of chunk j: keys after them and (FINE) pieces their mask row
   // does not keep.  (A half that is not mine at all gets lse = +inf instead: P = dS = 0.)
-  auto mask_half = [&](f32x16& s2, int j, int kt) S2_INLINE {
-    const int qpos = qw0 + l32;
+  auto mask_half = [&](f32x4 (&s2)[2][2], int j, int kt) S2_INLINE {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int m = 0; m < 2; ++m) {
       int row, bits = 3;
       if constexpr (FINE) {
-        piece_at(j, 2 * kt + u, row, bits);
+        piece_at(j, 2 * kt + m, row, bits);
       } else if (DENSE) {
-        row = j * CH + 32 * kt + 16 * u;
+        row = j * CH + 32 * kt + 16 * m;
       } else {
-        row = (list.peek(j >> cpb_sh) >> 16) * S + (j & cpb_m) * CH + 32 * kt + 16 * u;
+        row = (list.peek(j >> cpb_sh) >> 16) * S + (j & cpb_m) * CH + 32 * kt + 16 * m;
       }
-      // how many of the piece's keys I see, counted from the first one my half of the wavefront holds
-      int lim = qpos - row + 1 - 4 * half;
-      if (FINE && !((bits >> (l32 >> 4)) & 1)) lim = -4;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (8 * (i >> 2) + (i & 3) >= lim) s2[8 * u + i] = kNegInf;
+      for (int nt = 0; nt < 2; ++nt) {
+        if (FINE && !((bits >> nt) & 1)) {  // the mask row of these queries drops the piece
+          s2[m][nt] = f32x4{kNegInf, kNegInf, kNegInf, kNegInf};
+        } else if (row + 15 > qw0 + 16 * nt) {
+          // how many of the piece's keys my query sees, counted from the first one that my lane holds
+          const int lim = qw0 + 16 * nt + l16 - row + 1 - 4 * g;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (r >= lim) s2[m][nt][r] = kNegInf;
+        }
+      }
     }
   };
 
@@ -246,23 +284,25 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   // S, dP and P of the first half, one after the other
   {
     const uint32_t k_row = k_lane, v_row = k_lane + v_from_k;
-    sc[0] = f32x16{};
-    dp = f32x16{};
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      sc[0] = mfma32(__builtin_bit_cast(bf16x8, lds_read16(k_row, 32 * kk)), qf[kk], sc[0]);
-      dp = mfma32(__builtin_bit_cast(bf16x8, lds_read16(v_row, 32 * kk)), gf[kk], dp);
+    for (int f = 0; f < KK; ++f) {
+      const int m = f & 1, kk = f >> 1;
+      const bf16x8 kr = __builtin_bit_cast(bf16x8, lds_read16(k_row, Tile::row_off(m, kk))), vr = __builtin_bit_cast(bf16x8, lds_read16(v_row, Tile::row_off(m, kk)));
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        sc[0][m][nt] = mfma16(kr, qf[kk][nt], kk == 0 ? f32x4{} : sc[0][m][nt]);
+        dp[m][nt] = mfma16(vr, gf[kk][nt], kk == 0 ? dp0[nt] : dp[m][nt]);
+      }
     }
     act_cur = state_c & 1;
     on_cur = (state_c >> 4) & 3;
     if (state_c & 4) mask_half(sc[0], 0, 0);
-    const float l0 = act_cur ? lse_l : __builtin_inff();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sc[0][r] = fast_exp2(__builtin_fmaf(sc[0][r], c, -l0));
+    for (int x = 0; x < 16; ++x) S2_AT(sc[0], x) = fast_exp2(__builtin_fmaf(S2_AT(sc[0], x), c, act_cur ? -lse_l[x >> 3] : kNegInf));
     if (!act_cur || (FINE && on_cur != 3)) {  // (what does not come from a piece of mine may not be a number)
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (!act_cur || !((on_cur >> (r >> 3)) & 1)) sc[0][r] = dp[r] = 0.f;
+      for (int x = 0; x < 16; ++x)
+        if (!act_cur || !((on_cur >> ((x >> 2) & 1)) & 1)) S2_AT(sc[0], x) = S2_AT(dp, x) = 0.f;
     }
   }
 
@@ -284,81 +324,88 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
     act_cur = act_n;
     on_cur = on_n;
     if (!act_this && !act_n) {
-      sc[PAR ^ 1] = f32x16{};
-      dp = f32x16{};
+#pragma unroll
+      for (int x = 0; x < 16; ++x) S2_AT(sc[PAR ^ 1], x) = S2_AT(dp, x) = 0.f;
       return;
     }
     const uint32_t from_n = stn * (uint32_t)Tile::kBytes + 32 * KTN * RB, from_this = stc * (uint32_t)Tile::kBytes + 32 * KT * RB;
     const uint32_t row_off = act_n ? from_n : from_this, tr_off = act_this ? from_this : from_n;
-    uint32_t k_row = k_lane + row_off, k_tr = tr_lane + tr_off, k_tr1 = k_tr;
+    // rows of the next half's 16-key tiles, and of this half's (the transposed fragments hold both)
+    uint32_t k_row = k_lane + row_off, k_row1 = k_row, k_tr = tr_lane + tr_off, k_tr1 = k_tr;
     if constexpr (FINE) {
       const int on_r = act_n ? on_n : on_this, on_t = act_this ? on_this : on_n;
-      if (on_r != 3) k_row += (on_r == 1 ? 0 : 16 * RB) - (l32 >> 4) * 16 * RB;
-      if (on_t != 3) {
-        if (on_t == 2) k_tr += 16 * RB;
-        k_tr1 = k_tr - 16 * RB;
-      }
+      if (on_r == 2) k_row += 16 * RB;
+      if (on_r == 1) k_row1 -= 16 * RB;
+      if (on_t == 2) k_tr += 16 * RB;
+      if (on_t == 1) k_tr1 -= 16 * RB;
     }
-    uint32_t v_row = k_row + v_from_k;
-    asm volatile("" : "+v"(k_row), "+v"(v_row), "+v"(k_tr));
-    if constexpr (FINE) asm volatile("" : "+v"(k_tr1));
+    asm volatile("" : "+v"(k_row), "+v"(k_tr));
+    if constexpr (FINE) asm volatile("" : "+v"(k_row1), "+v"(k_tr1));
     bf16x8 fr[kRing];
-    // fragment f of the half step, in the order the MFMAs use them: KK row fragments of the next
-    // half's K, KK transposed fragments of this half's K (16-key slab, feature tile), KK row fragments
-    // of the next half's V
+    // fragment f of the half step, in the order the MFMAs use them: KK row fragments of the next half's K (tile f % 2, step f / 2), KK
+    // transposed fragments of this half's K (feature tile), KK row fragments of the next half's V
     auto frag_load = [&](auto fc) S2_INLINE {
       constexpr int f = decltype(fc)::value;
+      const uint32_t row_at = FINE && (f & 1) ? k_row1 : k_row;
       if constexpr (f < KK)
-        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(k_row, 32 * f));
+        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(row_at, Tile::row_off(f & 1, f >> 1)));
       else if constexpr (f < 2 * KK)
-        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read_tr(FINE && f - KK >= DT ? k_tr1 : k_tr, 16 * ((f - KK) / DT) * RB + 64 * ((f - KK) % DT), RB));
+        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read_tr2(k_tr, FINE ? k_tr1 : k_tr, Tile::tr_off(0, f - KK), Tile::tr_off(0, f - KK) + 16 * RB));
       else
-        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(v_row, 32 * (f - 2 * KK)));
+        fr[f % kRing] = __builtin_bit_cast(bf16x8, lds_read16(row_at, v_from_k + Tile::row_off(f & 1, (f - 2 * KK) >> 1)));
     };
     static_for<kLead>([&](auto fc) S2_INLINE { frag_load(fc); });
-    const float ln = act_n ? lse_l : __builtin_inff();
+    float neg_ln[2] = {act_n ? -lse_l[0] : kNegInf, act_n ? -lse_l[1] : kNegInf};
     S2_FENCE();
     static_for<kSlots>([&](auto nc) S2_INLINE {
       constexpr int n = decltype(nc)::value;
       if constexpr (n + kLead < kSlots) frag_load(std::integral_constant<int, n + kLead>{});
-      // the MFMA of the slot
-      if constexpr (n < KK)  // S of the next half
-        sc[PAR ^ 1] = mfma32(fr[n % kRing], qf[n], n == 0 ? f32x16{} : sc[PAR ^ 1]);
-      else if constexpr (n < 2 * KK)  // dQ of this half: slab, feature tile
-        acc[(n - KK) % DT] = mfma32(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[(n - KK) / DT]), acc[(n - KK) % DT]);
-      else  // dP of the next half
-        dp = mfma32(fr[n % kRing], gf[n - 2 * KK], n == 2 * KK ? f32x16{} : dp);
-      // dS = P * (dP - delta) of this half under the S MFMAs: RS registers a slot, a slab packed in the
-      // slot after its last one
-      constexpr int RS = 16 / KK;
-      if constexpr (n < KK) {
+      // the two MFMAs of the slot
 #pragma unroll
-        for (int r = RS * n; r < RS * (n + 1); ++r) dp[r] = sc[PAR][r] * (dp[r] - delta_l);
+      for (int nt = 0; nt < 2; ++nt) {
+        if constexpr (n < KK) {  // S of the next half
+          constexpr int m = n & 1, kk = n >> 1;
+          sc[PAR ^ 1][m][nt] = mfma16(fr[n % kRing], qf[kk][nt], kk == 0 ? f32x4{} : sc[PAR ^ 1][m][nt]);
+        } else if constexpr (n < 2 * KK) {  // dQ of this half: feature tile
+          acc[n - KK][nt] = mfma16(fr[n % kRing], __builtin_bit_cast(bf16x8, dsb[nt]), acc[n - KK][nt]);
+        } else {  // dP of the next half
+          constexpr int m = n & 1, kk = (n - 2 * KK) >> 1;
+          dp[m][nt] = mfma16(fr[n % kRing], gf[kk][nt], kk == 0 ? dp0[nt] : dp[m][nt]);
+        }
       }
-      if constexpr (n == KK / 2 || n == KK) {
-        constexpr int u = n == KK / 2 ? 0 : 1;
+      // dS = P * (dP - delta) of this half under the S MFMAs, complete and packed before dQ begins
+      constexpr int ND = KK - 1;
+      auto dupto = [](int i) { return i >= ND ? 16 : (16 * i + ND - 1) / ND; };
+      if constexpr (n < ND) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dsb[u][i] = pack2(dp[8 * u + 2 * i], dp[8 * u + 2 * i + 1]);
+        for (int x = dupto(n); x < dupto(n + 1); ++x) S2_AT(dp, x) *= S2_AT(sc[PAR], x);
+      }
+      if constexpr (n == KK - 1) {
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          dsb[nt] = u32x4{pack2(dp[0][nt][0], dp[0][nt][1]), pack2(dp[0][nt][2], dp[0][nt][3]), pack2(dp[1][nt][0], dp[1][nt][1]),
+                          pack2(dp[1][nt][2], dp[1][nt][3])};
       }
       // P = exp2(S * c - lse) of the next half under the dQ and dP MFMAs: RS registers a slot from the second slot after the
       // S MFMAs on, the exponential one slot behind the multiply-add
       if constexpr (n == KK + 1) {
         if (masked_n) mask_half(sc[PAR ^ 1], jn, KTN);
       }
-      constexpr int P0 = KK + 2;
+      constexpr int RS = 16 / KK, P0 = KK + 2;
       static_assert(P0 + KK + 1 <= kSlots, "all sixteen registers");
       if constexpr (n >= P0 && n < P0 + KK) {
 #pragma unroll
-        for (int r = RS * (n - P0); r < RS * (n - P0 + 1); ++r) sc[PAR ^ 1][r] = __builtin_fmaf(sc[PAR ^ 1][r], c, -ln);
+        for (int x = RS * (n - P0); x < RS * (n - P0 + 1); ++x) S2_AT(sc[PAR ^ 1], x) = __builtin_fmaf(S2_AT(sc[PAR ^ 1], x), c, neg_ln[x >> 3]);
       }
       if constexpr (n >= P0 + 1 && n < P0 + KK + 1) {
 #pragma unroll
-        for (int r = RS * (n - P0 - 1); r < RS * (n - P0); ++r) sc[PAR ^ 1][r] = fast_exp2(sc[PAR ^ 1][r]);
+        for (int x = RS * (n - P0 - 1); x < RS * (n - P0); ++x) S2_AT(sc[PAR ^ 1], x) = fast_exp2(S2_AT(sc[PAR ^ 1], x));
       }
       // Nothing to execute: ties the probabilities to this slot.  Their first use is in the next
       // half step, and the optimiser would otherwise collect the arithmetic there, after the last
       // MFMA of this one and out of its shadow.
-      if constexpr (n >= P0 && n < P0 + KK + 1) asm volatile("" : "+v"(sc[PAR ^ 1]));
+      if constexpr (n >= P0 && n < P0 + KK + 1)
+        asm volatile("" : "+v"(sc[PAR ^ 1][0][0]), "+v"(sc[PAR ^ 1][0][1]), "+v"(sc[PAR ^ 1][1][0]), "+v"(sc[PAR ^ 1][1][1]));
       S2_FENCE();
     });
   };
@@ -369,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   // when the second half step reads its K and V rows
   for (int ch = 0; ch < total; ++ch) {
     const int st = ch & 1;
-    issue_chunk(row_n, st ^ 1);  // past the end of the list: the last chunk once more
+    if (ch + 1 < total) issue_chunk(row_n, st ^ 1);
     half_step(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, st, st, ch, state_c);
     wait_all_loads();
     __syncthreads();
@@ -391,13 +438,13 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
   uint16_t* stage = sm.k[0] + wave * MW * RS;
   static_assert(4 * MW * RS <= 2 * Tile::kElems, "the staging rows fit the K stages");
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt)
+  for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int nt = 0; nt < 2; ++nt) {
       bf16x4 w;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[dt][4 * g + e] * p.scale);
-      *reinterpret_cast<bf16x4*>(stage + l32 * RS + 32 * dt + 8 * g + 4 * half) = w;
+      for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[ft][nt][e] * p.scale);
+      *reinterpret_cast<bf16x4*>(stage + (16 * nt + l16) * RS + 16 * ft + 4 * g) = w;
     }
   uint16_t* obase = p.dq + q_off + (int64_t)qw0 * p.q_st;
   constexpr int PPR = D / 8, RPI = 64 / PPR;  // 16-byte pieces per row, rows per instruction
@@ -408,6 +455,8 @@ __global__ __launch_bounds__(kThreads, 2) void dq_pipe_kernel(const AttnParams p
     if (!VARLEN || qw0 + r < N) *reinterpret_cast<u32x4*>(obase + (int64_t)r * p.q_st + 8 * piece) = x;
   }
 }
+
+#undef S2_AT
 
 // A kernel's dynamic LDS limit is a per-device attribute: remember, per device, that it is set.
 constexpr int kMaxDevices = 64;

@@ -49,7 +49,7 @@ __device__ __forceinline__ u32x4 lds_read16(uint32_t addr, int byte_off) {
 __device__ __forceinline__ f32x4 lds_read_f32x4(uint32_t addr, int byte_off) {
   return *S2_LDS_PTR(f32x4, addr + byte_off);
 }
-// transposed fragment (see DmaTile::tr_frag): two ds_read_b64_tr_b16, the second 8 rows further on ...
+// transposed fragment (see DmaTile::tr_base, ChunkTile::tr_lane): two ds_read_b64_tr_b16, the second 8 rows further on ...
 __device__ __forceinline__ u32x4 lds_read_tr2(uint32_t addr_lo, uint32_t addr_hi, int off_lo, int off_hi) {
   typedef short s16x4_ __attribute__((ext_vector_type(4)));
   typedef short s16x8_ __attribute__((ext_vector_type(8)));
