@@ -274,6 +274,18 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     ds_wave = p.ds_store + ((int64_t)b * p.ds_units + (((int64_t)ent_lo << cpb_sh) * 2 + (wave >> 1))) * 4096 + (wave & 1) * 2048;
   EntryList list;
   if (!DENSE) list.init(p.kv_tiles.ent + ent_lo, n_ent, lane);
+  // K and V fragments (B operands) [32-feature step][16-key tile], lane % 16 = key of the tile; requested while the list is on its way
+  bf16x8 kf[KS][2], vf[KS][2];
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    // (a lane whose key does not exist reads an existing one: every pair of it is masked and nothing is stored)
+    const int64_t row = kv_off + (int64_t)min(key_of(16 * nt + (lane & 15)), N - 1) * p.kv_st + 8 * (lane >> 4);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      kf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.k + row + 32 * kk);
+      vf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.v + row + 32 * kk);
+    }
+  }
   // FINE: the entries of step j, in lanes EPC * j % 64 and on (0 after the end of the list: attends nobody)
   auto entries_at = [&](int j) S2_INLINE { return ((EPC * j) >> 6) != list.batch ? list.nxt : list.cur; };
   auto entry = [&](int src, int i) S2_INLINE { return (uint32_t)__builtin_amdgcn_readlane(src, i & 63); };
@@ -359,19 +371,6 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   }
   if (!kSplits || total > 0) issue_chunk(plan, it0, it0 & 1, lane);  // (where a head's tile is short for its rank a part may be empty)
 
-  // K and V fragments (B operands) [32-feature step][16-key tile], lane % 16 = key of the tile
-  bf16x8 kf[KS][2], vf[KS][2];
-#pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    // (a lane whose key does not exist reads an existing one: every pair of it is masked and nothing is stored)
-    const int64_t row = kv_off + (int64_t)min(key_of(16 * nt + (lane & 15)), N - 1) * p.kv_st + 8 * (lane >> 4);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      kf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.k + row + 32 * kk);
-      vf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.v + row + 32 * kk);
-    }
-  }
-
   // dK and dV, transposed [16-feature tile][16-key tile]: lane % 16 = key, register r = feature 4 * (lane / 16) + r
   f32x4 acc_dk[FT][2], acc_dv[FT][2];
 #pragma unroll
@@ -388,18 +387,22 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
   // whose entries are in ents.
   uint32_t ents[EPC] = {};
   int it = __builtin_amdgcn_readfirstlane(it0) - 1, qt = 0, qt1 = 0, q0 = 0, stores = 0;  // stores: dS stores since the last direct loads
-  // opens step it: requests the chunk of the step after it into the other stage, and finds the halves that hold something for my keys
-  auto open_step = [&]() S2_INLINE {
-    const int ln = lane_now();
-    // keeps the entry window moving (entries of this step on)
-    if (!DENSE) (void)list.get(FINE ? EPC * it : it >> cpb_sh, ln);
-    if (it + 1 < total) {
-      typename Piece::Plan pl;
-#pragma unroll
-      for (int n = 0; n < Piece::kLoads; ++n) pl.goff[n] = sm.goff[n][ln];
-      issue_chunk(pl, it + 1, (it + 1) & 1, ln);
-    }
+  bool refill = false;  // the chunk of the step after this one has yet to be requested, into the other stage
+  auto request_next = [&]() S2_INLINE {
+    refill = false;
     stores = 0;
+    if (it + 1 >= total) return;
+    const int ln = lane_now();
+    typename Piece::Plan pl;
+#pragma unroll
+    for (int n = 0; n < Piece::kLoads; ++n) pl.goff[n] = sm.goff[n][ln];
+    issue_chunk(pl, it + 1, (it + 1) & 1, ln);
+  };
+  // opens step it: finds the halves that hold something for my keys
+  auto open_step = [&]() S2_INLINE {
+    // keeps the entry window moving (entries of this step on)
+    if (!DENSE) (void)list.get(FINE ? EPC * it : it >> cpb_sh, lane_now());
+    refill = true;
     int lo = 0, hi = 0;
     if constexpr (FINE) {
       // which pieces of the step attend keys of mine, from every lane's entry at once
@@ -438,6 +441,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
       it = __builtin_amdgcn_readfirstlane(it + 1);
       if (it >= total) return false;
       open_step();
+      if (qt >= qt1) request_next();
     } while (qt >= qt1);
     return true;
   };
@@ -484,6 +488,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
     stats_load(0);
     stats_load(1);
     static_for<kLead>([&](auto fc) S2_INLINE { frag_load(fc); });
+    request_next();
     do {
       // row of tile m's first row, and (FINE) the list entry it comes from
       int row[2] = {q0 + 32 * qt, q0 + 32 * qt + 16};
@@ -528,6 +533,9 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dkdv_kernel(const 
           aim_rows();
         }
         frag_load(std::integral_constant<int, n + kLead>{});
+        if constexpr (n == 4 * KK - 1) {
+          if (refill) request_next();  // (after the first fragments of the step, which its MFMAs wait for)
+        }
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
           if constexpr (n < KK) {

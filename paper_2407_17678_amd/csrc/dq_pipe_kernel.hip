@@ -160,6 +160,30 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dq_pipe_kernel(con
     if (VARLEN) row = min(row, N - 1);
   };
 
+  // Q^T and dO^T fragments (B operands), lane = query; delta = rowsum(dO * O) of my query from the
+  // dO fragments (my half of the row's features, then the two halves added), written out with LSE
+  // as the dK/dV kernel, which runs after this one, wants them.  A lane without a row of its own
+  // reads the last row; nothing of it is stored.
+  // [32-feature step][16-query tile nt]
+  bf16x8 qf[KS][2], gf[KS][2];
+  float delta_l[2], lse_l[2];
+  bf16x8 of[KS][2];
+  int64_t stat_row[2];
+  // (all loads first, while the list is on its way: a wait between them would be a second trip to memory at every tile's start)
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int my_row = min(qw0 + 16 * nt + l16, N - 1);
+    const int64_t at = q_off + (int64_t)my_row * p.q_st + 8 * g;
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+      qf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.q + at + 32 * kk);
+      gf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.d_o + at + 32 * kk);
+      of[kk][nt] = *reinterpret_cast<const bf16x8*>(p.o + at + 32 * kk);
+    }
+    stat_row[nt] = VARLEN ? (int64_t)h * p.seqlen + row_base + my_row  // [heads, rows of the tensors]
+                          : ((int64_t)b * p.heads + h) * N + my_row;
+    lse_l[nt] = p.lse[stat_row[nt]];
+  }
   typename Piece::Plan plan = Piece::plan(p.kv_st, lane);
   auto issue_chunk = [&](int row, int stage) S2_INLINE {
     // where a packed sequence ends inside the rows I fetch they are limited to the rows that exist; the
@@ -181,49 +205,23 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void dq_pipe_kernel(con
     issue_chunk(row_c, 0);
   }
 
-  // Q^T and dO^T fragments (B operands), lane = query; delta = rowsum(dO * O) of my query from the
-  // dO fragments (my half of the row's features, then the two halves added), written out with LSE
-  // as the dK/dV kernel, which runs after this one, wants them.  A lane without a row of its own
-  // reads the last row; nothing of it is stored.
-  // [32-feature step][16-query tile nt]
-  bf16x8 qf[KS][2], gf[KS][2];
-  float delta_l[2], lse_l[2];
-  {
-    bf16x8 of[KS][2];
-    int64_t stat_row[2];
-    // (all loads first: a wait between them would be a second trip to memory at every tile's start)
+  S2_FENCE();
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const int my_row = min(qw0 + 16 * nt + l16, N - 1);
-      const int64_t at = q_off + (int64_t)my_row * p.q_st + 8 * g;
+  for (int nt = 0; nt < 2; ++nt) {
+    float part = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        qf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.q + at + 32 * kk);
-        gf[kk][nt] = *reinterpret_cast<const bf16x8*>(p.d_o + at + 32 * kk);
-        of[kk][nt] = *reinterpret_cast<const bf16x8*>(p.o + at + 32 * kk);
-      }
-      stat_row[nt] = VARLEN ? (int64_t)h * p.seqlen + row_base + my_row  // [heads, rows of the tensors]
-                            : ((int64_t)b * p.heads + h) * N + my_row;
-      lse_l[nt] = p.lse[stat_row[nt]];
+    for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)gf[kk][nt][e], (float)of[kk][nt][e], part);
+    delta_l[nt] = sum_groups(part);
+  }
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    if (g == 0 && qw0 + 16 * nt + l16 < N) {
+      p.neg_delta[stat_row[nt]] = -delta_l[nt];
+      p.neg_lse[stat_row[nt]] = lse_l[nt] * p.neg_inv_scale;
     }
-    S2_FENCE();
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      float part = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) part = __builtin_fmaf((float)gf[kk][nt][e], (float)of[kk][nt][e], part);
-      delta_l[nt] = sum_groups(part);
-    }
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      if (g == 0 && qw0 + 16 * nt + l16 < N) {
-        p.neg_delta[stat_row[nt]] = -delta_l[nt];
-        p.neg_lse[stat_row[nt]] = lse_l[nt] * p.neg_inv_scale;
-      }
-      lse_l[nt] *= kLog2e;
-    }
+    lse_l[nt] *= kLog2e;
   }
 
   f32x4 acc[FT][2];  // dQ transposed [16-feature tile][16-query tile]: lane % 16 = query, register r = feature 4 * g + r
