@@ -106,6 +106,9 @@ hipError_t launch_bwd(const AttnParams& p, bool dense, int stages, hipStream_t s
 hipError_t launch_dq(const AttnParams& p, bool dense, hipStream_t stream);
 // The dQ launch of the backward that keeps dS: dQ = scale * dS K over the stored units.
 hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream);
+// dQ and dK/dV of a backward that recomputes S and dP in one launch, after delta: whether the two are better off so, and the launch.
+bool bwd_is_merged(const AttnParams& p);
+hipError_t launch_bwd_merged(const AttnParams& p, bool dense, hipStream_t stream);
 // The most workgroups of a decode call that are of eight wavefronts instead of four.  One to a compute unit,
 // they keep twice the units of a (sequence, head) in flight: 32 pairs of 16 units in one split 13.2 -> 9.8 us, 19
 // units 15.8 -> 11.1; 64 pairs of 34 units in three splits 13.2 -> 11.3.  A grid with more of them brings no
