@@ -1,5 +1,5 @@
-// One workgroup's share of the dK/dV launch: a tile of 128 keys (or a part of one), column-stationary - see bwd_kernel.hip, and
-// bwd_merged_kernel.hip for launches that hold dQ tiles too.
+// One workgroup's share of the dK/dV launch: a tile of 128 keys (or a part of one), column-stationary - of the launch in bwd_kernel.hip, or
+// of that in bwd_merged_kernel.hip, which holds dQ tiles too.
 //
 // The dK/dV loop is written out fragment by fragment, one slot and two MFMAs each (see sched_util.h): for 32 query rows S, dP, dV and dK one
 // after the other, the exponentials under dP, dS = P * dP under dV, each LDS fragment requested three slots ahead of its use through a ring

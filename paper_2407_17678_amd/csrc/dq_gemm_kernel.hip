@@ -2,8 +2,8 @@
 // dK/dV kernel, which runs first, has left dS = P * (dP - delta) in the workspace, rounded to bf16
 // exactly as its own dK contraction takes it, so what remains of the gradient of section 3.2's
 // forward on the query side is the single contraction dQ = scale * dS K over the kept blocks -
-// nothing is recomputed (the row-stationary kernels in bwd_kernel.hip / dq_pipe_kernel.hip form S
-// and dP a second time to get at dS).
+// nothing is recomputed (the row-stationary kernel in dq_pipe_kernel.hip forms S and dP a second time
+// to get at dS).
 //
 // A workgroup owns 128 query rows and walks the 64-key chunks of the KV blocks its mask rows keep,
 // as the other row-stationary kernels do.  Its four wavefronts split a chunk two by two: 64 query

@@ -1,9 +1,8 @@
 // One workgroup's share of the dQ launch: a tile of 128 query rows, the row-stationary half of the backward pass (the gradient of the forward of section 3.2).
 // Same tiles, lists, staging and orientation as the forward (fwd_pipe_kernel.hip) - a workgroup owns 128
 // query rows, a wavefront 32 of them, and walks the 64-key chunks of the KV blocks its mask rows keep,
-// recomputing P and forming dS = P * (dP - delta), dQ += scale * dS K; it also computes
-// delta = rowsum(dO * O) and leaves the row statistics in the workspace for the dK/dV
-// kernel - with a hand-scheduled inner loop:
+// recomputing P and forming dS = P * (dP - delta), dQ += scale * dS K; where dK/dV is a later launch it also computes
+// delta = rowsum(dO * O) and leaves the row statistics in the workspace for it - with a hand-scheduled inner loop:
 //
 //   * it runs in half chunks of 32 keys, skewed by one half: S and dP of the next half are computed
 //     around the dQ MFMAs of this one, with this half's dS arithmetic under the former and the next
