@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
     (128, 3, 8, 2560, 16, 16, False, False),                                       # 2.36
     (64, 1, 8, 10240, 4, 8, False, True),                                          # 8.9
 ])
-def test_cut_into_a_second_round(D, batch, H, N, local, stride, keep_ds, cut):
-    print("second round", D, batch, H, N, local, keep_ds, flush=True)
+def test_cut_beyond_the_slots(D, batch, H, N, local, stride, keep_ds, cut):
+    print("cut beyond the slots", D, batch, H, N, local, keep_ds, flush=True)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(D + batch + N + local)
     q, k, v, g = (torch.randn((batch, H, N, D), device="cuda", generator=gen).bfloat16() for _ in range(4))
