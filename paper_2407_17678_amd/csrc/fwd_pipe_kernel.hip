@@ -157,9 +157,10 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   float mc = 0.f;         // the same times scale * log2(e); 0 while nothing was seen
   float l_run = 0.f;      // sum of the probabilities over my half's key rows
   const float c = p.scale_log2e;
-  // how far a score may exceed the reference maximum before it is moved (raw scores; see the top of this file)
+  // how far a score may exceed the reference maximum before it is moved (raw scores; see the top of this file).  Finite, also
+  // where 2^kTau is out of reach of any score: the first maximum has to move it from -inf.
   const bool lazy_ref = D == 128 && (VARLEN ? (tile + 1) * BM <= N : p.q_rows % BM == 0);
-  const float tau = lazy_ref ? kTau / c : 0.f;
+  const float tau = lazy_ref ? fminf(kTau / c, 3.4e38f) : 0.f;
   // The lane offsets of my direct loads, for K and for V.  Where a packed sequence ends inside the rows
   // I fetch (VARLEN) they are limited to the rows that exist; the lists ascend, so from then on every
   // piece is such a piece, with fewer and fewer rows.
