@@ -148,8 +148,11 @@ s2::AttnParams make_params(const s2_tensors* t, float scale) {
   p.kv_st = t->kv_stride_t;
   p.scale = scale;
   p.scale_log2e = scale * 1.4426950408889634f;
-  // (clamped so that lse / scale stays finite where no score is beyond 2^100)
-  p.neg_inv_scale = -1.0f / fmaxf(scale, 4e-38f);
+  // The dK/dV kernel forms P as exp(s * (S - lse / s)).  s is the scale, but not below 2^-120, so that lse / s is finite; where it is not
+  // the scale P is off by a factor of exp(S * (s - scale)), which is 1 to float32's precision for |S| up to 2^96.
+  const float s = std::max(scale, 0x1p-120f);
+  p.neg_inv_scale = -1.0f / s;
+  p.p_scale_log2e = s * 1.4426950408889634f;
   return p;
 }
 

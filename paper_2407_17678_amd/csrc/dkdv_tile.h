@@ -309,7 +309,7 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
   for (int ft = 0; ft < FT; ++ft)
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) acc_dk[ft][nt] = acc_dv[ft][nt] = f32x4{};
-  const float c = p.scale_log2e;
+  const float c = p.p_scale_log2e;
   if (wave == 0) {
 #pragma unroll
     for (int n = 0; n < Piece::kLoads; ++n) sm.goff[n][lane] = plan.goff[n];

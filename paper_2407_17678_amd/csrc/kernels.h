@@ -27,9 +27,9 @@ struct AttnParams {
   uint16_t* dk;
   uint16_t* dv;
   // Workspace, [batch, heads, seqlen] each: what the dK/dV kernel's accumulators begin with, so that the score contraction ends
-  // at S - lse / scale (P = exp2 of it times scale * log2(e)) and the other at dP - delta
+  // at S - lse / scale (P = exp2 of it times p_scale_log2e) and the other at dP - delta
   float* neg_delta;  // -rowsum(dO * O)
-  float* neg_lse;    // -lse / scale
+  float* neg_lse;    // lse * neg_inv_scale
   int batch, heads, seqlen, head_dim;
   // q, o, lse hold q_rows rows, local row r being sequence position q_row0 + r (the whole sequence,
   // as in every backward of a fixed length: q_row0 = 0, q_rows = seqlen)
@@ -43,7 +43,9 @@ struct AttnParams {
   int64_t kv_sb, kv_sh, kv_st;
   float scale;        // softmax scale
   float scale_log2e;  // scale * log2(e)
-  float neg_inv_scale;  // -1 / scale (backward)
+  // Backward: the scale of the dK/dV kernel's exponent is the softmax scale or, if that is smaller, 2^-120 (make_params)
+  float neg_inv_scale;  // -1 / that
+  float p_scale_log2e;  // that * log2(e)
   int block_size;     // S (sparse path); 64 on the dense path
   DevTiles q_tiles;   // row tiles of the forward and dQ kernels -> KV blocks
   DevTiles kv_tiles;  // column tiles -> Q blocks

@@ -1,5 +1,6 @@
 """The dK/dV kernel starts its score accumulators at -lse / scale: gradients over softmax scales at which that is large
-against the scores (small scales), of their size, and small against them (large ones), for each form of the kernel."""
+against the scores (small scales, down to the smallest that is accepted, where it would not be finite), of their size, and small
+against them (large ones), for each form of the kernel."""
 
 import numpy as np
 import pytest
@@ -15,7 +16,7 @@ pytestmark = pytest.mark.gpu
 GRAD_TOL = 2e-2  # relative L2 bound on gradients, as in test_gpu_bwd.py
 
 
-@pytest.mark.parametrize("scale", [1e-30, 1e-4, 0.125, 2.0])
+@pytest.mark.parametrize("scale", [2.0 ** -149, 1e-38, 2e-38, 5e-38, 2.0 ** -121, 1e-30, 1e-4, 0.125, 2.0, 1e30])
 @pytest.mark.parametrize("D,S,N,form", [(128, 64, 192, "small"), (128, 64, 320, "keep"), (64, 64, 192, "small"), (128, 16, 160, "small"),
                                         (64, 32, 224, "small"), (128, 64, 203, "packed"), (64, 16, 75, "packed"), (128, 64, 256, "dense")])
 def test_scales(D, S, N, form, scale):
@@ -24,7 +25,9 @@ def test_scales(D, S, N, form, scale):
     rng = np.random.Generator(np.random.PCG64([synth.BASE_SEED, D, S, N]))
     # scores of about +-3 after scaling where the scale is large, so that rows are peaked but not of one key
     size = min(1.0, 3.0 / (scale * np.sqrt(D)))
-    bits = [synth.round_to_bf16_bits(rng.standard_normal((1, H, N, D)).astype(np.float32) * f) for f in (size, 1.0, 1.0, 1.0)]
+    # gradients of about 1e-30 or more, which bf16 holds with all its bits
+    grad = np.float32(max(1.0, 1e-30 / scale))
+    bits = [synth.round_to_bf16_bits(rng.standard_normal((1, H, N, D)).astype(np.float32) * np.float32(f)) for f in (size, 1.0, 1.0, grad)]
     q, k, v, g = (G.to_dev(b) for b in bits)
     o, lse = torch.empty_like(q), torch.empty((1, H, N), dtype=torch.float32, device="cuda")
     grads = [torch.empty_like(q) for _ in range(3)]
