@@ -280,7 +280,8 @@ size_t s2_attn_bwd_varlen_workspace_bytes(int32_t heads, int32_t rows, int32_t h
  * (an OR of the flags below) so that a profiler or a benchmark can time each launch on its own;
  * with S2_BWD_ALL it is s2_attn_bwd.  S2_BWD_DKDV needs delta in the workspace: from S2_BWD_DQ in
  * the same or an earlier call, or from S2_BWD_DELTA, a stand-alone delta kernel that only runs
- * when S2_BWD_DQ is not part of the call.  With the larger workspace of
+ * when S2_BWD_DQ is not part of the call.  A call that does not form delta itself takes that
+ * and nothing else from the earlier one: a small launch ahead of dK/dV forms what depends on its own scale and lse.  With the larger workspace of
  * s2_attn_bwd_layout_workspace_bytes the order is delta kernel (S2_BWD_DELTA), dK/dV (S2_BWD_DKDV,
  * needs delta, leaves dS), dQ (S2_BWD_DQ, needs dS from S2_BWD_DKDV in the same or an earlier call
  * on the same workspace).  Errors as s2_attn_bwd, plus BAD_PARAM for stages. */

@@ -153,14 +153,18 @@ hipError_t launch_delta(const AttnParams& p, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// The counters of the cut key tiles for a dK/dV launch that is not preceded by delta or dQ in its own call: what
-// an earlier call left there is not known (it may have had a smaller workspace).
-__global__ __launch_bounds__(256) void clear_counts_kernel(const AttnParams p) { clear_split_counts(p, blockIdx.x * 256 + threadIdx.x); }
+// For a dK/dV launch that is not preceded by delta or dQ in its own call, which brings delta from an earlier one and nothing else: -lse /
+// scale goes by this call's scale, and what is in the counters of the cut key tiles is not known (the earlier call may
+// have had a smaller workspace).
+__global__ __launch_bounds__(256) void prepare_dkdv_kernel(const AttnParams p) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (more rows than tiles)
+  clear_split_counts(p, (int)min(i, (int64_t)1 << 30));
+  if (i < (int64_t)p.batch * p.heads * p.seqlen) p.neg_lse[i] = p.lse[i] * p.neg_inv_scale;
+}
 
-hipError_t launch_clear_counts(const AttnParams& p, hipStream_t stream) {
-  if (p.split_items == 0) return hipSuccess;
-  const int tiles = p.batch * p.heads * p.kv_tiles.tiles_per_head;
-  hipLaunchKernelGGL(clear_counts_kernel, dim3((tiles + 255) / 256), dim3(256), 0, stream, p);
+hipError_t launch_prepare_dkdv(const AttnParams& p, hipStream_t stream) {
+  const int64_t rows = (int64_t)p.batch * p.heads * p.seqlen;
+  hipLaunchKernelGGL(prepare_dkdv_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream, p);
   return hipGetLastError();
 }
 
@@ -174,7 +178,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
       if (stages & kBwdDelta)
         e = launch_delta<D>(p, stream);
       else if (stages & kBwdDkDv)
-        e = launch_clear_counts(p, stream);
+        e = launch_prepare_dkdv(p, stream);
       if (e == hipSuccess && (stages & kBwdDkDv)) e = launch_dkdv<D, false, 0, false, true>(p, stream);
       if (e == hipSuccess && (stages & kBwdDq)) e = launch_dq_gemm(p, stream);
       return e;
@@ -193,7 +197,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
   else if (stages & kBwdDelta)
     e = launch_delta<D>(p, stream);
   else
-    e = launch_clear_counts(p, stream);
+    e = launch_prepare_dkdv(p, stream);
   if (e != hipSuccess || !(stages & kBwdDkDv)) return e;
   if (dense) return launch_dkdv<D, true, 0, false, false>(p, stream);
   if (p.cu_seqlens) {

@@ -52,8 +52,8 @@ struct AttnParams {
   // Key tiles cut into parts (SplitLevel in layout.h; split_items == 0: none are): the first split_items
   // items of a head are parts of its first split_long tiles.  The parts' sums go to split_sums, [batch *
   // heads][item][wavefront][accumulator quad][lane][4] floats, and split_count[batch * heads][tile] counts the
-  // parts that are done: it is zero before the launch (the launch before it clears it: the one that leaves delta, or one
-  // of its own where the call has none of those).
+  // parts that are done: it is zero before the launch (the launch before it clears it: the one that leaves delta, or the
+  // one that prepares a call for dK/dV alone).
   const int32_t* split_codes;
   float* split_sums;
   int32_t* split_count;
