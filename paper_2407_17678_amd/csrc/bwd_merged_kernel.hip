@@ -74,8 +74,13 @@ hipError_t launch_dim(const AttnParams& p, bool dense, hipStream_t stream) {
 // The compute units hold 512 (head_dim 128) or 768 (64) of these workgroups at a time.  A launch of a few times as many gains by the start and the
 // end that it has once instead of twice; at 4096 that has sunk to what the pass over O and dO on its own costs, and from 8192 on that pass costs
 // up to 2 % (measured above).
+// Two launches also where dK and dV replace K and V (either way round): a key tile writes only what it alone reads, but in one launch the
+// dQ tiles read every tile's K and V beside it.
 constexpr int kMergedGrid = 4096;
-bool bwd_is_merged(const AttnParams& p) { return (int64_t)key_grid(p) + query_grid(p) <= kMergedGrid; }
+bool bwd_is_merged(const AttnParams& p) {
+  const bool in_place = p.dk == p.k || p.dk == p.v || p.dv == p.k || p.dv == p.v;
+  return !in_place && (int64_t)key_grid(p) + query_grid(p) <= kMergedGrid;
+}
 
 hipError_t launch_bwd_merged(const AttnParams& p, bool dense, hipStream_t stream) {
   return p.head_dim == 128 ? launch_dim<128>(p, dense, stream) : launch_dim<64>(p, dense, stream);
