@@ -1,5 +1,5 @@
 """Up to 4096 workgroups in all a backward runs dQ and dK/dV in one launch after delta: its gradients are those of the two
-launches, bit for bit, on both sides of that size."""
+launches, bit for bit, on both sides of that size, and so the kernels of either are held to the results of the other."""
 
 import numpy as np
 import pytest
@@ -67,3 +67,58 @@ def test_packed_sequences_as_if_alone(D, S):
             assert torch.isfinite(b.float()).all(), name
             assert torch.equal(a[:, :, lo:lo + n], b), (name, n)
         lo += n
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_dense_in_one_launch_and_two(D):
+    # 72 heads of 29 tiles of either kind are beyond 4096 workgroups, 36 of them are not
+    H, N, scale = 72, 3712, D ** -0.5
+    print("dense backward", H, N, D, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(D)
+    q, k, v, g = (torch.randn((1, H, N, D), device="cuda", generator=gen).bfloat16() for _ in range(4))
+
+    def run(q, k, v, g):
+        heads = q.shape[1]
+        o, lse = torch.empty_like(q), torch.empty((1, heads, N), dtype=torch.float32, device="cuda")
+        grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+        ws = torch.full((B.s2_dense_causal_bwd_workspace_bytes(1, heads, N, D),), 0xFF, dtype=torch.uint8, device="cuda")
+        B.s2_dense_causal_fwd(q, k, v, o, lse, scale)
+        B.s2_dense_causal_bwd(q, k, v, o, lse, g, *grads, scale, ws)
+        torch.cuda.synchronize()
+        return grads
+
+    whole = run(q, k, v, g)
+    for lo in (0, 36):
+        part = run(*(x[:, lo:lo + 36].contiguous() for x in (q, k, v, g)))
+        for name, a, b in zip(("dq", "dk", "dv"), whole, part):
+            assert torch.isfinite(a.float()).all(), name
+            assert torch.equal(a[:, lo:lo + 36], b), (name, lo)
+
+
+@pytest.mark.parametrize("S", [16, 32, 64, 128])
+@pytest.mark.parametrize("D", [64, 128])
+def test_packed_in_one_launch_and_two(D, S):
+    # The grid goes by the layout (key tiles) and by the longest length allowed (query tiles): the same sequences with a small
+    # and with a large one are 8 * (258 + 5) and 8 * (258 + 258) workgroups.
+    H, lens, scale, long = 2, [200, 37, 600, 128], D ** -0.5, 258 * 128
+    total = sum(lens)
+    print("packed backward", D, S, flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(D + S)
+    q, k, v, g = (torch.randn((1, H, total, D), device="cuda", generator=gen).bfloat16() for _ in range(4))
+    lay = B.s2_layout_build(B.layout_params(H, long // S, S, max(1, 64 // S), 5))
+    assert B.s2_layout_get_tiles(lay, B.TILES_DKDV)["tiles_per_head"] == 258
+    cu = torch.tensor([0] + list(np.cumsum(lens)), dtype=torch.int32, device="cuda")
+    o, lse = torch.empty_like(q), torch.empty((H, total), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd_varlen(lay, q, k, v, o, lse, cu, 640, scale)
+    out = []
+    for longest in (640, long):
+        grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+        ws = torch.full((B.s2_attn_bwd_varlen_workspace_bytes(H, total, D),), 0xFF, dtype=torch.uint8, device="cuda")
+        B.s2_attn_bwd_varlen(lay, q, k, v, o, lse, g, *grads, cu, longest, scale, ws)
+        torch.cuda.synchronize()
+        out.append(grads)
+    for name, a, b in zip(("dq", "dk", "dv"), *out):
+        assert torch.isfinite(a.float()).all(), name
+        assert torch.equal(a, b), name
