@@ -20,12 +20,11 @@
 // 16 + 4 * g + 0..3].
 #include <hip/hip_runtime.h>
 
-#include <atomic>
-
 #include "config.h"
 #include "device_util.h"
 #include "kernels.h"
 #include "sched_util.h"
+#include "smem_limit.h"
 
 namespace s2 {
 
@@ -232,23 +231,12 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
   }
 }
 
-// A kernel's dynamic LDS limit is a per-device attribute: remember, per device, that it is set.
-constexpr int kMaxDevices = 64;
-std::atomic<unsigned char> g_smem_set[kMaxDevices];
-
 }  // namespace
 
 hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream) {
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
+  static SmemSet set;  // zero-initialised
+  const hipError_t e = set_smem(&dq_gemm_kernel<128>, sizeof(DqGemmSmem<128>), set);
   if (e != hipSuccess) return e;
-  const bool tracked = dev >= 0 && dev < kMaxDevices;
-  if (!tracked || !g_smem_set[dev].load(std::memory_order_acquire)) {
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&dq_gemm_kernel<128>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(DqGemmSmem<128>));
-    if (e != hipSuccess) return e;
-    if (tracked) g_smem_set[dev].store(1, std::memory_order_release);
-  }
   const int grid = grid_for(p.batch * p.heads, p.q_tiles.tiles_per_head);
   hipLaunchKernelGGL((dq_gemm_kernel<128>), dim3(grid), dim3(kThreads), sizeof(DqGemmSmem<128>), stream, p);
   return hipGetLastError();
