@@ -274,9 +274,9 @@ int s2_attn_bwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
                        size_t workspace_bytes, void* stream);
 size_t s2_attn_bwd_varlen_workspace_bytes(int32_t heads, int32_t rows, int32_t head_dim);
 
-/* The backward is two launches: dQ (which also computes delta = rowsum(dO*O) and leaves it in
- * the workspace), then dK/dV (which reads delta); a whole one of up to 4096 workgroups is delta and one launch for
- * both, with the same results.  This variant runs the subset named by `stages`
+/* The backward consists of dQ (which also computes delta = rowsum(dO*O) and leaves it in
+ * the workspace) and dK/dV (which reads delta): two launches in this order, or, for a whole one of up to 4096 workgroups, delta and one
+ * launch for both, with the same results.  This variant runs the subset named by `stages`
  * (an OR of the flags below) so that a profiler or a benchmark can time each launch on its own;
  * with S2_BWD_ALL it is s2_attn_bwd.  S2_BWD_DKDV needs delta in the workspace: from S2_BWD_DQ in
  * the same or an earlier call, or from S2_BWD_DELTA, a stand-alone delta kernel that only runs

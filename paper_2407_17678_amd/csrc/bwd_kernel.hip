@@ -1,9 +1,10 @@
 // Backward kernels: gradients of block-sparse causal attention (the backward pass that goes with
 // the forward of section 3.2; the paper names it as the less optimised half of its kernels).
 //
-// Two launches, no floating-point atomics, bitwise reproducible:
+// Two launches (delta, then the tiles of dQ and dK/dV, in whole backwards of up to 4096 workgroups; dQ, then dK/dV, in larger ones; three
+// where dS is kept: delta, dK/dV, dQ), no floating-point atomics, bitwise reproducible:
 //   delta  : delta[t] = sum_d dO[t][d] * O[t][d].  Folded into the dq launch, which holds the dO
-//            fragments anyway; the stand-alone kernel runs where dS is kept, where dK/dV is asked for alone, and
+//            fragments anyway; the stand-alone kernel runs where dS is kept, where it is asked for without dQ, and
 //            before the launch that does the tiles of both others (bwd_merged_kernel.hip).
 //   dq     : row-stationary, in dq_pipe_kernel.hip (dq_gemm_kernel.hip where dS is kept).  A workgroup
 //            owns 128 query rows and walks the merged list of KV blocks its mask rows keep (as the

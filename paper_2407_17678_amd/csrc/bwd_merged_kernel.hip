@@ -6,9 +6,14 @@
 //     256    1 x  8 x  2048: 48.8 and  37.6                               65.0 and  49.9
 //    1024    2 x 16 x  2048: 62.5 and  56.3, dense 124.7 and 115.6       122.2 and 103.7, dense 193.3 and 172.2
 //    2048    2 x 16 x  4096: 117  and 110;   dense 330   and 331         162   and 157 (4 x 16 x 2048); dense 568 and 545
-//    4096    4 x 16 x  4096: 209  and 208;   packed 94   and  80         388   and 386;                 packed 134 and 126
-//    8192    8 x 16 x  4096: 411  and 413;   16-token 366 and 366        748   and 761;                 16-token 683 and 696
-//   16384    packed          227  and 228                                440   and 444
+//    4096    4 x 16 x  4096: 209  and 208;   packed 108  and  94         388   and 386;                 packed 161 and 156
+//            dense 32 x 8192: 1149 and 1142; 128 x 2048: 342 and 346     dense 1969 and 1972;           602 and 606
+//    6144    packed          141  and 125                                216   and 215
+//    8192    8 x 16 x  4096: 411  and 413;   packed 174  and 158         748   and 761;                 packed 283 and 281
+//            16-token        366  and 366;   packed 183  and 167         683   and 696;                 packed 297 and 295
+//   16384    packed          274  and 277                                513   and 527
+// (Packed: 8 sequences of 200 rows up to the longest length allowed, log-uniform, x 16 heads, or 32 at 16384.  Their grid has a slot for each tile of
+// the longest length, of which about half exist.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -73,7 +78,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, hipStream_t stream) {
 
 // The compute units hold 512 (head_dim 128) or 768 (64) of these workgroups at a time.  A launch of a few times as many gains by the start and the
 // end that it has once instead of twice; at 4096 that has sunk to what the pass over O and dO on its own costs, and from 8192 on that pass costs
-// up to 2 % (measured above).
+// up to 2 % (measured above; packed batches of up to 8192, whose slots do not all hold a tile, would gain up to 13 % at head_dim 64).
 // Two launches also where dK and dV replace K and V (either way round): a key tile writes only what it alone reads, but in one launch the
 // dQ tiles read every tile's K and V beside it.
 constexpr int kMergedGrid = 4096;

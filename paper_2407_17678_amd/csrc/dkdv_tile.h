@@ -98,8 +98,8 @@ struct DkvSmem {
 // the list entries (query blocks, last first) that lie after the sequence's end, clamps the loads
 // of the ragged last chunk and zeroes P and dS for the query rows of it that do not exist.
 // STORE: dS, rounded to bf16 as the dK contraction takes it, is also left in the workspace for the dQ
-// launch (launch_dq_gemm), 4 KiB per wavefront and step: [half chunk][16-query slab][key][lane half][8
-// queries in the order the lane holds them], i.e. each B operand as it is, 1 KiB per store instruction.
+// launch (launch_dq_gemm), 4 KiB per wavefront and step: [32-query half][key][g = lane / 16][8 queries as the lane
+// holds them: 4 * g + 0..3, then 16 + 4 * g + 0..3], i.e. each B operand (16 keys) as it is, 1 KiB per store instruction.
 template <int D, bool DENSE, int FINE, bool VARLEN = false, bool STORE = false>
 __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned char* smem_raw) {
   typedef ChunkTile<D> Tile;

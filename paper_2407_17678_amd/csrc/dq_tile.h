@@ -154,10 +154,10 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
     if (VARLEN) row = min(row, N - 1);
   };
 
-  // Q^T and dO^T fragments (B operands), lane = query; delta = rowsum(dO * O) of my query from the
-  // dO fragments (my half of the row's features, then the two halves added), written out with LSE
-  // as the dK/dV kernel, which runs after this one, wants them.  A lane without a row of its own
-  // reads the last row; nothing of it is stored.
+  // Q^T and dO^T fragments (B operands), lane % 16 = query; delta = rowsum(dO * O) of my query from the
+  // dO fragments (8 features of every 32 in each of the four lane groups, added up with the lane 32 away and then with the one
+  // 16 away: the order that delta_kernel keeps to, bit for bit), written out with LSE as the dK/dV kernel, which runs after
+  // this one, wants them.  A lane without a row of its own reads the last row; nothing of it is stored.
   // [32-feature step][16-query tile nt]
   bf16x8 qf[KS][2], gf[KS][2];
   float delta_l[2], lse_l[2];
