@@ -1,10 +1,11 @@
-"""ctypes binding of libs2attn.so: argument marshalling only.
+"""Binding of libs2attn.so: argument marshalling only.
 
 Every function here has the name of the C entry point it calls (see
 ``include/s2attn.h``) and does nothing but turn torch tensors into pointers,
-sizes and strides.  torch is used for device memory and streams; all of the
+sizes and strides: for the calls that launch attention kernels in the extension _marshal.so
+(``csrc/marshal.cpp``), for the others through ctypes.  torch is used for device memory and streams; all of the
 attention arithmetic runs inside the HIP library.  There is no fallback: if
-the shared library is missing, importing this module raises.
+a shared library is missing, its first use raises.
 """
 
 import ctypes as C
@@ -92,7 +93,27 @@ EXPORTS = (
     "s2_last_hip_error", "s2_version",
 )
 
+# the entry points that _marshal.so calls, in the order its bind() takes their addresses
+_MARSHALLED = ("s2_attn_fwd", "s2_attn_fwd_rows", "s2_attn_fwd_varlen", "s2_attn_bwd_stages", "s2_attn_bwd_varlen", "s2_dense_causal_fwd",
+               "s2_dense_causal_bwd", "s2_attn_decode", "s2_attn_decode_static", "s2_attn_decode_layout", "s2_attn_decode_paged",
+               "s2_attn_decode_paged_layout")
+
 _lib = None
+_calls = None
+
+
+def _marshal():
+    """The extension that makes the compute calls, bound to the loaded library."""
+    global _calls
+    if _calls is None:
+        L = lib()
+        try:
+            from . import _marshal as calls
+        except ImportError as e:
+            raise ImportError("_marshal.so is not built: run `python -m paper_2407_17678_amd.build`") from e
+        calls.bind(*(C.cast(getattr(L, name), C.c_void_p).value for name in _MARSHALLED))
+        _calls = calls
+    return _calls
 
 
 def lib():
@@ -165,12 +186,41 @@ def _check(status, where):
         raise S2Error(status, where)
 
 
-def _stream_ptr(stream):
+_raw_stream = None  # once torch's GPU side is up: (current device, its current stream) as plain integers
+
+
+def _forget_streams():
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_streams)  # (torch refuses the GPU in a forked child: its own check comes first again)
+
+
+def _stream(stream):
     """torch stream (or None = torch's current stream) -> hipStream_t as an integer."""
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        device, current = _raw_stream
+        return current(device())
+    import torch
+    handle = torch.cuda.current_stream().cuda_stream  # (brings the GPU side up, or raises)
+    # the same two values without a stream object, which takes 3 us to make
+    _raw_stream = (torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    return handle
+
+
+def _stream_ptr(stream):
+    return C.c_void_p(_stream(stream))
+
+
+def _params_ptr(params):
+    """Address of a LayoutParams (any other object is refused as ctypes refuses it)."""
+    if type(params) is not LayoutParams:
+        C.POINTER(LayoutParams).from_param(C.byref(params))
+    return C.addressof(params)
 
 
 def layout_params(num_heads, num_blocks, block_size, local_blocks, stride, head_index_base=0,
@@ -267,36 +317,19 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(None)
 
 
-def _tensors(q, k, v, o, lse, d_o=None, dq=None, dk=None, dv=None):
-    Bt, H, N, D = q.shape
-    assert q.stride(3) == 1 and k.stride(3) == 1 and v.stride(3) == 1 and o.stride(3) == 1
-    assert k.stride() == v.stride() and q.stride() == o.stride()
-    for g, ref in ((d_o, q), (dq, q), (dk, k), (dv, k)):
-        assert g is None or g.stride() == ref.stride()
-    assert lse.is_contiguous()
-    return Tensors(_ptr(q), _ptr(k), _ptr(v), _ptr(o), _ptr(lse), _ptr(d_o), _ptr(dq), _ptr(dk), _ptr(dv),
-                   Bt, H, N, D, q.stride(0), q.stride(1), q.stride(2), k.stride(0), k.stride(1), k.stride(2))
-
-
 def s2_attn_fwd(layout, q, k, v, o, lse, scale, stream=None):
-    t = _tensors(q, k, v, o, lse)
-    _check(lib().s2_attn_fwd(layout.handle, C.byref(t), scale, _stream_ptr(stream)), "s2_attn_fwd")
+    _check(_marshal().fwd(layout.handle, q, k, v, o, lse, scale, _stream(stream)), "s2_attn_fwd")
 
 
 def s2_attn_fwd_rows(layout, q, k, v, o, lse, q_row_start, scale, stream=None):
     """q, o: [Bt, H, q_rows, D] (the tokens at positions q_row_start ...); k, v: [Bt, H, N_k, D]."""
-    t = _tensors(q, k, v, o, lse)
-    t.seqlen = k.shape[2]
-    _check(lib().s2_attn_fwd_rows(layout.handle, C.byref(t), q_row_start, q.shape[2], scale,
-                                  _stream_ptr(stream)), "s2_attn_fwd_rows")
+    _check(_marshal().fwd_rows(layout.handle, q, k, v, o, lse, q_row_start, scale, _stream(stream)), "s2_attn_fwd_rows")
 
 
 def s2_attn_fwd_varlen(layout, q, k, v, o, lse, cu_seqlens, max_seqlen, scale, stream=None):
     """q, k, v, o: [1, H, total_rows, D] packed sequences; lse: [H, total_rows]; cu_seqlens: device int32 [n+1]."""
-    t = _tensors(q, k, v, o, lse)
-    assert q.shape[0] == 1 and cu_seqlens.is_contiguous() and cu_seqlens.numel() >= 2
-    _check(lib().s2_attn_fwd_varlen(layout.handle, C.byref(t), _ptr(cu_seqlens), cu_seqlens.numel() - 1,
-                                    max_seqlen, scale, _stream_ptr(stream)), "s2_attn_fwd_varlen")
+    _check(_marshal().fwd_varlen(layout.handle, q, k, v, o, lse, cu_seqlens, max_seqlen, scale, _stream(stream)),
+           "s2_attn_fwd_varlen")
 
 
 def s2_attn_bwd_varlen_workspace_bytes(heads, rows, head_dim):
@@ -305,11 +338,8 @@ def s2_attn_bwd_varlen_workspace_bytes(heads, rows, head_dim):
 
 def s2_attn_bwd_varlen(layout, q, k, v, o, lse, d_o, dq, dk, dv, cu_seqlens, max_seqlen, scale, workspace, stream=None):
     """Gradient of s2_attn_fwd_varlen; d_o, dq, dk, dv packed like q."""
-    t = _tensors(q, k, v, o, lse, d_o, dq, dk, dv)
-    assert q.shape[0] == 1 and cu_seqlens.is_contiguous() and cu_seqlens.numel() >= 2
-    _check(lib().s2_attn_bwd_varlen(layout.handle, C.byref(t), _ptr(cu_seqlens), cu_seqlens.numel() - 1, max_seqlen,
-                                    scale, _ptr(workspace), workspace.numel() * workspace.element_size(),
-                                    _stream_ptr(stream)), "s2_attn_bwd_varlen")
+    _check(_marshal().bwd_varlen(layout.handle, q, k, v, o, lse, d_o, dq, dk, dv, cu_seqlens, max_seqlen, scale, workspace,
+                                 _stream(stream)), "s2_attn_bwd_varlen")
 
 
 def s2_attn_bwd_workspace_bytes(batch, heads, seqlen, head_dim):
@@ -321,9 +351,8 @@ def s2_attn_bwd_layout_workspace_bytes(layout, batch, heads, seqlen, head_dim):
 
 
 def s2_attn_bwd(layout, q, k, v, o, lse, d_o, dq, dk, dv, scale, workspace, stream=None):
-    t = _tensors(q, k, v, o, lse, d_o, dq, dk, dv)
-    _check(lib().s2_attn_bwd(layout.handle, C.byref(t), scale, _ptr(workspace),
-                             workspace.numel() * workspace.element_size(), _stream_ptr(stream)),
+    # (s2_attn_bwd is s2_attn_bwd_stages with all of them)
+    _check(_marshal().bwd_stages(layout.handle, q, k, v, o, lse, d_o, dq, dk, dv, scale, workspace, BWD_ALL, _stream(stream)),
            "s2_attn_bwd")
 
 
@@ -331,10 +360,8 @@ BWD_DELTA, BWD_DKDV, BWD_DQ, BWD_ALL = 1, 2, 4, 7
 
 
 def s2_attn_bwd_stages(layout, q, k, v, o, lse, d_o, dq, dk, dv, scale, workspace, stages, stream=None):
-    t = _tensors(q, k, v, o, lse, d_o, dq, dk, dv)
-    _check(lib().s2_attn_bwd_stages(layout.handle, C.byref(t), scale, _ptr(workspace),
-                                    workspace.numel() * workspace.element_size(), stages,
-                                    _stream_ptr(stream)), "s2_attn_bwd_stages")
+    _check(_marshal().bwd_stages(layout.handle, q, k, v, o, lse, d_o, dq, dk, dv, scale, workspace, stages, _stream(stream)),
+           "s2_attn_bwd_stages")
 
 
 def s2_dense_causal_bwd_workspace_bytes(batch, heads, seqlen, head_dim):
@@ -342,15 +369,11 @@ def s2_dense_causal_bwd_workspace_bytes(batch, heads, seqlen, head_dim):
 
 
 def s2_dense_causal_fwd(q, k, v, o, lse, scale, stream=None):
-    t = _tensors(q, k, v, o, lse)
-    _check(lib().s2_dense_causal_fwd(C.byref(t), scale, _stream_ptr(stream)), "s2_dense_causal_fwd")
+    _check(_marshal().dense_fwd(q, k, v, o, lse, scale, _stream(stream)), "s2_dense_causal_fwd")
 
 
 def s2_dense_causal_bwd(q, k, v, o, lse, d_o, dq, dk, dv, scale, workspace, stream=None):
-    t = _tensors(q, k, v, o, lse, d_o, dq, dk, dv)
-    _check(lib().s2_dense_causal_bwd(C.byref(t), scale, _ptr(workspace),
-                                     workspace.numel() * workspace.element_size(), _stream_ptr(stream)),
-           "s2_dense_causal_bwd")
+    _check(_marshal().dense_bwd(q, k, v, o, lse, d_o, dq, dk, dv, scale, workspace, _stream(stream)), "s2_dense_causal_bwd")
 
 
 def s2_attn_decode_workspace_bytes(nseq, heads, head_dim, max_len, num_splits=0):
@@ -363,72 +386,36 @@ def s2_attn_decode_default_splits(nseq, heads, max_len):
 
 def s2_attn_decode(params, q, k_cache, v_cache, seq_lens, o, lse, scale, workspace, max_len,
                    num_splits=0, stream=None):
-    nseq, H, D = q.shape
-    assert q.is_contiguous() and o.is_contiguous() and k_cache.stride() == v_cache.stride()
-    assert k_cache.stride(3) == 1
-    a = DecodeArgs(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), _ptr(o), _ptr(lse),
-                   nseq, H, D, max_len, num_splits,
-                   k_cache.stride(0), k_cache.stride(1), k_cache.stride(2))
-    _check(lib().s2_attn_decode(C.byref(params), C.byref(a), scale, _ptr(workspace),
-                                workspace.numel() * workspace.element_size(), _stream_ptr(stream)),
-           "s2_attn_decode")
+    _check(_marshal().decode(_params_ptr(params), q, k_cache, v_cache, seq_lens, o, lse, scale, workspace, max_len, num_splits,
+                             _stream(stream)), "s2_attn_decode")
 
 
 def s2_attn_decode_static(params, q, k_cache, v_cache, seq_lens, o, lse, scale, max_len, num_splits=0,
                           stream=None):
     """s2_attn_decode with the split partials in the library's own static device buffer."""
-    nseq, H, D = q.shape
-    assert q.is_contiguous() and o.is_contiguous() and k_cache.stride() == v_cache.stride()
-    assert k_cache.stride(3) == 1
-    a = DecodeArgs(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), _ptr(o), _ptr(lse),
-                   nseq, H, D, max_len, num_splits,
-                   k_cache.stride(0), k_cache.stride(1), k_cache.stride(2))
-    _check(lib().s2_attn_decode_static(C.byref(params), C.byref(a), scale, _stream_ptr(stream)),
-           "s2_attn_decode_static")
+    _check(_marshal().decode_static(_params_ptr(params), q, k_cache, v_cache, seq_lens, o, lse, scale, max_len, num_splits,
+                                    _stream(stream)), "s2_attn_decode_static")
 
 
 def s2_attn_decode_layout(layout, q, k_cache, v_cache, seq_lens, o, lse, scale, workspace, max_len,
                           num_splits=0, stream=None):
     """s2_attn_decode following the rows of a Layout (any pattern) instead of the closed form."""
-    nseq, H, D = q.shape
-    assert q.is_contiguous() and o.is_contiguous() and k_cache.stride() == v_cache.stride()
-    assert k_cache.stride(3) == 1
-    a = DecodeArgs(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(seq_lens), _ptr(o), _ptr(lse),
-                   nseq, H, D, max_len, num_splits,
-                   k_cache.stride(0), k_cache.stride(1), k_cache.stride(2))
-    _check(lib().s2_attn_decode_layout(layout.handle, C.byref(a), scale, _ptr(workspace),
-                                       workspace.numel() * workspace.element_size(), _stream_ptr(stream)),
-           "s2_attn_decode_layout")
+    _check(_marshal().decode_layout(layout.handle, q, k_cache, v_cache, seq_lens, o, lse, scale, workspace, max_len, num_splits,
+                                    _stream(stream)), "s2_attn_decode_layout")
 
 
 def s2_attn_decode_paged(params, q, k_pages, v_pages, block_table, seq_lens, o, lse, scale, workspace,
                          missing=None, num_splits=0, stream=None):
     """k_pages, v_pages: [num_pages, block_size, head_dim]; block_table: int32 [nseq, heads, max_blocks]."""
-    nseq, H, D = q.shape
-    assert q.is_contiguous() and o.is_contiguous() and block_table.is_contiguous()
-    assert k_pages.stride() == v_pages.stride() and k_pages.stride(2) == 1
-    assert tuple(block_table.shape[:2]) == (nseq, H)
-    a = PagedDecodeArgs(_ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table), _ptr(seq_lens), _ptr(o),
-                        _ptr(lse), _ptr(missing), nseq, H, D, block_table.shape[2], k_pages.shape[0],
-                        num_splits, k_pages.stride(0), k_pages.stride(1))
-    _check(lib().s2_attn_decode_paged(C.byref(params), C.byref(a), scale, _ptr(workspace),
-                                      workspace.numel() * workspace.element_size(), _stream_ptr(stream)),
-           "s2_attn_decode_paged")
+    _check(_marshal().decode_paged(_params_ptr(params), q, k_pages, v_pages, block_table, seq_lens, o, lse, scale, workspace, missing,
+                                   num_splits, _stream(stream)), "s2_attn_decode_paged")
 
 
 def s2_attn_decode_paged_layout(layout, q, k_pages, v_pages, block_table, seq_lens, o, lse, scale, workspace,
                                 missing=None, num_splits=0, stream=None):
     """s2_attn_decode_paged following the rows of a Layout (any pattern) instead of the closed form."""
-    nseq, H, D = q.shape
-    assert q.is_contiguous() and o.is_contiguous() and block_table.is_contiguous()
-    assert k_pages.stride() == v_pages.stride() and k_pages.stride(2) == 1
-    assert tuple(block_table.shape[:2]) == (nseq, H)
-    a = PagedDecodeArgs(_ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table), _ptr(seq_lens), _ptr(o),
-                        _ptr(lse), _ptr(missing), nseq, H, D, block_table.shape[2], k_pages.shape[0],
-                        num_splits, k_pages.stride(0), k_pages.stride(1))
-    _check(lib().s2_attn_decode_paged_layout(layout.handle, C.byref(a), scale, _ptr(workspace),
-                                             workspace.numel() * workspace.element_size(), _stream_ptr(stream)),
-           "s2_attn_decode_paged_layout")
+    _check(_marshal().decode_paged_layout(layout.handle, q, k_pages, v_pages, block_table, seq_lens, o, lse, scale, workspace, missing,
+                                          num_splits, _stream(stream)), "s2_attn_decode_paged_layout")
 
 
 def s2_kv_resident_blocks(params, head, length):
