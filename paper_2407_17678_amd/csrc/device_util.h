@@ -326,6 +326,11 @@ struct EntryList {
   __device__ __forceinline__ int peek(int j) const {
     return (j >> 6) != batch ? __builtin_amdgcn_readlane(nxt, j & 63) : __builtin_amdgcn_readlane(cur, j & 63);
   }
+  // the same without a branch, and 0 past the list's end
+  __device__ __forceinline__ int at(int j) const {
+    const int a = __builtin_amdgcn_readlane(cur, j & 63), b = __builtin_amdgcn_readlane(nxt, j & 63);
+    return (j >> 6) == batch ? a : b;
+  }
   // entry e+1, given that get(e) was the last call; does not advance
   __device__ __forceinline__ int peek_next(int e) const {
     return ((e + 1) >> 6) != batch ? __builtin_amdgcn_readlane(nxt, 0)

@@ -28,7 +28,15 @@
 //     closer to the exact result (relative error of O against 64 bits, exact and lazy: 2 x 4 heads x 4096 x
 //     64, blocks of 64 2.10e-3 and 2.20e-3; 8192 x 128, blocks of 16 2.12e-3 and 2.25e-3);
 //   * the direct loads of a tile are issued two or three to a write of M0 (their LDS targets are told
-//     apart by the instruction's immediate offset).
+//     apart by the instruction's immediate offset);
+//   * what a step needs to know (its first key, whether it is mine, where its rows lie) is formed inside the slots of the step
+//     before it, without branches, and the fragment ring and the barrier lie there too: a scalar instruction is hidden
+//     beside an MFMA, but takes a wavefront that has nothing else to do 10 cycles (its first use of a lane's value 30, a
+//     compare and branch on vector values 38, a taken branch 22), and each step began with 75 of them.
+//
+// The last point, before and after, us: 1 x 32 heads x 32768 x 128 1066 -> 1028, 4 x 16 x 8192 254 -> 245, 2 x 16 x 3904 48.3 -> 45.9, 2 x 16 x 4096 x 64
+// 32.4 -> 30.5, 1 x 32 x 131072 in blocks of 128 6047 -> 5937, dense 1 x 32 x 8192 508 -> 504; with few tiles on the chip 1 x 4 x 512 x 64 10.2 -> 8.1, 128 rows x 32
+// heads against 30720 keys 50.7 -> 45.7.  (Direct loads one or two steps further ahead, in the LDS that a lone workgroup could have, change nothing there.)
 //
 // One loop serves both head sizes, blocks of 64 and 128 tokens and ragged ends (blocks of 16 and 32:
 // fwd_gather_kernel.hip).  Against the phase-by-phase kernel that head_dim 64 and partial 128-row tiles used to
@@ -71,7 +79,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   constexpr int NG = Piece::kGroups;
   // LDS fragments are requested kLead MFMAs ahead (3 to 7 measure the same at D = 128; at D = 64 three keep a
   // wavefront at 168 registers, so that three fit a SIMD)
-  constexpr int kLead = D == 128 ? 5 : 3, kRing = kLead + 1;
+  constexpr int kLead = D == 128 ? 5 : 3, kRing = D == 64 ? kLead + 1 : 8;
+  // The ring goes on from one step to the next, and across the barrier between them: it lies kLead slots before a step's end, when every
+  // wavefront has asked for its last fragments.  (In packed batches at D = 64 it begins again with each step: no registers are left for
+  // it, a Q fragment would be spilled.)
+  constexpr bool kAcross = !VARLEN || D == 128;
+  static_assert(!kAcross || (NS % kRing == 0 && kRing > kLead), "a fragment has the same place in every step");
   static_assert(!(DENSE && VARLEN), "the dense form walks 64-key blocks of whole sequences");
 
   const int tid = threadIdx.x;
@@ -106,8 +119,8 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
   // minus the bias the grouped direct loads put into their lane offsets
-  const uint16_t* kb = p.k + kv_off - Piece::kBias / 2;
-  const uint16_t* vb = p.v + kv_off - Piece::kBias / 2;
+  const char* kb = reinterpret_cast<const char*>(p.k + kv_off) - Piece::kBias;
+  const char* vb = reinterpret_cast<const char*>(p.v + kv_off) - Piece::kBias;
 
   int ent_lo = 0, n_ent;
   if (DENSE) {
@@ -129,26 +142,27 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   for (int kk = 0; kk < KK; ++kk)
     qf[kk] = *reinterpret_cast<const bf16x8*>(p.q + q_off + (int64_t)q_lane * p.q_st + 16 * kk + 8 * half);
 
-  // Step j of the tile's list (clamped to the last one): the first key row of the 16 that I fetch;
-  // whether I have anything to compute there (my mask rows keep some of it, and not every key lies
-  // after every one of my queries); and whether some of it has to be masked for me.
-  auto chunk_at = [&](int j, int& row, bool& act, bool& masked) S2_INLINE {
-    const bool inside = j < total;
-    j = min(j, total - 1);
-    int kv0;
-    bool keep = true;
+  // Step j of the tile's list: its first key (0 past the end of a list, where entries are 0), and whether I have anything to
+  // compute there: my mask rows keep some of it, and not every key lies after every one of my queries (q_end: past my last
+  // one, 0 where I have none).
+  const int q_end = wave_on ? qw0 + MW : 0, s_sh = 6 + cpb_sh;
+  auto chunk_at = [&](int j, int& kv0, bool& act) S2_INLINE {
     if (DENSE) {
       kv0 = j * CH;
+      act = kv0 < q_end;
     } else {
-      const int e = list.peek(j >> cpb_sh);
-      kv0 = (e >> 16) * S + (j & cpb_m) * CH;
-      keep = (e >> my_member) & 1;
+      const uint32_t e = (uint32_t)list.at(j >> cpb_sh);
+      kv0 = (int)(e >> 16 << s_sh) + ((j & cpb_m) << 6);
+      act = ((e >> my_member) & (uint32_t)(kv0 < q_end)) != 0;
     }
-    row = kv0 + 16 * wave;
-    act = inside && wave_on && keep && kv0 <= qw0 + MW - 1;
-    masked = kv0 + CH - 1 > qw0;
-    if (VARLEN) row = min(row, N - 1);
   };
+  // how far (bytes) from the first key of my sequence the 16 rows lie that I fetch of the chunk that begins at key kv0
+  const uint32_t row_bytes = (uint32_t)(2 * p.kv_st);  // (api.hip: at most 2^25)
+  auto piece_row = [&](int kv0) S2_INLINE {
+    if (DENSE) kv0 = min(kv0, (total - 1) * CH);
+    return VARLEN ? min(kv0 + 16 * wave, N - 1) : kv0 + 16 * wave;
+  };
+  auto piece_off = [&](int row) S2_INLINE { return (uint64_t)(uint32_t)row * row_bytes; };
 
   f32x16 acc[DT];
 #pragma unroll
@@ -161,19 +175,22 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // where 2^kTau is out of reach of any score: the first maximum has to move it from -inf.
   const bool lazy_ref = D == 128 && (VARLEN ? (tile + 1) * BM <= N : p.q_rows % BM == 0);
   const float tau = lazy_ref ? fminf(kTau / c, 3.4e38f) : 0.f;
-  // The lane offsets of my direct loads, for K and for V.  Where a packed sequence ends inside the rows
-  // I fetch (VARLEN) they are limited to the rows that exist; the lists ascend, so from then on every
-  // piece is such a piece, with fewer and fewer rows.
-  typename Piece::Plan plan_k = Piece::plan(p.kv_st, lane), plan_v = plan_k;
-  auto limit_plan = [&](typename Piece::Plan& pl, int row) S2_INLINE {
-    if (VARLEN && row + 16 > N) Piece::limit(pl, N - row, p.kv_st);
+  // The lane offsets of my direct loads.  Where a packed sequence ends inside the 16 rows I fetch (VARLEN) no lane's goes past
+  // end_off, the last piece of the last row that exists.
+  const typename Piece::Plan plan = Piece::plan(p.kv_st, lane);
+  auto end_off = [&](int row) S2_INLINE {
+    return VARLEN && row + 16 > N ? (uint32_t)(N - 1 - row) * row_bytes + (2 * D - 16 + Piece::kBias) : ~0u;
   };
-  // group g of the loads of my 16 rows, which start at `base`
-  auto dma_k = [&](auto gc, const uint16_t* base, const uint16_t* stage) S2_INLINE {
-    Piece::template issue<decltype(gc)::value>(plan_k, base, stage, wave);
-  };
-  auto dma_v = [&](auto gc, const uint16_t* base, const uint16_t* stage) S2_INLINE {
-    Piece::template issue<decltype(gc)::value>(VARLEN ? plan_v : plan_k, base, stage, wave);
+  // group g of the loads of my 16 rows, which start `off` bytes after the first key
+  auto dma = [&](auto gc, const char* base, uint64_t off, uint32_t end, const uint16_t* stage) S2_INLINE {
+    if constexpr (VARLEN) {
+      typename Piece::Plan pl = plan;
+#pragma unroll
+      for (int n = 0; n < Piece::kLoads; ++n) pl.goff[n] = min(pl.goff[n], end - Piece::imm(n));
+      Piece::template issue<decltype(gc)::value>(pl, base + off, stage, wave);
+    } else {
+      Piece::template issue<decltype(gc)::value>(plan, base + off, stage, wave);
+    }
   };
   // lane parts of the addresses the fragments are read at
   const uint32_t k_lane = lds_addr(tiles) + l32 * RB + 16 * half, v_lane = lds_addr(tiles) + 2 * Tile::tr_base(lane);
@@ -241,12 +258,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // element index reached after slot sl: five elements every four slots, or (D = 64) three a slot
   constexpr int kPace = D == 128 ? 40 : 48;
   auto p_upto = [](int sl) S2_INLINE { return (kPace * (sl + 1)) / NS; };
-  // drops what my query does not see of step j: keys after it
-  auto mask_step = [&](f32x16 (&sn)[2], int j) S2_INLINE {
+  // drops what my query does not see of the step that begins at key kv0: keys after it
+  auto mask_step = [&](f32x16 (&sn)[2], int kv0) S2_INLINE {
     const int qpos = qw0 + l32;
 #pragma unroll
     for (int pc = 0; pc < 4; ++pc) {
-      const int row = (DENSE ? j * CH : (list.peek(j >> cpb_sh) >> 16) * S + (j & cpb_m) * CH) + 16 * pc;
+      const int row = kv0 + 16 * pc;
       // how many of these 16 keys I see, counted from the first one my half of the wavefront holds
       const int lim = qpos - row + 1 - 4 * half;
 #pragma unroll
@@ -262,7 +279,6 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // moves the reference maximum where the new scores exceed it by more than tau (always for the first
   // step, when it is -inf) and rescales what has been accumulated so far
   auto update_ref = [&](float mx) S2_INLINE {
-    mx = max_halves(mx);
     // (a lane that has seen no key yet has m_ref = -inf: its first score always exceeds that, and while it
     // sees none the difference is not a number, which does not)
     if (__any(mx - m_ref > tau)) {
@@ -278,12 +294,14 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
       mc = m_use * c;
     }
   };
-  // maximum of the scores in sn (masked on the diagonal), then the reference maximum
-  auto finish_scores = [&](f32x16 (&sn)[2], int j, bool act, bool masked, float mx) S2_INLINE {
-    if (masked) {
-      mask_step(sn, min(j, total - 1));
+  // maximum of the scores in sn (masked on the diagonal), then the reference maximum; kv0: the step's first key
+  auto finish_scores = [&](f32x16 (&sn)[2], int kv0, int act, float mx) S2_INLINE {
+    if (kv0 + CH - 1 > qw0) {
+      S2_FENCE();
+      mask_step(sn, kv0);
       mx = kNegInf;
       max_part(0, 32, sn, mx);
+      mx = max_halves(mx);
     }
     if (!act) mx = kNegInf;
     update_ref(mx);
@@ -293,20 +311,24 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // A step this wavefront has nothing to compute in (its mask row drops the block, or every key
   // lies after its queries) runs through the same instruction stream when the step before or
   // after it is its own (see `step`); two such steps in a row are skipped.
-  int row_n, row_nn;  // the key rows I fetch of the next step and the one after it
-  bool act_c, act_n, act_nn, masked_c, masked_n, masked_nn;
+  bool act_c, act_n;
+  int kv_n;         // first key of the next step
+  uint64_t off_n;   // where the key rows lie that I fetch of it, and where they end
+  uint32_t end_n;
   {
-    int row_c;
-    chunk_at(0, row_c, act_c, masked_c);
-    chunk_at(1, row_n, act_n, masked_n);
-    limit_plan(plan_k, row_c);
-    limit_plan(plan_v, row_c);
+    int kv_c;
+    chunk_at(0, kv_c, act_c);
+    chunk_at(1, kv_n, act_n);
+    const int row_c = piece_row(kv_c), row_n = piece_row(kv_n);
+    const uint64_t off_c = piece_off(row_c);
+    const uint32_t end_c = end_off(row_c);
+    off_n = piece_off(row_n);
+    end_n = end_off(row_n);
     static_for<NG>([&](auto gc) S2_INLINE {
-      dma_k(gc, kb + (int64_t)row_c * p.kv_st, sk[0]);
-      dma_v(gc, vb + (int64_t)row_c * p.kv_st, sv[0]);
+      dma(gc, kb, off_c, end_c, sk[0]);
+      dma(gc, vb, off_c, end_c, sv[0]);
     });
-    limit_plan(plan_k, row_n);
-    static_for<NG>([&](auto gc) S2_INLINE { dma_k(gc, kb + (int64_t)row_n * p.kv_st, sk[1]); });
+    static_for<NG>([&](auto gc) S2_INLINE { dma(gc, kb, off_n, end_n, sk[1]); });
   }
   wait_all_loads();
   __syncthreads();
@@ -322,51 +344,86 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     });
   }
   {
+    int kv_c;
+    chunk_at(0, kv_c, act_c);
     float mx = kNegInf;
-    if (!masked_c) max_part(0, 32, s[0], mx);
-    finish_scores(s[0], 0, act_c, masked_c, mx);
+    if (kv_c + CH - 1 <= qw0) {
+      max_part(0, 32, s[0], mx);
+      mx = max_halves(mx);
+    }
+    finish_scores(s[0], kv_c, act_c, mx);
   }
   __syncthreads();  // all wavefronts are done with K(0) before step 0 loads K(2) over it
 
   // ------------------------------------------------------------------ one step
-  // On entry: K(it+1) and V(it) are in LDS, sc holds the scores of step it and the reference
+  // While step `it` runs, K(it+1) and V(it) are in LDS, sc holds the scores of step it and the reference
   // maximum already covers them.
-  auto step = [&](int it, f32x16 (&sc)[2], f32x16 (&sn)[2]) S2_INLINE {
-    const int par = it & 1;
-    chunk_at(it + 2, row_nn, act_nn, masked_nn);
+  int it = 0;
+  int kv_nn;           // the step after the next one
+  bool act_nn;
+  uint64_t off_nn;
+  uint32_t end_nn;
+  uint32_t ks, vs;     // where the lane's fragments of this step's K and V are
+  bf16x8 fr[kRing];
+  // what step `it` (of parity par) needs to know
+  auto open_step = [&](auto pc) S2_INLINE {
+    constexpr int par = decltype(pc)::value;
+    chunk_at(it + 2, kv_nn, act_nn);
+    const int row_nn = piece_row(kv_nn);
+    off_nn = piece_off(row_nn);
+    end_nn = end_off(row_nn);
     // Where one of the two steps is not mine its scores stay out of the maximum and its probabilities are 0,
     // and the rows of the other one stand in for its own: whatever the rows hold that I do not attend, the scores
     // are finite (so that the probabilities are 0) and nothing of them is accumulated.
-    uint32_t ks = k_lane + (uint32_t)Tile::kBytes * (act_n ? par ^ 1 : 2 + par);
-    uint32_t vs = v_lane + (uint32_t)Tile::kBytes * (act_c ? 2 + par : par ^ 1);
+    ks = k_lane + (uint32_t)Tile::kBytes * (act_n ? par ^ 1 : 2 + par);
+    vs = v_lane + (uint32_t)Tile::kBytes * (act_c ? 2 + par : par ^ 1);
     asm volatile("" : "+v"(ks), "+v"(vs));
+  };
+  // From step `it` to the next: everything this one loads has landed, and every wavefront has read what it needs of it
+  auto next_step = [&](auto pc) S2_INLINE {
+    constexpr int par = decltype(pc)::value;
+    wait_all_loads();
+    __syncthreads();
+    it = __builtin_amdgcn_readfirstlane(it + 1);
+    act_c = act_n;
+    off_n = off_nn;
+    end_n = end_nn;
+    kv_n = kv_nn;
+    act_n = act_nn;
+    open_step(std::integral_constant<int, par ^ 1>{});
+  };
+  auto first_frags = [&]() S2_INLINE {
+#pragma unroll
+    for (int f = 0; f < kLead; ++f) frag_load(f, ks, vs, fr);
+  };
+  auto step = [&](auto pc, f32x16 (&sc)[2], f32x16 (&sn)[2]) S2_INLINE {
+    constexpr int par = decltype(pc)::value;
     // group d of this step's direct loads: 0..NG-1 for K(it+2), into the stage K(it) was in, then
     // V(it+1), into the stage V(it-1) was in
-    const uint16_t* kg = kb + (int64_t)row_nn * p.kv_st;
-    const uint16_t* vg = vb + (int64_t)row_n * p.kv_st;
     auto step_dma = [&](auto dc) S2_INLINE {
       constexpr int d = decltype(dc)::value;
       if constexpr (d < NG)
-        dma_k(dc, kg, sk[par]);
+        dma(dc, kb, off_nn, end_nn, sk[par]);
       else
-        dma_v(std::integral_constant<int, d - NG>{}, vg, sv[par ^ 1]);
+        dma(std::integral_constant<int, d - NG>{}, vb, off_n, end_n, sv[par ^ 1]);
     };
-    limit_plan(plan_k, row_nn);
-    limit_plan(plan_v, row_n);
+    // keeps the entry window moving, two steps at a time: what is asked for until the next time is of steps it + 3 and it + 4
+    if (!DENSE && par == 0) (void)list.get((it + 2) >> cpb_sh, lane);
     if (act_c || act_n) {
       // a step that is not mine: every probability exp2(s*c - inf) = 0
       const float mc_keep = mc;
       if (!act_c) mc = __builtin_inff();
-      bf16x8 fr[kRing];
+      const int kv_s = __builtin_amdgcn_readfirstlane(kv_n);
+      const bool act_s = act_n;
       u32x4 pb[4];
       float mx = kNegInf;
-#pragma unroll
-      for (int f = 0; f < kLead; ++f) frag_load(f, ks, vs, fr);
+      if constexpr (!kAcross) first_frags();
       S2_FENCE();
       // NQK + NPV slots, one MFMA each
       static_for<NS>([&](auto slc) S2_INLINE {
         constexpr int sl = decltype(slc)::value;
-        if constexpr (sl + kLead < NS) frag_load(sl + kLead, ks, vs, fr);
+        if constexpr (kAcross && sl + kLead == NS) next_step(pc);
+        if constexpr (kAcross || sl + kLead < NS) frag_load((sl + kLead) % NS, ks, vs, fr);
         if constexpr (sl < NQK)
           qk_mfma(sl, sn, fr);
         else
@@ -379,9 +436,10 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
         p_stage3(p_upto(sl - 3), p_upto(sl - 2), sc, pb);
         // maximum of the next step's scores, once its MFMAs are done
         constexpr int kMaxSlots = D == 128 ? 8 : 6, kMaxStep = D == 128 ? 4 : 6;
-        static_assert(NQK + 2 + kMaxSlots <= NS && kMaxSlots * kMaxStep >= 32, "all 32 registers");
+        static_assert(NQK + 1 + kMaxSlots <= NS - 1 && kMaxSlots * kMaxStep >= 32, "all 32 registers");
         if constexpr (sl >= NQK + 2 && sl < NQK + 2 + kMaxSlots)
           max_part(kMaxStep * (sl - NQK - 2), std::min(32, kMaxStep * (sl - NQK - 1)), sn, mx);
+        if constexpr (sl == std::min(NS - 1, NQK + 2 + kMaxSlots)) mx = max_halves(mx);
         // Nothing to execute: ties the running sum and maximum to this slot, or the optimiser
         // collects their additions and comparisons after the last MFMA.
         asm volatile("" : "+v"(l_run), "+v"(mx));
@@ -389,26 +447,26 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
         S2_FENCE();
       });
       mc = mc_keep;
-      finish_scores(sn, it + 1, act_n, masked_n, mx);
+      finish_scores(sn, kv_s, act_s, mx);
+      if constexpr (!kAcross) next_step(pc);
     } else {
       static_for<2 * NG>([&](auto dc) S2_INLINE { step_dma(dc); });
+      next_step(pc);
+      if constexpr (kAcross) first_frags();
     }
-    // keeps the entry window moving (entries of step it+1 on)
-    if (!DENSE) (void)list.get(min(it + 1, total - 1) >> cpb_sh, lane);
-    act_c = act_n;
-    row_n = row_nn;
-    act_n = act_nn;
-    masked_n = masked_nn;
-    wait_all_loads();
-    __syncthreads();
   };
 
-  int it = 0;
-  for (; it + 1 < total; it += 2) {
-    step(it, s[0], s[1]);
-    step(it + 1, s[1], s[0]);
+  constexpr std::integral_constant<int, 0> even;
+  constexpr std::integral_constant<int, 1> odd;
+  open_step(even);
+  if constexpr (kAcross) first_frags();
+  // (after the last step the wavefronts still have fragments on their way, from inside the stages, that nothing uses)
+  for (;;) {
+    step(even, s[0], s[1]);
+    if (it >= total) break;
+    step(odd, s[1], s[0]);
+    if (it >= total) break;
   }
-  if (it < total) step(it, s[0], s[1]);
 
   // ------------------------------------------------------------------ epilogue
   if (!wave_on) return;
