@@ -365,7 +365,8 @@ namespace {
 // 1.9 (4 x 8 x 2048 x 128) 139 and 146 there.
 void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, unsigned char* room) {
   const double slots = p.head_dim == 128 ? 64 : 80;
-  const int pairs = (p.batch * p.heads + 7) / 8, T = p.kv_tiles.tiles_per_head;  // (batch, head) pairs of an XCD
+  const int T = p.kv_tiles.tiles_per_head;
+  const double pairs = p.batch * p.heads / 8.0;  // (batch, head) pairs of an XCD, which shares those that are left over
   const double even = pairs * (L->kv_head_steps + 5.0 * T) / slots;
   if (L->kv_max_steps <= 1.1 * even) return;
   const double best = 0.75 * even + 3;

@@ -138,7 +138,7 @@ hipError_t launch_dkdv(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   hipError_t e = set_smem(&dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>, sizeof(DkvSmem<D>), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(grid_for(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long)),
+  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(grid_for_interleaved(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long)),
                      dim3(kThreads), sizeof(DkvSmem<D>), stream, p);
   return hipGetLastError();
 }

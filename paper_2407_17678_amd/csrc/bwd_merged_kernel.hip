@@ -30,7 +30,7 @@ namespace {
 
 // key tiles first: they are the longer ones
 __host__ __device__ inline int key_grid(const AttnParams& p) {
-  return grid_for(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long);
+  return grid_for_interleaved(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long);
 }
 __host__ inline int query_grid(const AttnParams& p) {
   return grid_for(p.batch * p.heads, p.cu_seqlens ? (p.q_rows + kBwdBM - 1) / kBwdBM : p.q_tiles.tiles_per_head);

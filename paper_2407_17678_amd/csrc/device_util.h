@@ -1,6 +1,6 @@
 // Internal device-side helpers for the gfx950 kernels: MFMA fragment types, the LDS tile that a
-// 64-row bf16 chunk is staged in (direct global -> LDS loads, row and transposed fragment reads),
-// and the workgroup -> tile mappings.
+// 64-row bf16 chunk is staged in (direct global -> LDS loads, row and transposed fragment reads);
+// with the workgroup -> tile mappings (tile_map.h).
 //
 // Fragment conventions of v_mfma_f32_32x32x16_bf16 (D = A x B + C, 64 lanes, half = lane / 32):
 //   A (32 x 16): lane holds row (lane % 32), the 8 k-values of its half.
@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+
+#include "tile_map.h"
 
 namespace s2 {
 
@@ -337,54 +339,5 @@ struct EntryList {
                                    : __builtin_amdgcn_readlane(cur, (e + 1) & 63);
   }
 };
-
-// Workgroup index -> (batch*head, rank inside the head) such that all tiles of one (batch, head)
-// run on one XCD.  Workgroups are handed to the 8 XCDs round-robin by linear index, and each XCD
-// has its own L2: keeping a head's key/value stripes and moving window on one XCD lets every
-// later query tile of that head hit in that L2.
-// The pairs of an XCD are taken `group` at a time, a group's tiles by rank: all its longest tiles first,
-// then all its second longest (map_group chooses).
-__device__ __forceinline__ bool map_workgroup(int wg, int bh_total, int tiles, int group, int& bh, int& rank) {
-  const int x = wg & 7, slot = wg >> 3;
-  const int g = slot / (group * tiles);
-  if (group == 1) {
-    rank = slot - g * tiles;
-    bh = x + 8 * g;
-    return bh < bh_total;
-  }
-  const int per_xcd = (bh_total + 7) >> 3;  // slots are laid out for the fullest XCD
-  const int in = slot - g * (group * tiles);
-  const int size = min(group, per_xcd - g * group);
-  rank = in / size;
-  bh = x + 8 * (g * group + in - rank * size);
-  return bh < bh_total;
-}
-// Same XCD assignment, but the (batch, head) pairs of an XCD are interleaved: all their longest
-// tiles are dispatched first, then all their second longest, ...  Used where tile lengths are very
-// uneven (key tiles on a stripe are attended by hundreds of query blocks, the others by a few), so
-// that the longest tile of the last head does not start late and become the tail of the launch.
-__device__ __forceinline__ bool map_workgroup_interleaved(int wg, int bh_total, int tiles, int& bh,
-                                                          int& rank) {
-  const int x = wg & 7, slot = wg >> 3;
-  const int per_xcd = (bh_total + 7) >> 3;  // slots are laid out for the fullest XCD
-  rank = slot / per_xcd;
-  bh = x + 8 * (slot - rank * per_xcd);
-  return bh < bh_total;
-}
-// How many pairs of an XCD to take at a time.  One after the other leaves the longest tiles of the last
-// pair for the end of the launch, which counts when an XCD's 64 workgroup slots go round only a few
-// times: forward / dQ of 2 x 16 heads x 4096 x 64 36.1 / 46.6 us one by one, 32.9 / 42.6 in fours; dense 32
-// heads x 8192 542 / 781 and 518 / 731.
-// From about eight rounds on the tail is nothing, while four heads' stripes then share an L2: 32 heads x
-// 32768 the same both ways, 32 heads x 131072 (2 MB of stripes a head) 5.90 ms one by one, 6.06 in fours.
-// Pairs of a packed batch are of different lengths and go one after the other: neighbouring workgroups of an
-// XCD go to its four shader engines in turn, so with four pairs side by side each engine had the tiles of
-// one, and the launch waited for the engine with the longest sequence.  Forward / dQ of 20 x 5 heads x up to
-// 8832 x 128 197.7 / 277.4 us in fours, 119.2 / 166.5 one by one; 11 x 10 heads x 64 87.7 / 107.7 and 61.2 / 76.8;
-// 8 x 32 heads of 200 to 8192 rows 330.8 / 448.4 and 331.6 / 454.1.
-__host__ inline int map_group(int bh_total, int tiles, bool packed) {
-  return !packed && (int64_t)((bh_total + 7) / 8) * tiles <= 8 * 64 ? 4 : 1;
-}
-__host__ __device__ inline int grid_for(int bh_total, int tiles) { return 8 * ((bh_total + 7) / 8) * tiles; }
 
 }  // namespace s2

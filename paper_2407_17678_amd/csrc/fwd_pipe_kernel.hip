@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // how far a score may exceed the reference maximum before it is moved (raw scores; see the top of this file).  Finite, also
   // where 2^kTau is out of reach of any score: the first maximum has to move it from -inf.
   const bool lazy_ref = D == 128 && (VARLEN ? (tile + 1) * BM <= N : p.q_rows % BM == 0);
-  const float tau = lazy_ref ? fminf(kTau / c, 3.4e38f) : 0.f;
+  const float tau = lazy_ref ? __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, fminf(kTau / c, 3.4e38f)))) : 0.f;
   // The lane offsets of my direct loads.  Where a packed sequence ends inside the 16 rows I fetch (VARLEN) no lane's goes past
   // end_off, the last piece of the last row that exists.
   const typename Piece::Plan plan = Piece::plan(p.kv_st, lane);
@@ -260,12 +260,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   auto p_upto = [](int sl) S2_INLINE { return (kPace * (sl + 1)) / NS; };
   // drops what my query does not see of the step that begins at key kv0: keys after it
   auto mask_step = [&](f32x16 (&sn)[2], int kv0) S2_INLINE {
-    const int qpos = qw0 + l32;
+    const int ln = lane_now();  // (formed anew: at D = 64 no register is left for what the lane number gives)
 #pragma unroll
     for (int pc = 0; pc < 4; ++pc) {
       const int row = kv0 + 16 * pc;
       // how many of these 16 keys I see, counted from the first one my half of the wavefront holds
-      const int lim = qpos - row + 1 - 4 * half;
+      const int lim = qw0 + (ln & 31) - row + 1 - 4 * (ln >> 5);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         if (8 * (i >> 2) + (i & 3) >= lim) sn[pc >> 1][8 * (pc & 1) + i] = kNegInf;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
         dma(std::integral_constant<int, d - NG>{}, vb, off_n, end_n, sv[par ^ 1]);
     };
     // keeps the entry window moving, two steps at a time: what is asked for until the next time is of steps it + 3 and it + 4
-    if (!DENSE && par == 0) (void)list.get((it + 2) >> cpb_sh, lane);
+    if (!DENSE && par == 0) (void)list.get((it + 2) >> cpb_sh, lane_now());
     if (act_c || act_n) {
       // a step that is not mine: every probability exp2(s*c - inf) = 0
       const float mc_keep = mc;

@@ -1,0 +1,60 @@
+"""CPU test of the workgroup -> tile mappings (csrc/tile_map.h), compiled with the host compiler: over numbers of (batch, head) pairs and tiles
+every tile has exactly one workgroup, no XCD has more tiles than another but for the granularity they are dealt out in, pairs
+that need not be shared stay on one XCD, and the interleaved order never goes back to a longer rank."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2407_17678_amd", "csrc")
+
+DRIVER = r"""
+#include <algorithm>
+#include <cstdio>
+#include <set>
+#include <utility>
+#include "tile_map.h"
+using namespace s2;
+static int check(bool ok, const char* what, int P, int T, int G, int w) {
+  if (!ok) std::printf("%s: %d pairs, %d tiles, group %d, workgroup %d\n", what, P, T, G, w);
+  return ok ? 0 : 1;
+}
+int main() {
+  for (int P = 1; P <= 41; ++P)
+    for (int T : {1, 2, 3, 5, 8, 13, 31, 32, 33, 62, 63, 64, 65, 66, 127, 128, 129, 130, 131, 257})
+      for (int G : {0, 1, 4}) {  // 0: interleaved
+        std::set<std::pair<int, int>> seen;
+        int count[8] = {}, last[8] = {};
+        const int grid = G ? grid_for(P, T) : grid_for_interleaved(P, T);
+        if (check(grid % 8 == 0, "grid", P, T, G, grid)) return 1;
+        for (int w = 0; w < grid; ++w) {
+          int bh = -1, rank = -1;
+          if (!(G ? map_workgroup(w, P, T, G, bh, rank) : map_workgroup_interleaved(w, P, T, bh, rank))) continue;
+          const int x = w & 7;
+          if (check(bh >= 0 && bh < P && rank >= 0 && rank < T, "range", P, T, G, w)) return 1;
+          if (check(seen.insert({bh, rank}).second, "twice", P, T, G, w)) return 1;
+          if (check(bh >= P / 8 * 8 || bh % 8 == x, "XCD", P, T, G, w)) return 1;
+          if (!G && check(rank >= last[x], "order", P, T, G, w)) return 1;
+          last[x] = rank;
+          ++count[x];
+        }
+        if (check((int)seen.size() == P * T, "missing", P, T, G, grid)) return 1;
+        // at most a run more, and the last run may be short
+        const int most = *std::max_element(count, count + 8), least = *std::min_element(count, count + 8);
+        if (check(most - least <= (P % 8 ? 2 * deal_run(T) : 0), "balance", P, T, G, grid)) return 1;
+      }
+  std::printf("mapped\n");
+  return 0;
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_every_tile_has_one_workgroup(tmp_path):
+    src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
+    src.write_text(DRIVER)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True, capture_output=True, text=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout == "mapped\n", r.stdout
