@@ -141,7 +141,7 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
   }
   const int tile = DENSE ? rank : p.kv_tiles.order[h * T + nth];  // dense: first key tiles are longest
   const int S = DENSE ? CH : FINE ? FINE : p.block_size;
-  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
+  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1, s_sh = 6 + cpb_sh;  // chunks per list entry; S of one as a shift
   int row_base = 0, N = p.seqlen;
   if (VARLEN) {
     const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
@@ -177,8 +177,9 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
   // minus the bias the grouped direct loads put into their lane offsets
-  const uint16_t* qb = p.q + q_off - Piece::kBias / 2;
-  const uint16_t* gb = p.d_o + q_off - Piece::kBias / 2;
+  const char* qb = reinterpret_cast<const char*>(p.q + q_off) - Piece::kBias;
+  const char* gb = reinterpret_cast<const char*>(p.d_o + q_off) - Piece::kBias;
+  const uint32_t row_bytes = (uint32_t)(2 * p.q_st);  // (api.hip: at most 2^25)
   // packed batch: the row statistics are [heads, rows of the tensors]
   const int64_t stats_off = VARLEN ? (int64_t)h * p.seqlen + row_base : ((int64_t)b * p.heads + h) * N;
   const float* lse_b = p.neg_lse + stats_off;
@@ -227,8 +228,8 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
       q0 = N - CH - j * CH;  // from the last query chunk down, like the sparse lists
       keep = true;
     } else {
-      const int e = list.peek(j >> cpb_sh);
-      q0 = (e >> 16) * S + (cpb_m - (j & cpb_m)) * CH;
+      const uint32_t e = (uint32_t)list.at(j >> cpb_sh);
+      q0 = (int)(e >> 16 << s_sh) + ((cpb_m - (j & cpb_m)) << 6);
       keep = (e >> my_member) & 1;
     }
   };
@@ -261,8 +262,8 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
       row = min(row, N - 1);
       Piece::limit(pl, N - row, p.q_st);
     }
-    const uint16_t* qg = qb + (int64_t)row * p.q_st;
-    const uint16_t* gg = gb + (int64_t)row * p.q_st;
+    const uint64_t at = (uint64_t)(uint32_t)row * row_bytes;
+    const char *qg = qb + at, *gg = gb + at;
     static_for<Piece::kGroups>([&](auto gc) S2_INLINE { Piece::template issue<decltype(gc)::value>(pl, qg, sm.q[buf], wave); });
     static_for<Piece::kGroups>([&](auto gc) S2_INLINE { Piece::template issue<decltype(gc)::value>(pl, gg, sm.g[buf], wave); });
     // 64 floats of each array: lanes 0..15 fetch delta, lanes 16..31 lse, 16 bytes each, in one direct load.
@@ -279,9 +280,9 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
         if (VARLEN) pr = min(pr, N - 1);
         off = 4 * pr + 16 * (ln & 3) + ((ln & 16) ? stats_gap : 0u);
       } else {
-        off = 16 * (ln & 15) + ((ln & 16) ? stats_gap : 0u);
+        off = 16 * (ln & 15) + ((ln & 16) ? stats_gap : 0u) + 4 * (VARLEN && q0 >= N ? 0 : q0);
       }
-      if (ln < 32) dma16(FINE ? delta_b : delta_b + (VARLEN && q0 >= N ? 0 : q0), off, lds_addr(&sm.rs[buf]));
+      if (ln < 32) dma16(delta_b, off, lds_addr(&sm.rs[buf]));
     }
   };
   // first step: a packed sequence skips the leading entries, query blocks that lie after its end (most

@@ -76,7 +76,7 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
     tile = T_seq - 1 - rank;
   }
   const int S = DENSE ? CH : p.block_size;  // FINE: 16 or 32, else 64 or 128
-  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
+  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1, s_sh = 6 + cpb_sh;  // chunks per list entry; S of one as a shift
   const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-key pieces per list entry
   const int qw0 = tile * BM + wave * MW;  // first query row of this wavefront
   const bool wave_on = qw0 < N;           // whether I have query rows at all
@@ -85,8 +85,9 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
   // minus the bias the grouped direct loads put into their lane offsets
-  const uint16_t* kb = p.k + kv_off - Piece::kBias / 2;
-  const uint16_t* vb = p.v + kv_off - Piece::kBias / 2;
+  const char* kb = reinterpret_cast<const char*>(p.k + kv_off) - Piece::kBias;
+  const char* vb = reinterpret_cast<const char*>(p.v + kv_off) - Piece::kBias;
+  const uint32_t row_bytes = (uint32_t)(2 * p.kv_st);  // (api.hip: at most 2^25)
 
   int ent_lo = 0, n_ent;
   if (DENSE) {
@@ -111,6 +112,7 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
     if (i >= n_ent) bits = 0;
   };
   const uint32_t late_from = (uint32_t)(qw0 >> (4 + ppe_sh)) << 16;  // FINE: entries from my first row's block on
+  const int q_end = wave_on ? qw0 + MW : 0;  // past my last query
   // Chunk j of the tile's list: the first key row of the 16 that I fetch (past the end any that exist), and
   // for either 32-key half whether I have anything to compute in it (bit kt: my mask rows keep some of
   // it and not every key lies after every one of my queries), whether some of it has to be masked
@@ -133,24 +135,21 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
       }
       state = (on & 3 ? 1 : 0) | (on & 12 ? 2 : 0) | ((all & 3) != 3 ? 4 : 0) | ((all & 12) != 12 ? 8 : 0) | on << 4;
     } else {
-      j = min(j, total - 1);
-      int kv0;
-      bool keep = true;
+      // (branches kept out: past a list's end entries are 0, kept by nobody, and dense chunks lie past q_end)
+      int kv0, keep = 3;
       if (DENSE) {
         kv0 = j * CH;
+        row = min(kv0, (total - 1) * CH) + 16 * wave;
       } else {
-        const int e = list.peek(j >> cpb_sh);
-        kv0 = (e >> 16) * S + (j & cpb_m) * CH;
-        keep = (e >> my_member) & 1;
+        const uint32_t e = (uint32_t)list.at(j >> cpb_sh);
+        kv0 = (int)(e >> 16 << s_sh) + ((j & cpb_m) << 6);
+        keep = 3 * ((e >> my_member) & 1);
+        row = kv0 + 16 * wave;
       }
-      row = kv0 + 16 * wave;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        if (keep && kv0 + 32 * kt <= qw0 + MW - 1) state |= 1 << kt;
-        if (kv0 + 32 * kt + 31 > qw0) state |= 4 << kt;
-      }
+      const int seen = q_end - kv0;  // half kt: mine if more than 32 * kt, masked if less than 32 * kt + 63
+      state = (keep & ((int)(seen > 0) | (int)(seen > 32) << 1)) | (int)(seen < 63) << 2 | (int)(seen < 95) << 3;
     }
-    if (!inside || !wave_on) state &= ~3;
+    if (FINE && (!inside || !wave_on)) state &= ~3;
     if (VARLEN) row = min(row, N - 1);
   };
 
@@ -184,8 +183,8 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
     // where a packed sequence ends inside the rows I fetch they are limited to the rows that exist; the
     // lists ascend, so from then on every piece is such a piece, with fewer and fewer rows
     if (VARLEN && row + 16 > N) Piece::limit(plan, N - row, p.kv_st);
-    const uint16_t* kg = kb + (int64_t)row * p.kv_st;
-    const uint16_t* vg = vb + (int64_t)row * p.kv_st;
+    const uint64_t at = (uint64_t)(uint32_t)row * row_bytes;
+    const char *kg = kb + at, *vg = vb + at;
     static_for<NG>([&](auto gc) S2_INLINE {
       constexpr int n = decltype(gc)::value;
       Piece::template issue<n>(plan, kg, sm.k[stage], wave);
