@@ -138,7 +138,7 @@ hipError_t launch_dkdv(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   hipError_t e = set_smem(&dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>, sizeof(DkvSmem<D>), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(grid_for_interleaved(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long)),
+  hipLaunchKernelGGL((dkdv_kernel<D, DENSE, FINE, VARLEN, STORE>), dim3(p.key_map.grid()),
                      dim3(kThreads), sizeof(DkvSmem<D>), stream, p);
   return hipGetLastError();
 }
@@ -215,7 +215,10 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
 
 hipError_t launch_bwd(const AttnParams& params, bool dense, int stages, hipStream_t stream) {
   AttnParams p = params;
-  p.map_group = map_group(p.batch * p.heads, (p.q_rows + kBwdBM - 1) / kBwdBM, p.cu_seqlens != nullptr);
+  const int pairs = p.batch * p.heads, tiles = (p.q_rows + kBwdBM - 1) / kBwdBM;
+  p.row_map = row_map(pairs, tiles, map_group(pairs, tiles, p.cu_seqlens != nullptr));
+  p.key_map = key_map(pairs, p.kv_tiles.tiles_per_head + p.split_items - p.split_long);
+  p.by_heads = fast_div(p.heads);
   return p.head_dim == 128 ? launch_dim<128>(p, dense, stages, stream) : launch_dim<64>(p, dense, stages, stream);
 }
 

@@ -28,14 +28,6 @@ namespace s2 {
 
 namespace {
 
-// key tiles first: they are the longer ones
-__host__ __device__ inline int key_grid(const AttnParams& p) {
-  return grid_for_interleaved(p.batch * p.heads, p.kv_tiles.tiles_per_head + p.split_items - p.split_long);
-}
-__host__ inline int query_grid(const AttnParams& p) {
-  return grid_for(p.batch * p.heads, p.cu_seqlens ? (p.q_rows + kBwdBM - 1) / kBwdBM : p.q_tiles.tiles_per_head);
-}
-
 template <int D>
 union MergedSmem {
   DkvSmem<D> dkv;
@@ -43,10 +35,10 @@ union MergedSmem {
 };
 
 template <int D, bool DENSE, int FINE, bool VARLEN>
-__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void bwd_merged_kernel(const AttnParams p) {
+__global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void bwd_merged_kernel(const AttnParams p, int keys) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  const int wg = blockIdx.x, keys = key_grid(p);  // (a multiple of eight: either part keeps its workgroups' XCDs)
-  if (wg < keys)
+  const int wg = blockIdx.x;
+  if (wg < keys)  // key tiles first: they are the longer ones
     dkdv_tile<D, DENSE, FINE, VARLEN, false>(p, wg, smem_raw);
   else
     dq_tile<D, DENSE, FINE != 0, VARLEN, false>(p, wg - keys, smem_raw);
@@ -57,7 +49,8 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   const hipError_t e = set_smem(&bwd_merged_kernel<D, DENSE, FINE, VARLEN>, sizeof(MergedSmem<D>), set);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((bwd_merged_kernel<D, DENSE, FINE, VARLEN>), dim3(key_grid(p) + query_grid(p)), dim3(kThreads), sizeof(MergedSmem<D>), stream, p);
+  const int keys = p.key_map.grid();  // (a multiple of eight: either part keeps its workgroups' XCDs)
+  hipLaunchKernelGGL((bwd_merged_kernel<D, DENSE, FINE, VARLEN>), dim3(keys + p.row_map.grid()), dim3(kThreads), sizeof(MergedSmem<D>), stream, p, keys);
   return hipGetLastError();
 }
 
@@ -84,7 +77,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, hipStream_t stream) {
 constexpr int kMergedGrid = 4096;
 bool bwd_is_merged(const AttnParams& p) {
   const bool in_place = p.dk == p.k || p.dk == p.v || p.dv == p.k || p.dv == p.v;
-  return !in_place && (int64_t)key_grid(p) + query_grid(p) <= kMergedGrid;
+  return !in_place && (int64_t)p.key_map.grid() + p.row_map.grid() <= kMergedGrid;
 }
 
 hipError_t launch_bwd_merged(const AttnParams& p, bool dense, hipStream_t stream) {

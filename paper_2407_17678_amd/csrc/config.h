@@ -7,4 +7,5 @@ constexpr int kFwdBM = 128;     // query rows per forward workgroup (4 waves x 3
 constexpr int kBwdBM = 128;     // query rows per dQ workgroup
 constexpr int kBwdBN = 128;     // keys per dK/dV workgroup
 constexpr int kThreads = 256;   // 4 wavefronts of 64 lanes
+constexpr int kRowRec = 4, kColRec = 12;  // words of a tile's record (TileList::rec)
 }  // namespace s2

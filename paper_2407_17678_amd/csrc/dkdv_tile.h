@@ -125,13 +125,13 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
   const int T = p.kv_tiles.tiles_per_head;
   constexpr bool kSplits = !DENSE && !VARLEN;
   int bh, rank;
-  if (!map_workgroup_interleaved(wg, p.batch * p.heads, kSplits ? p.split_items + T - p.split_long : T, bh, rank)) return;
-  const int b = bh / p.heads, h = bh - b * p.heads;
+  if (!map_workgroup_interleaved(p.key_map, wg, bh, rank)) return;
+  const int b = bh / p.by_heads, h = bh - b * p.heads;
   // which part of which tile, in descending length: the parts of the tiles that are cut, then the others
   int part = 0, parts = 1, nth = rank;
   if (kSplits) {
     if (rank < p.split_items) {
-      const int code = p.split_codes[rank];
+      const int code = load_const<int32_t>(p.split_codes + rank);
       nth = code & 0xFFFF;
       part = (code >> 16) & 0xFF;
       parts = code >> 24;
@@ -139,12 +139,12 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
       nth = rank - p.split_items + p.split_long;
     }
   }
-  const int tile = DENSE ? rank : p.kv_tiles.order[h * T + nth];  // dense: first key tiles are longest
+  const int32_t* const rec = DENSE ? nullptr : p.kv_tiles.col_rec(h, nth);  // (dense: first key tiles are longest)
   const int S = DENSE ? CH : FINE ? FINE : p.block_size;
   const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1, s_sh = 6 + cpb_sh;  // chunks per list entry; S of one as a shift
   int row_base = 0, N = p.seqlen;
   if (VARLEN) {
-    const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
+    const int lo = load_const<int32_t>(p.cu_seqlens + b), hi = load_const<int32_t>(p.cu_seqlens + b + 1);
     row_base = min(max(lo, 0), p.seqlen);  // whatever the array holds, stay inside the tensors
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
   }
@@ -155,20 +155,24 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
   int kvw0, kvw1, my_member = 0;
   bool wave_active;
   if (DENSE) {
-    kvw0 = tile * kBwdBN + wave * 32;
+    kvw0 = rank * kBwdBN + wave * 32;
     kvw1 = kvw0 + 16;
     wave_active = kvw0 < N;
   } else {
-    const int32_t* mem = p.kv_tiles.members + (h * T + tile) * p.kv_tiles.group;
+    const int32_t* mem = rec + 4;
     if (VARLEN) {  // the whole workgroup leaves together when none of its columns is in the sequence
       bool any = false;
-      for (int m = 0; m < p.kv_tiles.group; ++m) any = any || (mem[m] >= 0 && mem[m] * S < N);
+      for (int m = 0; m < p.kv_tiles.group; ++m) {
+        const int blk = load_const<int32_t>(mem + m);
+        any = any || (blk >= 0 && blk * S < N);
+      }
       if (!any) return;
     }
-    my_member = (wave * 32) / S;
-    const int blk0 = mem[my_member], blk1 = mem[(wave * 32 + 16) / S];
-    kvw0 = blk0 < 0 ? kNoKey : blk0 * S + (wave * 32) % S;
-    kvw1 = blk1 < 0 ? kNoKey : blk1 * S + (wave * 32 + 16) % S;
+    const int sh = FINE == 16 ? 4 : FINE == 32 ? 5 : s_sh;
+    my_member = (wave * 32) >> sh;
+    const int blk0 = load_const<int32_t>(mem + my_member), blk1 = load_const<int32_t>(mem + ((wave * 32 + 16) >> sh));
+    kvw0 = blk0 < 0 ? kNoKey : blk0 * S + ((wave * 32) & (S - 1));
+    kvw1 = blk1 < 0 ? kNoKey : blk1 * S + ((wave * 32 + 16) & (S - 1));
     wave_active = FINE == 16 ? min(kvw0, kvw1) < N : kvw0 < N;
   }
   // key of row r (0..31) of mine
@@ -187,10 +191,10 @@ __device__ __forceinline__ void dkdv_tile(const AttnParams& p, int wg, unsigned 
 
   int ent_lo = 0, n_ent;
   if (DENSE) {
-    n_ent = (N - tile * kBwdBN) / kChunk;  // query chunks at or after the tile's first key
+    n_ent = (N - rank * kBwdBN) / kChunk;  // query chunks at or after the tile's first key
   } else {
-    ent_lo = p.kv_tiles.ptr[h * T + tile];
-    n_ent = p.kv_tiles.ptr[h * T + tile + 1] - ent_lo;
+    ent_lo = load_const<int32_t>(rec + 1);
+    n_ent = load_const<int32_t>(rec + 2);
   }
   if (kSplits && parts > 1) {  // my part: so many entries, or (FINE) so many full steps of entries
     const int units = FINE ? (n_ent + EPC - 1) / EPC : n_ent;

@@ -61,11 +61,11 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
-  const int T = p.q_tiles.tiles_per_head;
   int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T, p.map_group, bh, rank)) return;
-  const int b = bh / p.heads, h = bh - b * p.heads;
-  const int tile = p.q_tiles.order[h * T + rank];
+  if (!map_workgroup(p.row_map, blockIdx.x, bh, rank)) return;
+  const int b = bh / p.by_heads, h = bh - b * p.heads;
+  const DevTiles::RowRec rec = p.q_tiles.row_rec(h, rank);
+  const int tile = rec.tile;
   const int S = p.block_size;  // 64 or 128
   const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;
   const int qhalf = wave >> 1;             // which 64-row half of the tile: one dS unit per chunk
@@ -76,8 +76,7 @@ __global__ __launch_bounds__(kThreads, 2) void dq_gemm_kernel(const AttnParams p
   const uint16_t* kb = p.k + b * p.kv_sb + h * p.kv_sh;
   const unsigned char* ds_b = reinterpret_cast<const unsigned char*>(p.ds_store) + (int64_t)b * p.ds_units * 8192;
 
-  const int ent_lo = p.q_tiles.ptr[h * T + tile];
-  const int n_ent = p.q_tiles.ptr[h * T + tile + 1] - ent_lo;
+  const int ent_lo = rec.ent_lo, n_ent = rec.n_ent;
   const int total = n_ent << cpb_sh;  // chunks
   EntryList list, units;
   list.init(p.q_tiles.ent + ent_lo, n_ent, lane);
@@ -237,7 +236,7 @@ hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   const hipError_t e = set_smem(&dq_gemm_kernel<128>, sizeof(DqGemmSmem<128>), set);
   if (e != hipSuccess) return e;
-  const int grid = grid_for(p.batch * p.heads, p.q_tiles.tiles_per_head);
+  const int grid = p.row_map.grid();
   hipLaunchKernelGGL((dq_gemm_kernel<128>), dim3(grid), dim3(kThreads), sizeof(DqGemmSmem<128>), stream, p);
   return hipGetLastError();
 }

@@ -61,14 +61,19 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
   const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
   if (STATS && !DENSE && !VARLEN) clear_split_counts(p, wg * kThreads + tid);
   const int T = p.q_tiles.tiles_per_head;
-  const int T_run = VARLEN ? (p.q_rows + BM - 1) / BM : T;  // packed batch: tiles of the longest length allowed
   int bh, rank;
-  if (!map_workgroup(wg, p.batch * p.heads, T_run, p.map_group, bh, rank)) return;
-  const int b = bh / p.heads, h = bh - b * p.heads;
-  int tile = DENSE ? (T - 1 - rank) : VARLEN ? 0 : p.q_tiles.order[h * T + rank];
+  if (!map_workgroup(p.row_map, wg, bh, rank)) return;
+  const int b = bh / p.by_heads, h = bh - b * p.heads;
+  int tile = T - 1 - rank, ent_lo = 0, n_ent = 0;
+  if (!DENSE && !VARLEN) {
+    const DevTiles::RowRec rec = p.q_tiles.row_rec(h, rank);
+    tile = rec.tile;
+    ent_lo = rec.ent_lo;
+    n_ent = rec.n_ent;
+  }
   int N = p.seqlen, row_base = 0;  // my sequence's length, and the rows of the tensors before it
   if (VARLEN) {
-    const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
+    const int lo = load_const<int32_t>(p.cu_seqlens + b), hi = load_const<int32_t>(p.cu_seqlens + b + 1);
     row_base = min(max(lo, 0), p.seqlen);  // whatever the array holds, stay inside the tensors
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
     const int T_seq = (N + BM - 1) / BM;
@@ -80,7 +85,7 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
   const int ppe_sh = S == 32 ? 1 : 0;                              // FINE: 16-key pieces per list entry
   const int qw0 = tile * BM + wave * MW;  // first query row of this wavefront
   const bool wave_on = qw0 < N;           // whether I have query rows at all
-  const int my_member = (qw0 / S) - tile * (BM / S);
+  const int my_member = (wave * MW) >> s_sh;  // (not FINE)
 
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
@@ -89,12 +94,11 @@ __device__ __forceinline__ void dq_tile(const AttnParams& p, int wg, unsigned ch
   const char* vb = reinterpret_cast<const char*>(p.v + kv_off) - Piece::kBias;
   const uint32_t row_bytes = (uint32_t)(2 * p.kv_st);  // (api.hip: at most 2^25)
 
-  int ent_lo = 0, n_ent;
   if (DENSE) {
     n_ent = min(N, (tile + 1) * BM) / CH;
-  } else {
-    ent_lo = p.q_tiles.ptr[h * T + tile];
-    n_ent = p.q_tiles.ptr[h * T + tile + 1] - ent_lo;
+  } else if (VARLEN) {
+    ent_lo = load_const<int32_t>(p.q_tiles.ptr + h * T + tile);
+    n_ent = load_const<int32_t>(p.q_tiles.ptr + h * T + tile + 1) - ent_lo;
   }
   // chunks: those of an entry, or (FINE) as many as the entries' pieces fill
   const int total = FINE ? ((n_ent << ppe_sh) + 3) >> 2 : n_ent << cpb_sh;

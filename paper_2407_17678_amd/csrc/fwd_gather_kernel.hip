@@ -61,15 +61,21 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_gather_kernel(
   const int T = p.q_tiles.tiles_per_head;      // tiles of the whole sequence (indexes the lists)
   const int T_run = (p.q_rows + BM - 1) / BM;    // tiles this launch computes
   int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, p.map_group, bh, rank)) return;
-  const int b = bh / p.heads, h = bh - b * p.heads;
+  if (!map_workgroup(p.row_map, blockIdx.x, bh, rank)) return;
+  const int b = bh / p.by_heads, h = bh - b * p.heads;
   // longest tiles first: by the layout's order for a whole sequence, else simply last row first
   const bool whole = !VARLEN && p.q_row0 == 0 && T_run == T;
-  int tile = whole ? p.q_tiles.order[h * T + rank] : p.q_row0 / BM + (T_run - 1 - rank);
+  int tile = p.q_row0 / BM + (T_run - 1 - rank), ent_lo = 0, n_ent = 0;
+  if (whole) {
+    const DevTiles::RowRec rec = p.q_tiles.row_rec(h, rank);
+    tile = rec.tile;
+    ent_lo = rec.ent_lo;
+    n_ent = rec.n_ent;
+  }
   // my sequence's length, its query rows in this call, and the rows of the tensors before it
   int N = p.seqlen, n_q = p.q_rows, row_base = 0;
   if (VARLEN) {
-    const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
+    const int lo = load_const<int32_t>(p.cu_seqlens + b), hi = load_const<int32_t>(p.cu_seqlens + b + 1);
     row_base = min(max(lo, 0), p.seqlen);  // whatever the array holds, stay inside the tensors
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
     n_q = N;
@@ -87,8 +93,10 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_gather_kernel(
   const uint16_t* kb = p.k + kv_off - Piece::kBias / 2;
   const uint16_t* vb = p.v + kv_off - Piece::kBias / 2;
 
-  const int ent_lo = p.q_tiles.ptr[h * T + tile];
-  const int n_ent = p.q_tiles.ptr[h * T + tile + 1] - ent_lo;
+  if (!whole) {
+    ent_lo = load_const<int32_t>(p.q_tiles.ptr + h * T + tile);
+    n_ent = load_const<int32_t>(p.q_tiles.ptr + h * T + tile + 1) - ent_lo;
+  }
   const int total = (n_ent + EPC - 1) / EPC;  // chunks
   if (total <= 0) return;
   EntryList list;
@@ -317,7 +325,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_gather_kernel(
 
 template <int D, int S>
 hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
-  const dim3 grid(grid_for(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM)), block(kThreads);
+  const dim3 grid(p.row_map.grid()), block(kThreads);
   if (p.cu_seqlens)
     hipLaunchKernelGGL((fwd_gather_kernel<D, S, true>), grid, block, 0, stream, p);
   else

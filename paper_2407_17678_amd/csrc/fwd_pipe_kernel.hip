@@ -93,15 +93,21 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   const int T = p.q_tiles.tiles_per_head;      // tiles of the whole sequence (indexes the lists)
   const int T_run = (p.q_rows + BM - 1) / BM;    // tiles this launch computes
   int bh, rank;
-  if (!map_workgroup(blockIdx.x, p.batch * p.heads, T_run, p.map_group, bh, rank)) return;
-  const int b = bh / p.heads, h = bh - b * p.heads;
+  if (!map_workgroup(p.row_map, blockIdx.x, bh, rank)) return;
+  const int b = bh / p.by_heads, h = bh - b * p.heads;
   // longest tiles first: by the layout's order for a whole sequence, else simply last row first
   const bool whole = !VARLEN && p.q_row0 == 0 && T_run == T;
-  int tile = (DENSE || !whole) ? p.q_row0 / BM + (T_run - 1 - rank) : p.q_tiles.order[h * T + rank];
+  int tile = p.q_row0 / BM + (T_run - 1 - rank), ent_lo = 0, n_ent = 0;
+  if (!DENSE && whole) {
+    const DevTiles::RowRec rec = p.q_tiles.row_rec(h, rank);
+    tile = rec.tile;
+    ent_lo = rec.ent_lo;
+    n_ent = rec.n_ent;
+  }
   // my sequence's length, its query rows in this call, and the rows of the tensors before it
   int N = p.seqlen, n_q = p.q_rows, row_base = 0;
   if (VARLEN) {
-    const int lo = p.cu_seqlens[b], hi = p.cu_seqlens[b + 1];
+    const int lo = load_const<int32_t>(p.cu_seqlens + b), hi = load_const<int32_t>(p.cu_seqlens + b + 1);
     row_base = min(max(lo, 0), p.seqlen);  // whatever the array holds, stay inside the tensors
     N = min(min(max(hi - lo, 0), p.q_rows), p.seqlen - row_base);
     n_q = N;
@@ -110,11 +116,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
     tile = T_seq - 1 - rank;
   }
   const int S = DENSE ? CH : p.block_size;  // 64 or 128
-  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1;  // chunks per list entry
+  const int cpb_sh = S == 128 ? 1 : 0, cpb_m = (1 << cpb_sh) - 1, s_sh = 6 + cpb_sh;  // chunks per list entry; S as a shift
   const int qw0 = tile * BM + wave * MW;    // first query row of this wavefront (sequence position)
   const int ql0 = qw0 - p.q_row0;           // the same as a row of q / o / lse
   const bool wave_on = ql0 < n_q;           // whether I have query rows at all
-  const int my_member = (qw0 / S) - tile * (BM / S);
+  const int my_member = (wave * MW) >> s_sh;
 
   const int64_t q_off = (VARLEN ? row_base * p.q_st : b * p.q_sb) + h * p.q_sh;
   const int64_t kv_off = (VARLEN ? row_base * p.kv_st : b * p.kv_sb) + h * p.kv_sh;
@@ -122,12 +128,11 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   const char* kb = reinterpret_cast<const char*>(p.k + kv_off) - Piece::kBias;
   const char* vb = reinterpret_cast<const char*>(p.v + kv_off) - Piece::kBias;
 
-  int ent_lo = 0, n_ent;
   if (DENSE) {
     n_ent = min(N, (tile + 1) * BM) / CH;
-  } else {
-    ent_lo = p.q_tiles.ptr[h * T + tile];
-    n_ent = p.q_tiles.ptr[h * T + tile + 1] - ent_lo;
+  } else if (!whole) {
+    ent_lo = load_const<int32_t>(p.q_tiles.ptr + h * T + tile);
+    n_ent = load_const<int32_t>(p.q_tiles.ptr + h * T + tile + 1) - ent_lo;
   }
   const int total = n_ent << cpb_sh;  // steps: chunks of the entries
   if (total <= 0) return;
@@ -145,7 +150,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // Step j of the tile's list: its first key (0 past the end of a list, where entries are 0), and whether I have anything to
   // compute there: my mask rows keep some of it, and not every key lies after every one of my queries (q_end: past my last
   // one, 0 where I have none).
-  const int q_end = wave_on ? qw0 + MW : 0, s_sh = 6 + cpb_sh;
+  const int q_end = wave_on ? qw0 + MW : 0;
   auto chunk_at = [&](int j, int& kv0, bool& act) S2_INLINE {
     if (DENSE) {
       kv0 = j * CH;
@@ -479,7 +484,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
 
 template <int D>
 hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
-  const dim3 grid(grid_for(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM)), block(kThreads);
+  const dim3 grid(p.row_map.grid()), block(kThreads);
   if (dense)
     hipLaunchKernelGGL((fwd_pipe_kernel<D, true, false>), grid, block, 0, stream, p);
   else if (p.cu_seqlens)
@@ -493,7 +498,9 @@ hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
 
 hipError_t launch_fwd(const AttnParams& params, bool dense, hipStream_t stream) {
   AttnParams p = params;
-  p.map_group = map_group(p.batch * p.heads, (p.q_rows + kFwdBM - 1) / kFwdBM, p.cu_seqlens != nullptr);
+  const int pairs = p.batch * p.heads, tiles = (p.q_rows + kFwdBM - 1) / kFwdBM;
+  p.row_map = row_map(pairs, tiles, map_group(pairs, tiles, p.cu_seqlens != nullptr));
+  p.by_heads = fast_div(p.heads);
   if (!dense && p.block_size < 64) return launch_fwd_gather(p, stream);
   return p.head_dim == 128 ? launch_one<128>(p, dense, stream) : launch_one<64>(p, dense, stream);
 }

@@ -4,16 +4,38 @@
 
 #include <cstdint>
 
+#include "config.h"
+#include "tile_map.h"
+
 namespace s2 {
+
+// A word, or a few, that no kernel writes, at an address that is the same for the whole wavefront: a scalar load.  (Where a kernel has stored
+// something before, the compiler itself takes a vector load and waits for it.)
+template <class T>
+__device__ __forceinline__ T load_const(const void* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
 
 // Merged tile list on the device (see TileList in layout.h).
 struct DevTiles {
   const int32_t* ptr = nullptr;
   const int32_t* ent = nullptr;
-  const int32_t* order = nullptr;
-  const int32_t* members = nullptr;  // block index of each tile member (-1 = none)
+  const int32_t* rec = nullptr;  // [head][rank][kRowRec or kColRec]
   int tiles_per_head = 0;
   int group = 0;
+  // What the workgroup of head h's tile of a rank begins with (layout.h: TileList::rec).
+  // (The empty assembly has a row tile's words loaded together: left alone the compiler asks for each when it needs it.)
+  struct RowRec {
+    int tile, ent_lo, n_ent;
+  };
+  __device__ __forceinline__ RowRec row_rec(int h, int rank) const {
+    typedef int32_t words __attribute__((ext_vector_type(4)));
+    const words w = load_const<words>(rec + ((int64_t)h * tiles_per_head + rank) * kRowRec);
+    RowRec r{w[0], w[1], w[2]};
+    asm volatile("" : "+s"(r.tile), "+s"(r.ent_lo), "+s"(r.n_ent));
+    return r;
+  }
+  __device__ __forceinline__ const int32_t* col_rec(int h, int rank) const { return rec + ((int64_t)h * tiles_per_head + rank) * kColRec; }
 };
 
 struct AttnParams {
@@ -38,7 +60,10 @@ struct AttnParams {
   // sequence b owns rows cu_seqlens[b] .. cu_seqlens[b+1]-1 of q, k, v, o and lse; then batch is
   // the number of sequences, seqlen the rows in the tensors and q_rows the longest length allowed
   const int32_t* cu_seqlens;
-  int map_group;  // (batch, head) pairs of an XCD taken at a time by the row-tile kernels (map_group in device_util.h)
+  // which tile a workgroup computes (tile_map.h; set by launch_fwd and launch_bwd)
+  RowMap row_map;
+  KeyMap key_map;
+  FastDiv by_heads;
   int64_t q_sb, q_sh, q_st;
   int64_t kv_sb, kv_sh, kv_st;
   float scale;        // softmax scale
@@ -99,7 +124,7 @@ struct DecodeParams {
 
 // Each returns the hipError_t of the launch (hipGetLastError after the launch).
 hipError_t launch_fwd(const AttnParams& p, bool dense, hipStream_t stream);
-// The launch of it for mask blocks of 16 and 32 tokens (map_group set).
+// The launch of it for mask blocks of 16 and 32 tokens (row_map set).
 hipError_t launch_fwd_gather(const AttnParams& p, hipStream_t stream);
 // `stages` selects which of the three backward launches run: 1 = delta, 2 = dK/dV, 4 = dQ.
 constexpr int kBwdDelta = 1, kBwdDkDv = 2, kBwdDq = 4, kBwdAll = 7;

@@ -3,6 +3,8 @@
 // merged tile lists the kernels iterate over.  Integer work only; no HIP calls in this file.
 #include "layout.h"
 
+#include "config.h"
+
 #include <algorithm>
 #include <limits>
 #include <numeric>
@@ -273,6 +275,17 @@ void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
     std::iota(ord, ord + T, 0);
     const int32_t* hp = out.ptr.data() + (size_t)h * T;
     std::stable_sort(ord, ord + T, [&](int a, int b) { return hp[a + 1] - hp[a] > hp[b + 1] - hp[b]; });
+  }
+  const int words = transpose ? kColRec : kRowRec;
+  out.rec.assign((size_t)H * T * words, transpose ? -1 : 0);
+  for (size_t k = 0; k < (size_t)H * T; ++k) {
+    const int t = out.order[k];
+    const size_t at = k / T * T + t;
+    int32_t* r = out.rec.data() + k * words;
+    r[0] = transpose ? 0 : t;
+    r[1] = out.ptr[at];
+    r[2] = out.ptr[at + 1] - out.ptr[at];
+    if (transpose) std::copy_n(out.members.data() + at * group, group, r + 4);
   }
 }
 

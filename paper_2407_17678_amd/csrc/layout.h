@@ -25,10 +25,12 @@ struct TileList {
                                  // descending inside a column tile
   std::vector<int32_t> order;    // [H*tiles_per_head]: per head, tile ids by descending length
   std::vector<int32_t> members;  // [H*tiles_per_head*group]: block index of each member, -1 = none
+  // Per head and rank what a workgroup needs to begin with, so that it comes in one load: kRowRec or kColRec words a tile, (row tile) its
+  // number, (column tile) nothing; where its list begins in ent; the list's length; nothing; (column tile) its members, -1 = none
+  std::vector<int32_t> rec;
+  int32_t* d_rec = nullptr;
   int32_t* d_ptr = nullptr;      // device copies (owned by the layout)
   int32_t* d_ent = nullptr;
-  int32_t* d_order = nullptr;
-  int32_t* d_members = nullptr;
   int max_len = 0;
 };
 

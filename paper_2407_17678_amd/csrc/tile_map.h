@@ -11,6 +11,22 @@
 
 namespace s2 {
 
+// n / d of 0 <= n < 2^31 for a d that the host knows: n * ceil(2^(31 + l) / d) >> (31 + l), 2^l the first power of two from d on.  (The
+// factor is less than 2^-l too large, relative to d / 2^31.)  Three scalar instructions; the division that the compiler writes goes
+// through a vector reciprocal and back, and a tile's start had five to seven of them.  With them gone and a tile's record in one
+// scalar load (DevTiles in kernels.h), forward and backward, us: packed 13 x 18 heads of 100 to 6272 rows x 64 54.6 -> 51.5, 168 -> 162, 20 x 11 heads x 128
+// 146 -> 139, 423 -> 410, 8 x 32 heads 326 -> 323, 974 -> 961; 1 x 4 x 512 x 64 8.3 -> 7.9, 15.8 -> 15.7; 2 x 16 x 3904 x 128 45.5 -> 45.0, 129.4 -> 128.8.
+struct FastDiv {
+  uint32_t factor, shift;
+};
+inline FastDiv fast_div(uint32_t d) {
+  FastDiv f{0, 31};
+  while (((uint64_t)1 << (f.shift - 31)) < d) ++f.shift;
+  f.factor = (uint32_t)((((uint64_t)1 << f.shift) + d - 1) / d);
+  return f;
+}
+S2_HD inline int operator/(int n, const FastDiv& f) { return (int)(((uint64_t)(uint32_t)n * f.factor) >> f.shift); }
+
 // Workgroup index -> (batch*head, rank inside the head) such that all tiles of one (batch, head)
 // run on one XCD.  Workgroups are handed to the 8 XCDs round-robin by linear index, and each XCD
 // has its own L2: keeping a head's key/value stripes and moving window on one XCD lets every
@@ -21,38 +37,54 @@ namespace s2 {
 // 159 and 118, 520 and 339; 3 x 8192 44 and 29, 126 and 87; 20 x 4096 35 and 33, 106 and 92; 33 x 4096 x 64 37 and 31, 92 and 79; dense 19 x
 // 7168 290 and 234, 818 and 680; where seven are left over, and little is lost by an XCD each, 15 x 8192 x 128 84 and 81, 239 and 239.  (Single tiles instead of runs:
 // 118 and 361, 30 and 90, 33 and 93, 32 and 79, 233 and 701, 85 and 251; at 64 tiles runs of four are 1 to 3 % slower than of two, at 128 none is.)
-S2_HD inline int deal_run(int tiles) { return tiles >= 128 ? 4 : tiles >= 64 ? 2 : 1; }
-// The other pairs of an XCD are taken `group` at a time, a group's tiles by rank: all its longest tiles first,
+inline int deal_run_shift(int tiles) { return tiles >= 128 ? 2 : tiles >= 64 ? 1 : 0; }
+// The other pairs of an XCD are taken a group of one or four at a time, a group's tiles by rank: all its longest tiles first,
 // then all its second longest (map_group chooses).
-S2_HD inline bool map_workgroup(int wg, int bh_total, int tiles, int group, int& bh, int& rank) {
-  const int x = wg & 7, per_xcd = bh_total >> 3, left = bh_total & 7;
-  int slot = wg >> 3;
-  if (left > 0) {  // an XCD's slots for what is left over come first
-    const int run = deal_run(tiles), runs = (tiles + run - 1) / run, shared = run * ((left * runs + 7) >> 3);
-    if (slot < shared) {
-      const int i = 8 * (slot / run) + x, r = i / left;
-      rank = r * run + slot % run;
-      bh = 8 * per_xcd + i - r * left;
-      return rank < tiles;
-    }
-    slot -= shared;
-  }
-  const int g = slot / (group * tiles);
-  if (group == 1) {
-    rank = slot - g * tiles;
-    bh = x + 8 * g;
-    return g < per_xcd;
-  }
-  const int in = slot - g * (group * tiles);
-  const int size = group < per_xcd - g * group ? group : per_xcd - g * group;
-  if (size <= 0) return false;
-  rank = in / size;
-  bh = x + 8 * (g * group + in - rank * size);
-  return true;
+struct RowMap {
+  int per_xcd, left;    // pairs of an XCD's own, and left over
+  int tiles;            // of a pair
+  int run, shared;      // shift of the tiles to a run; an XCD's slots for what is left over, which come first
+  int group, in_group;  // shift of the pairs to a group, tiles of a group
+  FastDiv by_left, by_group, by_last;  // division by left, in_group and the pairs of the last group
+  int grid() const { return 8 * (per_xcd * tiles + shared); }
+};
+inline RowMap row_map(int bh_total, int tiles, int group) {
+  RowMap m{};
+  m.per_xcd = bh_total >> 3;
+  m.left = bh_total & 7;
+  m.tiles = tiles;
+  m.run = deal_run_shift(tiles);
+  m.shared = ((m.left * ((tiles + (1 << m.run) - 1) >> m.run) + 7) >> 3) << m.run;
+  m.group = group == 4 ? 2 : 0;
+  m.in_group = tiles << m.group;
+  m.by_left = fast_div(m.left > 0 ? m.left : 1);
+  m.by_group = fast_div(m.in_group);
+  const int last = m.per_xcd & ((1 << m.group) - 1);
+  m.by_last = fast_div(last > 0 ? last : 1);
+  return m;
 }
-S2_HD inline int grid_for(int bh_total, int tiles) {
-  const int left = bh_total & 7, run = deal_run(tiles), runs = (tiles + run - 1) / run;
-  return 8 * ((bh_total >> 3) * tiles + run * ((left * runs + 7) >> 3));
+S2_HD inline bool map_workgroup(const RowMap& m, int wg, int& bh, int& rank) {
+  const int x = wg & 7;
+  int slot = wg >> 3;
+  if (slot < m.shared) {
+    const int i = 8 * (slot >> m.run) + x, r = i / m.by_left;
+    rank = (r << m.run) + (slot & ((1 << m.run) - 1));
+    bh = 8 * m.per_xcd + i - r * m.left;
+    return rank < m.tiles;
+  }
+  slot -= m.shared;
+  const int g = slot / m.by_group, in = slot - g * m.in_group;
+  const int size = m.per_xcd - (g << m.group);  // pairs from the group on
+  int of_rank;
+  if (size >> m.group) {
+    rank = in >> m.group;
+    of_rank = in & ((1 << m.group) - 1);
+  } else {
+    rank = in / m.by_last;
+    of_rank = in - rank * size;
+  }
+  bh = x + 8 * ((g << m.group) + of_rank);
+  return size > 0;
 }
 // Same XCD assignment, but the (batch, head) pairs are interleaved: all their longest
 // tiles are dispatched first, then all their second longest, ...  Used where tile lengths are very
@@ -61,20 +93,30 @@ S2_HD inline int grid_for(int bh_total, int tiles) {
 // (Where pairs are left over the unit is the run: of run r of every pair an XCD has bh_total / 8, those of its own pairs, and one of what is
 // left over if there is one among numbers r * left, r * left + 1, ... that is its own modulo 8.  That makes (r * bh_total + 7 - x) / 8
 // before run r, and so the s-th run of XCD x is one of number (8 * s + x) / bh_total.  The XCD takes the tiles of its runs of one number by rank.)
-S2_HD inline bool map_workgroup_interleaved(int wg, int bh_total, int tiles, int& bh, int& rank) {
-  const int x = wg & 7, per_xcd = bh_total >> 3, left = bh_total & 7;
-  const int run = left > 0 ? deal_run(tiles) : 1;
-  const int slot = wg >> 3, r = (8 * (slot / run) + x) / bh_total;
-  const unsigned upto = (unsigned)r * bh_total + 7 - x;
-  const int before = upto >> 3, of_run = (int)((upto + bh_total) >> 3) - before;  // of_run: pairs of which the XCD has run r
-  const int i = slot - before * run, in_run = i / of_run, in = i - in_run * of_run;
-  rank = r * run + in_run;
-  bh = in < per_xcd ? x + 8 * in : 8 * per_xcd + ((x - r * left) & 7);
-  return rank < tiles;
+struct KeyMap {
+  int bh_total, tiles, run;                   // run: shift of the tiles to a run
+  FastDiv by_total, by_own, by_more;          // division by bh_total, bh_total / 8 and bh_total / 8 + 1
+  int grid() const { return (int)(((unsigned)bh_total * ((tiles + (1 << run) - 1) >> run) + 7) / 8 * 8) << run; }
+};
+inline KeyMap key_map(int bh_total, int tiles) {
+  KeyMap m{};
+  m.bh_total = bh_total;
+  m.tiles = tiles;
+  m.run = (bh_total & 7) > 0 ? deal_run_shift(tiles) : 0;
+  m.by_total = fast_div(bh_total);
+  m.by_own = fast_div(bh_total >= 8 ? bh_total >> 3 : 1);
+  m.by_more = fast_div((bh_total >> 3) + 1);
+  return m;
 }
-S2_HD inline int grid_for_interleaved(int bh_total, int tiles) {
-  const int run = (bh_total & 7) > 0 ? deal_run(tiles) : 1, runs = (tiles + run - 1) / run;
-  return (int)(((unsigned)bh_total * runs + 7) / 8 * 8) * run;
+S2_HD inline bool map_workgroup_interleaved(const KeyMap& m, int wg, int& bh, int& rank) {
+  const int x = wg & 7, per_xcd = m.bh_total >> 3, left = m.bh_total & 7;
+  const int slot = wg >> 3, r = (8 * (slot >> m.run) + x) / m.by_total;
+  const unsigned upto = (unsigned)r * m.bh_total + 7 - x;
+  const int before = upto >> 3, of_run = (int)((upto + m.bh_total) >> 3) - before;  // of_run: pairs of which the XCD has run r
+  const int i = slot - (before << m.run), in_run = of_run > per_xcd ? i / m.by_more : i / m.by_own, in = i - in_run * of_run;
+  rank = (r << m.run) + in_run;
+  bh = in < per_xcd ? x + 8 * in : 8 * per_xcd + ((x - r * left) & 7);
+  return rank < m.tiles;
 }
 // How many pairs of an XCD to take at a time.  One after the other leaves the longest tiles of the last
 // pair for the end of the launch, which counts when an XCD's 64 workgroup slots go round only a few

@@ -1,6 +1,7 @@
 """CPU test of the workgroup -> tile mappings (csrc/tile_map.h), compiled with the host compiler: over numbers of (batch, head) pairs and tiles
 every tile has exactly one workgroup, no XCD has more tiles than another but for the granularity they are dealt out in, pairs
-that need not be shared stay on one XCD, and the interleaved order never goes back to a longer rank."""
+that need not be shared stay on one XCD, and the interleaved order never goes back to a longer rank.  The division that the mappings
+use is compared with the compiler's."""
 
 import os
 import shutil
@@ -22,16 +23,26 @@ static int check(bool ok, const char* what, int P, int T, int G, int w) {
   return ok ? 0 : 1;
 }
 int main() {
+  // every quotient changes at a multiple of d: there, on either side of it, and at the ends of the range
+  for (long d = 1; d < (1l << 31); d += 1 + d / 37)
+    for (long q = 0; q * d < (1l << 31); q += 1 + q / 5)
+      for (long n : {q * d - 1, q * d, q * d + d - 1, (1l << 31) - 1 - q})
+        if (n >= 0 && n < (1l << 31) && (int)n / fast_div((uint32_t)d) != (int)(n / d)) {
+          std::printf("%ld / %ld\n", n, d);
+          return 1;
+        }
   for (int P = 1; P <= 41; ++P)
     for (int T : {1, 2, 3, 5, 8, 13, 31, 32, 33, 62, 63, 64, 65, 66, 127, 128, 129, 130, 131, 257})
       for (int G : {0, 1, 4}) {  // 0: interleaved
         std::set<std::pair<int, int>> seen;
         int count[8] = {}, last[8] = {};
-        const int grid = G ? grid_for(P, T) : grid_for_interleaved(P, T);
+        const RowMap rows = row_map(P, T, G);
+        const KeyMap keys = key_map(P, T);
+        const int grid = G ? rows.grid() : keys.grid();
         if (check(grid % 8 == 0, "grid", P, T, G, grid)) return 1;
         for (int w = 0; w < grid; ++w) {
           int bh = -1, rank = -1;
-          if (!(G ? map_workgroup(w, P, T, G, bh, rank) : map_workgroup_interleaved(w, P, T, bh, rank))) continue;
+          if (!(G ? map_workgroup(rows, w, bh, rank) : map_workgroup_interleaved(keys, w, bh, rank))) continue;
           const int x = w & 7;
           if (check(bh >= 0 && bh < P && rank >= 0 && rank < T, "range", P, T, G, w)) return 1;
           if (check(seen.insert({bh, rank}).second, "twice", P, T, G, w)) return 1;
@@ -43,7 +54,7 @@ int main() {
         if (check((int)seen.size() == P * T, "missing", P, T, G, grid)) return 1;
         // at most a run more, and the last run may be short
         const int most = *std::max_element(count, count + 8), least = *std::min_element(count, count + 8);
-        if (check(most - least <= (P % 8 ? 2 * deal_run(T) : 0), "balance", P, T, G, grid)) return 1;
+        if (check(most - least <= (P % 8 ? 2 << deal_run_shift(T) : 0), "balance", P, T, G, grid)) return 1;
       }
   std::printf("mapped\n");
   return 0;
