@@ -614,7 +614,7 @@ int check_pattern(const s2_layout_params* lp, const s2_layout* layout, int heads
 //    little.  From 384 units on where two fit (four in blocks of 32, whose units are half as large), from 512 where
 //    one does: 96 pairs of 128 to 512 units x 128 179 us in two splits, 163 in eight, all of 384 203 and 206; 80 pairs of 256
 //    to 1024 32-token units x 64 101 in three, 82 in twelve; 180 pairs of 128 to 512 x 128 370 in one, 350 in six.
-//  - Above that, up to 255 pairs: one split of four wavefronts while rows are short, then pieces of a dozen units.  At
+//  - Above that, up to 255 pairs: one split while rows are short, then pieces of a dozen units.  At
 //    head_dim 128 from 256 units on (200 pairs of 64 to 256 units 204 us in one split, 179 in six, all of 384 411 and 414, but
 //    all of 128 139 and 148), at 64 from 96 (all of 128 89 and 83, of 64 34 and 39), in blocks of 32 from 64 (of 64 x 128
 //    47 in one, 39 in two; of 256 to 1024 x 64 470 in one, 176 in six).
@@ -629,10 +629,11 @@ int choose_splits(const s2_layout_params* lp, const s2_layout* layout, int nseq,
   const int64_t units = S == 32 ? blocks : units64;       // as the kernel counts them, in the longest row
   const int64_t pairs = (int64_t)nseq * heads;
   int64_t cap;
-  const int64_t fit = s2::decode_wide_groups(S, 2) / pairs;  // splits of eight wavefronts that fit
-  if (pairs >= 256 && pairs > s2::decode_wide_groups(S, 1)) {
+  const int64_t fit = s2::kDecodeWideGroups / pairs;  // splits of eight wavefronts that fit
+  const int64_t few = S == 16 ? 256 : 192;                // the first range's pairs
+  if (pairs >= 256 && pairs > few) {
     cap = units64 / 12;
-  } else if (pairs > s2::decode_wide_groups(S, 1)) {
+  } else if (pairs > few) {
     cap = units >= (S == 32 ? 64 : head_dim == 64 ? 96 : 256) ? units / 12 : 1;
   } else if (units <= (head_dim == 128 ? 24 : 32)) {
     cap = 1;

@@ -1,9 +1,18 @@
 // Decode: one query token per sequence against a contiguous KV cache (section 4.1).  The query
 // at position L-1 reads only the KV blocks that block row (L-1) div S of the head's mask keeps:
 // the head's vertical stripes plus the local window (section 4.2), enumerated in closed form.
-// The work is one multiply-add per byte read, so the kernel is a bandwidth kernel: every lane
-// issues 16-byte loads, a row of K or V is covered by D/8 adjacent lanes, and both the K and V
-// loads of a 64-token unit are in flight before the first score is needed.
+// The work is one multiply-add per byte read, so the kernel is a bandwidth kernel in large calls and a chain of latencies
+// in small ones: every lane issues 16-byte loads, a row of K or V is covered by D/8 adjacent lanes, and a wavefront always
+// has a K or V tile of 64 tokens on its way: the next unit's K is requested as soon as this unit's scores have freed
+// the registers, its V as soon as the sums have.  What is the same in all lanes (the list entry, the page, the block's
+// address, the rows attended) is found by scalar instructions, a unit ahead, and counted once: a block is a
+// buffer that ends with its last attended row, so that a load needs no clamping (a row past the end reads as
+// zero and fetches nothing) and its address is one scalar addition.  Scores are added up across a row's lanes by lane
+// permutations inside the additions; through the LDS each took four round trips that a lone wavefront waits for.  Measured
+// against one lookup per lane and load, loads of a unit behind the sums of the one before and sums through the LDS: 16384 of
+// 30 x 40 paged rows x 64, blocks of 16 89 -> 71 us, 64 x 32 paged rows of 8192 to 32768 x 128 (blocks of 16) 267 -> 245
+// (5.6 TB/s), 224 rows of 8192, D = 64, blocks of 64 19.6 -> 14.7, one sequence of 32768 x 32 heads 14.5 -> 13.8,
+// calls of a few short rows 6.3 -> 4.6; large contiguous calls, at 5.5 to 5.7 TB/s before, are as they were.
 //
 // A caller-supplied pattern replaces the closed form by row (L-1) div S of the layout's lists.
 //
@@ -19,6 +28,7 @@
 #include "config.h"
 #include "device_util.h"
 #include "kernels.h"
+#include "sched_util.h"
 
 namespace s2 {
 
@@ -26,13 +36,25 @@ namespace {
 
 constexpr float kNegInf = -__builtin_inff();
 
+// From this token stride (in elements) on, the offsets of a unit's 64 rows do not fit into the 31 bits of a buffer's size.
+constexpr int64_t kFarRows = (int64_t)1 << 24;
+
+// x of a lane of the neighbouring group of M lanes (M = 1, 2, 4, 8), where x is the same in all M lanes of a group: the
+// value of lane ^ M, by a lane permutation that an addition takes along instead of a round through the LDS.
+template <int M>
+__device__ __forceinline__ float of_neighbour(float x) {
+  constexpr int kCtrl = M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 4 ? 0x141 : 0x140;  // quad_perm 1032, 2301; half row, row reversed
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kCtrl, 0xf, 0xf, true));
+}
+
 // Kept blocks of block row i, in ascending order, as (stripe run, local run), or as a list.
 struct RowBlocks {
   int first_stripe, n_stripe, stride, local_lo, count;
   const int32_t* cols;  // caller-supplied pattern: the row's list; nullptr = closed form
   __device__ int block(int n) const {
-    if (cols) return cols[n];
-    return n < n_stripe ? first_stripe + n * stride : local_lo + (n - n_stripe);
+    const int striped = first_stripe + n * stride, local = local_lo + (n - n_stripe);
+    if (cols) return load_const<int32_t>(cols + n);
+    return n < n_stripe ? striped : local;
   }
 };
 
@@ -44,9 +66,9 @@ __device__ inline RowBlocks row_blocks(const DecodeParams& p, int head, int i) {
   r.cols = nullptr;
   r.local_lo = 0;
   if (p.row_ptr) {
-    const int32_t lo = p.row_ptr[(int64_t)head * p.num_blocks + i];
+    const int32_t lo = load_const<int32_t>(p.row_ptr + (int64_t)head * p.num_blocks + i);
     r.cols = p.col_idx + lo;
-    r.count = p.row_ptr[(int64_t)head * p.num_blocks + i + 1] - lo;
+    r.count = load_const<int32_t>(p.row_ptr + (int64_t)head * p.num_blocks + i + 1) - lo;
     return r;
   }
   if (p.dense) {
@@ -56,13 +78,13 @@ __device__ inline RowBlocks row_blocks(const DecodeParams& p, int head, int i) {
   }
   r.local_lo = max(0, i - p.local_blocks + 1);
   if (p.stride > 0) {
-    const int o = (p.head_index_base + head) % p.stride;
+    const int o = p.head_index_base + head - (p.head_index_base + head) / p.by_stride * p.stride;
     const int lo = p.window_blocks > 0 ? max(0, i - p.window_blocks + 1) : 0;
     int first = o;
-    if (lo > o) first = o + ((lo - o + p.stride - 1) / p.stride) * p.stride;
+    if (lo > o) first = o + (lo - o + p.stride - 1) / p.by_stride * p.stride;
     if (first < r.local_lo) {
       r.first_stripe = first;
-      r.n_stripe = (r.local_lo - 1 - first) / p.stride + 1;
+      r.n_stripe = (r.local_lo - 1 - first) / p.by_stride + 1;
     }
   }
   r.count = r.n_stripe + (i - r.local_lo + 1);
@@ -73,9 +95,13 @@ __device__ inline RowBlocks row_blocks(const DecodeParams& p, int head, int i) {
 // of the row's list side by side, so that every load still fetches rows the query attends (a 16-token
 // block on its own would fill a quarter of the 64 rows a unit loads).
 //
-// W: wavefronts of a workgroup, each with a unit in flight (128 data registers, so two to a SIMD).
-template <int D, bool PAGED, bool GATHER, int W>
-__global__ __launch_bounds__(64 * W, 2) void decode_split_kernel(const DecodeParams p) {
+// W: wavefronts of a workgroup, each with a unit in flight (128 data registers at D = 128, so two to a SIMD; three, with the
+// registers pressed to 168, measured the same).
+//
+// FAR: the instantiation for caches whose tokens are so far apart that a unit does not fit a buffer's 31 bits (kFarRows): it
+// reads through 64-bit addresses, and a row past the last attended one reads that one.
+template <int D, bool PAGED, bool GATHER, int W, bool FAR>
+__global__ __launch_bounds__(64 * W, FAR ? 1 : D == 128 ? 2 : 4) void decode_split_kernel(const DecodeParams p) {
   constexpr int LPR = D / 8;     // lanes covering one row
   constexpr int RPI = 64 / LPR;  // rows covered by one wavefront-wide load
   constexpr int NI = 64 / RPI;   // loads per 64-token unit
@@ -83,25 +109,26 @@ __global__ __launch_bounds__(64 * W, 2) void decode_split_kernel(const DecodePar
   __shared__ float sh_m[W], sh_l[W];
   __shared__ float sh_acc[W][D];
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (a unit's blocks and pages are then found by scalar instructions)
   const int c = lane % LPR, g = lane / LPR;
   const int item = blockIdx.x;  // (b * heads + h) * splits + split
-  const int split = item % p.num_splits;
-  const int bh = item / p.num_splits;
-  const int b = bh / p.heads, h = bh - b * p.heads;
+  const int bh = item / p.by_splits, split = item - bh * p.num_splits;
+  const int b = bh / p.by_heads, h = bh - b * p.heads;
 
-  int L = p.seq_lens[b];
+  int L = load_const<int32_t>(p.seq_lens + b);
   L = min(max(L, 1), p.max_len);
   const int32_t* table = PAGED ? p.block_table + ((int64_t)b * p.heads + h) * p.max_blocks : nullptr;
   const int S = p.block_size;
   const int U = min(S, kChunk);  // tokens per unit of work: 64, or a whole block when it is shorter
-  const int cpb = S / U;
+  const int cpb_sh = S == 128 ? 1 : 0, cpb = 1 << cpb_sh;  // units of a block
   constexpr int BPU = 4;         // GATHER: blocks per unit
-  const int i = (L - 1) / S;
+  const int i = (L - 1) >> (31 - __builtin_clz(S));
   const RowBlocks rb = row_blocks(p, h, i);
-  const int units = GATHER ? (rb.count + BPU - 1) / BPU : rb.count * cpb;
-  const int u_lo = (int)((int64_t)units * split / p.num_splits);
-  const int u_hi = (int)((int64_t)units * (split + 1) / p.num_splits);
+  const int units = GATHER ? (rb.count + BPU - 1) / BPU : rb.count << cpb_sh;
+  // units * split / num_splits and units * (split + 1) / num_splits, without 64-bit divisions
+  const int even = units / p.by_splits, rest = units - even * p.num_splits;
+  const int u_lo = even * split + rest * split / p.by_splits, u_hi = even * (split + 1) + rest * (split + 1) / p.by_splits;
 
   // my 8 query features, as floats
   float qv[8];
@@ -110,8 +137,8 @@ __global__ __launch_bounds__(64 * W, 2) void decode_split_kernel(const DecodePar
 #pragma unroll
     for (int e = 0; e < 8; ++e) qv[e] = (float)q8[e];
   }
-  const uint16_t* kb = p.k_cache + (PAGED ? 0 : b * p.kv_ss + h * p.kv_sh) + 8 * c;
-  const uint16_t* vb = p.v_cache + (PAGED ? 0 : b * p.kv_ss + h * p.kv_sh) + 8 * c;
+  const uint16_t* kb = p.k_cache + (PAGED ? 0 : b * p.kv_ss + h * p.kv_sh);
+  const uint16_t* vb = p.v_cache + (PAGED ? 0 : b * p.kv_ss + h * p.kv_sh);
   int n_missing = 0;
   const float cl = p.scale_log2e;
 
@@ -120,91 +147,103 @@ __global__ __launch_bounds__(64 * W, 2) void decode_split_kernel(const DecodePar
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 
-  for (int u = u_lo + wave; u < u_hi; u += W) {
-    bf16x8 kr[NI], vr[NI];
-    bool live[NI];  // GATHER: whether my row of load n is a token the query attends
-    int tok0 = 0, tok_end = 0;
-    if constexpr (GATHER) {
-      // slot RPI * n + g of the unit is token (slot mod 16) of the unit's block (slot div 16); a slot
-      // past the list's end, past L or in a block that is not resident reads the first token of the
-      // row's first kept block instead (it exists) and counts for nothing
-      int64_t dead = (int64_t)rb.block(0) * S * p.kv_st;
-      if (PAGED) {
-        const int page = table[rb.block(0)];
-        dead = (page >= 0 && page < p.num_pages) ? (int64_t)page * p.kv_ss : 0;  // else page 0 of the pool
-      }
-      int64_t row_off[NI];
-#pragma unroll
-      for (int n = 0; n < NI; ++n) {
-        const int slot = RPI * n + g;
-        const int bi = u * BPU + (slot >> 4);
-        const bool inside = bi < rb.count;
-        const int blk = rb.block(inside ? bi : 0);
-        const int tok = blk * S + (slot & 15);
-        bool ok = inside && tok < L;
-        int64_t off = (int64_t)tok * p.kv_st;
-        if (PAGED) {
-          const int page = table[blk];
-          const bool resident = page >= 0 && page < p.num_pages;
-          // the lane that holds a block's first row counts a kept block that is not there
-          if (inside && !resident && (slot & 15) == 0 && lane == 0) ++n_missing;
-          ok = ok && resident;
-          off = (int64_t)page * p.kv_ss + (int64_t)(slot & 15) * p.kv_st;
-        }
-        live[n] = ok;
-        row_off[n] = ok ? off : dead;
-      }
-#pragma unroll
-      for (int n = 0; n < NI; ++n) kr[n] = *reinterpret_cast<const bf16x8*>(kb + row_off[n]);
-#pragma unroll
-      for (int n = 0; n < NI; ++n) vr[n] = *reinterpret_cast<const bf16x8*>(vb + row_off[n]);
-    } else {
-    const int blk = rb.block(u / cpb);
-    tok0 = blk * S + (u % cpb) * U;
-    tok_end = min(L, tok0 + U);  // a 32-token block fills half of the 64 rows loaded
-    if (tok0 >= L) continue;  // second half of a partial last block
-    // row `tok` of the cache is at base + (tok - shift) * kv_st
-    int64_t base = 0;
-    int shift = 0;
+  // A unit is 64 rows: NB blocks of 16 (GATHER), else a run of rows of one block.
+  constexpr int NB = GATHER ? BPU : 1, NPB = NI / NB;  // loads to a block
+  struct Unit {
+    int64_t base[NB];  // element offset of the block's first row of the unit
+    int rows[NB];      // how many of its rows the query attends (0: none, and the offset is that of some row that exists)
+  };
+  // where a block without a row to read is read instead: the first token of the row's first kept block (it exists)
+  int64_t dead = 0;
+  if (GATHER && FAR) {
+    dead = (int64_t)rb.block(0) * S * p.kv_st;
     if (PAGED) {
-      const int page = table[blk];
-      if (page < 0 || page >= p.num_pages) {  // kept by the mask but not resident
-        n_missing += (u % cpb) == 0;
-        continue;
+      const int page = load_const<int32_t>(table + rb.block(0));
+      dead = (page >= 0 && page < p.num_pages) ? (int64_t)page * p.kv_ss : 0;  // else page 0 of the pool
+    }
+  }
+  auto unit_at = [&](int u) {
+    Unit w;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int bi = GATHER ? u * BPU + i : u >> cpb_sh;
+      const bool inside = !GATHER || bi < rb.count;
+      const int blk = rb.block(inside ? bi : 0);
+      const int skip = GATHER ? 0 : (u & (cpb - 1)) * U;  // rows of the block before the unit's
+      const int tok0 = blk * S + skip;
+      w.rows[i] = inside ? min(L - tok0, U) : 0;
+      w.base[i] = FAR ? tok0 * p.kv_st : (int64_t)((uint64_t)(uint32_t)tok0 * (uint32_t)p.kv_st);
+      if (PAGED) {
+        const int page = load_const<int32_t>(table + blk);
+        const bool resident = page >= 0 && page < p.num_pages;
+        // kept by the mask but not there: counted, for a block of several units with the first
+        if (inside && !resident) {
+          n_missing += skip == 0;
+          w.rows[i] = 0;
+        }
+        w.base[i] = (int64_t)((uint64_t)(uint32_t)page * (uint64_t)p.kv_ss) + skip * p.kv_st;
       }
-      base = (int64_t)page * p.kv_ss;
-      shift = blk * S;
+      if (GATHER && w.rows[i] <= 0) w.base[i] = dead;
     }
+    return w;
+  };
+  // the first of the units u, u + W, ... before u_hi that has a row to read (GATHER: the unit u); u is moved there
+  auto find = [&](int& u) {
+    Unit w{};
+    for (; u < u_hi; u += W) {
+      w = unit_at(u);
+      if (GATHER || w.rows[0] > 0) break;  // else the second half of a partial last block, or a block that is not resident
+    }
+    return w;
+  };
+  const uint32_t mine = 2 * (g * (uint32_t)p.kv_st + 8 * c), step = 2 * RPI * (uint32_t)p.kv_st;
+  auto load = [&](const uint16_t* from, const Unit& w, bf16x8 (&x)[NI]) {
 #pragma unroll
-    for (int n = 0; n < NI; ++n) {
-      const int tok = min(tok0 + RPI * n + g, tok_end - 1);  // clamp: never read past the unit
-      kr[n] = *reinterpret_cast<const bf16x8*>(kb + base + (int64_t)(tok - shift) * p.kv_st);
-    }
+    for (int i = 0; i < NB; ++i) {
+      const uint16_t* at = from + w.base[i];
+      if constexpr (FAR) {
+        // (a row past the last one attended reads that one)
+        const int last = max(w.rows[i] - 1, 0);
 #pragma unroll
-    for (int n = 0; n < NI; ++n) {
-      const int tok = min(tok0 + RPI * n + g, tok_end - 1);
-      vr[n] = *reinterpret_cast<const bf16x8*>(vb + base + (int64_t)(tok - shift) * p.kv_st);
+        for (int n = 0; n < NPB; ++n)
+          x[NPB * i + n] = *reinterpret_cast<const bf16x8*>(at + (int64_t)min(RPI * n + g, last) * p.kv_st + 8 * c);
+      } else {
+        const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(at), 0, max(w.rows[i], 0) * (int)(2 * p.kv_st), 0x00020000);
+#pragma unroll
+        for (int n = 0; n < NPB; ++n)
+          x[NPB * i + n] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rows, mine + n * step, 0, 0));
+      }
     }
-    }
-    float s[NI];
-    float mx = kNegInf;
+  };
+
+  bf16x8 kr[NI], vr[NI];
+  float s[NI], mx;
+  auto scores = [&](const Unit& w) __attribute__((always_inline)) {
+    mx = kNegInf;
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
       float d = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) d = __builtin_fmaf(qv[e], (float)kr[n][e], d);
-#pragma unroll
-      for (int m = 1; m < LPR; m <<= 1) d += __shfl_xor(d, m, 64);
-      if (GATHER ? !live[n] : tok0 + RPI * n + g >= tok_end) d = kNegInf;
+      d += of_neighbour<1>(d);
+      d += of_neighbour<2>(d);
+      d += of_neighbour<4>(d);
+      if (LPR == 16) d += of_neighbour<8>(d);
+      if (RPI * (n % NPB) + g >= w.rows[n / NPB]) d = kNegInf;
       s[n] = d;
       mx = fmaxf(mx, d);
     }
-#pragma unroll
-    for (int m = LPR; m < 64; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-    const float m_new = fmaxf(m_run, mx);  // finite: token tok0 < L is always valid
-    if (GATHER && m_new == kNegInf) continue;  // nothing live yet (a paged cache with the unit's blocks missing)
-    const float alpha = fast_exp2((m_run - m_new) * cl);
-    const float mc = m_new * cl;
+  };
+  auto sums = [&]() __attribute__((always_inline)) {
+    if (LPR == 8) mx = fmaxf(mx, of_neighbour<8>(mx));
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float m_new = fmaxf(m_run, mx);
+    // (GATHER: nothing live yet in a paged cache with the unit's blocks missing, every weight is 0; else the unit's first
+    // token is attended)
+    const bool live = !GATHER || m_new != kNegInf;
+    const float alpha = fast_exp2(live ? (m_run - m_new) * cl : 0.f);
+    const float mc = live ? m_new * cl : 0.f;
     float psum = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] *= alpha;
@@ -217,6 +256,29 @@ __global__ __launch_bounds__(64 * W, 2) void decode_split_kernel(const DecodePar
     }
     l_run = l_run * alpha + psum;  // per row group; groups are summed at the end
     m_run = m_new;
+  };
+
+  int u = u_lo + wave;
+  Unit w = find(u);
+  if (u < u_hi) {
+    load(kb, w, kr);
+    load(vb, w, vr);
+    for (;;) {
+      u += W;
+      const Unit next = find(u);
+      if (u >= u_hi) break;
+      // the next unit's K goes into the registers that the scores have freed, its V into those that the sums free
+      scores(w);
+      __builtin_amdgcn_sched_barrier(0);  // (the compiler mixes the loads into the sums otherwise, and waits for the last of them)
+      load(kb, next, kr);
+      __builtin_amdgcn_sched_barrier(0);
+      sums();
+      __builtin_amdgcn_sched_barrier(0);
+      load(vb, next, vr);
+      w = next;
+    }
+    scores(w);
+    sums();
   }
 
   if (PAGED && p.missing && lane == 0 && n_missing > 0) atomicAdd(p.missing, n_missing);
@@ -318,28 +380,30 @@ __global__ __launch_bounds__(256) void decode_reduce_kernel(const DecodeParams p
   if (tid == 0 && p.lse) p.lse[bh] = l > 0.f ? m * p.scale + __logf(l) : kNegInf;
 }
 
-template <int D, int W>
+template <int D, int W, bool FAR>
 void launch_split(const DecodeParams& p, hipStream_t stream) {
   const dim3 grid(p.nseq * p.heads * p.num_splits), block(64 * W);
   if (p.block_size == 16) {
     if (p.block_table)
-      hipLaunchKernelGGL((decode_split_kernel<D, true, true, W>), grid, block, 0, stream, p);
+      hipLaunchKernelGGL((decode_split_kernel<D, true, true, W, FAR>), grid, block, 0, stream, p);
     else
-      hipLaunchKernelGGL((decode_split_kernel<D, false, true, W>), grid, block, 0, stream, p);
+      hipLaunchKernelGGL((decode_split_kernel<D, false, true, W, FAR>), grid, block, 0, stream, p);
   } else if (p.block_table) {
-    hipLaunchKernelGGL((decode_split_kernel<D, true, false, W>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((decode_split_kernel<D, true, false, W, FAR>), grid, block, 0, stream, p);
   } else {
-    hipLaunchKernelGGL((decode_split_kernel<D, false, false, W>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((decode_split_kernel<D, false, false, W, FAR>), grid, block, 0, stream, p);
   }
 }
 
 template <int D>
 hipError_t launch_one(const DecodeParams& p, hipStream_t stream) {
   const int bh = p.nseq * p.heads;
-  if (bh * p.num_splits <= decode_wide_groups(p.block_size, p.num_splits))
-    launch_split<D, 8>(p, stream);
+  if (p.kv_st >= kFarRows)
+    launch_split<D, 4, true>(p, stream);
+  else if (bh * p.num_splits <= decode_wide_groups(p.block_size, D))
+    launch_split<D, 8, false>(p, stream);
   else
-    launch_split<D, 4>(p, stream);
+    launch_split<D, 4, false>(p, stream);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.num_splits == 1) return e;  // a single split writes the result itself
   hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3(bh), dim3(256), 0, stream, p);
@@ -348,7 +412,11 @@ hipError_t launch_one(const DecodeParams& p, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_decode(const DecodeParams& p, hipStream_t stream) {
+hipError_t launch_decode(const DecodeParams& params, hipStream_t stream) {
+  DecodeParams p = params;
+  p.by_heads = fast_div(p.heads);
+  p.by_splits = fast_div(p.num_splits);
+  p.by_stride = fast_div(p.stride > 0 ? p.stride : 1);
   return p.head_dim == 128 ? launch_one<128>(p, stream) : launch_one<64>(p, stream);
 }
 

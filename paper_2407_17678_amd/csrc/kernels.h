@@ -120,6 +120,7 @@ struct DecodeParams {
   const int32_t* row_ptr;
   const int32_t* col_idx;
   int num_blocks;
+  FastDiv by_heads, by_splits, by_stride;  // set by launch_decode
 };
 
 // Each returns the hipError_t of the launch (hipGetLastError after the launch).
@@ -136,13 +137,17 @@ hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream);
 // dQ and dK/dV of a backward that recomputes S and dP in one launch, after delta: whether the two are better off so, and the launch.
 bool bwd_is_merged(const AttnParams& p);
 hipError_t launch_bwd_merged(const AttnParams& p, bool dense, hipStream_t stream);
-// The most workgroups of a decode call that are of eight wavefronts instead of four.  One to a compute unit,
-// they keep twice the units of a (sequence, head) in flight: 32 pairs of 16 units in one split 13.2 -> 9.8 us, 19
-// units 15.8 -> 11.1; 64 pairs of 34 units in three splits 13.2 -> 11.3.  A grid with more of them brings no
-// more loads and ends less evenly (192 pairs of 16 units 12.4 and 12.3, 240 pairs 14.6 and 15.1), except that with
-// 16-token blocks, whose loads wait for more addresses, eight stay ahead while the chip holds all (256 pairs of
-// 17 units 21.2 -> 18.2, 384 pairs 27.0 -> 29.2), and so do the splits of longer rows (96 x 2, 31 units: 14.6 and 14.5).
-constexpr int decode_wide_groups(int block_size, int splits) { return block_size == 16 || splits > 1 ? 256 : 192; }
+// The most workgroups of a decode call that are of eight wavefronts instead of four.  One to a compute unit, they
+// keep twice the units of a (sequence, head) in flight: 32 pairs of 16 units in one split 13.2 -> 9.8 us, 224 pairs of
+// 4096 to 8192 tokens, 64-token blocks, 8 local + stride 8, D = 64, 15.9 -> 15.7, with 32-token blocks (16 + stride 16)
+// 15.2 -> 12.9.  Once there are two to a compute unit four are enough, and end more evenly (288 pairs, 64-token blocks,
+// 16 + stride 16, 32768 tokens, D = 64: 38.8 and, with eight, 41.0), except that with 16-token blocks at D = 64, whose
+// units are the smallest, eight stay ahead in long rows up to 512 (288 pairs of 8192 tokens 13.4 -> 12.6, 512 pairs
+// 17.5 -> 17.2; rows of 2048 tokens 5.7 and 5.8).
+constexpr int kDecodeWideGroups = 256;
+constexpr int decode_wide_groups(int block_size, int head_dim) {
+  return block_size == 16 && head_dim == 64 ? 2 * kDecodeWideGroups : kDecodeWideGroups;
+}
 hipError_t launch_decode(const DecodeParams& p, hipStream_t stream);
 
 }  // namespace s2

@@ -144,3 +144,39 @@ def test_decode_split_count_left_to_the_library(nseq, heads, max_len, S, D, spli
     B.s2_attn_decode(p, q, kv, kv, torch.full((nseq,), max_len, dtype=torch.int32, device="cuda"), o, None, w.scale, ws, max_len)
     assert int((ws != 77.25).sum()) == (0 if splits == 1 else nseq * heads * splits * (D + 2))
     assert torch.equal(o, q)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("tok_stride", [2 ** 24 - 8, 2 ** 24])  # the last whose units are a buffer of 31 bits, the first read by 64-bit addresses
+@pytest.mark.parametrize("S,name", [(16, "7b_decode"), (64, "7b_decode"), (32, "tiny"), (16, "tiny")])
+def test_decode_of_far_tokens(paged, tok_stride, S, name):
+    w = dataclasses.replace(synth.WORKLOADS[name], block_size=S)
+    H, max_len = 3, 70                                         # more than one unit; each length leaves a block part full
+    qb, kcb, vcb, lens = synth.decode_inputs_small(w, 2, H, max_len, lengths=np.array([max_len, 35], dtype=np.int32))
+    D, rows = qb.shape[2], (min(S, max_len) if paged else max_len)
+    blocks = -(-max_len // S)
+    pad = [np.zeros((2, H, blocks * S, D), dtype=np.uint16) for _ in range(2)]
+    for x, bits in zip(pad, (kcb, vcb)):
+        x[:, :, :max_len] = bits[:, :, :max_len]
+    mem = torch.full((rows * tok_stride,), float("nan"), dtype=torch.bfloat16, device="cuda")  # one token every tok_stride elements
+    q, sl = G.to_dev(qb), torch.from_numpy(lens).cuda()
+    o = torch.empty_like(q)
+    p = B.layout_params(H, 1, S, 1, 0, 0, 0, 1)                # dense: every block is kept
+    ws = torch.empty(B.s2_attn_decode_workspace_bytes(2, H, D, blocks * S), dtype=torch.uint8, device="cuda")
+    print("far tokens", paged, tok_stride, S, name, flush=True)
+    if paged:
+        n = 2 * H * blocks                                     # page = its place in [sequence, head, block]
+        k, v = (mem.as_strided((n, rows, D), (D, tok_stride, 1), i * n * D) for i in (0, 1))
+        for x, bits in zip((k, v), pad):
+            x.copy_(G.to_dev(bits.reshape(n, S, D))[:, :rows])
+        live = torch.arange(n, dtype=torch.int32, device="cuda").view(2, H, blocks)
+        B.s2_attn_decode_paged(p, q, k, v, live, sl, o, None, w.scale, ws)
+    else:
+        k, v = (mem.as_strided((2, H, rows, D), (H * D, D, tok_stride, 1), 2 * i * H * D) for i in (0, 1))
+        for x, bits in zip((k, v), pad):
+            x.copy_(G.to_dev(bits)[:, :, :rows])
+            for s in range(2):
+                x[s, :, int(lens[s]):] = float("nan")          # tokens that no query attends
+        B.s2_attn_decode(p, q, k, v, sl, o, None, w.scale, ws, max_len)
+    O, _ = _oracle(dataclasses.replace(w, heads=H), qb, kcb, vcb, lens, dense=True)
+    assert G.o_excess(G.to_f64(o), O) <= 0
