@@ -91,10 +91,13 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p, int tile
   do {
     const int t0 = row0 + (tid >> 2);
     bf16x8 o[PASSES][KS], d[PASSES][KS];
+    float lse[PASSES];
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
       // (a row past the end reads the last one; nothing of it is stored)
-      const int64_t off = base + (int64_t)min(t0 + 64 * i, p.seqlen - 1) * p.q_st;
+      const int t = min(t0 + 64 * i, p.seqlen - 1);
+      const int64_t off = base + t * p.q_st;
+      lse[i] = p.lse[(int64_t)bh * p.seqlen + t];
 #pragma unroll
       for (int kk = 0; kk < KS; ++kk) {
         o[i][kk] = *reinterpret_cast<const bf16x8*>(p.o + off + 32 * kk);
@@ -114,13 +117,14 @@ __global__ __launch_bounds__(256) void delta_kernel(const AttnParams p, int tile
       for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc = __builtin_fmaf((float)d[i][kk][e], (float)o[i][kk][e], acc);
-      acc += __shfl_xor(acc, 2, 64);
-      acc += __shfl_xor(acc, 1, 64);
+      // (without the LDS; with lse on its way from the start 1 x 5 x 4096 x 64 backward 27.8 -> 27.1 us, 1 x 4 x 512 15.8 -> 15.5)
+      acc += dpp<0x4E>(acc);  // quad_perm 2301: of lane ^ 2
+      acc += dpp<0xB1>(acc);  // quad_perm 1032: of lane ^ 1
       const int t = t0 + 64 * i;
       if (g == 0 && t < end) {
         const int64_t row = (int64_t)bh * p.seqlen + t;
         p.neg_delta[row] = -acc;
-        p.neg_lse[row] = p.lse[row] * p.neg_inv_scale;
+        p.neg_lse[row] = lse[i] * p.neg_inv_scale;
       }
     }
     row0 += tiles * ROWS;

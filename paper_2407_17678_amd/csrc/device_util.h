@@ -68,10 +68,32 @@ __device__ __forceinline__ float sum_halves(float x) {
 
 // The same with the lane 16 positions away (v_permlane16_swap exchanges the odd rows of 16 lanes of one register with the even
 // rows of another), and so over the four lanes that hold one column of a 16x16 tile.
-__device__ __forceinline__ float sum_groups(float x) {
-  float even = sum_halves(x), odd = even;
+__device__ __forceinline__ void swap_rows(float x, float& even, float& odd) {
+  even = x;
+  odd = x;
   asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(even), "+v"(odd));
-  return even + odd;
+}
+__device__ __forceinline__ float max_rows(float x) {
+  float a, b;
+  swap_rows(x, a, b);
+  return fmaxf(a, b);
+}
+__device__ __forceinline__ float sum_rows(float x) {
+  float a, b;
+  swap_rows(x, a, b);
+  return a + b;
+}
+__device__ __forceinline__ float sum_groups(float x) { return sum_rows(sum_halves(x)); }
+
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+// x of a lane of the neighbouring group of M lanes (M = 1, 2, 4, 8), where x is the same in all M lanes of a group: the
+// value of lane ^ M, by a lane permutation that an addition takes along instead of a round through the LDS.
+template <int M>
+__device__ __forceinline__ float of_neighbour(float x) {
+  return dpp<M == 1 ? 0xB1 : M == 2 ? 0x4E : M == 4 ? 0x141 : 0x140>(x);  // quad_perm 1032, 2301; half row, row reversed
 }
 
 // ---------------------------------------------------------------------------------------------
