@@ -58,13 +58,14 @@ namespace s2 {
 namespace {
 
 constexpr float kNegInf = -__builtin_inff();
+constexpr unsigned kComputeUnits = 256;
 constexpr float kTau = 8.0f;  // log2 units a score may exceed a lazily moved reference maximum by
 
 // VARLEN: a packed batch of sequences of different lengths.  A workgroup finds its sequence's rows in
 // cu_seqlens and treats them as a sequence of its own.  In its last, partial tile no lane fetches past
 // the sequence's last token (keys after it lie after every query, which the causal mask drops) and
 // stores are guarded per row.
-template <int D, bool DENSE, bool VARLEN>
+template <int D, bool DENSE, bool VARLEN, bool LONE>
 __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(const AttnParams p) {
   typedef DmaTile<D> Tile;
   typedef PieceTile<D> Piece;
@@ -83,7 +84,12 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // The ring goes on from one step to the next, and across the barrier between them: it lies kLead slots before a step's end, when every
   // wavefront has asked for its last fragments.  (In packed batches at D = 64 it begins again with each step: no registers are left for
   // it, a Q fragment would be spilled.)
-  constexpr bool kAcross = !VARLEN || D == 128;
+  // LONE: a run of rows against a cache, with a workgroup to a compute unit at most.  Its K and V come from HBM, one step ahead, and the ring's
+  // early barrier only lengthens the wait for them: 4 x 8 heads, 768 rows against 44928 keys, 3 local + stride 11 (192 tiles) 84.6 us with
+  // the ring going on, 76.5 with a new one each step; 2 x 27 heads, 128 rows against 45568 73.3 and 66.9; 1 x 32 heads x 64, 512 rows against 30720 42.2 and
+  // 41.1.  (Two to a compute unit wait for each other's: 2048 rows against 44928 146.0 and 147.0.  A whole short sequence finds its keys in an L2: 1 x 8
+  // x 2048 14.1 and 14.5.)
+  constexpr bool kAcross = !LONE && (!VARLEN || D == 128);
   static_assert(!kAcross || (NS % kRing == 0 && kRing > kLead), "a fragment has the same place in every step");
   static_assert(!(DENSE && VARLEN), "the dense form walks 64-key blocks of whole sequences");
 
@@ -486,11 +492,13 @@ template <int D>
 hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
   const dim3 grid(p.row_map.grid()), block(kThreads);
   if (dense)
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, true, false>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, true, false, false>), grid, block, 0, stream, p);
   else if (p.cu_seqlens)
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, true, false>), grid, block, 0, stream, p);
+  else if (p.q_rows < p.seqlen && grid.x <= kComputeUnits)
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false, true>), grid, block, 0, stream, p);
   else
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false>), grid, block, 0, stream, p);
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, false, false, false>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 

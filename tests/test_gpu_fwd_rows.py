@@ -98,3 +98,17 @@ def test_forward_rows_argument_errors():
     assert status(mk(128), -128) == -3
     assert status(mk(128), 0, kk=mk(1024)) == -3   # more keys than the layout has blocks for
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("heads", [256, 257])  # tiles of a chunk: a compute unit each, and one more
+def test_forward_rows_of_a_chip_of_tiles(heads, D):
+    g = torch.Generator().manual_seed(heads + D)
+    q, k, v = (torch.randn((1, heads, 512, D), generator=g).to(torch.bfloat16).cuda() for _ in range(3))
+    lay = B.s2_layout_build(B.layout_params(heads, 8, 64, 2, 3))
+    o, lse = torch.empty_like(q), torch.empty((1, heads, 512), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, D ** -0.5)
+    oc, lc = torch.empty_like(q[:, :, 384:]).contiguous(), torch.empty((1, heads, 128), dtype=torch.float32, device="cuda")
+    print("forward rows of a chip of tiles", heads, D, flush=True)
+    B.s2_attn_fwd_rows(lay, q[:, :, 384:].contiguous(), k, v, oc, lc, 384, D ** -0.5)
+    assert torch.equal(oc, o[:, :, 384:]) and torch.equal(lc, lse[:, :, 384:])
