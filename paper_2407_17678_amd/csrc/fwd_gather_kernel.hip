@@ -20,7 +20,7 @@
 // blocks of 32, window 3 42 / 48 / 42; 34 x 7136 x 128, blocks of 32, window 3 70 / 81 / 72; 26 x 16064 x 128, window 4 154 / 156 /
 // 144; 45 x 12704 x 64, blocks of 16 182 / 144 / 136; 60 x 4864 rows of 34560 x 128, blocks of 16 (nearly every half kept) 667 / 369 /
 // 398; packed 11 x 32 x 64, blocks of 32 99 / 124 / 109; 60 x 8192 x 64, blocks of 32, window 4 96 / 111 / 101.  At head_dim 64 it is bound
-// by the vector instructions (an exponential is four of them), at 128 by those, the matrix pipe and the LDS alike;
+// by the vector instructions (an exponential takes the time of two), at 128 by those, the matrix pipe and the LDS alike;
 // short lists by a tile's start and end, where the first of the three, at head_dim 64, had five workgroups to a compute
 // unit (three here: steps of 32 keys would halve the LDS, but four wavefronts to a SIMD spill and measured slower).
 #include <hip/hip_runtime.h>
