@@ -143,17 +143,8 @@ __global__ __launch_bounds__(64 * W, FAR ? 1 : D == 128 ? 2 : 4) void decode_spl
   constexpr int NB = GATHER ? BPU : 1, NPB = NI / NB;  // loads to a block
   struct Unit {
     int64_t base[NB];  // element offset of the block's first row of the unit
-    int rows[NB];      // how many of its rows the query attends (0: none, and the offset is that of some row that exists)
+    int rows[NB];      // how many of its rows the query attends (GATHER: none of a block past the list's end, past L or not there)
   };
-  // where a block without a row to read is read instead: the first token of the row's first kept block (it exists)
-  int64_t dead = 0;
-  if (GATHER && FAR) {
-    dead = (int64_t)rb.block(0) * S * p.kv_st;
-    if (PAGED) {
-      const int page = load_const<int32_t>(table + rb.block(0));
-      dead = (page >= 0 && page < p.num_pages) ? (int64_t)page * p.kv_ss : 0;  // else page 0 of the pool
-    }
-  }
   auto unit_at = [&](int u) {
     Unit w;
 #pragma unroll
@@ -175,7 +166,6 @@ __global__ __launch_bounds__(64 * W, FAR ? 1 : D == 128 ? 2 : 4) void decode_spl
         }
         w.base[i] = (int64_t)((uint64_t)(uint32_t)page * (uint64_t)p.kv_ss) + skip * p.kv_st;
       }
-      if (GATHER && w.rows[i] <= 0) w.base[i] = dead;
     }
     return w;
   };
@@ -194,11 +184,12 @@ __global__ __launch_bounds__(64 * W, FAR ? 1 : D == 128 ? 2 : 4) void decode_spl
     for (int i = 0; i < NB; ++i) {
       const uint16_t* at = from + w.base[i];
       if constexpr (FAR) {
-        // (a row past the last one attended reads that one)
-        const int last = max(w.rows[i] - 1, 0);
+        // (a row past the last one attended reads that one; a block without one is zeros, as from an empty buffer: its weights
+        // are 0, and 0 times what lies in a page that nobody owns need not be)
+        const int last = w.rows[i] - 1;
 #pragma unroll
         for (int n = 0; n < NPB; ++n)
-          x[NPB * i + n] = *reinterpret_cast<const bf16x8*>(at + (int64_t)min(RPI * n + g, last) * p.kv_st + 8 * c);
+          x[NPB * i + n] = last < 0 ? bf16x8{} : *reinterpret_cast<const bf16x8*>(at + (int64_t)min(RPI * n + g, last) * p.kv_st + 8 * c);
       } else {
         const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(at), 0, max(w.rows[i], 0) * (int)(2 * p.kv_st), 0x00020000);
 #pragma unroll

@@ -1,6 +1,8 @@
 """GPU parity of decoding against a paged KV cache with evicted blocks (through the C ABI) against
 the fp64 oracle; the pages and the block table are inputs that both sides receive."""
 
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -169,3 +171,58 @@ def test_paged_argument_errors():
     with pytest.raises(B.S2Error) as e:
         B.s2_attn_decode_paged(_params(w, heads), q, kp, kp, tb, sl, o, None, w.scale, small)
     assert e.value.status == -5  # WORKSPACE
+
+
+@pytest.mark.parametrize("splits", [1, 2, 3])
+@pytest.mark.parametrize("tok_stride", [None, 2 ** 24 - 8, 2 ** 24])  # tokens side by side; the last stride of a buffer's 31 bits, the first of 64-bit addresses
+@pytest.mark.parametrize("name", ["7b_decode", "tiny"])
+def test_missing_blocks_of_16_tokens(name, tok_stride, splits):
+    # four blocks are a unit of work.  Units that are missing whole (the row's first, a later one), in part, and all of a row;
+    # whatever lies in the pages that nobody owns (among them page 0) contributes nothing
+    w = dataclasses.replace(synth.WORKLOADS[name], block_size=16)
+    S, H, D, max_len = 16, 3, w.head_dim, 648                  # 11 units, the last of one block, half full
+    blocks = -(-max_len // S)
+    qb, kcb, vcb, lens = synth.decode_inputs_small(w, 2, H, max_len, lengths=np.array([max_len, 323], dtype=np.int32))
+    keep = -(-lens // S)                                       # dense: every block up to the newest
+    live = np.arange(blocks) < keep[:, None, None]
+    live = np.broadcast_to(live, (2, H, blocks)).copy()
+    live[0, 0, :4] = live[0, 0, 20:24] = live[0, 0, [9, 30]] = False    # the first unit, one of a wavefront's second trip, two in part
+    live[0, 1, 1:36] = False                                   # all but the first block and the last units
+    live[0, 2, 40] = live[1, 0, 0] = False                     # the newest, the oldest
+    live[1, 1, :] = False
+    live[1, 2, :16] = False                                    # each wavefront's first unit
+    n = int(live.sum()) + 3                                    # pages 0 .. 2 are nobody's
+    table = np.where(np.arange(2 * H * blocks).reshape(2, H, blocks) % 2, -1, n + 7).astype(np.int32)
+    table[live] = 3 + np.random.Generator(np.random.PCG64(9)).permutation(n - 3)
+    table[~np.broadcast_to(np.arange(blocks) < keep[:, None, None], live.shape)] = 1    # blocks after the newest: never looked up
+    missing = int(sum(H * int(k) for k in keep) - live.sum())
+    if tok_stride is None:
+        k, v = (torch.empty((n, S, D), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    else:                                                      # page = its place beside the others inside a token's stride
+        mem = torch.empty((S * tok_stride,), dtype=torch.bfloat16, device="cuda")
+        k, v = (mem.as_strided((n, S, D), (D, tok_stride, 1), i * n * D) for i in (0, 1))
+    k.fill_(float("nan"))
+    v.fill_(float("nan"))
+    v[1].fill_(float("inf"))
+    pad = blocks * S - max_len
+    for x, bits in ((k, kcb), (v, vcb)):
+        full = np.concatenate([bits[:, :, :max_len], np.full((2, H, pad, D), 0x7FC0, np.uint16)], axis=2).reshape(2, H, blocks, S, D)
+        x[torch.from_numpy(table[live].astype(np.int64)).cuda()] = G.to_dev(full[live])
+    q, sl, tb = G.to_dev(qb), torch.from_numpy(lens).cuda(), torch.from_numpy(table).cuda()
+    o, lse = torch.empty_like(q), torch.empty((2, H), dtype=torch.float32, device="cuda")
+    count = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(B.s2_attn_decode_workspace_bytes(2, H, D, blocks * S, splits), dtype=torch.uint8, device="cuda")
+    print("missing blocks of 16", name, tok_stride, splits, flush=True)
+    B.s2_attn_decode_paged(_params(w, H, dense=1), q, k, v, tb, sl, o, lse, w.scale, ws, missing=count, num_splits=splits)
+    assert int(count.item()) == missing
+    o, lse = G.to_f64(o), G.to_f64(lse)
+    for b in range(2):
+        for h in range(H):
+            there = np.repeat(live[b, h], S)[:lens[b]]
+            if not there.any():
+                assert (o[b, h] == 0).all() and lse[b, h] == -np.inf
+                continue
+            s = G.bits_f64(kcb[b, h][:lens[b]][there]) @ G.bits_f64(qb[b, h]) * w.scale
+            e = np.exp(s - s.max())
+            assert G.o_excess(o[b, h], e @ G.bits_f64(vcb[b, h][:lens[b]][there]) / e.sum()) <= 0, (b, h)
+            assert abs(lse[b, h] - (s.max() + np.log(e.sum()))) <= LSE_TOL, (b, h)
