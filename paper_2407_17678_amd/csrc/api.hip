@@ -488,6 +488,8 @@ int s2_attn_bwd_varlen(const s2_layout* layout, const s2_tensors* t, const int32
   const int64_t pairs = 8 * (((int64_t)num_seqs * t->heads + 7) / 8);
   const int64_t slots = pairs * std::max<int64_t>((max_seqlen + s2::kBwdBM - 1) / s2::kBwdBM, layout->kv_tiles.tiles_per_head);
   if (slots > std::numeric_limits<int32_t>::max()) return S2_ERR_SHAPE;
+  // (whole runs of key tiles can be a few more)
+  if (s2::key_map(num_seqs * t->heads, layout->kv_tiles.tiles_per_head).grid() > std::numeric_limits<int32_t>::max()) return S2_ERR_SHAPE;
   return hip_ok(s2::launch_bwd(p, false, s2::kBwdAll, static_cast<hipStream_t>(stream))) ? S2_OK : S2_ERR_HIP;
 }
 

@@ -49,7 +49,7 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   const hipError_t e = set_smem(&bwd_merged_kernel<D, DENSE, FINE, VARLEN>, sizeof(MergedSmem<D>), set);
   if (e != hipSuccess) return e;
-  const int keys = p.key_map.grid();  // (a multiple of eight: either part keeps its workgroups' XCDs)
+  const int keys = (int)p.key_map.grid();  // (a multiple of eight: either part keeps its workgroups' XCDs)
   hipLaunchKernelGGL((bwd_merged_kernel<D, DENSE, FINE, VARLEN>), dim3(keys + p.row_map.grid()), dim3(kThreads), sizeof(MergedSmem<D>), stream, p, keys);
   return hipGetLastError();
 }
@@ -77,7 +77,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, hipStream_t stream) {
 constexpr int kMergedGrid = 4096;
 bool bwd_is_merged(const AttnParams& p) {
   const bool in_place = p.dk == p.k || p.dk == p.v || p.dv == p.k || p.dv == p.v;
-  return !in_place && (int64_t)p.key_map.grid() + p.row_map.grid() <= kMergedGrid;
+  return !in_place && p.key_map.grid() + p.row_map.grid() <= kMergedGrid;
 }
 
 hipError_t launch_bwd_merged(const AttnParams& p, bool dense, hipStream_t stream) {

@@ -236,7 +236,7 @@ hipError_t launch_dq_gemm(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   const hipError_t e = set_smem(&dq_gemm_kernel<128>, sizeof(DqGemmSmem<128>), set);
   if (e != hipSuccess) return e;
-  const int grid = p.row_map.grid();
+  const int grid = (int)p.row_map.grid();
   hipLaunchKernelGGL((dq_gemm_kernel<128>), dim3(grid), dim3(kThreads), sizeof(DqGemmSmem<128>), stream, p);
   return hipGetLastError();
 }

@@ -21,7 +21,7 @@ hipError_t launch_one(const AttnParams& p, hipStream_t stream) {
   static SmemSet set;  // zero-initialised
   const hipError_t e = set_smem(&dq_pipe_kernel<D, DENSE, FINE, VARLEN>, sizeof(DqPipeSmem<D>), set);
   if (e != hipSuccess) return e;
-  const int grid = p.row_map.grid();
+  const int grid = (int)p.row_map.grid();
   hipLaunchKernelGGL((dq_pipe_kernel<D, DENSE, FINE, VARLEN>), dim3(grid), dim3(kThreads), sizeof(DqPipeSmem<D>), stream, p);
   return hipGetLastError();
 }

@@ -46,7 +46,7 @@ struct RowMap {
   int run, shared;      // shift of the tiles to a run; an XCD's slots for what is left over, which come first
   int group, in_group;  // shift of the pairs to a group, tiles of a group
   FastDiv by_left, by_group, by_last;  // division by left, in_group and the pairs of the last group
-  int grid() const { return 8 * (per_xcd * tiles + shared); }
+  int64_t grid() const { return 8 * ((int64_t)per_xcd * tiles + shared); }
 };
 inline RowMap row_map(int bh_total, int tiles, int group) {
   RowMap m{};
@@ -96,7 +96,8 @@ S2_HD inline bool map_workgroup(const RowMap& m, int wg, int& bh, int& rank) {
 struct KeyMap {
   int bh_total, tiles, run;                   // run: shift of the tiles to a run
   FastDiv by_total, by_own, by_more;          // division by bh_total, bh_total / 8 and bh_total / 8 + 1
-  int grid() const { return (int)(((unsigned)bh_total * ((tiles + (1 << run) - 1) >> run) + 7) / 8 * 8) << run; }
+  // (of whole runs, so up to a run less one more to a pair than it has tiles)
+  int64_t grid() const { return ((int64_t)bh_total * ((tiles + (1 << run) - 1) >> run) + 7) / 8 * 8 << run; }
 };
 inline KeyMap key_map(int bh_total, int tiles) {
   KeyMap m{};

@@ -221,3 +221,17 @@ def test_varlen_row_offsets_that_make_no_sense_stay_inside_the_tensors():
         assert (t.view(torch.int16)[0, :, 512:600] == SENTINEL).all()
         assert (t.view(torch.int16)[0, :, 1412:1450] == SENTINEL).all()
         assert torch.isfinite(t[0, :, :512].float()).all() and torch.isfinite(t[0, :, 900:1412].float()).all()
+
+
+def test_more_key_tiles_than_a_grid_holds_are_refused():
+    # 129 tiles of each of 16647159 pairs are dealt out in runs of four: fewer than 2^31 tiles, more than 2^31 workgroups
+    seqs, rows, D = 16647159, 128, 64
+    lay = B.s2_layout_build(B.layout_params(1, 129, 128, 1, 2))
+    t = [torch.zeros((1, 1, rows, D), dtype=torch.bfloat16, device="cuda") for _ in range(8)]
+    lse = torch.zeros((1, rows), dtype=torch.float32, device="cuda")
+    cu = torch.full((seqs + 1,), rows, dtype=torch.int32, device="cuda")
+    cu[0] = 0                                                   # one sequence of all rows, the others empty
+    ws = torch.empty(B.s2_attn_bwd_varlen_workspace_bytes(1, rows, D), dtype=torch.uint8, device="cuda")
+    with pytest.raises(B.S2Error) as e:
+        B.s2_attn_bwd_varlen(lay, *t[:4], lse, *t[4:], cu, rows, 1.0, ws)
+    assert e.value.status == -3

@@ -38,7 +38,7 @@ int main() {
         int count[8] = {}, last[8] = {};
         const RowMap rows = row_map(P, T, G);
         const KeyMap keys = key_map(P, T);
-        const int grid = G ? rows.grid() : keys.grid();
+        const int grid = (int)(G ? rows.grid() : keys.grid());
         if (check(grid % 8 == 0, "grid", P, T, G, grid)) return 1;
         for (int w = 0; w < grid; ++w) {
           int bh = -1, rank = -1;
@@ -56,6 +56,13 @@ int main() {
         const int most = *std::max_element(count, count + 8), least = *std::min_element(count, count + 8);
         if (check(most - least <= (P % 8 ? 2 << deal_run_shift(T) : 0), "balance", P, T, G, grid)) return 1;
       }
+  // as many workgroups as 32 bits hold, and a few more: grids are counted in 64, and never less than the tiles
+  for (int T : {64, 65, 129, 131, 8193})
+    for (int left = 0; left < 8; ++left) {
+      const int P = (int)((1ll << 31) / T / 8 * 8) + left;
+      const long long rows = row_map(P, T, 1).grid(), keys = key_map(P, T).grid(), tiles = 1ll * P * T;
+      if (check(rows >= tiles && rows <= tiles + 64 && keys >= tiles && keys <= tiles + 4ll * P + 64, "far", P, T, 0, 0)) return 1;
+    }
   std::printf("mapped\n");
   return 0;
 }
