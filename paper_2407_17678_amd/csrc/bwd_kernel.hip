@@ -220,7 +220,7 @@ hipError_t launch_dim(const AttnParams& p, bool dense, int stages, hipStream_t s
 hipError_t launch_bwd(const AttnParams& params, bool dense, int stages, hipStream_t stream) {
   AttnParams p = params;
   const int pairs = p.batch * p.heads, tiles = (p.q_rows + kBwdBM - 1) / kBwdBM;
-  p.row_map = row_map(pairs, tiles, map_group(pairs, tiles, p.cu_seqlens != nullptr));
+  p.row_map = row_map(pairs, tiles, map_group(pairs, tiles, p.cu_seqlens != nullptr), dense ? kDenseRows : kSparseRows, xcd_slots(p.head_dim));
   p.key_map = key_map(pairs, p.kv_tiles.tiles_per_head + p.split_items - p.split_long);
   p.by_heads = fast_div(p.heads);
   return p.head_dim == 128 ? launch_dim<128>(p, dense, stages, stream) : launch_dim<64>(p, dense, stages, stream);

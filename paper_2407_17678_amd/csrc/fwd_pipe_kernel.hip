@@ -507,7 +507,8 @@ hipError_t launch_one(const AttnParams& p, bool dense, hipStream_t stream) {
 hipError_t launch_fwd(const AttnParams& params, bool dense, hipStream_t stream) {
   AttnParams p = params;
   const int pairs = p.batch * p.heads, tiles = (p.q_rows + kFwdBM - 1) / kFwdBM;
-  p.row_map = row_map(pairs, tiles, map_group(pairs, tiles, p.cu_seqlens != nullptr));
+  p.row_map = row_map(pairs, tiles, map_group(pairs, tiles, p.cu_seqlens != nullptr), dense ? kDenseRows : p.q_rows < p.seqlen ? kRowsOfCache : kSparseRows,
+                      xcd_slots(p.head_dim));
   p.by_heads = fast_div(p.heads);
   if (!dense && p.block_size < 64) return launch_fwd_gather(p, stream);
   return p.head_dim == 128 ? launch_one<128>(p, dense, stream) : launch_one<64>(p, dense, stream);
