@@ -146,3 +146,26 @@ def test_whether_tiles_are_cut(D, S, H, N, local, cut):
     B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, w.scale, ws)
     count, sums = _counters_and_sums(ws, lay, 1, H, N, D, False)
     assert (int(count.max()) > 1) == cut and bool((sums != 0xFF).any()) == cut
+
+
+@pytest.mark.parametrize("D,S,batch,H,N,local,stride,parts", [
+    (128, 64, 1, 7, 8192, 4, 8, 8), (64, 64, 1, 2, 8192, 4, 8, 11), (128, 128, 3, 4, 3072, 3, 4, 3),   # pairs / 8 alone would give 3, 22 and 6 parts
+    (128, 64, 4, 23, 768, 3, 7, 0), (128, 128, 4, 21, 512, 3, 5, 0),                                     # ... and two
+    (64, 64, 1, 8, 8192, 4, 8, 8),                                                                       # no pairs left over, parts that fit only if twice as long
+])
+def test_parts_of_the_longest_tile(D, S, batch, H, N, local, stride, parts):
+    # pairs that are left over from a multiple of eight count as a whole one for whether tiles are cut, as half a one more for how long parts are
+    w = dataclasses.replace(synth.WORKLOADS["tiny" if D == 64 else "1p3b_8k"], block_size=S)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(H + N)
+    q, k, v, g = (torch.randn((batch, H, N, D), device="cuda", generator=gen).bfloat16() for _ in range(4))
+    lay = B.s2_layout_build(B.layout_params(H, N // S, S, local, stride))
+    o, lse = torch.empty_like(q), torch.empty((batch, H, N), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, w.scale)
+    ws = torch.full((B.s2_attn_bwd_workspace_bytes(batch, H, N, D),), 0xFF, dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(q) for _ in range(3)]
+    print("parts of the longest tile", D, S, batch, H, N, flush=True)
+    B.s2_attn_bwd(lay, q, k, v, o, lse, g, *grads, w.scale, ws)
+    count, sums = _counters_and_sums(ws, lay, batch, H, N, D, False)
+    assert bool((sums != 0xFF).any()) == (parts > 0)
+    assert parts == 0 or int(count.max()) == parts
