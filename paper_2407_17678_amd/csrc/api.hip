@@ -352,26 +352,26 @@ namespace {
 // equivalent of 80 of 64).  Measured, forward + backward with the longest tile / even = 4.4 (8 heads
 // x 4096): 202 -> 89 us; 2.3 (2 x 16 x 3904): 255 -> 183; 3.0 (16 x 16384): 969 -> 637; 1.5 (2 x 20 x 8192,
 // blocks of 128): 677 -> 616; 1.2 (3 x 16 x 8192): 791 -> 764; 0.88 (4 x 16 x 8192): 999 uncut, 1026 cut.  The
-// best length of a part was 6 to 8, 24, 64, 48 to 64 and 64 steps, that is about 4/5 of `even` plus 3: a
+// best length of a part was 6 to 8, 24, 64, 48 to 64 and 64 steps, that is about 3/4 of `even` plus 3: a
 // part's own cost (its start, 64 KB per 128 keys and 64 features written and read again) against the evenness of the launch.
 // Where all tiles start at once they should still do so when cut: 52 heads x 800 x 128 in blocks of 32, 49 workgroups for
 // an XCD's 64 slots uncut and 84 cut, forward and backward 78 us uncut, 90 cut; 42 heads, 42 and 54, 66 and 54.  Where no
-// cut leaves it so, a second round still costs less than a tile much longer than a part: with longest tile / best = 9 (8 heads x
-// 8192 x 128, 64 workgroups and 88) 311 us uncut and 109 cut, 4.5 (16 x 4096 x 128) 191 and 112, 2.6 (4 x 8 x 2048 x 128) 123 and 89, 8.4 (8 x
-// 10240 x 64) 262 and 119, but with 2.3 (3 x 8 x 2560 x 128) 172 and 168, or 141 and 152 in the launch that has the dQ tiles too, and with
-// 1.8 (4 x 8 x 2048 x 128) 139 and 146 there.  A cut that leaves it so is no good either where its parts are far from the best length: half as
-// long again, or two thirds.
+// cut leaves it so, a second round still costs less than a tile much longer than a part: with longest tile / best = 10 (8 heads x
+// 8192 x 128, 64 workgroups and 88) 311 us uncut and 109 cut, 4.7 (16 x 4096 x 128) 191 and 112, 2.7 (4 x 8 x 2048 x 128) 123 and 89, 8.9 (8 x
+// 10240 x 64) 262 and 119, but with 2.4 (3 x 8 x 2560 x 128) 172 and 168, or 141 and 152 in the launch that has the dQ tiles too, and with
+// 1.9 (4 x 8 x 2048 x 128) 139 and 146 there.
 // (batch, head) pairs that are left over from a multiple of eight are shared by the XCDs.  They count as a whole pair for whether to cut and
-// what starts at once, as the parts of one tile lie on XCDs next to each other, and half of that for the best length.  Backward, us, with pairs / 8, with that rounded up and so: 7 heads x 8192 x 128
-// 122, 105 and 102, 4 x 23 x 768 79, 72 and 72, 2 x 8192 x 64 38, 56 and 35, 9 x 8192 x 64 84, 66 and 67, 3 x 4 x 3072 x 128, blocks of 128, 72, 57 and 57.  Over 332
-// shapes with pairs left over each is this much behind the best of all cuts: 4.0, 3.5 and 2.4 %; over 66 without 2.7, 2.7 and 2.5.
+// what starts at once, as the parts of one tile lie on XCDs next to each other; for the best length three quarters of what they lack of one are added. And a
+// cut whose parts all start at once is then no good where they are half as long again as the best length, or two thirds of it.  Backward, us,
+// with pairs / 8, with that rounded up and so: 7 heads x 8192 x 128 122, 105 and 102, 4 x 23 x 768 79, 72 and 72, 2 x 8192 x 64 38, 56 and 35, 9 x 8192 x 64 84, 66 and 67, 3 x 4
+// x 3072 x 128, blocks of 128, 72, 57 and 57.  Over 332 shapes with pairs left over each is this much behind the best of all cuts: 4.0, 3.5 and 2.6 %.
 void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, unsigned char* room) {
   const double slots = p.head_dim == 128 ? 64 : 80;
   const int T = p.kv_tiles.tiles_per_head;
   const int pairs = (p.batch * p.heads + 7) / 8;  // of an XCD
   const double even = (L->kv_head_steps + 5.0 * T) / slots;  // of each of them
   if (L->kv_max_steps <= 1.1 * pairs * even) return;
-  const double best = 0.8 * (pairs + p.batch * p.heads / 8.0) / 2 * even + 3;
+  const double best = 0.75 * (3 * pairs + p.batch * p.heads / 8.0) / 4 * even + 3;
   double off;  // how far from the best length the parts are of the cut that `closest` has found
   auto closest = [&](bool one_round) {
     const s2::SplitLevel* use = nullptr;
@@ -388,7 +388,8 @@ void choose_split(s2::AttnParams& p, const s2_layout* L, const BwdWorkspace& w, 
   };
   const bool one_round = pairs * T <= slots;
   const s2::SplitLevel* use = closest(one_round);
-  if (one_round && (!use || off > 1.5) && L->kv_max_steps > 2.4 * best) use = closest(false);
+  const double far = p.batch * p.heads % 8 ? 1.5 : HUGE_VAL;
+  if (one_round && (!use || off > far) && L->kv_max_steps > 2.4 * best) use = closest(false);
   if (!use) return;
   p.split_codes = L->d_kv_split_codes + use->offset;
   p.split_items = use->n_items;

@@ -11,10 +11,10 @@ pytestmark = pytest.mark.gpu
 
 # an XCD's slots (64, and as many as 80 of head_dim 64) hold all tiles and no cut of them; longest tile / best length of a part
 @pytest.mark.parametrize("D,batch,H,N,local,stride,keep_ds,cut", [
-    (128, 4, 8, 2048, 2, 16, False, True), (128, 4, 8, 2048, 2, 16, True, True),   # 3.0
-    (128, 3, 8, 2560, 4, 8, False, True), (128, 3, 8, 2560, 4, 8, True, True),     # 3.3
-    (128, 3, 8, 2560, 16, 16, False, False),                                       # 2.24
-    (64, 1, 8, 10240, 4, 8, False, True),                                          # 8.4
+    (128, 4, 8, 2048, 2, 16, False, True), (128, 4, 8, 2048, 2, 16, True, True),   # 3.1
+    (128, 3, 8, 2560, 4, 8, False, True), (128, 3, 8, 2560, 4, 8, True, True),     # 3.4
+    (128, 3, 8, 2560, 16, 16, False, False),                                       # 2.36
+    (64, 1, 8, 10240, 4, 8, False, True),                                          # 8.9
 ])
 def test_cut_beyond_the_slots(D, batch, H, N, local, stride, keep_ds, cut):
     print("cut beyond the slots", D, batch, H, N, local, keep_ds, flush=True)

@@ -151,10 +151,10 @@ def test_whether_tiles_are_cut(D, S, H, N, local, cut):
 @pytest.mark.parametrize("D,S,batch,H,N,local,stride,parts", [
     (128, 64, 1, 7, 8192, 4, 8, 8), (64, 64, 1, 2, 8192, 4, 8, 11), (128, 128, 3, 4, 3072, 3, 4, 3),   # pairs / 8 alone would give 3, 22 and 6 parts
     (128, 64, 4, 23, 768, 3, 7, 0), (128, 128, 4, 21, 512, 3, 5, 0),                                     # ... and two
-    (64, 64, 1, 8, 8192, 4, 8, 8),                                                                       # no pairs left over, parts that fit only if twice as long
+    (64, 64, 1, 8, 8192, 4, 8, 4), (128, 32, 1, 16, 3584, 16, 16, 3),                                    # no pairs left over
 ])
 def test_parts_of_the_longest_tile(D, S, batch, H, N, local, stride, parts):
-    # pairs that are left over from a multiple of eight count as a whole one for whether tiles are cut, as half a one more for how long parts are
+    # pairs that are left over from a multiple of eight count as a whole one for whether tiles are cut, as most of one for how long parts are
     w = dataclasses.replace(synth.WORKLOADS["tiny" if D == 64 else "1p3b_8k"], block_size=S)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(H + N)
