@@ -276,6 +276,7 @@ void build_tiles(const s2_layout& L, int group, bool transpose, TileList& out) {
     const int32_t* hp = out.ptr.data() + (size_t)h * T;
     std::stable_sort(ord, ord + T, [&](int a, int b) { return hp[a + 1] - hp[a] > hp[b + 1] - hp[b]; });
   }
+  static_assert(kRowRec >= 3 && kColRec >= 4 + kBwdBN / 16, "a record holds the members of a column tile of the smallest blocks");
   const int words = transpose ? kColRec : kRowRec;
   out.rec.assign((size_t)H * T * words, transpose ? -1 : 0);
   for (size_t k = 0; k < (size_t)H * T; ++k) {

@@ -26,6 +26,19 @@ static int fails = 0;
 static size_t levels_seen = 0;
 #define CHECK(c) do { if (!(c)) { std::printf("FAILED %s line %d\n", #c, __LINE__); ++fails; } } while (0)
 
+// what a workgroup begins with (TileList::rec) is what the lists that the views show say of the tile of its rank
+static void check_records(const s2::TileList& t, int H, int words, bool transpose) {
+  CHECK(t.rec.size() == (size_t)H * t.tiles_per_head * words);
+  for (int h = 0; h < H; ++h)
+    for (int k = 0; k < t.tiles_per_head; ++k) {
+      const int32_t* r = t.rec.data() + ((size_t)h * t.tiles_per_head + k) * words;
+      const size_t at = (size_t)h * t.tiles_per_head + t.order[(size_t)h * t.tiles_per_head + k];
+      CHECK(r[1] == t.ptr[at] && r[2] == t.ptr[at + 1] - t.ptr[at]);
+      if (!transpose) CHECK(r[0] == t.order[(size_t)h * t.tiles_per_head + k]);
+      for (int m = 0; transpose && m < words - 4; ++m) CHECK(r[4 + m] == (m < t.group ? t.members[at * t.group + m] : -1));
+    }
+}
+
 static void exercise(const s2_layout_params& p) {
   s2_layout L;
   const int st = s2::build_host(p, L);
@@ -48,8 +61,10 @@ static void exercise(const s2_layout_params& p) {
   s2::TileList t;
   s2::build_tiles(L, s2::kFwdBM / S > 0 ? s2::kFwdBM / S : 1, false, t);
   CHECK((int)t.ptr.size() == H * t.tiles_per_head + 1 && t.ptr.back() == (int32_t)t.ent.size());
+  check_records(t, H, s2::kRowRec, false);
   s2::build_tiles(L, s2::kBwdBN / S > 0 ? s2::kBwdBN / S : 1, true, t);
   CHECK((int)t.members.size() == H * t.tiles_per_head * t.group);
+  check_records(t, H, s2::kColRec, true);
   // the ways to cut the longest key tiles: the codes of a level are the parts 0 .. parts - 1 of the tiles
   // 0 .. n_long - 1 of every head's order, as many as keep the longest head's tile within the level's steps
   s2::build_tiles(L, s2::kBwdBN / S, true, L.kv_tiles);
