@@ -55,7 +55,7 @@ int main() {
         if (check((int)seen.size() == P * T, "missing", P, T, G, grid)) return 1;
         // at most a run more, and the last run may be short
         const int most = *std::max_element(count, count + 8), least = *std::min_element(count, count + 8);
-        if (check(most - least <= (P % 8 ? 2 << deal_run_shift(T) : 0), "balance", P, T, G, grid)) return 1;
+        if (check(most - least <= (P % 8 ? 1 << deal_run_shift(T) : 0), "balance", P, T, G, grid)) return 1;
       }
   // as many workgroups as 32 bits hold, and a few more: grids are counted in 64, and never less than the tiles
   for (int T : {64, 65, 129, 131, 8193})
