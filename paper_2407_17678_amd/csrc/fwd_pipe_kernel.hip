@@ -91,6 +91,7 @@ __global__ __launch_bounds__(kThreads, D == 128 ? 2 : 3) void fwd_pipe_kernel(co
   // x 2048 14.1 and 14.5.)
   constexpr bool kAcross = !LONE && (!VARLEN || D == 128);
   static_assert(!kAcross || (NS % kRing == 0 && kRing > kLead), "a fragment has the same place in every step");
+  static_assert(!kAcross || 2 * NG <= NS - kLead, "all direct loads of a step are issued before its barrier");
   static_assert(!(DENSE && VARLEN), "the dense form walks 64-key blocks of whole sequences");
 
   const int tid = threadIdx.x;
