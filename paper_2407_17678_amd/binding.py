@@ -111,6 +111,8 @@ def _marshal():
             from . import _marshal as calls
         except ImportError as e:
             raise ImportError("_marshal.so is not built: run `python -m paper_2407_17678_amd.build`") from e
+        if getattr(calls, "entry_points", None) != _MARSHALLED:
+            raise ImportError("_marshal.so is built from other sources: run `python -m paper_2407_17678_amd.build`")
         calls.bind(*(C.cast(getattr(L, name), C.c_void_p).value for name in _MARSHALLED))
         _calls = calls
     return _calls

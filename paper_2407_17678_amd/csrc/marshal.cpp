@@ -14,21 +14,17 @@
 
 namespace {
 
-// Entry points, in the order bind() is given their addresses (kEntryPoints in binding.py): those of the library that ctypes has loaded,
-// so that there is one copy of it in the process.
+// Entry points, in the order bind() is given their addresses (_MARSHALLED in binding.py, which compares it with `entry_points`): those of
+// the library that ctypes has loaded, so that there is one copy of it in the process.
+#define S2_ENTRY_POINTS(X) \
+  X(s2_attn_fwd, fwd) X(s2_attn_fwd_rows, fwd_rows) X(s2_attn_fwd_varlen, fwd_varlen) X(s2_attn_bwd_stages, bwd_stages) \
+  X(s2_attn_bwd_varlen, bwd_varlen) X(s2_dense_causal_fwd, dense_fwd) X(s2_dense_causal_bwd, dense_bwd) X(s2_attn_decode, decode) \
+  X(s2_attn_decode_static, decode_static) X(s2_attn_decode_layout, decode_layout) X(s2_attn_decode_paged, decode_paged) \
+  X(s2_attn_decode_paged_layout, decode_paged_layout)
 struct Api {
-  decltype(&s2_attn_fwd) fwd;
-  decltype(&s2_attn_fwd_rows) fwd_rows;
-  decltype(&s2_attn_fwd_varlen) fwd_varlen;
-  decltype(&s2_attn_bwd_stages) bwd_stages;
-  decltype(&s2_attn_bwd_varlen) bwd_varlen;
-  decltype(&s2_dense_causal_fwd) dense_fwd;
-  decltype(&s2_dense_causal_bwd) dense_bwd;
-  decltype(&s2_attn_decode) decode;
-  decltype(&s2_attn_decode_static) decode_static;
-  decltype(&s2_attn_decode_layout) decode_layout;
-  decltype(&s2_attn_decode_paged) decode_paged;
-  decltype(&s2_attn_decode_paged_layout) decode_paged_layout;
+#define X(entry, name) decltype(&entry) name;
+  S2_ENTRY_POINTS(X)
+#undef X
 };
 union {
   Api f;
@@ -406,5 +402,19 @@ PyMODINIT_FUNC PyInit__marshal(void) {
                    {&names.numel, "numel"},       {&names.element_size, "element_size"}, {&names.value, "value"}};
   for (const auto& n : all)
     if (!(*n.at = PyUnicode_InternFromString(n.text))) return nullptr;
-  return PyModule_Create(&module);
+  const Ref m(PyModule_Create(&module));
+  if (!m.o) return nullptr;
+#define X(entry, name) #entry,
+  const char* const entries[] = {S2_ENTRY_POINTS(X)};
+#undef X
+  const Ref order(PyTuple_New(kEntryPoints));
+  if (!order.o) return nullptr;
+  for (Py_ssize_t i = 0; i < kEntryPoints; ++i) {
+    PyObject* const name = PyUnicode_FromString(entries[i]);
+    if (!name) return nullptr;
+    PyTuple_SET_ITEM(order.o, i, name);
+  }
+  if (PyObject_SetAttrString(m.o, "entry_points", order.o)) return nullptr;
+  Py_INCREF(m.o);
+  return m.o;
 }

@@ -183,3 +183,12 @@ def test_a_destroyed_layout_is_a_null_handle():
     with pytest.raises(B.S2Error) as e:
         B.s2_attn_fwd(gone, *t[:5], 0.5, stream=Stream())
     assert e.value.status == -1
+
+
+def test_an_extension_of_other_sources_is_refused(monkeypatch):
+    # (its functions call by position)
+    B._marshal()
+    monkeypatch.setattr(B, "_calls", None)
+    monkeypatch.setattr(B, "_MARSHALLED", B._MARSHALLED[::-1])
+    with pytest.raises(ImportError):
+        B._marshal()
