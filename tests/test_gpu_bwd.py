@@ -1,5 +1,6 @@
 """GPU parity of the backward kernels against the fp64 oracle (through the C ABI)."""
 
+import ctypes as C
 import dataclasses
 
 import numpy as np
@@ -186,3 +187,21 @@ def test_peaked_softmax_and_wide_dynamic_range():
     for n, got, ref in (("dq", dq2, dQ), ("dk", dk2, dK), ("dv", dv2, dV)):
         assert torch.isfinite(got.float()).all()
         assert G.rel_l2(G.to_f64(got), ref) <= GRAD_TOL, n
+
+
+def test_the_c_entry_of_a_whole_backward():
+    # s2_attn_bwd, which the Python function of that name reaches as all stages of s2_attn_bwd_stages
+    w = synth.WORKLOADS["tiny"]
+    q, k, v, g = (G.to_dev(x) for x in synth.train_inputs(w))
+    Bt, H, N, D = q.shape
+    lay = B.s2_layout_build(B.layout_params(H, N // w.block_size, w.block_size, w.local_blocks, w.stride))
+    o, lse = torch.empty_like(q), torch.empty((Bt, H, N), dtype=torch.float32, device="cuda")
+    B.s2_attn_fwd(lay, q, k, v, o, lse, w.scale)
+    ws = torch.empty(B.s2_attn_bwd_workspace_bytes(Bt, H, N, D), dtype=torch.uint8, device="cuda")
+    want, got = ([torch.full_like(q, float("nan")) for _ in range(3)] for _ in range(2))
+    B.s2_attn_bwd(lay, q, k, v, o, lse, g, *want, w.scale, ws)
+    t = B.Tensors(*(x.data_ptr() for x in (q, k, v, o, lse, g, *got)), Bt, H, N, D, *q.stride()[:3], *k.stride()[:3])
+    args = (lay.handle, C.byref(t), w.scale, C.c_void_p(ws.data_ptr()))
+    assert B.lib().s2_attn_bwd(*args, ws.numel(), C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    assert B.lib().s2_attn_bwd(*args, 16, None) == -5

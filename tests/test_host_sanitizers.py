@@ -1,12 +1,14 @@
 """The host side of the library (the closed-form layout builder, the builder from caller-supplied
 rows, the merged tile lists and the unit table of the backward that keeps dS; integer code, no HIP) compiled with g++ under AddressSanitizer and
 UndefinedBehaviorSanitizer and driven over the training workloads, a random parameter sweep and
-the inputs the builders reject."""
+the inputs the builders reject; and the extension that makes the compute calls under UndefinedBehaviorSanitizer, driven by its
+own tests."""
 
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 import pytest
 
@@ -183,3 +185,30 @@ def test_layout_builder_under_asan_and_ubsan(tmp_path):
     r = subprocess.run([str(exe)], capture_output=True, text=True, env=env, timeout=300)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-3000:])
     assert "sanitizer driver: ok" in r.stdout
+
+
+PLUGGED = """
+import ctypes as C, importlib.util, sys
+import pytest
+from paper_2407_17678_amd import binding as B
+spec = importlib.util.spec_from_file_location("_marshal", sys.argv[1])
+calls = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(calls)
+calls.bind(*(C.cast(getattr(B.lib(), n), C.c_void_p).value for n in B._MARSHALLED))
+B._calls = calls
+code = pytest.main(["-q", "-p", "no:cacheprovider", "tests/test_binding_marshal.py", "-k", "not other_sources"])
+assert B._calls is calls
+sys.exit(code)
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_marshalling_under_ubsan(tmp_path):
+    ext = tmp_path / "_marshal.so"
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fPIC", "-shared", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-static-libubsan",
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "marshal.cpp"), "-o", str(ext)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    r = subprocess.run([sys.executable, "-c", PLUGGED, str(ext)], capture_output=True, text=True, cwd=ROOT, timeout=300)
+    assert r.returncode == 0, (r.stdout[-3000:], r.stderr[-2000:])
+    assert "passed" in r.stdout
