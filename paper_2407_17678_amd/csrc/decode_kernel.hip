@@ -266,11 +266,11 @@ __global__ __launch_bounds__(64 * W, FAR ? 1 : D == 128 ? 2 : 4) void decode_spl
   if (PAGED && p.missing && lane == 0 && n_missing > 0) atomicAdd(p.missing, n_missing);
 
   // sum the row groups of the wavefront
-  if (LPR == 8) l_run += __shfl_xor(l_run, 8, 64);  // (not the same in all lanes of a group)
+  if (LPR == 8) l_run += of_neighbour<8>(l_run);
   l_run = sum_halves(sum_rows(l_run));
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    if (LPR == 8) acc[e] += __shfl_xor(acc[e], 8, 64);
+    if (LPR == 8) acc[e] += __shfl_xor(acc[e], 8, 64);  // (other features in each lane of a group)
     acc[e] = sum_halves(sum_rows(acc[e]));
   }
   if (lane == 0) {

@@ -355,11 +355,6 @@ struct EntryList {
     const int a = __builtin_amdgcn_readlane(cur, j & 63), b = __builtin_amdgcn_readlane(nxt, j & 63);
     return (j >> 6) == batch ? a : b;
   }
-  // entry e+1, given that get(e) was the last call; does not advance
-  __device__ __forceinline__ int peek_next(int e) const {
-    return ((e + 1) >> 6) != batch ? __builtin_amdgcn_readlane(nxt, 0)
-                                   : __builtin_amdgcn_readlane(cur, (e + 1) & 63);
-  }
 };
 
 }  // namespace s2
