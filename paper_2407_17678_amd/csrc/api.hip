@@ -623,7 +623,7 @@ int check_pattern(const s2_layout_params* lp, const s2_layout* layout, int heads
 //    little.  From 384 units on where two fit (four in blocks of 32, whose units are half as large), from 512 where
 //    one does: 96 pairs of 128 to 512 units x 128 179 us in two splits, 163 in eight, all of 384 203 and 206; 80 pairs of 256
 //    to 1024 32-token units x 64 101 in three, 82 in twelve; 180 pairs of 128 to 512 x 128 370 in one, 350 in six.
-//  - Above that, up to 255 pairs: one split while rows are short, then pieces of a dozen units.  At
+//  - Above that (192 pairs, 256 in blocks of 16), up to 255 pairs: one split while rows are short, then pieces of a dozen units.  At
 //    head_dim 128 from 256 units on (200 pairs of 64 to 256 units 204 us in one split, 179 in six, all of 384 411 and 414, but
 //    all of 128 139 and 148), at 64 from 96 (all of 128 89 and 83, of 64 34 and 39), in blocks of 32 from 64 (of 64 x 128
 //    47 in one, 39 in two; of 256 to 1024 x 64 470 in one, 176 in six).

@@ -9,10 +9,10 @@
 // buffer that ends with its last attended row, so that a load needs no clamping (a row past the end reads as
 // zero and fetches nothing) and its address is one scalar addition.  Scores are added up across a row's lanes by lane
 // permutations inside the additions; through the LDS each took four round trips that a lone wavefront waits for.  Measured
-// against one lookup per lane and load, loads of a unit behind the sums of the one before and sums through the LDS: 16384 of
-// 30 x 40 paged rows x 64, blocks of 16 89 -> 71 us, 64 x 32 paged rows of 8192 to 32768 x 128 (blocks of 16) 267 -> 245
-// (5.6 TB/s), 224 rows of 8192, D = 64, blocks of 64 19.6 -> 14.7, one sequence of 32768 x 32 heads 14.5 -> 13.8,
-// calls of a few short rows 6.3 -> 4.6; large contiguous calls, at 5.5 to 5.7 TB/s before, are as they were.
+// against one lookup per lane and load, loads of a unit behind the sums of the one before and sums through the LDS: 40 x 30 paged
+// rows of 4000 to 16384 x 64, blocks of 16 87 -> 70 us, 64 x 32 paged rows of 8192 to 32768 x 128 (blocks of 16) 258 -> 238
+// (5.8 TB/s), 224 rows of 4096 to 8192, D = 64, blocks of 64 17.5 -> 14.0, one sequence of 32768 x 32 heads with its merge 14.6 -> 13.3,
+// calls of a few short rows 6.3 -> 4.6; 64 x 32 contiguous rows of 8192 to 16384 x 128 308 -> 305 (the same).
 //
 // A caller-supplied pattern replaces the closed form by row (L-1) div S of the layout's lists.
 //

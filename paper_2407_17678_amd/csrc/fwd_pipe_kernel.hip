@@ -34,16 +34,16 @@
 //     beside an MFMA, but takes a wavefront that has nothing else to do 10 cycles (its first use of a lane's value 30, a
 //     compare and branch on vector values 38, a taken branch 22), and each step began with 75 of them.
 //
-// The last point, before and after, us: 1 x 32 heads x 32768 x 128 1066 -> 1028, 4 x 16 x 8192 254 -> 245, 2 x 16 x 3904 48.3 -> 45.9, 2 x 16 x 4096 x 64
-// 32.4 -> 30.5, 1 x 32 x 131072 in blocks of 128 6047 -> 5937, dense 1 x 32 x 8192 508 -> 504; with few tiles on the chip 1 x 4 x 512 x 64 10.2 -> 8.1, 128 rows x 32
-// heads against 30720 keys 50.7 -> 45.7.  (Direct loads one or two steps further ahead, in the LDS that a lone workgroup could have, change nothing there.)
+// Before the last point and now (with a tile's start in tile_map.h), us, caches cold: 1 x 32 heads x 32768 x 128 1064 -> 1028, 4 x 16 x 8192 255 -> 246, 2 x 16 x 3904
+// 52.1 -> 50.2, 2 x 16 x 4096 x 64 32.9 -> 30.6, 1 x 32 x 131072 in blocks of 128 6092 -> 5921, dense 1 x 32 x 8192 513 -> 508; with few tiles on the chip 1 x 4 x 512 x 64
+// 9.8 -> 7.9, 128 rows x 32 heads against 30720 keys 50.8 -> 48.1.  (Direct loads one or two steps further ahead, in the LDS that a lone workgroup could have, change nothing there.)
 //
 // One loop serves both head sizes, blocks of 64 and 128 tokens and ragged ends (blocks of 16 and 32:
 // fwd_gather_kernel.hip).  Against the phase-by-phase kernel that head_dim 64 and partial 128-row tiles used to
 // run (per launch): 2 x 16 heads x 4096 x 64, blocks of 64: 38.3 -> 36.0 us; 2 x 16 x 3904 x 128 (61 blocks): 53.7 -> 48.8 us; a
 // packed batch of 8 sequences of 200 to 8192 rows x 32 heads: 367 us in two launches -> 348 us in one.  What bounds it: with
 // many steps per tile the matrix and vector pipes (head_dim 128 about 1.05 PFLOP/s; at 64 the vector work per MFMA
-// doubles), with few the latency of a tile's start and end (about 12 us of a workgroup slot against 1.6 us per step).
+// doubles), with few the latency of a tile's start and end (10.8 us of a workgroup slot against 1.7 us per step; 7.8 and 1.7 at 64).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

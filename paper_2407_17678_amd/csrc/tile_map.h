@@ -11,8 +11,9 @@
 
 namespace s2 {
 
-// n / d of 0 <= n < 2^31 for a d that the host knows: n * ceil(2^(31 + l) / d) >> (31 + l), 2^l the first power of two from d on.  (The
-// factor is less than 2^-l too large, relative to d / 2^31.)  Three scalar instructions; the division that the compiler writes goes
+// n / d of 0 <= n < 2^31 for a d that the host knows: n * ceil(2^(31 + l) / d) >> (31 + l), 2^l the first power of two from d on (Granlund
+// and Montgomery's division by invariant integers).  Rounding the factor up adds less than 2^l / 2^(31 + l) / d * n < 1 / d to the
+// quotient, which does not reach the next whole number.  Three scalar instructions; the division that the compiler writes goes
 // through a vector reciprocal and back, and a tile's start had five to seven of them.  With them gone and a tile's record in one
 // scalar load (DevTiles in kernels.h), forward and backward, us: packed 13 x 18 heads of 100 to 6272 rows x 64 54.6 -> 51.5, 168 -> 162, 20 x 11 heads x 128
 // 146 -> 139, 423 -> 410, 8 x 32 heads 326 -> 323, 974 -> 961; 1 x 4 x 512 x 64 8.3 -> 7.9, 15.8 -> 15.7; 2 x 16 x 3904 x 128 45.5 -> 45.0, 129.4 -> 128.8.

@@ -102,8 +102,8 @@ def test_decode_merges_any_number_of_splits(name, splits):
                                                   (4, 64, 520, 16), (1, 257, 520, 16)])
 def test_decode_splits_left_to_the_library(nseq, heads, max_len, S):
     # one split up to 24 units of work, then one to every eight units, as many as 256 workgroups (or three,
-    # where that is one); above 192 (sequence, head) pairs, or 256 with 16-token blocks, four wavefronts to a
-    # workgroup instead of eight and one split, from 256 on one to every twelve units
+    # where that is one); above 192 (sequence, head) pairs, or 256 with 16-token blocks, one split, from 256 on one to
+    # every twelve units.  Up to 256 workgroups (512 of 16-token blocks at head_dim 64) are of eight wavefronts, more of four
     w = dataclasses.replace(synth.WORKLOADS["7b_decode"], block_size=S)
     qb, kcb, vcb, lens = synth.decode_inputs_small(w, nseq, heads, max_len, lengths=np.full(nseq, max_len, dtype=np.int32))
     p = B.layout_params(heads, 1, w.block_size, 1, 0, 0, 0, 1)
