@@ -38,6 +38,10 @@ S2_HD inline int operator/(int n, const FastDiv& f) { return (int)(((uint64_t)(u
 // 159 and 118, 520 and 339; 3 x 8192 44 and 29, 126 and 87; 20 x 4096 35 and 33, 106 and 92; 33 x 4096 x 64 37 and 31, 92 and 79; dense 19 x
 // 7168 290 and 234, 818 and 680; where seven are left over, and little is lost by an XCD each, 15 x 8192 x 128 84 and 81, 239 and 239.  (Single tiles instead of runs:
 // 118 and 361, 30 and 90, 33 and 93, 32 and 79, 233 and 701, 85 and 251; at 64 tiles runs of four are 1 to 3 % slower than of two, at 128 none is.)
+// Over 947 launches of drawn cases 10 % faster in the mean than an XCD to a pair and 2.5 % slower at worst; over 246 of packed batches 3 % faster in the mean.  Where an XCD to a pair
+// is known to be ahead: dense backward 1 x 25 heads x 1280 x 128 56.0 and 58.5 (31 or 32 key tiles to an XCD, so that its longest query tiles go to the compute units of its longest
+// key tiles), dS kept 2 x 31 x 1152 92.6 and 96.8, 1 x 23 x 992 in blocks of 16 37.3 and 38.4; packed, where it depends on whose pairs are left over, forward 3 x 6 heads of up to
+// 6528 rows x 64 29.0 and 33.6, 2 x 39 in blocks of 32 85.8 and 89.2, backward 15 x 15 in blocks of 16 834 and 911, 20 x 5 770 and 805, 11 x 6 561 and 581.
 inline int deal_run_shift(int tiles) { return tiles >= 128 ? 2 : tiles >= 64 ? 1 : 0; }
 // The pairs interleaved: all their longest
 // tiles are dispatched first, then all their second longest, ...  Used where tile lengths are very
